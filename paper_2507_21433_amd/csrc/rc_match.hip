@@ -947,25 +947,65 @@ __global__ __launch_bounds__(kThreads, 1) void match_tile_kernel(const MatchPara
 
 namespace {
 
-// Merge the per-pool-tile partial results of every query and take the decision against tau.
-__global__ __launch_bounds__(256) void match_finalize_kernel(const Part* __restrict__ part, int npt, long long LQ,
-                                                             int Q, float tau, int32_t* __restrict__ best_idx,
-                                                             float* __restrict__ best_score,
-                                                             int32_t* __restrict__ match_idx,
-                                                             float* __restrict__ second_score) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= LQ) return;
-  const long long l = i / Q, q = i % Q;
-  float best = -INFINITY, second = -INFINITY;
-  int bidx = -1;
-  for (int t = 0; t < npt; ++t) {
-    const Part u = part[(l * npt + t) * Q + q];
-    top2_merge(best, bidx, second, u.best, u.idx, u.second);
+// Merge the partial results of every query (one per pool tile, or per pool chunk of a selection kernel) and take
+// the decision.  part: [L][nparts][Q].  DISTANCE: the values are negated distances (layer-mean mode), reported
+// with their sign turned and matched iff distance <= threshold; else scores, matched iff score >= threshold.
+// 1 << lanes_log threads share a query, each merges every (1 << lanes_log)-th part, then a tree in LDS: a part
+// costs a memory round trip of about 0.3 us and a query can have 128 of them, walked by as few as Q threads.
+// Measured, one thread per query -> this: 16 queries x 128 parts 38.4 -> 4.7 us, 32768 x 64 parts 40.6 -> 10.0 us,
+// 16384 x 16 parts 11.7 -> 6.1 us, 32 x 8 parts 4.6 us both (a kernel's fixed cost).
+template <bool DISTANCE>
+__global__ __launch_bounds__(256) void merge_parts_kernel(const Part* __restrict__ part, int nparts, int lanes_log,
+                                                          long long LQ, int Q, float threshold,
+                                                          int32_t* __restrict__ best_idx, float* __restrict__ best_value,
+                                                          int32_t* __restrict__ match_idx,
+                                                          float* __restrict__ second_value) {
+  __shared__ Part s_part[256];
+  const int queries_log = 8 - lanes_log;
+  const int tq = threadIdx.x & ((1 << queries_log) - 1), tc = threadIdx.x >> queries_log;
+  const long long i = ((long long)blockIdx.x << queries_log) + tq;
+  Part t;
+  t.best = -INFINITY;
+  t.second = -INFINITY;
+  t.idx = -1;
+  t.pad = 0;
+  if (i < LQ) {
+    const Part* src = part + (i / Q) * nparts * Q + i % Q;
+#pragma unroll 4
+    for (int c = tc; c < nparts; c += 1 << lanes_log) {
+      const Part u = src[(long long)c * Q];
+      top2_merge(t.best, t.idx, t.second, u.best, u.idx, u.second);
+    }
   }
-  best_idx[i] = bidx;
-  best_score[i] = best;
-  match_idx[i] = (bidx >= 0 && best >= tau) ? bidx : -1;
-  if (second_score) second_score[i] = second;
+  if (lanes_log > 0) {
+    s_part[threadIdx.x] = t;
+    __syncthreads();
+    for (int half = 128; half >= 1 << queries_log; half >>= 1) {
+      if ((int)threadIdx.x < half) {
+        const Part u = s_part[threadIdx.x + half];
+        top2_merge(t.best, t.idx, t.second, u.best, u.idx, u.second);
+        s_part[threadIdx.x] = t;
+      }
+      __syncthreads();
+    }
+  }
+  if (tc != 0 || i >= LQ) return;
+  const float value = DISTANCE ? -t.best : t.best;
+  best_idx[i] = t.idx;
+  best_value[i] = value;
+  match_idx[i] = (t.idx >= 0 && (DISTANCE ? value <= threshold : value >= threshold)) ? t.idx : -1;
+  if (second_value) second_value[i] = DISTANCE ? -t.second : t.second;
+}
+
+template <bool DISTANCE>
+rc_status merge_parts(const Part* part, int64_t nparts, long long LQ, int Q, float threshold, int32_t* best_idx,
+                      float* best_value, int32_t* match_idx, float* second_value, hipStream_t st, const char* what) {
+  int lanes_log = 0;  // about four parts per thread, at most a wave's worth of threads per query
+  while (lanes_log < 6 && (int64_t)(4 << lanes_log) < nparts) ++lanes_log;
+  const long long queries = 256 >> lanes_log;
+  merge_parts_kernel<DISTANCE><<<(unsigned)((LQ + queries - 1) / queries), 256, 0, st>>>(
+      part, (int)nparts, lanes_log, LQ, Q, threshold, best_idx, best_value, match_idx, second_value);
+  return check_launch(what);
 }
 
 // Float index of element (row r, column c) of a 256x256 tile of sums as the tile kernel stores it
@@ -1122,39 +1162,6 @@ inline int select_rows(int64_t P, int64_t Q) {
   int64_t rows = (P + chunks - 1) / chunks;
   rows = (rows + 31) / 32 * 32;
   return (int)(rows < 32 ? 32 : rows);
-}
-
-// 64 queries per workgroup, four threads per query, each merging every fourth chunk.
-__global__ __launch_bounds__(256) void layer_mean_finalize_kernel(const Part* __restrict__ part, int nchunks, int Q,
-                                                                  float thr, int32_t* __restrict__ best_idx,
-                                                                  float* __restrict__ best_dist,
-                                                                  int32_t* __restrict__ match_idx,
-                                                                  float* __restrict__ second_dist) {
-  __shared__ Part s_part[4][64];
-  const int tq = threadIdx.x & 63, tc = threadIdx.x >> 6;
-  const int q = blockIdx.x * 64 + tq;
-  Part t;
-  t.best = -INFINITY;
-  t.second = -INFINITY;
-  t.idx = -1;
-  t.pad = 0;
-  if (q < Q)
-    for (int c = tc; c < nchunks; c += 4) {
-      const Part u = part[(long long)c * Q + q];
-      top2_merge(t.best, t.idx, t.second, u.best, u.idx, u.second);
-    }
-  s_part[tc][tq] = t;
-  __syncthreads();
-  if (tc != 0 || q >= Q) return;
-#pragma unroll
-  for (int w = 1; w < 4; ++w) {
-    const Part u = s_part[w][tq];
-    top2_merge(t.best, t.idx, t.second, u.best, u.idx, u.second);
-  }
-  best_idx[q] = t.idx;
-  best_dist[q] = -t.best;
-  match_idx[q] = (t.idx >= 0 && -t.best <= thr) ? t.idx : -1;
-  if (second_dist) second_dist[q] = -t.second;
 }
 
 // Layer-mean mode: how the L layers are split into groups.  A workgroup walks the layers of one
@@ -1441,9 +1448,8 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
     tile_sums_select_kernel<<<sgrid, 256, 0, st>>>(mp.dpart, S, (int)P, (int)Q, (int)sl.npt, (int)sl.nqt, sl.sel_rows,
                                                    -1.0f, heads ? 1 : 0, pool_live, part);
     if (rc_status s = check_launch("rc_match_blocks(select)")) return s;
-    match_finalize_kernel<<<(unsigned)((LQ + 255) / 256), 256, 0, st>>>(part, (int)sl.nchunks, LQ, (int)Q, tau, best_idx,
-                                                                       best_score, match_idx, second_score);
-    return check_launch("rc_match_blocks(finalize)");
+    return merge_parts<false>(part, sl.nchunks, LQ, (int)Q, tau, best_idx, best_score, match_idx, second_score, st,
+                              "rc_match_blocks(finalize)");
   }
 
   if (P > 0) {
@@ -1484,10 +1490,8 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
       launch_tiles<false>(mode, mp, grid, st);
     if (rc_status s = check_launch("rc_match_blocks(tiles)")) return s;
   }
-  match_finalize_kernel<<<(unsigned)((LQ + 255) / 256), 256, 0, st>>>(static_cast<const Part*>(workspace), (int)npt, LQ,
-                                                                     (int)Q, tau, best_idx, best_score, match_idx,
-                                                                     second_score);
-  return check_launch("rc_match_blocks(finalize)");
+  return merge_parts<false>(static_cast<const Part*>(workspace), npt, LQ, (int)Q, tau, best_idx, best_score, match_idx,
+                            second_score, st, "rc_match_blocks(finalize)");
 }
 
 extern "C" size_t rc_layer_mean_workspace_size(const rc_kv_desc* qdesc, int64_t Q, int64_t P) {
@@ -1590,9 +1594,8 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
     layer_mean_shares_select_kernel<<<sgrid, 256, 0, st>>>(dpart, S, L, (int)P, (int)Q, (int)sl.npt, (int)sl.nqt, sl.sel_rows,
                                                            scale, pool_live, q_ksq, q_vsq, p_ksq, p_vsq, part);
     if (rc_status s = check_launch("rc_match_blocks_layer_mean(select)")) return s;
-    layer_mean_finalize_kernel<<<(unsigned)((Q + 63) / 64), 256, 0, st>>>(part, (int)sl.nchunks, (int)Q, threshold, best_idx,
-                                                                          best_dist, match_idx, second_dist);
-    return check_launch("rc_match_blocks_layer_mean(finalize)");
+    return merge_parts<true>(part, sl.nchunks, Q, (int)Q, threshold, best_idx, best_dist, match_idx, second_dist, st,
+                             "rc_match_blocks_layer_mean(finalize)");
   }
   Part* part = reinterpret_cast<Part*>(static_cast<char*>(workspace) + layer_mean_part_offset(ls.groups, npt, nqt));
   const int sel_rows = select_rows(P, Q);
@@ -1639,7 +1642,6 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
                                                     pool_live, part);
     if (rc_status s = check_launch("rc_match_blocks_layer_mean(select)")) return s;
   }
-  layer_mean_finalize_kernel<<<(unsigned)((Q + 63) / 64), 256, 0, st>>>(part, (int)nchunks, (int)Q, threshold, best_idx,
-                                                                        best_dist, match_idx, second_dist);
-  return check_launch("rc_match_blocks_layer_mean(finalize)");
+  return merge_parts<true>(part, nchunks, Q, (int)Q, threshold, best_idx, best_dist, match_idx, second_dist, st,
+                           "rc_match_blocks_layer_mean(finalize)");
 }
