@@ -54,6 +54,7 @@ constexpr int kMaxGrid = 512;                          // workgroups of a tile-k
 constexpr int kScheduleHeader = (8 + kMaxGrid) * 32;   // ints ahead of the claim words of a dynamic tile schedule
 constexpr int kPoolStages = 3, kQueryStages = 2;
 
+constexpr int kShareRotation = 8;  // slices
 // Partial selection result of one pool tile for one query.
 struct Part {
   float best;
@@ -182,8 +183,8 @@ struct Cursor {
 // MODE 4 = the same for the per-head-all score: S = H shares, share h computes the score of head h
 // over the head's K and V slices, and the second kernel takes the minimum over the shares.
 // SHARED_POOL: several query tiles, i.e. several workgroups read every pool slice (see the pool loads below).
-template <bool BF16, int BP, int BQ, int MODE, bool SHARED_POOL = false>
-__global__ __launch_bounds__(kThreads, 1) void match_tile_kernel(const MatchParams p) {
+template <bool BF16, int BP, int BQ, int MODE, bool SHARED_POOL>
+__device__ __forceinline__ void tile_body(const MatchParams& p) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
   constexpr int NT = kThreads, WP = kPoolWaves, WQ = kQueryWaves;
   constexpr int WTP = BP / WP, WTQ = BQ / WQ;
@@ -193,10 +194,9 @@ __global__ __launch_bounds__(kThreads, 1) void match_tile_kernel(const MatchPara
   constexpr int A_STAGE = BP * kRowBytes, B_STAGE = BQ * kRowBytes;
   constexpr int RING = SA * A_STAGE + SB * B_STAGE;
   static_assert(BP % (32 * WP) == 0 && BQ % (32 * WQ) == 0, "wave tiles are multiples of 32");
-  static_assert(NT >= BQ, "one thread per query column in the tile epilogue");
   static_assert(RING <= 160 * 1024, "ring fits the LDS of a compute unit");
   static_assert(sizeof(Part) * WP * BQ <= RING, "the epilogue scratch reuses the ring");
-  static_assert(MODE < 2 || (BP == 256 && BQ == 256 && WP == 2 && WQ == 2), "sum_index() decodes this tile shape");
+  static_assert(MODE < 2 || (BP == 256 && BQ % 64 == 0 && WP == 2 && WQ == 2), "sum_index() decodes these tile shapes");
   constexpr bool SHARES = (MODE == 3 || MODE == 4);    // several workgroups per tile, results stored as tiles of floats
   constexpr bool PER_HEAD = (MODE == 1 || MODE == 4);  // phases are heads' [T][Dh] slices, norms are per head
 
@@ -367,15 +367,21 @@ __global__ __launch_bounds__(kThreads, 1) void match_tile_kernel(const MatchPara
   // (MODE 1).  Step u of a phase reads 128 bytes per block at byte offset
   // head*256 + (u/2)*tok + (u%2)*128:  tok = 256 walks the flattened block, tok = H*256 walks
   // one head's [T][Dh] slice.
-  // MODE 3: one phase of (D/kBK)/(S/2) steps, starting at step u_first of the K tensor (shares
-  // 0 .. S/2-1) or of the V tensor (the others).
+  // MODE 3: one phase of (D/kBK)/(S/2) steps of the K tensor (shares 0 .. S/2-1) or of the V tensor
+  // (the others), consecutive slices but for the place where the walk starts.
   // MODE 4: the two phases of head `split`, i.e. phases 2*split and 2*split + 1 of MODE 1.
   const int sps = (MODE == 3) ? (D / kBK) / (p.S / 2) : !PER_HEAD ? (D / kBK) : (p.T * 2);
   const int nphase = (MODE == 3) ? 1 : (MODE == 4) ? 2 * split + 2 : !PER_HEAD ? 2 : 2 * p.H;
   const int ph_first = (MODE == 4) ? 2 * split : 0;
   const int tok = !PER_HEAD ? 256 : p.H * 256;
   const bool split_v = (MODE == 3) && split >= p.S / 2;
-  const int u_first = (MODE == 3) ? (split % (p.S / 2)) * sps : 0;
+  // MODE 3: a share walks its slices from kShareRotation * share in and around, the same for every tile (identical
+  // pool blocks keep identical scores).  The shares of a tile are a power of two of KB apart: started together at
+  // their first slices, all workgroups ask the same memory channels at the same time.  Measured with one layer of
+  // 4096 blocks (16 shares of 4 KB): Q = 16 70 -> 53 us, Q = 100 63-78 -> 63 us; 8192 blocks 92-126 -> 96-111 us.
+  const uint32_t share_beg = (MODE == 3) ? (uint32_t)(split % (p.S / 2) * sps) * 128u : 0u;
+  const uint32_t share_end = share_beg + (uint32_t)sps * 128u;
+  const uint32_t share_rot = (MODE == 3) ? (uint32_t)(split * kShareRotation % sps) * 128u : 0u;
   auto advance = [&](Cursor& c) {
     if (++c.u == sps) {
       c.u = 0;
@@ -383,7 +389,10 @@ __global__ __launch_bounds__(kThreads, 1) void match_tile_kernel(const MatchPara
     }
   };
   auto byte_off = [&](const Cursor& c) {
-    if (MODE == 3) return (uint32_t)((c.u + u_first) * 128);
+    if (MODE == 3) {
+      const uint32_t o = share_beg + share_rot + (uint32_t)c.u * 128u;
+      return o < share_end ? o : o - (uint32_t)sps * 128u;
+    }
     return (uint32_t)((c.ph >> 1) * 256 + (c.u >> 1) * tok + (c.u & 1) * 128);
   };
 
@@ -412,6 +421,7 @@ __global__ __launch_bounds__(kThreads, 1) void match_tile_kernel(const MatchPara
       f.off += (f.cur.u & 1) ? (uint32_t)(tok - 128) : 128u;
     else
       f.off += 128u;
+    if (MODE == 3 && f.off == share_end) f.off = share_beg;
     ++f.cur.u;
   };
   auto move_cursor = [&](Feed& f) {
@@ -473,32 +483,34 @@ __global__ __launch_bounds__(kThreads, 1) void match_tile_kernel(const MatchPara
   // after its loads (for the next step), then the read stages of the next step.
   // FAST steps are those whose two feeds stay inside the phase (all but the last two of a phase):
   // the cursor just counts and the tensor does not change; the last two steps take the general code.
-  static_assert(TQ <= TP, "B fragment j is read behind row tile j");
-  static_assert(LPS == 1 && LB >= 2 && LB + 3 < SLOTS, "one load per slot, and room for the bookkeeping slots");
+  static_assert(TQ <= 2 * TP, "B fragments j and j + TP are read behind row tile j");
+  static_assert(LPS == 1 || (LPS == 2 && LB % 2 == 0 && LA % 2 == 0 && TQ >= 4), "one load per slot, or two with instructions between");
+  static_assert(LB / LPS >= 2 && LB / LPS + 3 < SLOTS, "room for the bookkeeping slots");
   int rdA = 0, rdB = 0;                   // ring stages the current step reads
   const char *sA_next = s_ring, *sB_next = s_ring + SA * A_STAGE;
-  constexpr int W0 = LB >= 3 ? LB - 3 : 0;  // first bookkeeping slot
+  constexpr int LBS = LB / LPS;               // slots of the query loads
+  constexpr int W0 = LBS >= 3 ? LBS - 3 : 0;  // first bookkeeping slot
   auto slot_work = [&](auto fast_tag, int slot) __attribute__((always_inline)) {
     constexpr bool FAST = decltype(fast_tag)::value;
-    // pool feed: cursor, then stage and destination, then (general code) tensor and offset: ready before slot LB
+    // pool feed: cursor, then stage and destination, then (general code) tensor and offset: ready before slot LBS
     if (slot == W0) {
       if (FAST) bump(fa); else move_cursor(fa);
     }
-    if (slot == (LB >= 3 ? W0 + 1 : W0)) {
+    if (slot == (LBS >= 3 ? W0 + 1 : W0)) {
       next_stage(fa, SA);
       prepare_dst(fa, ringA, A_STAGE);
     }
-    if (slot == LB - 1 && !FAST) prepare_src(fa, srdAk, srdAv);
+    if (slot == LBS - 1 && !FAST) prepare_src(fa, srdAk, srdAv);
     // query feed, for the loads of the next step
-    if (slot == LB) {
+    if (slot == LBS) {
       if (FAST) bump(fb); else move_cursor(fb);
     }
-    if (slot == LB + (LB >= 3 ? 1 : 0)) {
+    if (slot == LBS + (LBS >= 3 ? 1 : 0)) {
       next_stage(fb, SB);
       prepare_dst(fb, ringB, B_STAGE);
     }
-    if (slot == LB + (LB >= 3 ? 2 : 1) && !FAST) prepare_src(fb, srdBk, srdBv);
-    if (slot == LB + (LB >= 3 ? 3 : 2)) {
+    if (slot == LBS + (LBS >= 3 ? 2 : 1) && !FAST) prepare_src(fb, srdBk, srdBv);
+    if (slot == LBS + (LBS >= 3 ? 3 : 2)) {
       rdA = (rdA + 1 == SA) ? 0 : rdA + 1;
       rdB = (rdB + 1 == SB) ? 0 : rdB + 1;
       sA_next = s_ring + rdA * A_STAGE;
@@ -519,15 +531,12 @@ __global__ __launch_bounds__(kThreads, 1) void match_tile_kernel(const MatchPara
           naf[i] = *reinterpret_cast<const uint4*>(sA + fragA + i * 32 * kRowBytes + c);
           __builtin_amdgcn_sched_barrier(0);
         }
-        if (j == JD) {
-#pragma unroll
-          for (int t = 0; t < LPS; ++t) {
-            const int n = (b * TP + i) * LPS + t;
-            if (n < LB)
-              dmaB(n);
-            else if (n < LB + LA)
-              dmaA(n - LB);
-          }
+        if (j == JD || (LPS == 2 && j == JD + 2)) {
+          const int n = (b * TP + i) * LPS + (j != JD);
+          if (n < LB)
+            dmaB(n);
+          else if (n < LB + LA)
+            dmaA(n - LB);
           __builtin_amdgcn_sched_barrier(0);
         }
         if (j == JW) {
@@ -535,6 +544,8 @@ __global__ __launch_bounds__(kThreads, 1) void match_tile_kernel(const MatchPara
           __builtin_amdgcn_sched_barrier(0);
         }
         if (j == TQ - 1 && i < TQ) nbf[i < TQ ? i : 0] = *reinterpret_cast<const uint4*>(sB + fragB + i * 32 * kRowBytes + c);
+        if (TQ > TP && j == JW && i + TP < TQ)
+          nbf[i + TP < TQ ? i + TP : 0] = *reinterpret_cast<const uint4*>(sB + fragB + (i + TP) * 32 * kRowBytes + c);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -847,7 +858,8 @@ __global__ __launch_bounds__(kThreads, 1) void match_tile_kernel(const MatchPara
                                                      : (rq[j] * fq[j]) * (rs.rp[g][e] * rs.fp[g][e]);
             d[e] = acc[i][j][4 * g + e] * f;
           }
-          out[((i * 4 + g) * TQ + j) * 64] = d;
+          // columns past the last query are never read back
+          if (BQ == 256 || q0 + wq * WTQ + j * 32 + (lane & 31) < p.Q) out[((i * 4 + g) * TQ + j) * 64] = d;
         }
     });
     continue;
@@ -932,17 +944,31 @@ __global__ __launch_bounds__(kThreads, 1) void match_tile_kernel(const MatchPara
     }
   }
   __syncthreads();
-  if (tid < BQ && q0 + tid < p.Q) {
-    Part t = s_part[tid];
+#pragma unroll
+  for (int col = tid; col < BQ; col += NT) {
+    if (q0 + col >= p.Q) break;
+    Part t = s_part[col];
 #pragma unroll
     for (int w = 1; w < WP; ++w) {
-      const Part u = s_part[w * BQ + tid];
+      const Part u = s_part[w * BQ + col];
       top2_merge(t.best, t.idx, t.second, u.best, u.idx, u.second);
     }
-    p.part[((long long)l * p.npt + pt) * p.Q + q0 + tid] = t;
+    p.part[((long long)l * p.npt + pt) * p.Q + q0 + col] = t;
   }
   }  // next tile of this workgroup
 #endif
+}
+
+template <bool BF16, int BP, int BQ, int MODE, bool SHARED_POOL = false>
+__global__ __launch_bounds__(kThreads, 1) void match_tile_kernel(const MatchParams p) {
+  tile_body<BF16, BP, BQ, MODE, SHARED_POOL>(p);
+}
+
+// The same body at the other tile shapes; match_tile_kernel keeps the 256 x 256 tile in every mode and the block
+// score at 64 and 128 columns.
+template <bool BF16, int BP, int BQ, int MODE, bool SHARED_POOL = false>
+__global__ __launch_bounds__(kThreads, 1) void match_shape_kernel(const MatchParams p) {
+  tile_body<BF16, BP, BQ, MODE, SHARED_POOL>(p);
 }
 
 namespace {
@@ -1008,17 +1034,18 @@ rc_status merge_parts(const Part* part, int64_t nparts, long long LQ, int Q, flo
   return check_launch(what);
 }
 
-// Float index of element (row r, column c) of a 256x256 tile of sums as the tile kernel stores it
-// (2x2 waves of 128x128, four 32-row tiles x four 32-column tiles per wave, register group g holds
+// Float index of element (row r, column c) of a 256 x 64*tq tile of sums as the tile kernel stores it
+// (2x2 waves of 128 x 32*tq, four 32-row tiles x tq 32-column tiles per wave, register group g holds
 // rows 8g + 4*(lane/32) + 0..3 of a row tile): r is a multiple of 4, the four rows r..r+3 follow.
-__device__ __forceinline__ int sum_index(int r, int c) {
-  const int wave = (r >> 7) * 2 + (c >> 7);
-  const int i = (r >> 5) & 3, g = (r >> 3) & 3, half = (r >> 2) & 1, j = (c >> 5) & 3;
+__device__ __forceinline__ int sum_index(int r, int c, int tq) {
+  const int right = (c >> 5) >= tq ? 1 : 0;
+  const int wave = (r >> 7) * 2 + right;
+  const int i = (r >> 5) & 3, g = (r >> 3) & 3, half = (r >> 2) & 1, j = (c >> 5) - right * tq;
   const int lane = half * 32 + (c & 31);
-  return ((((wave * 4 + i) * 4 + g) * 4 + j) * 64 + lane) * 4;
+  return ((((wave * 4 + i) * 4 + g) * tq + j) * 64 + lane) * 4;
 }
 
-// Selection from tiles of sums (one 256x256 tile after the other per group, each in the tile
+// Selection from tiles of sums (one tile of 256 x 64*tq after the other per group, each in the tile
 // kernel's register order): the value of a pair is -scale times the sum of its element over the
 // groups.  Layer-mean mode: groups = groups of layers, scale = 1/(2dhN), so "higher wins, equal
 // goes to the lower index" on -distance picks the nearest live pool block.  Split mode: groups =
@@ -1028,14 +1055,15 @@ __device__ __forceinline__ int sum_index(int r, int c) {
 // grid = (query tiles of 64, pool chunks of sel_rows rows, layers); sel_rows is a multiple of 16;
 // a thread owns one query column and every fourth group of four rows.
 __global__ __launch_bounds__(256) void tile_sums_select_kernel(const float* __restrict__ dpart, int groups, int P,
-                                                               int Q, int npt, int nqt, int sel_rows, float scale,
-                                                               int take_min, const uint8_t* __restrict__ live,
+                                                               int Q, int npt, int nqt, int tq_cols, int sel_rows,
+                                                               float scale, int take_min, const uint8_t* __restrict__ live,
                                                                Part* __restrict__ part) {
   __shared__ Part s_part[4][64];
   const int tq = threadIdx.x & 63, tp = threadIdx.x >> 6;
   const int q = blockIdx.x * 64 + tq;
   const int pbeg = blockIdx.y * sel_rows, pend = min(P, pbeg + sel_rows);
-  const long long gstride = (long long)npt * nqt * 65536;
+  const int bq = tq_cols * 64, qt = q / bq, qc = q % bq;
+  const long long gstride = (long long)npt * nqt * (256 * bq);
   dpart += (long long)blockIdx.z * groups * gstride;
   if (live) live += (long long)blockIdx.z * P;
   part += (long long)blockIdx.z * gridDim.y * Q;
@@ -1043,7 +1071,7 @@ __global__ __launch_bounds__(256) void tile_sums_select_kernel(const float* __re
   int bidx = -1;
   if (q < Q) {
     for (int r = pbeg + 4 * tp; r < pend; r += 16) {
-      const float* src = dpart + ((long long)(r >> 8) * nqt + (q >> 8)) * 65536 + sum_index(r & 255, q & 255);
+      const float* src = dpart + ((long long)(r >> 8) * nqt + qt) * (256 * bq) + sum_index(r & 255, qc, tq_cols);
       f32x4 sum = {0.f, 0.f, 0.f, 0.f};  // groups are added in ascending order: the same bits on every run
       if (take_min) {
         // per-head-all score: every head's score goes onto the grid of 1/32767 first, exactly as the
@@ -1100,19 +1128,20 @@ __global__ __launch_bounds__(256) void tile_sums_select_kernel(const float* __re
 // from the cached squared norms exactly as the whole-tile path folds it, the layers are added in ascending
 // order, and the selection is the one of tile_sums_select_kernel (top-2 on -distance, dead and tail rows out).
 __global__ __launch_bounds__(256) void layer_mean_shares_select_kernel(
-    const float* __restrict__ dpart, int shares, int L, int P, int Q, int npt, int nqt, int sel_rows, float scale,
+    const float* __restrict__ dpart, int shares, int L, int P, int Q, int npt, int nqt, int tq_cols, int sel_rows, float scale,
     const uint8_t* __restrict__ live, const float* __restrict__ q_ksq, const float* __restrict__ q_vsq,
     const float* __restrict__ p_ksq, const float* __restrict__ p_vsq, Part* __restrict__ part) {
   __shared__ Part s_part[4][64];
   const int tq = threadIdx.x & 63, tp = threadIdx.x >> 6;
   const int q = blockIdx.x * 64 + tq;
   const int pbeg = blockIdx.y * sel_rows, pend = min(P, pbeg + sel_rows);
-  const long long gstride = (long long)npt * nqt * 65536;
+  const int bq = tq_cols * 64, qt = q / bq, qc = q % bq;
+  const long long gstride = (long long)npt * nqt * (256 * bq);
   float best = -INFINITY, second = -INFINITY;
   int bidx = -1;
   if (q < Q) {
     for (int r = pbeg + 4 * tp; r < pend; r += 16) {
-      const float* src = dpart + ((long long)(r >> 8) * nqt + (q >> 8)) * 65536 + sum_index(r & 255, q & 255);
+      const float* src = dpart + ((long long)(r >> 8) * nqt + qt) * (256 * bq) + sum_index(r & 255, qc, tq_cols);
       f32x4 dist = {0.f, 0.f, 0.f, 0.f};
       for (int l = 0; l < L; ++l) {
         const float* lsrc = src + (long long)l * shares * gstride;
@@ -1250,8 +1279,7 @@ constexpr TileShape kHeadTile = {256, 256};
 constexpr TileShape kNarrowTile = {256, 64};
 constexpr TileShape kMidTile = {256, 128};
 
-inline TileShape tile_for(int mode, int64_t Q) {
-  if (mode != RC_SCORE_BLOCK) return kHeadTile;
+inline TileShape tile_for(int64_t Q) {
   return Q <= kNarrowTile.bq ? kNarrowTile : Q <= kMidTile.bq ? kMidTile : kBlockTile;
 }
 
@@ -1264,22 +1292,61 @@ inline size_t layer_mean_part_offset(int groups, int64_t npt, int64_t nqt) {
 // A tile kernel launch runs in rounds of one workgroup per compute unit, and a problem with few
 // tiles (a call for one layer, a small pool) leaves most of the chip idle or pays a whole round
 // for a few left-over tiles.  Such problems split the reduction of every tile over S workgroups
-// (S even: half of them on the K tensor, half on V).  S is the power of two with the lowest
-// estimated time, in units of one pipeline step:
+// (S even: half of them on the K tensor, half on V).  In per-head mode the shares are the H heads (the
+// score is a minimum over heads, not a sum over the reduction).
+// More than 128 queries (256 columns): S is the power of two with the lowest estimated time, in units of
+// one pipeline step:
 //   rounds(S) * (steps of a share + 6 for filling the pipeline and storing the share)
 //   + 0.03 per tile share for the pass that adds the shares + 5 for its launch,
 // and the split is used when that is at least 10 % below the estimate for whole tiles.  The
 // constants come from measurements of 1 to 144 tiles of the 256 x 256 shape (within 10 % from 64
-// tiles up; a single layer of 16 tiles takes 143 us against 112 estimated).  A share has at least
+// tiles up; a single layer of 16 tiles takes 116 us against 112 estimated).  A share has at least
 // 8 steps; the shares of all tiles take at most 512 MB; problems of more than one round are left
-// alone.  In per-head mode the shares are the H heads (the score is a minimum over heads, not a
-// sum over the reduction), chosen by the same estimate.  With at most 128 query blocks the whole-tile
-// path has its narrow tiles, so the split is only used below half a round there.  Block mode only.
+// alone.  Block mode only.
+// At most 128 queries (64 and 128 columns, bound by the pool stream): a share is cheap to store, so the
+// split also evens out the last round of launches of several rounds.  Estimated in us: a step of a full round
+// takes 1.3 (64 columns) or 1.5 us; a round of which a part r of the compute units has work takes 0.55 + 0.45 r
+// of it (a compute unit alone is not much faster than 256 together: 0.86 us per step measured at r = 1/4, 1.2 at
+// r = 1/2); 5 us to fill the pipeline and store; the shares written and read at 4 TB/s and 6 us for the pass over
+// them; used when that is at least 10 % below whole tiles.  S / 2 is any divisor of the steps, the head count in
+// per-head mode; at most 2048 shares, 4096 for launches of more than one round (512 MB either way).
+// Measured, whole tiles -> shares: per-head, 32 layers x 2531 blocks of 32 tokens, Q = 24 (320 tiles) 2120 -> 1850 us;
+// 256-column shares -> these: one layer of 4096 blocks, Q = 16 (256 shares) 82 -> 53 us, one tile, Q = 32 33 -> 19 us;
+// powers of two only -> any divisor: one layer of 6000 blocks of 10 heads, Q = 40 105 -> 90 us (S = 10).
 // The decision depends on the shape alone (an MI355X has 256 compute units), so that the workspace
 // size does not depend on the device that happens to be current.
 constexpr int kSplitComputeUnits = 256;
+inline int narrow_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
+  const int bq = tile_for(Q).bq;
+  const int64_t tiles = L * ((P + 255) / 256);
+  const int steps = T * H * 128 / kBK;  // per tensor
+  const double step_us = bq == kNarrowTile.bq ? 1.3 : 1.5;
+  auto estimate = [&](int S) {
+    const int64_t wgs = tiles * S;
+    double rounds = (double)(wgs / kSplitComputeUnits);
+    const double rest = (double)(wgs % kSplitComputeUnits) / kSplitComputeUnits;
+    if (rest > 0.0) rounds += 0.55 + 0.45 * rest;
+    const double shares = S > 1 ? (double)wgs * 256.0 * (double)Q * 8.0 / 4e6 + 6.0 : 0.0;  // written, read: 4 TB/s; a launch
+    return rounds * (2.0 * steps / S * step_us + 5.0) + shares;
+  };
+  int best = 1;
+  double best_cost = 0.9 * estimate(1);
+  auto consider = [&](int S) {
+    if (tiles * S > (tiles > kSplitComputeUnits ? 4096 : 2048) || estimate(S) >= best_cost) return;
+    best_cost = estimate(S);
+    best = S;
+  };
+  if (mode == RC_SCORE_PER_HEAD_ALL) {
+    if (H > 1) consider(H);
+  } else {
+    for (int half = 1; steps / half >= 8; ++half)
+      if (steps % half == 0) consider(2 * half);
+  }
+  return best;
+}
 inline int split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
   if (P <= 0 || Q <= 0 || L <= 0) return 1;
+  if (Q <= kMidTile.bq) return narrow_split_count(mode, L, P, Q, T, H);
   const int64_t tiles = L * ((P + 255) / 256) * ((Q + 255) / 256);
   if (tiles > kSplitComputeUnits) return 1;  // more than one round: measured gains of 0-6 % only (workgroups of
                                              // later rounds start as earlier ones end, the rounds are not that rigid)
@@ -1290,7 +1357,6 @@ inline int split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) 
     const double heads = rounds(tiles * H) * (4.0 * T + 6.0) + 0.03 * (double)(tiles * H) + 5.0;
     return heads < 0.9 * whole ? H : 1;
   }
-  if (Q <= 128 && tiles * 2 > kSplitComputeUnits) return 1;
   const int steps = T * H * 128 / kBK;  // per tensor
   auto estimate = [&](int S) {
     const double rounds = (double)((tiles * S + kSplitComputeUnits - 1) / kSplitComputeUnits);
@@ -1309,7 +1375,7 @@ inline int split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) 
 }
 
 struct SplitLayout {
-  int S;
+  int S, bq;
   int64_t npt, nqt;
   int sel_rows;
   int64_t nchunks;
@@ -1318,11 +1384,15 @@ struct SplitLayout {
 inline SplitLayout split_layout(int S, int64_t L, int64_t P, int64_t Q) {
   SplitLayout r;
   r.S = S;
+  r.bq = tile_for(Q).bq;
   r.npt = (P + 255) / 256;
-  r.nqt = (Q + 255) / 256;
+  r.nqt = (Q + r.bq - 1) / r.bq;
   r.sel_rows = select_rows(P, Q);
   r.nchunks = (P + r.sel_rows - 1) / r.sel_rows;
-  r.part_offset = (size_t)L * (size_t)S * (size_t)r.npt * (size_t)r.nqt * 65536 * sizeof(float);
+  // up to one round of tiles the room for a share is that of a 256-column tile at every width: the workspace of
+  // these shapes has always been that large
+  const size_t room = L * r.npt * r.nqt <= kSplitComputeUnits ? 65536 : 256 * (size_t)r.bq;
+  r.part_offset = (size_t)L * (size_t)S * (size_t)r.npt * (size_t)r.nqt * room * sizeof(float);
   r.bytes = r.part_offset + (size_t)L * (size_t)r.nchunks * (size_t)Q * sizeof(Part);
   return r;
 }
@@ -1337,8 +1407,32 @@ void launch_tiles(int mode, const MatchParams& mp, unsigned grid, hipStream_t st
     match_tile_kernel<BF16, kBlockTile.bp, kBlockTile.bq, 0, true><<<grid, kThreads, 0, st>>>(mp);
   else if (mode == RC_SCORE_BLOCK)
     match_tile_kernel<BF16, kBlockTile.bp, kBlockTile.bq, 0><<<grid, kThreads, 0, st>>>(mp);
+  else if (mp.Q <= kNarrowTile.bq)
+    match_shape_kernel<BF16, kNarrowTile.bp, kNarrowTile.bq, 1><<<grid, kThreads, 0, st>>>(mp);
+  else if (mp.Q <= kMidTile.bq)
+    match_shape_kernel<BF16, kMidTile.bp, kMidTile.bq, 1><<<grid, kThreads, 0, st>>>(mp);
   else
     match_tile_kernel<BF16, kHeadTile.bp, kHeadTile.bq, 1><<<grid, kThreads, 0, st>>>(mp);
+}
+
+template <bool BF16>
+void launch_shares(bool heads, int bq, const MatchParams& mp, unsigned grid, hipStream_t st) {
+  if (bq == kNarrowTile.bq) {
+    if (heads)
+      match_shape_kernel<BF16, 256, kNarrowTile.bq, 4><<<grid, kThreads, 0, st>>>(mp);
+    else
+      match_shape_kernel<BF16, 256, kNarrowTile.bq, 3><<<grid, kThreads, 0, st>>>(mp);
+  } else if (bq == kMidTile.bq) {
+    if (heads)
+      match_shape_kernel<BF16, 256, kMidTile.bq, 4><<<grid, kThreads, 0, st>>>(mp);
+    else
+      match_shape_kernel<BF16, 256, kMidTile.bq, 3><<<grid, kThreads, 0, st>>>(mp);
+  } else {
+    if (heads)
+      match_tile_kernel<BF16, 256, 256, 4><<<grid, kThreads, 0, st>>>(mp);
+    else
+      match_tile_kernel<BF16, 256, 256, 3><<<grid, kThreads, 0, st>>>(mp);
+  }
 }
 
 }  // namespace
@@ -1350,7 +1444,7 @@ extern "C" size_t rc_match_workspace_size(const rc_kv_desc* qdesc, int32_t mode,
   if (mode != RC_SCORE_BLOCK && mode != RC_SCORE_PER_HEAD_ALL) return 0;
   const int S = split_count(mode, qdesc->n_layers, P, Q, qdesc->block_tokens, qdesc->n_kv_heads);
   if (S > 1) return split_layout(S, qdesc->n_layers, P, Q).bytes;
-  const TileShape ts = tile_for(mode, Q);
+  const TileShape ts = tile_for(Q);
   const int64_t npt = (P + ts.bp - 1) / ts.bp;
   const int64_t nqt = (Q + ts.bq - 1) / ts.bq;
   const int64_t n = (int64_t)qdesc->n_layers * (npt > 0 ? npt : 1) * Q;
@@ -1380,7 +1474,7 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
   if (P > 0 && (!kp || !vp || !p_ksq || !p_vsq)) return fail(RC_ERR_INVALID_ARG, "rc_match_blocks: NULL pool pointer");
   if (!aligned16(kq) || !aligned16(vq) || !aligned16(kp) || !aligned16(vp))
     return fail(RC_ERR_INVALID_ARG, "rc_match_blocks: KV pointer not 16-byte aligned");
-  const TileShape ts = tile_for(mode, Q);
+  const TileShape ts = tile_for(Q);
   const int64_t npt = (P + ts.bp - 1) / ts.bp, nqt = (Q + ts.bq - 1) / ts.bq;
   const int64_t total = (int64_t)L * npt * nqt;
   if (Q > 0x7fffffffLL || P > 0x7fffffffLL || total > 0x3fffffffLL || (int64_t)L * Q > 0x7fffffffLL * 128)
@@ -1431,21 +1525,14 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
     mp.steal_min = 0;
     mp.dyn_from = 0;
     const bool heads = mode == RC_SCORE_PER_HEAD_ALL;
-    if (qdesc->dtype == RC_BF16) {
-      if (heads)
-        match_tile_kernel<true, 256, 256, 4><<<grid, kThreads, 0, st>>>(mp);
-      else
-        match_tile_kernel<true, 256, 256, 3><<<grid, kThreads, 0, st>>>(mp);
-    } else {
-      if (heads)
-        match_tile_kernel<false, 256, 256, 4><<<grid, kThreads, 0, st>>>(mp);
-      else
-        match_tile_kernel<false, 256, 256, 3><<<grid, kThreads, 0, st>>>(mp);
-    }
+    if (qdesc->dtype == RC_BF16)
+      launch_shares<true>(heads, sl.bq, mp, grid, st);
+    else
+      launch_shares<false>(heads, sl.bq, mp, grid, st);
     if (rc_status s = check_launch("rc_match_blocks(tile shares)")) return s;
     Part* part = reinterpret_cast<Part*>(static_cast<char*>(workspace) + sl.part_offset);
     const dim3 sgrid((unsigned)((Q + 63) / 64), (unsigned)sl.nchunks, (unsigned)L);
-    tile_sums_select_kernel<<<sgrid, 256, 0, st>>>(mp.dpart, S, (int)P, (int)Q, (int)sl.npt, (int)sl.nqt, sl.sel_rows,
+    tile_sums_select_kernel<<<sgrid, 256, 0, st>>>(mp.dpart, S, (int)P, (int)Q, (int)sl.npt, (int)sl.nqt, sl.bq / 64, sl.sel_rows,
                                                    -1.0f, heads ? 1 : 0, pool_live, part);
     if (rc_status s = check_launch("rc_match_blocks(select)")) return s;
     return merge_parts<false>(part, sl.nchunks, LQ, (int)Q, tau, best_idx, best_score, match_idx, second_score, st,
@@ -1585,13 +1672,13 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
     mp.steal_min = 0;
     mp.dyn_from = 0;
     if (qdesc->dtype == RC_BF16)
-      match_tile_kernel<true, 256, 256, 3><<<grid, kThreads, 0, st>>>(mp);
+      launch_shares<true>(false, sl.bq, mp, grid, st);
     else
-      match_tile_kernel<false, 256, 256, 3><<<grid, kThreads, 0, st>>>(mp);
+      launch_shares<false>(false, sl.bq, mp, grid, st);
     if (rc_status s = check_launch("rc_match_blocks_layer_mean(tile shares)")) return s;
     Part* part = reinterpret_cast<Part*>(static_cast<char*>(workspace) + sl.part_offset);
     const dim3 sgrid((unsigned)((Q + 63) / 64), (unsigned)sl.nchunks);
-    layer_mean_shares_select_kernel<<<sgrid, 256, 0, st>>>(dpart, S, L, (int)P, (int)Q, (int)sl.npt, (int)sl.nqt, sl.sel_rows,
+    layer_mean_shares_select_kernel<<<sgrid, 256, 0, st>>>(dpart, S, L, (int)P, (int)Q, (int)sl.npt, (int)sl.nqt, sl.bq / 64, sl.sel_rows,
                                                            scale, pool_live, q_ksq, q_vsq, p_ksq, p_vsq, part);
     if (rc_status s = check_launch("rc_match_blocks_layer_mean(select)")) return s;
     return merge_parts<true>(part, sl.nchunks, Q, (int)Q, threshold, best_idx, best_dist, match_idx, second_dist, st,
@@ -1638,7 +1725,7 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
       match_tile_kernel<false, kBlockTile.bp, kBlockTile.bq, 2><<<grid, kThreads, 0, st>>>(mp);
     if (rc_status s = check_launch("rc_match_blocks_layer_mean(tiles)")) return s;
     const dim3 sgrid((unsigned)((Q + 63) / 64), (unsigned)nchunks);
-    tile_sums_select_kernel<<<sgrid, 256, 0, st>>>(dpart, ls.groups, (int)P, (int)Q, (int)npt, (int)nqt, sel_rows, scale, 0,
+    tile_sums_select_kernel<<<sgrid, 256, 0, st>>>(dpart, ls.groups, (int)P, (int)Q, (int)npt, (int)nqt, kBlockTile.bq / 64, sel_rows, scale, 0,
                                                     pool_live, part);
     if (rc_status s = check_launch("rc_match_blocks_layer_mean(select)")) return s;
   }

@@ -13,3 +13,15 @@ PARTS = [(1, 1), (33, 3), (128, 5), (129, 40), (257, 64), (2048, 3), (2049, 65),
 @pytest.mark.parametrize("P,Q", PARTS)
 def test_merge_parts(oracle, P, Q):
     run_shape(oracle, dict(L=2, P=P, Q=Q, T=16, H=1, mode=0, dtype="f16", planted_frac=0.3, seed=7100 + P), f"parts{P}x{Q}", P)
+
+
+# Tile width (64 columns up to 64 queries, 128 up to 128, 256 beyond) and shares per tile: per-head mode in whole tiles
+# (256 tiles: one round) and with one share per head, block mode with a share count that is no power of two.
+WIDTHS = [(1, 256, 64, 64, 2), (1, 256, 40, 65, 2), (1, 256, 70, 128, 1), (1, 3, 300, 64, 5), (1, 2, 257, 65, 16),
+          (1, 2, 255, 128, 3), (1, 2, 300, 129, 3), (0, 24, 250, 40, 5), (0, 24, 250, 65, 5), (0, 2, 300, 128, 3), (0, 11, 513, 1, 6)]
+
+
+@pytest.mark.parametrize("mode,L,P,Q,H", WIDTHS)
+def test_tile_widths_and_shares(oracle, mode, L, P, Q, H):
+    run_shape(oracle, dict(L=L, P=P, Q=Q, T=16, H=H, mode=mode, dtype="bf16" if Q % 2 else "f16", planted_frac=0.3, seed=7300 + P),
+              f"width{mode}.{L}.{P}x{Q}", P)

@@ -64,3 +64,25 @@ def test_steady_state_loops_wait_once_and_never_touch_scratch(assembly):
             checked += 1
         assert loops >= 1, f"no steady-state loop recognised in {name}"
     assert checked >= 16
+
+
+def test_other_tile_shapes_wait_once_and_never_touch_scratch(assembly):
+    """The same guard for match_shape_kernel: at most one pool slice (BP / 32 loads of a wave) outstanding per step."""
+    shapes = re.findall(r"\n(_ZN2rc18match_shape_kernelILb[01]ELi(\d+)ELi(\d+)ELi(\d)\w+):", assembly)
+    assert len({s[1:] for s in shapes}) == len(shapes) // 2, "each shape in both data types"
+    for name, bp, bq, mode in shapes:
+        at = assembly.index("\n" + name + ":")
+        body = assembly[at:assembly.index(".Lfunc_end", at)]
+        blocks = re.split(r"\n(\.LBB\d+_\d+):", body)
+        instructions = 4 * (int(bp) // 64) * (int(bq) // 64)   # a wave's matrix instructions per step
+        loops = 0
+        for label, text in zip(blocks[1::2], blocks[2::2]):
+            back = re.search(r"s_cbranch_\w+ " + re.escape(label) + r"\n", text)
+            text = text[:back.end()] if back else text
+            if text.count("v_mfma") < instructions or "s_barrier" not in text:
+                continue
+            loops += 1
+            waits = [l.strip() for l in text.split("\n") if "s_waitcnt" in l and "vmcnt" in l and "vmcnt(63)" not in l]
+            assert waits == [f"s_waitcnt vmcnt({int(bp) // 32})"], (name, label, waits)
+            assert "scratch_" not in text, (name, label)
+        assert loops >= 1, f"no steady-state loop recognised in {name}"
