@@ -1273,15 +1273,47 @@ struct TileShape {
   int bp, bq;
 };
 constexpr TileShape kBlockTile = {256, 256};
-constexpr TileShape kHeadTile = {256, 256};
 // Few query blocks (a decoding step of a handful of requests): a 64-column tile does a quarter of
 // the matrix work per pool slice and leaves the kernel to the speed of the pool stream.
 constexpr TileShape kNarrowTile = {256, 64};
 constexpr TileShape kMidTile = {256, 128};
 
-inline TileShape tile_for(int64_t Q) {
-  return Q <= kNarrowTile.bq ? kNarrowTile : Q <= kMidTile.bq ? kMidTile : kBlockTile;
+// Query counts that a 256-column grid pads badly (160 queries are 1.6 times their work, 300 are 1.7 times):
+// a 192-column tile, and one of 192 pool rows x 320 columns with as many accumulators as fit beside it.
+constexpr TileShape kWideTile = {256, 192};
+constexpr TileShape kLowTile = {192, 320};
+
+// Tile of a search in whole tiles.  Up to 128 queries the narrow ones.  Beyond, the shape with the lowest estimate
+//   rounds(shape) * (us per pipeline step of a full round, by the number of query tiles: 1, 2, more)
+// where a last round of which a part r of the compute units has work takes 0.55 + 0.45 r of a full one; another
+// shape than 256 x 256 is taken when it is at least 4 % below.  The constants are measured (48 layers x 4096 blocks,
+// 16 layers x 4100 blocks of 32 tokens per head); where the lines lie, in us per launch, 256 / 192 / 320 columns:
+//   block     Q = 160 2802 / 2487 / 3427   256 3074 / 4038 / 3903   320 4950 / 4363 / 3987   384 5072 / 4490 / 7117
+//             Q = 512 5475 / 6188 / 7469   640 7470 / 7835 / 7124   960 10230 / 10388 / 10239
+//   per head  Q = 160 3239 / 2647 / 2900   300 5281 / 4007 / 3519   384 4914 / 4098 / 4998   640 7213 / 7005 / 5026
+inline TileShape tile_for(int mode, int64_t L, int64_t P, int64_t Q) {
+  if (Q <= kNarrowTile.bq) return kNarrowTile;
+  if (Q <= kMidTile.bq) return kMidTile;
+  constexpr TileShape shapes[3] = {kBlockTile, kWideTile, kLowTile};
+  constexpr double step_us[2][3][3] = {{{2.0, 1.75, 1.65}, {1.67, 1.42, 1.31}, {1.69, 1.6, 1.57}},
+                                       {{2.0, 2.0, 1.9}, {1.65, 1.5, 1.45}, {2.0, 1.7, 1.65}}};
+  int best = 0;
+  double best_cost = 0.0;
+  for (int i = 0; i < 3; ++i) {
+    const int64_t nqt = (Q + shapes[i].bq - 1) / shapes[i].bq;
+    const double part = (double)(L * ((P + shapes[i].bp - 1) / shapes[i].bp)) * (double)nqt / 256.0;  // an MI355X has 256 compute units
+    double rounds = (double)(int64_t)part;
+    if (part > rounds) rounds += 0.55 + 0.45 * (part - rounds);
+    const double cost = rounds * step_us[mode == RC_SCORE_PER_HEAD_ALL][i][nqt < 3 ? nqt - 1 : 2];
+    if (i == 0 || cost < (best == 0 ? 0.96 : 1.0) * best_cost) {
+      best = i;
+      best_cost = cost;
+    }
+  }
+  return shapes[best];
 }
+// Columns of a tile whose reduction is shared by several workgroups.
+inline int share_columns(int64_t Q) { return Q <= kNarrowTile.bq ? kNarrowTile.bq : Q <= kMidTile.bq ? kMidTile.bq : kBlockTile.bq; }
 
 // byte offset of the selection partials inside the layer-mean workspace (after the sums: one
 // 256x256 tile of floats per (group, pool tile, query tile))
@@ -1317,7 +1349,7 @@ inline size_t layer_mean_part_offset(int groups, int64_t npt, int64_t nqt) {
 // size does not depend on the device that happens to be current.
 constexpr int kSplitComputeUnits = 256;
 inline int narrow_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
-  const int bq = tile_for(Q).bq;
+  const int bq = share_columns(Q);
   const int64_t tiles = L * ((P + 255) / 256);
   const int steps = T * H * 128 / kBK;  // per tensor
   const double step_us = bq == kNarrowTile.bq ? 1.3 : 1.5;
@@ -1384,7 +1416,7 @@ struct SplitLayout {
 inline SplitLayout split_layout(int S, int64_t L, int64_t P, int64_t Q) {
   SplitLayout r;
   r.S = S;
-  r.bq = tile_for(Q).bq;
+  r.bq = share_columns(Q);
   r.npt = (P + 255) / 256;
   r.nqt = (Q + r.bq - 1) / r.bq;
   r.sel_rows = select_rows(P, Q);
@@ -1398,21 +1430,37 @@ inline SplitLayout split_layout(int S, int64_t L, int64_t P, int64_t Q) {
 }
 
 template <bool BF16>
-void launch_tiles(int mode, const MatchParams& mp, unsigned grid, hipStream_t st) {
-  if (mode == RC_SCORE_BLOCK && mp.Q <= kNarrowTile.bq)
-    match_tile_kernel<BF16, kNarrowTile.bp, kNarrowTile.bq, 0><<<grid, kThreads, 0, st>>>(mp);
-  else if (mode == RC_SCORE_BLOCK && mp.Q <= kMidTile.bq)
-    match_tile_kernel<BF16, kMidTile.bp, kMidTile.bq, 0><<<grid, kThreads, 0, st>>>(mp);
-  else if (mode == RC_SCORE_BLOCK && mp.nqt > 1)
-    match_tile_kernel<BF16, kBlockTile.bp, kBlockTile.bq, 0, true><<<grid, kThreads, 0, st>>>(mp);
-  else if (mode == RC_SCORE_BLOCK)
-    match_tile_kernel<BF16, kBlockTile.bp, kBlockTile.bq, 0><<<grid, kThreads, 0, st>>>(mp);
-  else if (mp.Q <= kNarrowTile.bq)
-    match_shape_kernel<BF16, kNarrowTile.bp, kNarrowTile.bq, 1><<<grid, kThreads, 0, st>>>(mp);
-  else if (mp.Q <= kMidTile.bq)
-    match_shape_kernel<BF16, kMidTile.bp, kMidTile.bq, 1><<<grid, kThreads, 0, st>>>(mp);
-  else
-    match_tile_kernel<BF16, kHeadTile.bp, kHeadTile.bq, 1><<<grid, kThreads, 0, st>>>(mp);
+void launch_tiles(int mode, TileShape ts, const MatchParams& mp, unsigned grid, hipStream_t st) {
+  auto is = [&](TileShape t) { return ts.bp == t.bp && ts.bq == t.bq; };
+  if (mode == RC_SCORE_BLOCK) {
+    if (is(kNarrowTile))
+      match_tile_kernel<BF16, kNarrowTile.bp, kNarrowTile.bq, 0><<<grid, kThreads, 0, st>>>(mp);
+    else if (is(kMidTile))
+      match_tile_kernel<BF16, kMidTile.bp, kMidTile.bq, 0><<<grid, kThreads, 0, st>>>(mp);
+    else if (is(kWideTile) && mp.nqt > 1)
+      match_shape_kernel<BF16, kWideTile.bp, kWideTile.bq, 0, true><<<grid, kThreads, 0, st>>>(mp);
+    else if (is(kWideTile))
+      match_shape_kernel<BF16, kWideTile.bp, kWideTile.bq, 0><<<grid, kThreads, 0, st>>>(mp);
+    else if (is(kLowTile) && mp.nqt > 1)
+      match_shape_kernel<BF16, kLowTile.bp, kLowTile.bq, 0, true><<<grid, kThreads, 0, st>>>(mp);
+    else if (is(kLowTile))
+      match_shape_kernel<BF16, kLowTile.bp, kLowTile.bq, 0><<<grid, kThreads, 0, st>>>(mp);
+    else if (mp.nqt > 1)
+      match_tile_kernel<BF16, kBlockTile.bp, kBlockTile.bq, 0, true><<<grid, kThreads, 0, st>>>(mp);
+    else
+      match_tile_kernel<BF16, kBlockTile.bp, kBlockTile.bq, 0><<<grid, kThreads, 0, st>>>(mp);
+  } else {
+    if (is(kNarrowTile))
+      match_shape_kernel<BF16, kNarrowTile.bp, kNarrowTile.bq, 1><<<grid, kThreads, 0, st>>>(mp);
+    else if (is(kMidTile))
+      match_shape_kernel<BF16, kMidTile.bp, kMidTile.bq, 1><<<grid, kThreads, 0, st>>>(mp);
+    else if (is(kWideTile))
+      match_shape_kernel<BF16, kWideTile.bp, kWideTile.bq, 1><<<grid, kThreads, 0, st>>>(mp);
+    else if (is(kLowTile))
+      match_shape_kernel<BF16, kLowTile.bp, kLowTile.bq, 1><<<grid, kThreads, 0, st>>>(mp);
+    else
+      match_tile_kernel<BF16, kBlockTile.bp, kBlockTile.bq, 1><<<grid, kThreads, 0, st>>>(mp);
+  }
 }
 
 template <bool BF16>
@@ -1444,7 +1492,7 @@ extern "C" size_t rc_match_workspace_size(const rc_kv_desc* qdesc, int32_t mode,
   if (mode != RC_SCORE_BLOCK && mode != RC_SCORE_PER_HEAD_ALL) return 0;
   const int S = split_count(mode, qdesc->n_layers, P, Q, qdesc->block_tokens, qdesc->n_kv_heads);
   if (S > 1) return split_layout(S, qdesc->n_layers, P, Q).bytes;
-  const TileShape ts = tile_for(Q);
+  const TileShape ts = tile_for(mode, qdesc->n_layers, P, Q);
   const int64_t npt = (P + ts.bp - 1) / ts.bp;
   const int64_t nqt = (Q + ts.bq - 1) / ts.bq;
   const int64_t n = (int64_t)qdesc->n_layers * (npt > 0 ? npt : 1) * Q;
@@ -1474,7 +1522,7 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
   if (P > 0 && (!kp || !vp || !p_ksq || !p_vsq)) return fail(RC_ERR_INVALID_ARG, "rc_match_blocks: NULL pool pointer");
   if (!aligned16(kq) || !aligned16(vq) || !aligned16(kp) || !aligned16(vp))
     return fail(RC_ERR_INVALID_ARG, "rc_match_blocks: KV pointer not 16-byte aligned");
-  const TileShape ts = tile_for(Q);
+  const TileShape ts = tile_for(mode, L, P, Q);
   const int64_t npt = (P + ts.bp - 1) / ts.bp, nqt = (Q + ts.bq - 1) / ts.bq;
   const int64_t total = (int64_t)L * npt * nqt;
   if (Q > 0x7fffffffLL || P > 0x7fffffffLL || total > 0x3fffffffLL || (int64_t)L * Q > 0x7fffffffLL * 128)
@@ -1572,9 +1620,9 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
     const unsigned grid = launch_grid((unsigned)mp.vgrid);
     if (rc_status s = prepare_schedule(mp, grid, static_cast<char*>(workspace) + need - schedule_bytes(total), st)) return s;
     if (qdesc->dtype == RC_BF16)
-      launch_tiles<true>(mode, mp, grid, st);
+      launch_tiles<true>(mode, ts, mp, grid, st);
     else
-      launch_tiles<false>(mode, mp, grid, st);
+      launch_tiles<false>(mode, ts, mp, grid, st);
     if (rc_status s = check_launch("rc_match_blocks(tiles)")) return s;
   }
   return merge_parts<false>(static_cast<const Part*>(workspace), npt, LQ, (int)Q, tau, best_idx, best_score, match_idx,

@@ -25,3 +25,16 @@ WIDTHS = [(1, 256, 64, 64, 2), (1, 256, 40, 65, 2), (1, 256, 70, 128, 1), (1, 3,
 def test_tile_widths_and_shares(oracle, mode, L, P, Q, H):
     run_shape(oracle, dict(L=L, P=P, Q=Q, T=16, H=H, mode=mode, dtype="bf16" if Q % 2 else "f16", planted_frac=0.3, seed=7300 + P),
               f"width{mode}.{L}.{P}x{Q}", P)
+
+
+# Shape of whole tiles beyond 128 queries: 256 x 192, 192 x 320 and 256 x 256 with one and more query tiles, pools that end
+# on and beside an edge of a tile.
+SHAPES = [(0, 260, 8, 129, 1), (0, 260, 193, 192, 1), (0, 260, 257, 193, 1), (0, 260, 192, 257, 1), (0, 260, 193, 320, 1),
+          (0, 260, 31, 321, 1), (0, 260, 40, 640, 1), (0, 260, 5, 641, 1), (1, 260, 193, 160, 1), (1, 130, 191, 300, 2), (1, 260, 40, 384, 1),
+          (1, 260, 20, 640, 1)]
+
+
+@pytest.mark.parametrize("mode,L,P,Q,H", SHAPES)
+def test_tile_shapes(oracle, mode, L, P, Q, H):
+    run_shape(oracle, dict(L=L, P=P, Q=Q, T=16, H=H, mode=mode, dtype="bf16" if Q % 2 else "f16", planted_frac=0.0 if P < 64 else 0.3,
+                           seed=7500 + P), f"shape{mode}.{L}.{P}x{Q}", P)
