@@ -440,10 +440,11 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
   // find each other's slice in the L2, and a line that is not kept can be gone before the last of them asks for
   // it: 0.5-1.4 % on the Q = 1024 workloads, and in the layer-mean mode, where those workgroups leave a fold
   // (a read-modify-write of 256 KB each) a few microseconds apart, twice the L2-out traffic and 6 % of the
-  // launch.  The cosine mode is compiled in both forms, the layer-mean mode without the hint; the per-head and
+  // launch.  The cosine mode is compiled in both forms, the layer-mean mode with the hint in the tiles of at most
+  // 128 columns, which are alone on their pool tile (1756 -> 1577 us, 64 layers x 2048 x 128); the per-head and
   // the few-tiles modes keep it (measured: no difference there).
   auto dmaA = [&](int i) {
-    dma16<MODE != 2 && !SHARED_POOL>(fa.srd, voff, fa.off + i * load_stride, fa.dst + i * NT * 16);
+    dma16<MODE == 2 ? BQ <= 128 : !SHARED_POOL>(fa.srd, voff, fa.off + i * load_stride, fa.dst + i * NT * 16);
   };
   auto dmaB = [&](int i) { dma16<false>(fb.srd, voff, fb.off + i * load_stride, fb.dst + i * NT * 16); };
 
@@ -706,6 +707,25 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
   // register order, not row-major: the four values a lane holds for (row tile i, register group
   // g, column tile j) are one 16-byte word at index ((wave*TP + i)*4 + g)*TQ + j)*64 + lane, so
   // every access of a wave is 1 KB contiguous (sum_index() below is the inverse map).
+  // Tiles of at most 128 columns have room: the running sum stays in registers until the group's last layer
+  // (REG_SUMS), the same additions in the same order.
+  constexpr bool REG_SUMS = MODE == 2 && TP * TQ <= 8;
+  f32x16 rsum[REG_SUMS ? TP : 1][REG_SUMS ? TQ : 1];
+  auto store_sums = [&]() {
+    f32x4* sums = reinterpret_cast<f32x4*>(p.dpart) + (((long long)lz * p.npt + pt) * p.nqt + qt) * (BP * BQ / 4) +
+                  (long long)wave * (TP * 4 * TQ * 64) + lane;
+#pragma unroll
+    for (int i = 0; i < TP; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int j = 0; j < TQ; ++j) {
+          const f32x16& r = rsum[REG_SUMS ? i : 0][REG_SUMS ? j : 0];
+          const f32x4 d = {r[4 * g], r[4 * g + 1], r[4 * g + 2], r[4 * g + 3]};
+          // columns past the last query are never read back
+          if (q0 + wq * WTQ + j * 32 + (lane & 31) < p.Q) sums[((i * 4 + g) * TQ + j) * 64] = d;
+        }
+  };
   auto fold = [&](const __amdgpu_buffer_rsrc_t& nQ, const __amdgpu_buffer_rsrc_t& nP, auto first_tag) {
     constexpr bool first = decltype(first_tag)::value;
     typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
@@ -725,7 +745,7 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         np[g] = __builtin_bit_cast(f32x4, (u32x4_t)__builtin_amdgcn_raw_buffer_load_b128(nP, (p0 + row_of(i, g)) * 4, 0, 0));
-        if (!first) {
+        if (!first && !REG_SUMS) {
 #pragma unroll
           for (int j = 0; j < TQ; ++j) old[g][j] = sums[((i * 4 + g) * TQ + j) * 64];
         }
@@ -740,10 +760,15 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
           for (int e = 0; e < 4; ++e) {
             const float d2 = fmaf(-2.f, acc[i][j][4 * g + e], nq[j] + np[g][e]);
             d[e] = __builtin_amdgcn_sqrtf(fmaxf(d2, 0.f));
-            if (!first) d[e] += old[g][j][e];
             acc[i][j][4 * g + e] = 0.f;
+            if (REG_SUMS) {
+              f32x16& r = rsum[REG_SUMS ? i : 0][REG_SUMS ? j : 0];
+              r[4 * g + e] = first ? d[e] : r[4 * g + e] + d[e];
+            } else if (!first) {
+              d[e] += old[g][j][e];
+            }
           }
-          sums[((i * 4 + g) * TQ + j) * 64] = d;
+          if (!REG_SUMS) sums[((i * 4 + g) * TQ + j) * 64] = d;
         }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -830,6 +855,7 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
       fb = Feed{{0, 0}, 0, srdBk, 0, 0};
       prologue();
     }
+    if (REG_SUMS) store_sums();
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the surplus refills of the last steps have landed
   claim_next();
@@ -1315,10 +1341,20 @@ inline TileShape tile_for(int mode, int64_t L, int64_t P, int64_t Q) {
 // Columns of a tile whose reduction is shared by several workgroups.
 inline int share_columns(int64_t Q) { return Q <= kNarrowTile.bq ? kNarrowTile.bq : Q <= kMidTile.bq ? kMidTile.bq : kBlockTile.bq; }
 
+// Layer-mean search in whole tiles of 256 rows: the columns of a tile.  As in tile_for, by the cost of a step; the
+// launch has rounds enough (layer_split) for their number not to matter.  64 layers x 2048 blocks, Q = 128:
+// 256 columns 1962 us, 128 columns and the sums in registers 1756, its pool loads
+// non-temporal 1577.
+inline int mean_columns(int64_t Q) {
+  if (Q <= kMidTile.bq) return share_columns(Q);
+  constexpr double step_us[2][3] = {{2.0, 1.75, 1.65}, {1.67, 1.42, 1.31}};
+  const int64_t n256 = (Q + 255) / 256, n192 = (Q + 191) / 192;
+  return n192 * step_us[1][n192 < 3 ? n192 - 1 : 2] < 0.96 * n256 * step_us[0][n256 < 3 ? n256 - 1 : 2] ? kWideTile.bq : kBlockTile.bq;
+}
 // byte offset of the selection partials inside the layer-mean workspace (after the sums: one
-// 256x256 tile of floats per (group, pool tile, query tile))
-inline size_t layer_mean_part_offset(int groups, int64_t npt, int64_t nqt) {
-  return (size_t)groups * (size_t)npt * (size_t)nqt * 65536 * sizeof(float);
+// tile of 256 x bq floats per (group, pool tile, query tile))
+inline size_t layer_mean_part_offset(int groups, int64_t npt, int64_t nqt, int bq) {
+  return (size_t)groups * (size_t)npt * (size_t)nqt * 256 * (size_t)bq * sizeof(float);
 }
 
 // A tile kernel launch runs in rounds of one workgroup per compute unit, and a problem with few
@@ -1483,6 +1519,18 @@ void launch_shares(bool heads, int bq, const MatchParams& mp, unsigned grid, hip
   }
 }
 
+template <bool BF16>
+void launch_mean(int bq, const MatchParams& mp, unsigned grid, hipStream_t st) {
+  if (bq == kNarrowTile.bq)
+    match_shape_kernel<BF16, 256, kNarrowTile.bq, 2><<<grid, kThreads, 0, st>>>(mp);
+  else if (bq == kMidTile.bq)
+    match_shape_kernel<BF16, 256, kMidTile.bq, 2><<<grid, kThreads, 0, st>>>(mp);
+  else if (bq == kWideTile.bq)
+    match_shape_kernel<BF16, 256, kWideTile.bq, 2><<<grid, kThreads, 0, st>>>(mp);
+  else
+    match_tile_kernel<BF16, 256, 256, 2><<<grid, kThreads, 0, st>>>(mp);
+}
+
 }  // namespace
 }  // namespace rc
 
@@ -1632,13 +1680,14 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
 extern "C" size_t rc_layer_mean_workspace_size(const rc_kv_desc* qdesc, int64_t Q, int64_t P) {
   using namespace rc;
   if (!qdesc || Q < 0 || P < 0 || qdesc->n_layers <= 0) return 0;
-  const int64_t npt = (P + kBlockTile.bp - 1) / kBlockTile.bp, nqt = (Q + kBlockTile.bq - 1) / kBlockTile.bq;
+  const int bq = mean_columns(Q);
+  const int64_t npt = (P + 255) / 256, nqt = (Q + bq - 1) / bq;
   const int S = split_count(RC_SCORE_BLOCK, qdesc->n_layers, P, Q, qdesc->block_tokens, qdesc->n_kv_heads);
   if (S > 1) return split_layout(S, qdesc->n_layers, P, Q).bytes;  // few tiles: shares of every tile's reduction
   const LayerSplit ls = layer_split(qdesc->n_layers, npt * nqt);
   const int sel_rows = select_rows(P, Q);
   const int64_t nchunks = (P + sel_rows - 1) / sel_rows;
-  return layer_mean_part_offset(ls.groups, npt, nqt) + (size_t)(nchunks > 0 ? nchunks : 1) * (size_t)(Q > 0 ? Q : 1) * sizeof(Part);
+  return layer_mean_part_offset(ls.groups, npt, nqt, bq) + (size_t)(nchunks > 0 ? nchunks : 1) * (size_t)(Q > 0 ? Q : 1) * sizeof(Part);
 }
 
 extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const rc_kv_desc* pdesc, const void* kq,
@@ -1665,8 +1714,8 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
     return fail(RC_ERR_INVALID_ARG, "rc_match_blocks_layer_mean: NULL pool pointer");
   if (!aligned16(kq) || !aligned16(vq) || !aligned16(kp) || !aligned16(vp))
     return fail(RC_ERR_INVALID_ARG, "rc_match_blocks_layer_mean: KV pointer not 16-byte aligned");
-  const TileShape ts = kBlockTile;
-  const int64_t npt = (P + ts.bp - 1) / ts.bp, nqt = (Q + ts.bq - 1) / ts.bq;
+  const int bq = mean_columns(Q);
+  const int64_t npt = (P + 255) / 256, nqt = (Q + bq - 1) / bq;
   const LayerSplit ls = layer_split(L, npt * nqt);
   const int64_t total = (int64_t)ls.groups * npt * nqt;
   if (Q > 0x7fffffffLL || P > 0x7fffffffLL || total > 0x3fffffffLL || Q > (1LL << 20))
@@ -1732,7 +1781,7 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
     return merge_parts<true>(part, sl.nchunks, Q, (int)Q, threshold, best_idx, best_dist, match_idx, second_dist, st,
                              "rc_match_blocks_layer_mean(finalize)");
   }
-  Part* part = reinterpret_cast<Part*>(static_cast<char*>(workspace) + layer_mean_part_offset(ls.groups, npt, nqt));
+  Part* part = reinterpret_cast<Part*>(static_cast<char*>(workspace) + layer_mean_part_offset(ls.groups, npt, nqt, bq));
   const int sel_rows = select_rows(P, Q);
   const int64_t nchunks = (P + sel_rows - 1) / sel_rows;
   if (P > 0) {
@@ -1768,12 +1817,12 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
     const unsigned grid = launch_grid((unsigned)mp.vgrid);
     if (rc_status s = prepare_schedule(mp, grid, nullptr, st)) return s;  // a group of layers per tile: few, long tiles
     if (qdesc->dtype == RC_BF16)
-      match_tile_kernel<true, kBlockTile.bp, kBlockTile.bq, 2><<<grid, kThreads, 0, st>>>(mp);
+      launch_mean<true>(bq, mp, grid, st);
     else
-      match_tile_kernel<false, kBlockTile.bp, kBlockTile.bq, 2><<<grid, kThreads, 0, st>>>(mp);
+      launch_mean<false>(bq, mp, grid, st);
     if (rc_status s = check_launch("rc_match_blocks_layer_mean(tiles)")) return s;
     const dim3 sgrid((unsigned)((Q + 63) / 64), (unsigned)nchunks);
-    tile_sums_select_kernel<<<sgrid, 256, 0, st>>>(dpart, ls.groups, (int)P, (int)Q, (int)npt, (int)nqt, kBlockTile.bq / 64, sel_rows, scale, 0,
+    tile_sums_select_kernel<<<sgrid, 256, 0, st>>>(dpart, ls.groups, (int)P, (int)Q, (int)npt, (int)nqt, bq / 64, sel_rows, scale, 0,
                                                     pool_live, part);
     if (rc_status s = check_launch("rc_match_blocks_layer_mean(select)")) return s;
   }

@@ -1,7 +1,10 @@
 """Shapes at the edges of the library's dispatch rules, every entry point against the CPU oracle on the same inputs:
 each list names the rule whose two sides it stands on.  Needs a real MI355X."""
+import numpy as np
 import pytest
 
+from paper_2507_21433_amd import synth
+from tests.test_gpu_layer_mean import run_case
 from tests.test_gpu_sweep import run_shape
 
 pytestmark = pytest.mark.gpu
@@ -38,3 +41,11 @@ SHAPES = [(0, 260, 8, 129, 1), (0, 260, 193, 192, 1), (0, 260, 257, 193, 1), (0,
 def test_tile_shapes(oracle, mode, L, P, Q, H):
     run_shape(oracle, dict(L=L, P=P, Q=Q, T=16, H=H, mode=mode, dtype="bf16" if Q % 2 else "f16", planted_frac=0.0 if P < 64 else 0.3,
                            seed=7500 + P), f"shape{mode}.{L}.{P}x{Q}", P)
+
+
+# Layer-mean search at 128 columns (running sums in registers) and at 192 (in memory), layers in groups of 2, 2 and 1: 172
+# pool tiles of 5 layers; and at 192 columns with two query tiles.
+@pytest.mark.parametrize("L,P,Q", [(5, 44000, 65), (5, 44000, 129), (90, 300, 257)])
+def test_layer_mean_widths(oracle, L, P, Q):
+    w = synth.scaled(synth.WORKLOADS[2], name=f"lm{L}.{P}x{Q}", L=L, P=P, Q=Q, T=16, H=1, planted_frac=0.3, R=1, E=P + Q, seed=7700)
+    run_case(oracle, w, 0.5 * np.sqrt(w.Dh / (w.T * w.H)))
