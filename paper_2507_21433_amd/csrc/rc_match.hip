@@ -1079,12 +1079,16 @@ __device__ __forceinline__ int sum_index(int r, int c, int tq) {
 // take_min: the groups are combined by the minimum instead of the sum (per-head-all score, one
 // share per head).
 // grid = (query tiles of 64, pool chunks of sel_rows rows, layers); sel_rows is a multiple of 16;
-// a thread owns one query column and every fourth group of four rows.
-__global__ __launch_bounds__(256) void tile_sums_select_kernel(const float* __restrict__ dpart, int groups, int P,
-                                                               int Q, int npt, int nqt, int tq_cols, int sel_rows,
-                                                               float scale, int take_min, const uint8_t* __restrict__ live,
-                                                               Part* __restrict__ part) {
-  __shared__ Part s_part[4][64];
+// a thread owns one query column and every kSelRowGroups-th group of four rows.  What the kernel takes is
+// round trips to memory, one after the other: 8 groups are asked for at once (a call of one pool tile has
+// 64 to 128 shares per pair and fills a handful of workgroups).  Four row groups and 4 loads -> 8 and 8: P = 256,
+// Q = 32, 64 shares 13.4 -> 7.8 us, 128 shares 22.7 -> 11.9; 32 layers x 2531 x 24, 8 shares 19.7 -> 18.5; 16 loads
+// at once: 8.5, 11.9 and 34 (too many registers where workgroups are many).
+constexpr int kSelRowGroups = 8;
+__global__ __launch_bounds__(64 * kSelRowGroups) void tile_sums_select_kernel(
+    const float* __restrict__ dpart, int groups, int P, int Q, int npt, int nqt, int tq_cols, int sel_rows, float scale,
+    int take_min, const uint8_t* __restrict__ live, Part* __restrict__ part) {
+  __shared__ Part s_part[kSelRowGroups][64];
   const int tq = threadIdx.x & 63, tp = threadIdx.x >> 6;
   const int q = blockIdx.x * 64 + tq;
   const int pbeg = blockIdx.y * sel_rows, pend = min(P, pbeg + sel_rows);
@@ -1096,34 +1100,39 @@ __global__ __launch_bounds__(256) void tile_sums_select_kernel(const float* __re
   float best = -INFINITY, second = -INFINITY;
   int bidx = -1;
   if (q < Q) {
-    for (int r = pbeg + 4 * tp; r < pend; r += 16) {
+    for (int r = pbeg + 4 * tp; r < pend; r += 4 * kSelRowGroups) {
       const float* src = dpart + ((long long)(r >> 8) * nqt + qt) * (256 * bq) + sum_index(r & 255, qc, tq_cols);
       f32x4 sum = {0.f, 0.f, 0.f, 0.f};  // groups are added in ascending order: the same bits on every run
-      if (take_min) {
-        // per-head-all score: every head's score goes onto the grid of 1/32767 first, exactly as the
-        // whole-tile path keeps its running minimum, so that a pair reports the same bits on both paths
-        int qmin[4] = {32767, 32767, 32767, 32767};
-        for (int g = 0; g < groups; ++g) {
-          const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + g * gstride));
-#pragma unroll
-          for (int e = 0; e < 4; e += 2) {
-            const i16x2 q = quantise_pair(v[e], v[e + 1]);
-            qmin[e] = min(qmin[e], (int)q[0]);
-            qmin[e + 1] = min(qmin[e + 1], (int)q[1]);
-          }
+      // per-head-all score: every head's score goes onto the grid of 1/32767 first, exactly as the
+      // whole-tile path keeps its running minimum, so that a pair reports the same bits on both paths
+      int qmin[4] = {32767, 32767, 32767, 32767};
+      auto combine = [&](f32x4 v) __attribute__((always_inline)) {
+        if (!take_min) {
+          sum += v;
+          return;
         }
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+          const i16x2 q = quantise_pair(v[e], v[e + 1]);
+          qmin[e] = min(qmin[e], (int)q[0]);
+          qmin[e + 1] = min(qmin[e + 1], (int)q[1]);
+        }
+      };
+      auto batch = [&](int g, auto n_tag) __attribute__((always_inline)) {
+        constexpr int N = decltype(n_tag)::value;
+        f32x4 v[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + (g + u) * gstride));
+#pragma unroll
+        for (int u = 0; u < N; ++u) combine(v[u]);
+      };
+      int g = 0;
+      for (; g + 8 <= groups; g += 8) batch(g, std::integral_constant<int, 8>{});
+      for (; g + 4 <= groups; g += 4) batch(g, std::integral_constant<int, 4>{});
+      for (; g < groups; ++g) batch(g, std::integral_constant<int, 1>{});
+      if (take_min) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) sum[e] = (float)qmin[e] / 32767.f;
-      } else {
-        int g = 0;
-        for (; g + 4 <= groups; g += 4) {
-          f32x4 v[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + (g + u) * gstride));
-#pragma unroll
-          for (int u = 0; u < 4; ++u) sum += v[u];
-        }
-        for (; g < groups; ++g) sum += __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + g * gstride));
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -1139,7 +1148,7 @@ __global__ __launch_bounds__(256) void tile_sums_select_kernel(const float* __re
   __syncthreads();
   if (tp == 0 && q < Q) {
 #pragma unroll
-    for (int w = 1; w < 4; ++w) {
+    for (int w = 1; w < kSelRowGroups; ++w) {
       const Part u = s_part[w][tq];
       top2_merge(t.best, t.idx, t.second, u.best, u.idx, u.second);
     }
@@ -1151,57 +1160,76 @@ __global__ __launch_bounds__(256) void tile_sums_select_kernel(const float* __re
 // `shares` workgroups, the first half on the K tensor, the second on V, each storing its bare partial dot
 // products as a tile in register order, laid out [layer][share][pool tile][query tile]).  Per pair and layer the
 // shares of each tensor are added in ascending order, |x - y| = sqrt(max(|x|^2 + |y|^2 - 2 x.y, 0)) is formed
-// from the cached squared norms exactly as the whole-tile path folds it, the layers are added in ascending
-// order, and the selection is the one of tile_sums_select_kernel (top-2 on -distance, dead and tail rows out).
-__global__ __launch_bounds__(256) void layer_mean_shares_select_kernel(
+// from the cached squared norms exactly as the whole-tile path folds it, and the selection is the one of
+// tile_sums_select_kernel (top-2 on -distance, dead and tail rows out).
+// Bound by round trips to memory (up to 512 shares per pair, few workgroups): the 2 L distances of a pair (layer
+// by layer, K before V) are dealt in order to kMeanParts threads, each asks for up to 8 shares at once, and the
+// parts are added in ascending order.  One thread per pair and one load at a time -> this: 1 layer x 459 x 8
+// queries, 128 shares 68 -> 22 us; 7 x 251 x 43 194 -> 36; 12 x 1537 x 169 84 -> 38.
+constexpr int kMeanRowGroups = 4, kMeanParts = 4;
+__global__ __launch_bounds__(64 * kMeanRowGroups * kMeanParts) void layer_mean_shares_select_kernel(
     const float* __restrict__ dpart, int shares, int L, int P, int Q, int npt, int nqt, int tq_cols, int sel_rows, float scale,
     const uint8_t* __restrict__ live, const float* __restrict__ q_ksq, const float* __restrict__ q_vsq,
     const float* __restrict__ p_ksq, const float* __restrict__ p_vsq, Part* __restrict__ part) {
-  __shared__ Part s_part[4][64];
-  const int tq = threadIdx.x & 63, tp = threadIdx.x >> 6;
+  __shared__ f32x4 s_sum[kMeanParts][kMeanRowGroups][64];
+  __shared__ Part s_part[kMeanRowGroups][64];
+  const int tq = threadIdx.x & 63, tp = (threadIdx.x >> 6) % kMeanRowGroups, tl = (threadIdx.x >> 6) / kMeanRowGroups;
   const int q = blockIdx.x * 64 + tq;
   const int pbeg = blockIdx.y * sel_rows, pend = min(P, pbeg + sel_rows);
   const int bq = tq_cols * 64, qt = q / bq, qc = q % bq;
   const long long gstride = (long long)npt * nqt * (256 * bq);
+  const int per_tensor = shares / 2;
+  const int first = (int)(2LL * L * tl / kMeanParts), last = (int)(2LL * L * (tl + 1) / kMeanParts);
   float best = -INFINITY, second = -INFINITY;
   int bidx = -1;
-  if (q < Q) {
-    for (int r = pbeg + 4 * tp; r < pend; r += 16) {
+  for (int r0 = pbeg; r0 < pend; r0 += 4 * kMeanRowGroups) {
+    const int r = r0 + 4 * tp;
+    f32x4 dist = {0.f, 0.f, 0.f, 0.f};
+    if (q < Q && r < pend) {
       const float* src = dpart + ((long long)(r >> 8) * nqt + qt) * (256 * bq) + sum_index(r & 255, qc, tq_cols);
-      f32x4 dist = {0.f, 0.f, 0.f, 0.f};
-      for (int l = 0; l < L; ++l) {
-        const float* lsrc = src + (long long)l * shares * gstride;
-        f32x4 dot[2];
+      for (int it = first; it < last; ++it) {
+        const int l = it >> 1, t = it & 1;
+        const float* lsrc = src + ((long long)l * shares + t * per_tensor) * gstride;
+        const float* np = (t ? p_vsq : p_ksq) + (long long)l * P + r;
+        const float nq = (t ? q_vsq : q_ksq)[(long long)l * Q + q];
+        f32x4 n = {nq, nq, nq, nq}, dot = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          dot[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-          for (int g = 0; g < shares / 2; ++g)
-            dot[t] += __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(lsrc + (long long)(t * (shares / 2) + g) * gstride));
-        }
-        const float nqk = q_ksq[(long long)l * Q + q], nqv = q_vsq[(long long)l * Q + q];
+        for (int e = 0; e < 4; ++e)
+          if (r + e < pend) n[e] += np[e];
+        for (int g = 0; g < per_tensor; g += 8) {
+          f32x4 v[8];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (r + e >= pend) continue;
-          const float npk = p_ksq[(long long)l * P + r + e], npv = p_vsq[(long long)l * P + r + e];
-          dist[e] += __builtin_amdgcn_sqrtf(fmaxf(fmaf(-2.f, dot[0][e], nqk + npk), 0.f));
-          dist[e] += __builtin_amdgcn_sqrtf(fmaxf(fmaf(-2.f, dot[1][e], nqv + npv), 0.f));
+          for (int u = 0; u < 8; ++u)
+            if (g + u < per_tensor) v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(lsrc + (g + u) * gstride));
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (g + u < per_tensor) dot += v[u];
         }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dist[e] += __builtin_amdgcn_sqrtf(fmaxf(fmaf(-2.f, dot[e], n[e]), 0.f));
       }
+    }
+    if (tl > 0) s_sum[tl][tp][tq] = dist;
+    __syncthreads();
+    if (tl == 0 && q < Q && r < pend) {
+#pragma unroll
+      for (int u = 1; u < kMeanParts; ++u) dist += s_sum[u][tp][tq];
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (r + e < pend && (!live || live[r + e])) top2_push(-(dist[e] * scale), r + e, best, bidx, second);
     }
+    __syncthreads();
   }
   Part t;
   t.best = best;
   t.idx = bidx;
   t.second = second;
   t.pad = 0;
-  s_part[tp][tq] = t;
+  if (tl == 0) s_part[tp][tq] = t;
   __syncthreads();
-  if (tp == 0 && q < Q) {
+  if (tl == 0 && tp == 0 && q < Q) {
 #pragma unroll
-    for (int w = 1; w < 4; ++w) {
+    for (int w = 1; w < kMeanRowGroups; ++w) {
       const Part u = s_part[w][tq];
       top2_merge(t.best, t.idx, t.second, u.best, u.idx, u.second);
     }
@@ -1628,7 +1656,7 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
     if (rc_status s = check_launch("rc_match_blocks(tile shares)")) return s;
     Part* part = reinterpret_cast<Part*>(static_cast<char*>(workspace) + sl.part_offset);
     const dim3 sgrid((unsigned)((Q + 63) / 64), (unsigned)sl.nchunks, (unsigned)L);
-    tile_sums_select_kernel<<<sgrid, 256, 0, st>>>(mp.dpart, S, (int)P, (int)Q, (int)sl.npt, (int)sl.nqt, sl.bq / 64, sl.sel_rows,
+    tile_sums_select_kernel<<<sgrid, 64 * kSelRowGroups, 0, st>>>(mp.dpart, S, (int)P, (int)Q, (int)sl.npt, (int)sl.nqt, sl.bq / 64, sl.sel_rows,
                                                    -1.0f, heads ? 1 : 0, pool_live, part);
     if (rc_status s = check_launch("rc_match_blocks(select)")) return s;
     return merge_parts<false>(part, sl.nchunks, LQ, (int)Q, tau, best_idx, best_score, match_idx, second_score, st,
@@ -1775,7 +1803,7 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
     if (rc_status s = check_launch("rc_match_blocks_layer_mean(tile shares)")) return s;
     Part* part = reinterpret_cast<Part*>(static_cast<char*>(workspace) + sl.part_offset);
     const dim3 sgrid((unsigned)((Q + 63) / 64), (unsigned)sl.nchunks);
-    layer_mean_shares_select_kernel<<<sgrid, 256, 0, st>>>(dpart, S, L, (int)P, (int)Q, (int)sl.npt, (int)sl.nqt, sl.bq / 64, sl.sel_rows,
+    layer_mean_shares_select_kernel<<<sgrid, 64 * kMeanRowGroups * kMeanParts, 0, st>>>(dpart, S, L, (int)P, (int)Q, (int)sl.npt, (int)sl.nqt, sl.bq / 64, sl.sel_rows,
                                                            scale, pool_live, q_ksq, q_vsq, p_ksq, p_vsq, part);
     if (rc_status s = check_launch("rc_match_blocks_layer_mean(select)")) return s;
     return merge_parts<true>(part, sl.nchunks, Q, (int)Q, threshold, best_idx, best_dist, match_idx, second_dist, st,
@@ -1822,7 +1850,7 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
       launch_mean<false>(bq, mp, grid, st);
     if (rc_status s = check_launch("rc_match_blocks_layer_mean(tiles)")) return s;
     const dim3 sgrid((unsigned)((Q + 63) / 64), (unsigned)nchunks);
-    tile_sums_select_kernel<<<sgrid, 256, 0, st>>>(dpart, ls.groups, (int)P, (int)Q, (int)npt, (int)nqt, bq / 64, sel_rows, scale, 0,
+    tile_sums_select_kernel<<<sgrid, 64 * kSelRowGroups, 0, st>>>(dpart, ls.groups, (int)P, (int)Q, (int)npt, (int)nqt, bq / 64, sel_rows, scale, 0,
                                                     pool_live, part);
     if (rc_status s = check_launch("rc_match_blocks_layer_mean(select)")) return s;
   }

@@ -49,3 +49,12 @@ def test_tile_shapes(oracle, mode, L, P, Q, H):
 def test_layer_mean_widths(oracle, L, P, Q):
     w = synth.scaled(synth.WORKLOADS[2], name=f"lm{L}.{P}x{Q}", L=L, P=P, Q=Q, T=16, H=1, planted_frac=0.3, R=1, E=P + Q, seed=7700)
     run_case(oracle, w, 0.5 * np.sqrt(w.Dh / (w.T * w.H)))
+
+
+# Shares per pair added by the selection kernels: 8 at a time, then 4, then single ones, K and V layer by layer dealt to four
+# threads; pool chunks of 32 rows that end inside a group of four.
+@pytest.mark.parametrize("L,P,Q,H", [(1, 1, 1, 16), (1, 37, 66, 3), (1, 250, 9, 5), (3, 35, 129, 7), (9, 259, 2, 3)])
+def test_share_selection(oracle, L, P, Q, H):
+    for mode in (0, 1):
+        run_shape(oracle, dict(L=L, P=P, Q=Q, T=16, H=H, mode=mode, dtype="f16", planted_frac=0.0 if P < 64 else 0.3, seed=7900 + P),
+                  f"shares{mode}.{L}.{P}x{Q}", P)
