@@ -51,23 +51,27 @@ struct CandParams {
 // thread's chunk changes from one trip to the next, so every trip ends with the sum over the 16
 // lanes of a (token, head) group, added by the group's first lane to its own slot
 // hpart[candidate][K or V][head][group]: no two groups share a slot, so plain LDS updates do.
-constexpr int kCandPerWg = 16;
+// Few pairs: kCandFew candidates per workgroup, so that a call of a few queries has workgroups for more of the
+// chip and a thread more of its slices in flight.  4 layers x 30 queries x 16 candidates (120 workgroups of 16)
+// 41 -> 28 us; with 512 workgroups and more the queries' extra traffic costs more than it gives (64 layers x 256 x 16:
+// 8 per workgroup 2471 -> 2641 us).
+constexpr int kCandPerWg = 16, kCandFew = 4, kCandManyWgs = 512;
 
-template <bool BF16, bool ANYH>
+template <bool BF16, bool ANYH, int PER>
 __global__ __launch_bounds__(kCandThreads) void candidates_kernel(const CandParams p) {
-  __shared__ float part[kCandPerWg][2][kCandThreads / 16];
-  __shared__ float head_score[kCandPerWg][16];
-  __shared__ float hpart[ANYH ? kCandPerWg : 1][2][ANYH ? 16 : 1][ANYH ? kCandThreads / 16 : 1];
-  const int c0 = blockIdx.x * kCandPerWg, q = blockIdx.y, tid = threadIdx.x;
+  __shared__ float part[PER][2][kCandThreads / 16];
+  __shared__ float head_score[PER][16];
+  __shared__ float hpart[ANYH ? PER : 1][2][ANYH ? 16 : 1][ANYH ? kCandThreads / 16 : 1];
+  const int c0 = blockIdx.x * PER, q = blockIdx.y, tid = threadIdx.x;
   const long long l = blockIdx.z;
   const long long slot0 = (l * p.Q + q) * p.C + c0;
-  int pidx[kCandPerWg];
-  bool valid[kCandPerWg];
-  const u32x4* xp_k[kCandPerWg];
-  const u32x4* xp_v[kCandPerWg];
+  int pidx[PER];
+  bool valid[PER];
+  const u32x4* xp_k[PER];
+  const u32x4* xp_v[PER];
   bool any = false;
 #pragma unroll
-  for (int c = 0; c < kCandPerWg; ++c) {  // the same for the whole workgroup
+  for (int c = 0; c < PER; ++c) {  // the same for the whole workgroup
     pidx[c] = (c0 + c < p.C) ? p.cand[slot0 + c] : -1;
     valid[c] = pidx[c] >= 0 && pidx[c] < p.P && (!p.live || p.live[l * p.P + pidx[c]]);
     const long long off = l * p.p_lstride_b + (long long)(valid[c] ? pidx[c] : 0) * p.block_bytes;
@@ -79,26 +83,26 @@ __global__ __launch_bounds__(kCandThreads) void candidates_kernel(const CandPara
   if (!any) return;
   if (ANYH) {
     float* z = &hpart[0][0][0][0];
-    for (int i = tid; i < kCandPerWg * 2 * 16 * (kCandThreads / 16); i += kCandThreads) z[i] = 0.f;
+    for (int i = tid; i < PER * 2 * 16 * (kCandThreads / 16); i += kCandThreads) z[i] = 0.f;
     __syncthreads();
   }
   const u32x4* xq_k = reinterpret_cast<const u32x4*>(p.kq + l * p.q_lstride_b + (long long)q * p.block_bytes);
   const u32x4* xq_v = reinterpret_cast<const u32x4*>(p.vq + l * p.q_lstride_b + (long long)q * p.block_bytes);
   const int chunks = p.block_bytes / 16;
-  float dk[kCandPerWg], dv[kCandPerWg];
+  float dk[PER], dv[PER];
 #pragma unroll
-  for (int c = 0; c < kCandPerWg; ++c) dk[c] = dv[c] = 0.f;
+  for (int c = 0; c < PER; ++c) dk[c] = dv[c] = 0.f;
   auto trip = [&](int i) {
     const u32x4 qk = xq_k[i], qv = xq_v[i];
-    u32x4 pk[kCandPerWg], pv[kCandPerWg];
+    u32x4 pk[PER], pv[PER];
 #pragma unroll
-    for (int c = 0; c < kCandPerWg; ++c)
+    for (int c = 0; c < PER; ++c)
       if (valid[c]) {
         pk[c] = __builtin_nontemporal_load(xp_k[c] + i);
         pv[c] = __builtin_nontemporal_load(xp_v[c] + i);
       }
 #pragma unroll
-    for (int c = 0; c < kCandPerWg; ++c)
+    for (int c = 0; c < PER; ++c)
       if (valid[c]) {
         dk[c] = dot8<BF16>(qk, pk[c], dk[c]);
         dv[c] = dot8<BF16>(qv, pv[c], dv[c]);
@@ -106,7 +110,7 @@ __global__ __launch_bounds__(kCandThreads) void candidates_kernel(const CandPara
     if (ANYH) {
       const int head = (i >> 4) % p.heads;
 #pragma unroll
-      for (int c = 0; c < kCandPerWg; ++c)
+      for (int c = 0; c < PER; ++c)
         if (valid[c]) {  // the same for the whole workgroup
 #pragma unroll
           for (int off = 8; off > 0; off >>= 1) {
@@ -120,18 +124,18 @@ __global__ __launch_bounds__(kCandThreads) void candidates_kernel(const CandPara
           dk[c] = dv[c] = 0.f;
         }
     }
-  
   };
   // chunks = 16*T*H is a multiple of 256
   if (ANYH) {
     for (int i = tid; i < chunks; i += kCandThreads) trip(i);
   } else {
-#pragma unroll 2
+    constexpr int TRIPS = PER <= 4 ? 4 : 2;
+#pragma unroll TRIPS
     for (int i = tid; i < chunks; i += kCandThreads) trip(i);
   }
   // sum over the 16 lanes that share a (token, head) group, then over the groups of a head
 #pragma unroll
-  for (int c = 0; c < kCandPerWg; ++c) {
+  for (int c = 0; c < PER; ++c) {
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) {
       dk[c] += __shfl_xor(dk[c], off);
@@ -144,7 +148,7 @@ __global__ __launch_bounds__(kCandThreads) void candidates_kernel(const CandPara
   }
   __syncthreads();
   const int c = tid >> 4, h = tid & 15;  // one thread per (candidate, head)
-  if (c < kCandPerWg && h < p.heads && valid[c]) {
+  if (c < PER && h < p.heads && valid[c]) {
     float sk = 0.f, sv = 0.f;
     if (ANYH) {
       for (int g = 0; g < kCandThreads / 16; ++g) {
@@ -164,7 +168,7 @@ __global__ __launch_bounds__(kCandThreads) void candidates_kernel(const CandPara
     head_score[c][h] = 0.5f * (ck + cv);
   }
   __syncthreads();
-  if (tid < kCandPerWg && valid[tid]) {
+  if (tid < PER && valid[tid]) {
     float s = head_score[tid][0];
     for (int hh = 1; hh < p.heads; ++hh) s = fminf(s, head_score[tid][hh]);
     p.scores[slot0 + tid] = s;
@@ -241,16 +245,16 @@ struct CandDistParams {
 // layer it streams the listed pool blocks against the query chunk held in registers, reduces the
 // squared differences over the workgroup and adds the two square roots to the running sum that
 // thread c keeps for candidate c.
-template <bool BF16>
+template <bool BF16, int PER>
 __global__ __launch_bounds__(kCandThreads) void candidate_distances_kernel(const CandDistParams p) {
-  __shared__ float s_red[kCandThreads / 64][kCandPerWg][2];
-  const int c0 = blockIdx.x * kCandPerWg, q = blockIdx.y, tid = threadIdx.x;
+  __shared__ float s_red[kCandThreads / 64][PER][2];
+  const int c0 = blockIdx.x * PER, q = blockIdx.y, tid = threadIdx.x;
   const int l0 = blockIdx.z * p.G, nl = min(p.G, p.L - l0);
-  int pidx[kCandPerWg];
-  bool valid[kCandPerWg];
+  int pidx[PER];
+  bool valid[PER];
   bool any = false;
 #pragma unroll
-  for (int c = 0; c < kCandPerWg; ++c) {  // the same for the whole workgroup
+  for (int c = 0; c < PER; ++c) {  // the same for the whole workgroup
     pidx[c] = (c0 + c < p.C) ? p.cand[(long long)q * p.C + c0 + c] : -1;
     valid[c] = pidx[c] >= 0 && pidx[c] < p.P && (!p.live || p.live[pidx[c]]);
     any = any || valid[c];
@@ -262,28 +266,30 @@ __global__ __launch_bounds__(kCandThreads) void candidate_distances_kernel(const
     const long long l = l0 + li;
     const u32x4* xq_k = reinterpret_cast<const u32x4*>(p.kq + l * p.q_lstride_b + (long long)q * p.block_bytes);
     const u32x4* xq_v = reinterpret_cast<const u32x4*>(p.vq + l * p.q_lstride_b + (long long)q * p.block_bytes);
-    float dk[kCandPerWg], dv[kCandPerWg];
+    float dk[PER], dv[PER];
 #pragma unroll
-    for (int c = 0; c < kCandPerWg; ++c) dk[c] = dv[c] = 0.f;
+    for (int c = 0; c < PER; ++c) dk[c] = dv[c] = 0.f;
+    constexpr int TRIPS = PER <= 4 ? 4 : 1;
+#pragma unroll TRIPS
     for (int i = tid; i < chunks; i += kCandThreads) {
       const u32x4 qk = xq_k[i], qv = xq_v[i];
-      u32x4 pk[kCandPerWg], pv[kCandPerWg];
+      u32x4 pk[PER], pv[PER];
 #pragma unroll
-      for (int c = 0; c < kCandPerWg; ++c)
+      for (int c = 0; c < PER; ++c)
         if (valid[c]) {
           const long long off = l * p.p_lstride_b + (long long)pidx[c] * p.block_bytes;
           pk[c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p.kp + off) + i);
           pv[c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p.vp + off) + i);
         }
 #pragma unroll
-      for (int c = 0; c < kCandPerWg; ++c)
+      for (int c = 0; c < PER; ++c)
         if (valid[c]) {
           dk[c] = sqdiff8<BF16>(qk, pk[c], dk[c]);
           dv[c] = sqdiff8<BF16>(qv, pv[c], dv[c]);
         }
     }
 #pragma unroll
-    for (int c = 0; c < kCandPerWg; ++c) {
+    for (int c = 0; c < PER; ++c) {
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) {
         dk[c] += __shfl_xor(dk[c], off);
@@ -295,7 +301,7 @@ __global__ __launch_bounds__(kCandThreads) void candidate_distances_kernel(const
       }
     }
     __syncthreads();
-    if (tid < kCandPerWg) {
+    if (tid < PER) {
       float sk = 0.f, sv = 0.f;
 #pragma unroll
       for (int w = 0; w < kCandThreads / 64; ++w) {
@@ -306,11 +312,13 @@ __global__ __launch_bounds__(kCandThreads) void candidate_distances_kernel(const
     }
     __syncthreads();  // s_red is rewritten by the next layer
   }
-  if (tid < kCandPerWg && c0 + tid < p.C)
+  if (tid < PER && c0 + tid < p.C)
     p.part[((long long)blockIdx.z * p.Q + q) * p.C + c0 + tid] = total;
 }
 
-// One thread per query: layer groups added in order, scaled, validity re-derived, nearest candidate.
+// One wave per query, a candidate per lane: layer groups added in order (8 asked for at once), scaled, validity
+// re-derived, nearest candidate.  One thread per query walked all its candidates' groups one load at a time: 96
+// queries x 12 candidates x 24 groups 48 -> 5.6 us.
 __global__ __launch_bounds__(256) void candidate_distances_select_kernel(const float* __restrict__ part, int groups,
                                                                         const int32_t* __restrict__ cand,
                                                                         const uint8_t* __restrict__ live, int Q, int P,
@@ -319,16 +327,25 @@ __global__ __launch_bounds__(256) void candidate_distances_select_kernel(const f
                                                                         int32_t* __restrict__ best_idx,
                                                                         float* __restrict__ best_dist,
                                                                         int32_t* __restrict__ match_idx) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  const int q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (q >= Q) return;
   float best = INFINITY;
   int bidx = -1;
-  for (int c = 0; c < C; ++c) {
+  for (long long c = lane; c < C; c += 64) {
     const int pi = cand[(long long)q * C + c];
     float d = INFINITY;
     if (pi >= 0 && pi < P && (!live || live[pi])) {
+      const float* src = part + (long long)q * C + c;
+      const long long gstride = (long long)Q * C;
       float sum = 0.f;
-      for (int g = 0; g < groups; ++g) sum += part[((long long)g * Q + q) * C + c];
+      for (int g = 0; g < groups; g += 8) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = g + u < groups ? src[(g + u) * gstride] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (g + u < groups) sum += v[u];
+      }
       d = sum * scale;
       if (d < best || (d == best && pi < bidx)) {
         best = d;
@@ -337,6 +354,16 @@ __global__ __launch_bounds__(256) void candidate_distances_select_kernel(const f
     }
     dist[(long long)q * C + c] = d;
   }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const float d = __shfl_xor(best, off);
+    const int i = __shfl_xor(bidx, off);
+    if (d < best || (d == best && i >= 0 && i < bidx)) {
+      best = d;
+      bidx = i;
+    }
+  }
+  if (lane != 0) return;
   best_idx[q] = bidx;
   best_dist[q] = best;
   match_idx[q] = (bidx >= 0 && best <= thr) ? bidx : -1;
@@ -349,6 +376,26 @@ inline int cand_layers_per_group(int L, int64_t Q, int64_t C) {
   if (groups < 1) groups = 1;
   if (groups > L) groups = L;
   return (int)((L + groups - 1) / groups);
+}
+
+// candidates per workgroup of a launch over `lists` lists of C
+inline int cand_per_wg(int64_t lists, int64_t C) {
+  return lists * ((C + kCandPerWg - 1) / kCandPerWg) < kCandManyWgs ? kCandFew : kCandPerWg;
+}
+
+template <bool BF16>
+void launch_candidates(bool any_h, int per, dim3 grid, const CandParams& cp, hipStream_t st) {
+  if (per == kCandFew) {
+    if (any_h)
+      candidates_kernel<BF16, true, kCandFew><<<grid, kCandThreads, 0, st>>>(cp);
+    else
+      candidates_kernel<BF16, false, kCandFew><<<grid, kCandThreads, 0, st>>>(cp);
+  } else {
+    if (any_h)
+      candidates_kernel<BF16, true, kCandPerWg><<<grid, kCandThreads, 0, st>>>(cp);
+    else
+      candidates_kernel<BF16, false, kCandPerWg><<<grid, kCandThreads, 0, st>>>(cp);
+  }
 }
 
 }  // namespace
@@ -404,19 +451,13 @@ extern "C" rc_status rc_score_candidates(const rc_kv_desc* qdesc, const rc_kv_de
     cp.C = (int)C;
     cp.block_bytes = qdesc->block_tokens * H * qdesc->head_dim * 2;  // T >= 16, Dh = 128: a multiple of 16 KB / 4
     cp.heads = (mode == RC_SCORE_BLOCK) ? 1 : H;
-    const dim3 grid((unsigned)((C + kCandPerWg - 1) / kCandPerWg), (unsigned)Q, (unsigned)L);
+    const int per = cand_per_wg((int64_t)L * Q, C);
+    const dim3 grid((unsigned)((C + per - 1) / per), (unsigned)Q, (unsigned)L);
     const bool any_h = mode == RC_SCORE_PER_HEAD_ALL && (16 % H) != 0;  // a thread's chunks wander over the heads
-    if (qdesc->dtype == RC_BF16) {
-      if (any_h)
-        candidates_kernel<true, true><<<grid, kCandThreads, 0, st>>>(cp);
-      else
-        candidates_kernel<true, false><<<grid, kCandThreads, 0, st>>>(cp);
-    } else {
-      if (any_h)
-        candidates_kernel<false, true><<<grid, kCandThreads, 0, st>>>(cp);
-      else
-        candidates_kernel<false, false><<<grid, kCandThreads, 0, st>>>(cp);
-    }
+    if (qdesc->dtype == RC_BF16)
+      launch_candidates<true>(any_h, per, grid, cp, st);
+    else
+      launch_candidates<false>(any_h, per, grid, cp, st);
     if (rc_status s = check_launch("rc_score_candidates(score)")) return s;
   }
   const long long LQ = (long long)L * Q;
@@ -484,16 +525,24 @@ extern "C" rc_status rc_candidate_distances(const rc_kv_desc* qdesc, const rc_kv
     cp.L = L;
     cp.G = G;
     cp.block_bytes = qdesc->block_tokens * qdesc->n_kv_heads * qdesc->head_dim * 2;
-    const dim3 grid((unsigned)((C + kCandPerWg - 1) / kCandPerWg), (unsigned)Q, (unsigned)groups);
-    if (qdesc->dtype == RC_BF16)
-      candidate_distances_kernel<true><<<grid, kCandThreads, 0, st>>>(cp);
-    else
-      candidate_distances_kernel<false><<<grid, kCandThreads, 0, st>>>(cp);
+    const int per = cand_per_wg((int64_t)groups * Q, C);
+    const dim3 grid((unsigned)((C + per - 1) / per), (unsigned)Q, (unsigned)groups);
+    if (per == kCandFew) {
+      if (qdesc->dtype == RC_BF16)
+        candidate_distances_kernel<true, kCandFew><<<grid, kCandThreads, 0, st>>>(cp);
+      else
+        candidate_distances_kernel<false, kCandFew><<<grid, kCandThreads, 0, st>>>(cp);
+    } else {
+      if (qdesc->dtype == RC_BF16)
+        candidate_distances_kernel<true, kCandPerWg><<<grid, kCandThreads, 0, st>>>(cp);
+      else
+        candidate_distances_kernel<false, kCandPerWg><<<grid, kCandThreads, 0, st>>>(cp);
+    }
     if (rc_status s = check_launch("rc_candidate_distances(distances)")) return s;
   }
   const float scale = 1.0f / ((float)L * 2.0f * (float)qdesc->block_tokens * (float)qdesc->n_kv_heads);
-  candidate_distances_select_kernel<<<(unsigned)((Q + 255) / 256), 256, 0, st>>>(part, groups, cand, pool_live, (int)Q,
-                                                                               (int)P, (int)C, scale, threshold, dist,
-                                                                               best_idx, best_dist, match_idx);
+  candidate_distances_select_kernel<<<(unsigned)((Q + 3) / 4), 256, 0, st>>>(part, groups, cand, pool_live, (int)Q, (int)P,
+                                                                             (int)C, scale, threshold, dist, best_idx,
+                                                                             best_dist, match_idx);
   return check_launch("rc_candidate_distances(select)");
 }

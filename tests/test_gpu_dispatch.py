@@ -2,7 +2,9 @@
 each list names the rule whose two sides it stands on.  Needs a real MI355X."""
 import numpy as np
 import pytest
+import torch
 
+from paper_2507_21433_amd import binding as rc
 from paper_2507_21433_amd import synth
 from tests.test_gpu_layer_mean import run_case
 from tests.test_gpu_sweep import run_shape
@@ -58,3 +60,35 @@ def test_share_selection(oracle, L, P, Q, H):
     for mode in (0, 1):
         run_shape(oracle, dict(L=L, P=P, Q=Q, T=16, H=H, mode=mode, dtype="f16", planted_frac=0.0 if P < 64 else 0.3, seed=7900 + P),
                   f"shares{mode}.{L}.{P}x{Q}", P)
+
+
+# Few samples (one workgroup, up to 16 384) and many; few lists (4 candidates per workgroup) and many, more candidates than lanes.
+@pytest.mark.parametrize("n", [0, 1, 1023, 1024, 1025, 16383, 16384, 16385])
+def test_percentile_sample_counts(oracle, n):
+    rng = np.random.RandomState(n)
+    x = rng.choice(np.float32([0.15, -0.15, 1.4, np.inf, np.nan, -np.inf, 0.0, 1e-40]), size=n) * (1 + rng.randint(0, 3, size=n).astype(np.float32) * 2**-20)
+    x = torch.as_tensor(x.astype(np.float32), device="cuda:0")
+    for p in (0.0, 37.5, 100.0):
+        got = rc.rc_pat_threshold(x, p)
+        want, n_finite = oracle.pat_threshold(x.cpu().numpy(), p)
+        assert got["threshold"].cpu().numpy()[0] == want and int(got["n_finite"][0]) == n_finite
+
+
+@pytest.mark.parametrize("L,Q,C", [(1, 1, 5), (3, 170, 17), (3, 171, 16), (2, 130, 70)])
+def test_candidates_per_workgroup(oracle, L, Q, C):
+    w = synth.scaled(synth.WORKLOADS[2], name=f"lists{L}.{Q}x{C}", L=L, P=90, Q=Q, T=16, H=3, planted_frac=0.0, R=1, E=90 + Q, seed=8100)
+    pr = synth.make_problem(w, "cuda:0")
+    bits = [synth.bits(pr[n]) for n in ("kq", "vq", "kp", "vp")]
+    cand = np.random.RandomState(C).randint(-1, 90, size=(L, Q, C)).astype(np.int32)
+    for mode in (0, 1):
+        norms = [*rc.rc_block_norms(pr["kq"], pr["vq"], mode), *rc.rc_block_norms(pr["kp"], pr["vp"], mode)]
+        g = rc.rc_score_candidates(pr["kq"], pr["vq"], *norms[:2], pr["kp"], pr["vp"], *norms[2:], pr["live"],
+                                   torch.as_tensor(cand, device="cuda:0"), 0.9, mode)
+        o = oracle.candidates(0, mode, *bits, cand, pr["live"].cpu().numpy(), 0.9)
+        s, fin = g["scores"].cpu().numpy(), np.isfinite(o["scores"])
+        assert np.array_equal(np.isfinite(s), fin) and np.abs(s[fin] - o["scores"][fin]).max() <= 2e-5   # as in the sweep
+    live = pr["live"][0].contiguous()
+    g = rc.rc_candidate_distances(pr["kq"], pr["vq"], pr["kp"], pr["vp"], live, torch.as_tensor(cand[0], device="cuda:0"), 0.5)
+    o = oracle.candidate_distances(0, *bits, cand[0], live.cpu().numpy(), 0.5)
+    d, fin = g["dist"].cpu().numpy(), np.isfinite(o["dist"])
+    assert np.array_equal(np.isfinite(d), fin) and np.allclose(d[fin], o["dist"][fin], rtol=1e-5, atol=0)   # fp32 sums of exact differences
