@@ -1366,8 +1366,13 @@ inline TileShape tile_for(int mode, int64_t L, int64_t P, int64_t Q) {
   }
   return shapes[best];
 }
-// Columns of a tile whose reduction is shared by several workgroups.
-inline int share_columns(int64_t Q) { return Q <= kNarrowTile.bq ? kNarrowTile.bq : Q <= kMidTile.bq ? kMidTile.bq : kBlockTile.bq; }
+// Columns of a tile whose reduction is shared by several workgroups: 192 where 256 pad badly.  256 -> 192 columns, us per
+// launch: block, 2 layers x 4096, Q = 300 274 -> 231; per head, 3 x 11147, Q = 133 769 -> 707, 42 x 844, Q = 192 430 -> 354,
+// 4 x 4096, Q = 384 579 -> 491.
+inline int share_columns(int64_t Q) {
+  if (Q <= kMidTile.bq) return Q <= kNarrowTile.bq ? kNarrowTile.bq : kMidTile.bq;
+  return Q <= kWideTile.bq || (Q > kBlockTile.bq && Q <= 2 * kWideTile.bq) ? kWideTile.bq : kBlockTile.bq;
+}
 
 // Layer-mean search in whole tiles of 256 rows: the columns of a tile.  As in tile_for, by the cost of a step; the
 // launch has rounds enough (layer_split) for their number not to matter.  64 layers x 2048 blocks, Q = 128:
@@ -1390,7 +1395,7 @@ inline size_t layer_mean_part_offset(int groups, int64_t npt, int64_t nqt, int b
 // for a few left-over tiles.  Such problems split the reduction of every tile over S workgroups
 // (S even: half of them on the K tensor, half on V).  In per-head mode the shares are the H heads (the
 // score is a minimum over heads, not a sum over the reduction).
-// More than 128 queries (256 columns): S is the power of two with the lowest estimated time, in units of
+// More than 128 queries (192 or 256 columns): S is the power of two with the lowest estimated time, in units of
 // one pipeline step:
 //   rounds(S) * (steps of a share + 6 for filling the pipeline and storing the share)
 //   + 0.03 per tile share for the pass that adds the shares + 5 for its launch,
@@ -1443,7 +1448,8 @@ inline int narrow_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, 
 inline int split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
   if (P <= 0 || Q <= 0 || L <= 0) return 1;
   if (Q <= kMidTile.bq) return narrow_split_count(mode, L, P, Q, T, H);
-  const int64_t tiles = L * ((P + 255) / 256) * ((Q + 255) / 256);
+  const int bq = share_columns(Q);
+  const int64_t tiles = L * ((P + 255) / 256) * ((Q + bq - 1) / bq);
   if (tiles > kSplitComputeUnits) return 1;  // more than one round: measured gains of 0-6 % only (workgroups of
                                              // later rounds start as earlier ones end, the rounds are not that rigid)
   if (mode == RC_SCORE_PER_HEAD_ALL) {
@@ -1534,6 +1540,11 @@ void launch_shares(bool heads, int bq, const MatchParams& mp, unsigned grid, hip
       match_shape_kernel<BF16, 256, kNarrowTile.bq, 4><<<grid, kThreads, 0, st>>>(mp);
     else
       match_shape_kernel<BF16, 256, kNarrowTile.bq, 3><<<grid, kThreads, 0, st>>>(mp);
+  } else if (bq == kWideTile.bq) {
+    if (heads)
+      match_shape_kernel<BF16, 256, kWideTile.bq, 4><<<grid, kThreads, 0, st>>>(mp);
+    else
+      match_shape_kernel<BF16, 256, kWideTile.bq, 3><<<grid, kThreads, 0, st>>>(mp);
   } else if (bq == kMidTile.bq) {
     if (heads)
       match_shape_kernel<BF16, 256, kMidTile.bq, 4><<<grid, kThreads, 0, st>>>(mp);

@@ -23,7 +23,8 @@ def test_merge_parts(oracle, P, Q):
 # Tile width (64 columns up to 64 queries, 128 up to 128, 256 beyond) and shares per tile: per-head mode in whole tiles
 # (256 tiles: one round) and with one share per head, block mode with a share count that is no power of two.
 WIDTHS = [(1, 256, 64, 64, 2), (1, 256, 40, 65, 2), (1, 256, 70, 128, 1), (1, 3, 300, 64, 5), (1, 2, 257, 65, 16),
-          (1, 2, 255, 128, 3), (1, 2, 300, 129, 3), (0, 24, 250, 40, 5), (0, 24, 250, 65, 5), (0, 2, 300, 128, 3), (0, 11, 513, 1, 6)]
+          (1, 2, 255, 128, 3), (1, 2, 300, 129, 3), (0, 24, 250, 40, 5), (0, 24, 250, 65, 5), (0, 2, 300, 128, 3), (0, 11, 513, 1, 6),
+          (0, 2, 300, 192, 3), (0, 2, 300, 257, 3), (1, 2, 257, 384, 3), (1, 2, 40, 385, 5)]
 
 
 @pytest.mark.parametrize("mode,L,P,Q,H", WIDTHS)
