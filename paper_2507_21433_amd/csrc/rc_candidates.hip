@@ -52,10 +52,8 @@ struct CandParams {
 // lanes of a (token, head) group, added by the group's first lane to its own slot
 // hpart[candidate][K or V][head][group]: no two groups share a slot, so plain LDS updates do.
 // Few pairs: kCandFew candidates per workgroup, so that a call of a few queries has workgroups for more of the
-// chip and a thread more of its slices in flight.  4 layers x 30 queries x 16 candidates (120 workgroups of 16)
-// 41 -> 28 us; with 512 workgroups and more the queries' extra traffic costs more than it gives (64 layers x 256 x 16:
-// 8 per workgroup 2471 -> 2641 us).
-constexpr int kCandPerWg = 16, kCandFew = 4, kCandManyWgs = 512;
+// chip and a thread more of its slices in flight (rule and measurements at cand_per_wg).
+constexpr int kCandPerWg = 16, kCandFew = 4;
 
 template <bool BF16, bool ANYH, int PER>
 __global__ __launch_bounds__(kCandThreads) void candidates_kernel(const CandParams p) {
@@ -378,9 +376,16 @@ inline int cand_layers_per_group(int L, int64_t Q, int64_t C) {
   return (int)((L + groups - 1) / groups);
 }
 
-// candidates per workgroup of a launch over `lists` lists of C
+// Candidates per workgroup of a launch over `lists` lists of C: 4 while a launch of 16 per workgroup has fewer than
+// 512 workgroups and 22 pairs per compute unit, and does not just fill one round of them; beyond, the queries' extra
+// traffic costs more than the parallelism gives.  16 -> 4 per workgroup, us, blocks of 64 KB / 256 KB:
+//   C = 16  120 lists 38 -> 28 / 128 -> 90   180 42 -> 39 / 138 -> 137   250 50 -> 50 / 175 -> 185   320 72 -> 62 / 263 -> 236
+//           400 78 -> 80 / 286 -> 305   500 90 -> 96 / 333 -> 373
+//   C = 22  120 41 -> 36 / 139 -> 126   180 65 -> 53 / 229 -> 196   250 75 -> 67 / 267 -> 251   320 99 -> 98 / 358 -> 359
 inline int cand_per_wg(int64_t lists, int64_t C) {
-  return lists * ((C + kCandPerWg - 1) / kCandPerWg) < kCandManyWgs ? kCandFew : kCandPerWg;
+  const int64_t wgs = lists * ((C + kCandPerWg - 1) / kCandPerWg);
+  const bool one_round = wgs > 224 && wgs <= 256;
+  return wgs < 512 && lists * C < 22 * 256 && !one_round ? kCandFew : kCandPerWg;
 }
 
 template <bool BF16>

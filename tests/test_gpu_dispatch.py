@@ -75,7 +75,7 @@ def test_percentile_sample_counts(oracle, n):
         assert got["threshold"].cpu().numpy()[0] == want and int(got["n_finite"][0]) == n_finite
 
 
-@pytest.mark.parametrize("L,Q,C", [(1, 1, 5), (3, 170, 17), (3, 171, 16), (2, 130, 70)])
+@pytest.mark.parametrize("L,Q,C", [(1, 1, 5), (3, 109, 17), (1, 256, 17), (2, 112, 16), (2, 113, 16), (2, 130, 70)])
 def test_candidates_per_workgroup(oracle, L, Q, C):
     w = synth.scaled(synth.WORKLOADS[2], name=f"lists{L}.{Q}x{C}", L=L, P=90, Q=Q, T=16, H=3, planted_frac=0.0, R=1, E=90 + Q, seed=8100)
     pr = synth.make_problem(w, "cuda:0")
