@@ -179,7 +179,7 @@ struct Cursor {
 // adds |Kq-Kp| + |Vq-Vp| of every layer to the tile's running sum), 3 = block score of a problem
 // with too few tiles to fill the chip: S workgroups share a tile, each takes 1/(S/2) of the K or of
 // the V reduction and stores its share of the scores, (aKq aKp <Kq,Kp>)/2 or (aVq aVp <Vq,Vp>)/2
-// over its elements, as a 256x256 tile of floats; a second kernel adds the S shares and selects.
+// over its elements, as a 256 x BQ tile of floats; a second kernel adds the S shares and selects.
 // MODE 4 = the same for the per-head-all score: S = H shares, share h computes the score of head h
 // over the head's K and V slices, and the second kernel takes the minimum over the shares.
 // SHARED_POOL: several query tiles, i.e. several workgroups read every pool slice (see the pool loads below).
@@ -1319,10 +1319,10 @@ inline rc_status prepare_schedule(MatchParams& mp, unsigned grid, void* schedule
 }
 constexpr int kStaggerUnit = 6;  // x 1024 clocks per tile index, one to two pipeline steps (flat optimum between 3 and 8)
 
-// Tile shape: a 128x128 accumulator tile per wave (all 256 accumulation registers of a lane) in
-// every mode.  What is carried across phases is kept out of the fp32 register budget: the
+// Tile shape: with many queries a 128x128 accumulator tile per wave (all 256 accumulation registers
+// of a lane) in every mode.  What is carried across phases is kept out of the fp32 register budget: the
 // per-head mode packs its running minimum into 16-bit fixed point, the layer-mean mode keeps
-// its running sum in the workspace.
+// its running sum in the workspace (up to 128 columns in registers).
 struct TileShape {
   int bp, bq;
 };

@@ -33,7 +33,7 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 KERNEL_SOURCES = ("paper_2507_21433_amd/csrc/rc_match.hip", "paper_2507_21433_amd/csrc/rc_common.hpp")
-TILE_KERNEL = "match_tile_kernel"
+TILE_KERNELS = ("match_tile_kernel", "match_shape_kernel")   # one body, by tile shape
 COPY_KERNEL = "copyBuffer"
 CAL_BYTES = 1 << 30
 
@@ -101,7 +101,7 @@ def read_pass(d):
     vals, durs = {}, {}
     for r in csv.DictReader(open(files[0])):
         k = r["Kernel_Name"]
-        kind = "tile" if TILE_KERNEL in k else ("copy" if COPY_KERNEL in k else None)
+        kind = "tile" if any(t in k for t in TILE_KERNELS) else ("copy" if COPY_KERNEL in k else None)
         if kind is None:
             continue
         vals.setdefault(kind, {}).setdefault(r["Counter_Name"], {})[r["Dispatch_Id"]] = float(r["Counter_Value"])
@@ -319,7 +319,7 @@ def trace(args):
         if bench and run == "step":
             k = bench["kernels"]["rc_match_blocks"]
             flop = bench["roofline"]["algorithmic_flop"]
-            tile = next((r for r in rows if TILE_KERNEL in r["Name"]), None)
+            tile = next((r for r in rows if any(t in r["Name"] for t in TILE_KERNELS)), None)
             lines += ["", f"`bench.py` timed `rc_match_blocks` of {bench['config']['workload']} with events at **{k['ms']:.3f} ms** per call in "
                       "this run (the tile kernel, the clearing of its schedule words and the selection kernel after it)"
                       + (f"; the profiler's average for the tile kernel is **{float(tile['AverageNs']) / 1e6:.3f} ms** over {tile['Calls']} "
