@@ -40,7 +40,7 @@ typedef enum {
   RC_OK = 0,
   RC_ERR_INVALID_ARG = 1, /* null pointer, negative size, misaligned pointer, mismatching descriptors */
   RC_ERR_UNSUPPORTED = 2, /* shape, dtype or mode outside the supported set                           */
-  RC_ERR_WORKSPACE = 3,   /* workspace missing or smaller than rc_*_workspace_size() asks             */
+  RC_ERR_WORKSPACE = 3,   /* workspace missing, misaligned or too small                               */
   RC_ERR_DEVICE = 4       /* the HIP runtime refused a launch                                         */
 } rc_status;
 
@@ -77,12 +77,17 @@ rc_status rc_block_norms(const rc_kv_desc* desc, int32_t mode,
                          const void* k, const void* v, int64_t n_blocks,
                          float* k_sqnorm, float* v_sqnorm, void* hip_stream);
 
-/* Bytes of DEVICE workspace rc_match_blocks needs for this problem (0 on bad arguments).
- * 16 bytes per (layer, pool tile of 256 blocks, query block).  A problem of at most 256 tiles of
- * 256 x 256 blocks (one layer at a time, a small pool) may instead be computed as several shares
- * per tile (parts of the reduction, or heads in per-head mode) and then needs up to 512 MB: 256 KB
- * per share plus the 16-byte partials.  The size depends on the arguments only, not on the
- * current device. */
+/* Bytes of DEVICE workspace with which rc_match_blocks is fastest on this problem (0 on bad arguments).
+ * The size depends on the arguments only, not on the current device, and goes up and down with Q and P (whole tiles,
+ * shares of tiles: tens of KB to 512 MB).  A call takes less as well, and may be slower then, down to a floor:
+ *   - with tiles = n_layers * ceil(P/256) * ceil(Q/256) more than 256, or more than 128 in RC_SCORE_BLOCK mode with
+ *     Q <= 128: 16 bytes per (layer, pool tile of 256 blocks, query block), then 4 bytes per tile (rounded up to
+ *     a multiple of 256) and 68608 bytes for the tile schedule.  One workspace of that size for the largest Q and P
+ *     does for every smaller call of that many tiles;
+ *   - with fewer tiles (one layer at a time, a small pool) the same, or 256 KB per tile and share where the
+ *     reduction of a tile is shared (parts of the reduction, or heads in per-head mode: at most 2048 shares, 512 MB) plus
+ *     16 bytes per (layer, chunk of at least 32 pool blocks, query block).
+ * So a caller that keeps one workspace for many shapes takes the largest size over these shapes. */
 size_t rc_match_workspace_size(const rc_kv_desc* qdesc, int32_t mode, int64_t Q, int64_t P);
 
 /*
@@ -110,8 +115,9 @@ size_t rc_match_workspace_size(const rc_kv_desc* qdesc, int32_t mode, int64_t Q,
  *   match_idx       DEVICE int32 [L][Q]: best_idx if best_score >= tau, else -1
  *   second_score    DEVICE float [L][Q] or NULL: second-largest score over live pool
  *                   blocks, counted with multiplicity (-inf if fewer than two)
- *   workspace       DEVICE, >= rc_match_workspace_size() bytes, 16-byte aligned; contents
- *                   are scratch.  Calls that share a workspace must not overlap.
+ *   workspace       DEVICE, 16-byte aligned, rc_match_workspace_size() bytes or more; less, down to the
+ *                   floor above, is taken and gives a slower plan (RC_SCORE_BLOCK scores may then differ in
+ *                   their last bits).  Contents are scratch.  Calls that share a workspace must not overlap.
  * Accumulation is fp32 on the matrix cores, the epilogue is fp32.  In RC_SCORE_PER_HEAD_ALL
  * mode every head's score is rounded to the nearest multiple of 1/32767 before the minimum over
  * heads is taken (the running minimum is held as 16-bit fixed point next to the accumulators), so

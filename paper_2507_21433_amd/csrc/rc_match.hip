@@ -1445,11 +1445,10 @@ inline int narrow_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, 
   }
   return best;
 }
-inline int split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
+// The rule for 256-column tiles at every query count; block mode leaves at most 128 queries alone from half a round on.
+inline int wide_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
   if (P <= 0 || Q <= 0 || L <= 0) return 1;
-  if (Q <= kMidTile.bq) return narrow_split_count(mode, L, P, Q, T, H);
-  const int bq = share_columns(Q);
-  const int64_t tiles = L * ((P + 255) / 256) * ((Q + bq - 1) / bq);
+  const int64_t tiles = L * ((P + 255) / 256) * ((Q + 255) / 256);
   if (tiles > kSplitComputeUnits) return 1;  // more than one round: measured gains of 0-6 % only (workgroups of
                                              // later rounds start as earlier ones end, the rounds are not that rigid)
   if (mode == RC_SCORE_PER_HEAD_ALL) {
@@ -1459,6 +1458,7 @@ inline int split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) 
     const double heads = rounds(tiles * H) * (4.0 * T + 6.0) + 0.03 * (double)(tiles * H) + 5.0;
     return heads < 0.9 * whole ? H : 1;
   }
+  if (Q <= kMidTile.bq && tiles * 2 > kSplitComputeUnits) return 1;
   const int steps = T * H * 128 / kBK;  // per tensor
   auto estimate = [&](int S) {
     const double rounds = (double)((tiles * S + kSplitComputeUnits - 1) / kSplitComputeUnits);
@@ -1474,6 +1474,11 @@ inline int split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) 
     }
   }
   return best;
+}
+// 192 and 256 columns cut every query count the 192 are used for into the same number of tiles.
+inline int split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
+  if (P <= 0 || Q <= 0 || L <= 0) return 1;
+  return Q <= kMidTile.bq ? narrow_split_count(mode, L, P, Q, T, H) : wide_split_count(mode, L, P, Q, T, H);
 }
 
 struct SplitLayout {
@@ -1497,6 +1502,41 @@ inline SplitLayout split_layout(int S, int64_t L, int64_t P, int64_t Q) {
   r.part_offset = (size_t)L * (size_t)S * (size_t)r.npt * (size_t)r.nqt * room * sizeof(float);
   r.bytes = r.part_offset + (size_t)L * (size_t)r.nchunks * (size_t)Q * sizeof(Part);
   return r;
+}
+
+// ---- What a call computes depends on the workspace it is given as well: the plan of the rules above needs from tens of
+// KB (whole tiles) to 512 MB (shares), up and down with Q and P, and an engine that keeps one workspace for all its calls
+// must not be refused for a small step.  So every call takes a workspace of `floor` bytes, the need of the plan with
+// 256-column shares by wide_split_count or else with pool tiles of 256 rows, and uses the faster plan where it fits.
+struct MatchPlan {
+  int S;         // shares per tile, 1 = whole tiles of shape ts
+  TileShape ts;
+};
+inline size_t whole_tiles_bytes(TileShape ts, int64_t L, int64_t P, int64_t Q) {
+  const int64_t npt = (P + ts.bp - 1) / ts.bp, nqt = (Q + ts.bq - 1) / ts.bq;
+  const int64_t n = L * (npt > 0 ? npt : 1) * Q;
+  return (size_t)(n > 0 ? n : 1) * sizeof(Part) + schedule_bytes(L * npt * nqt);
+}
+inline TileShape floor_tile(int64_t Q) {
+  return Q <= kNarrowTile.bq ? kNarrowTile : Q <= kMidTile.bq ? kMidTile : kBlockTile;
+}
+// shares of 256 columns (256 KB each) and the partials of the pool chunks
+inline size_t wide_shares_bytes(int S, int64_t L, int64_t P, int64_t Q) {
+  const SplitLayout sl = split_layout(S, L, P, Q);
+  return sl.bytes - sl.part_offset + (size_t)L * (size_t)S * (size_t)sl.npt * (size_t)((Q + 255) / 256) * 65536 * sizeof(float);
+}
+inline size_t match_floor_bytes(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
+  const int S = wide_split_count(mode, L, P, Q, T, H);
+  return S > 1 ? wide_shares_bytes(S, L, P, Q) : whole_tiles_bytes(floor_tile(Q), L, P, Q);
+}
+inline size_t plan_bytes(const MatchPlan& p, int64_t L, int64_t P, int64_t Q) {
+  return p.S > 1 ? split_layout(p.S, L, P, Q).bytes : whole_tiles_bytes(p.ts, L, P, Q);
+}
+// The plan of a call with `avail` bytes, at least match_floor_bytes().
+inline MatchPlan match_plan(int mode, int64_t L, int64_t P, int64_t Q, int T, int H, size_t avail) {
+  MatchPlan p = {split_count(mode, L, P, Q, T, H), tile_for(mode, L, P, Q)};
+  if (plan_bytes(p, L, P, Q) > avail) p = {wide_split_count(mode, L, P, Q, T, H), floor_tile(Q)};
+  return p;
 }
 
 template <bool BF16>
@@ -1577,13 +1617,9 @@ extern "C" size_t rc_match_workspace_size(const rc_kv_desc* qdesc, int32_t mode,
   using namespace rc;
   if (!qdesc || Q < 0 || P < 0 || qdesc->n_layers < 0) return 0;
   if (mode != RC_SCORE_BLOCK && mode != RC_SCORE_PER_HEAD_ALL) return 0;
-  const int S = split_count(mode, qdesc->n_layers, P, Q, qdesc->block_tokens, qdesc->n_kv_heads);
-  if (S > 1) return split_layout(S, qdesc->n_layers, P, Q).bytes;
-  const TileShape ts = tile_for(mode, qdesc->n_layers, P, Q);
-  const int64_t npt = (P + ts.bp - 1) / ts.bp;
-  const int64_t nqt = (Q + ts.bq - 1) / ts.bq;
-  const int64_t n = (int64_t)qdesc->n_layers * (npt > 0 ? npt : 1) * Q;
-  return (size_t)(n > 0 ? n : 1) * sizeof(Part) + schedule_bytes((int64_t)qdesc->n_layers * npt * nqt);
+  const int L = qdesc->n_layers, T = qdesc->block_tokens, H = qdesc->n_kv_heads;
+  const size_t fast = plan_bytes(match_plan(mode, L, P, Q, T, H, SIZE_MAX), L, P, Q), floor = match_floor_bytes(mode, L, P, Q, T, H);
+  return fast > floor ? fast : floor;
 }
 
 extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* pdesc, int32_t mode, const void* kq,
@@ -1609,17 +1645,20 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
   if (P > 0 && (!kp || !vp || !p_ksq || !p_vsq)) return fail(RC_ERR_INVALID_ARG, "rc_match_blocks: NULL pool pointer");
   if (!aligned16(kq) || !aligned16(vq) || !aligned16(kp) || !aligned16(vp))
     return fail(RC_ERR_INVALID_ARG, "rc_match_blocks: KV pointer not 16-byte aligned");
-  const TileShape ts = tile_for(mode, L, P, Q);
-  const int64_t npt = (P + ts.bp - 1) / ts.bp, nqt = (Q + ts.bq - 1) / ts.bq;
-  const int64_t total = (int64_t)L * npt * nqt;
-  if (Q > 0x7fffffffLL || P > 0x7fffffffLL || total > 0x3fffffffLL || (int64_t)L * Q > 0x7fffffffLL * 128)
+  const TileShape ft = floor_tile(Q);
+  if (Q > 0x7fffffffLL || P > 0x7fffffffLL || L * ((P + ft.bp - 1) / ft.bp) * ((Q + ft.bq - 1) / ft.bq) > 0x3fffffffLL ||
+      (int64_t)L * Q > 0x7fffffffLL * 128)
     return fail(RC_ERR_UNSUPPORTED, "rc_match_blocks: problem beyond the grid limits");
-  const size_t need = rc_match_workspace_size(qdesc, mode, Q, P);
+  const size_t need = match_floor_bytes(mode, L, P, Q, qdesc->block_tokens, qdesc->n_kv_heads);
   if (!workspace || workspace_bytes < need || !aligned16(workspace))
     return fail(RC_ERR_WORKSPACE, "rc_match_blocks: workspace of %zu bytes needed (16-byte aligned), got %zu", need,
                 workspace_bytes);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  const int S = split_count(mode, L, P, Q, qdesc->block_tokens, qdesc->n_kv_heads);
+  const MatchPlan plan = match_plan(mode, L, P, Q, qdesc->block_tokens, qdesc->n_kv_heads, workspace_bytes);
+  const int S = plan.S;
+  const TileShape ts = plan.ts;
+  const int64_t npt = (P + ts.bp - 1) / ts.bp, nqt = (Q + ts.bq - 1) / ts.bq;
+  const int64_t total = (int64_t)L * npt * nqt;
   const long long LQ = (long long)L * Q;
 
   if (S > 1) {
@@ -1705,7 +1744,7 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
     mp.stagger_unit = kStaggerUnit;
     mp.vgrid = (int)virtual_grid(total);
     const unsigned grid = launch_grid((unsigned)mp.vgrid);
-    if (rc_status s = prepare_schedule(mp, grid, static_cast<char*>(workspace) + need - schedule_bytes(total), st)) return s;
+    if (rc_status s = prepare_schedule(mp, grid, static_cast<char*>(workspace) + plan_bytes(plan, L, P, Q) - schedule_bytes(total), st)) return s;
     if (qdesc->dtype == RC_BF16)
       launch_tiles<true>(mode, ts, mp, grid, st);
     else

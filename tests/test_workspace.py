@@ -1,0 +1,115 @@
+"""The bytes of workspace a search call insists on.  They do not follow the tile shapes and shares that are fastest: a
+smaller workspace than rc_match_workspace_size() gives a slower plan, down to a floor that is stated in include/rc.h."""
+import ctypes
+import re
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_21433_amd import binding as rc
+from paper_2507_21433_amd import synth
+from tests import parity
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import os
+    if not os.path.exists(rc.LIB_PATH):
+        from paper_2507_21433_amd import build
+        build.build()
+    return rc.lib()
+
+
+def descs(L, T, H, P, Q):
+    return [rc.KvDesc(L, T, H, 128, 0, n * T * H * 128) for n in (Q, P)]
+
+
+def needed(lib, mode, L, T, H, P, Q):
+    """What a call without a workspace says it needs (it is refused before anything is launched)."""
+    q, p = descs(L, T, H, P, Q)
+    fake = ctypes.c_void_p(0x1000)
+    assert lib.rc_match_blocks(ctypes.byref(q), ctypes.byref(p), mode, fake, fake, Q, fake, fake, fake, fake, P, fake, fake, None,
+                               0.9, fake, fake, fake, None, None, 0, None) == 3
+    return int(re.search(rb"workspace of (\d+) bytes needed", lib.rc_last_error()).group(1))
+
+
+def size(lib, mode, L, T, H, P, Q):
+    return lib.rc_match_workspace_size(ctypes.byref(descs(L, T, H, P, Q)[0]), mode, Q, P)
+
+
+def whole_tiles(L, P, Q):
+    """16 bytes per (layer, pool tile of 256, query), then the tile schedule: 520 words of 128 bytes, one claim word per
+    tile of the launch (rounded up to rounds of 256) and 512 more."""
+    npt, nqt = -(-P // 256), -(-Q // 256)
+    return L * npt * Q * 16 + 4 * (520 * 32 + -(-L * npt * nqt // 256) * 256 + 512)
+
+
+# more than 256 tiles of 256 x 256, or (block score, at most 128 queries) more than 128: never more than the partials
+@pytest.mark.parametrize("mode,L,T,H,P,Q", [(0, 48, 32, 10, 1289, 102), (1, 32, 32, 8, 2531, 24), (0, 24, 16, 10, 1635, 4),
+                                            (0, 7, 16, 10, 6272, 1), (1, 46, 16, 8, 1515, 1), (0, 40, 16, 10, 6201, 300),
+                                            (1, 16, 32, 8, 4100, 300), (0, 64, 16, 8, 4096, 256), (0, 260, 16, 1, 193, 640)])
+def test_search_takes_the_partials_of_whole_tiles(lib, mode, L, T, H, P, Q):
+    assert needed(lib, mode, L, T, H, P, Q) == whole_tiles(L, P, Q) <= size(lib, mode, L, T, H, P, Q)
+
+
+# fewer tiles: 256 KB per share and tile, and the partials of the pool chunks
+@pytest.mark.parametrize("mode,L,T,H,P,Q,nbytes", [(0, 1, 16, 8, 4096, 16, 67141632), (0, 2, 16, 8, 64, 4, 33554688),
+                                                   (1, 2, 16, 8, 257, 4, 8389760), (0, 2, 16, 8, 4096, 300, 68337664),
+                                                   (1, 3, 16, 4, 11147, 133, 140640048)])
+def test_search_takes_256_column_shares(lib, mode, L, T, H, P, Q, nbytes):
+    assert needed(lib, mode, L, T, H, P, Q) == nbytes <= size(lib, mode, L, T, H, P, Q)
+
+
+def test_one_workspace_for_the_largest_call(lib):
+    # an engine that sizes once for its largest step: every smaller step of more than one round of tiles is taken
+    for mode, L, T, H, P in [(0, 64, 16, 8, 4096), (1, 32, 32, 8, 2531), (0, 48, 16, 10, 3100), (1, 64, 16, 4, 1289)]:
+        largest = size(lib, mode, L, T, H, P, 256)
+        for Q in (1, 24, 40, 64, 65, 102, 128, 129, 192, 200, 255):
+            assert needed(lib, mode, L, T, H, P, Q) <= largest, (mode, L, P, Q)
+
+
+# ---- the slower plans give the oracle's results, and no plan writes past its workspace
+
+GUARD = 1 << 20
+
+
+def guarded(nbytes):
+    t = torch.full((nbytes + GUARD,), 0xA5, dtype=torch.uint8, device=DEV)
+    return t, t[:nbytes]
+
+
+def search(pr, w, ws):
+    qk, qv = rc.rc_block_norms(pr["kq"], pr["vq"], w.mode)
+    pk, pv = rc.rc_block_norms(pr["kp"], pr["vp"], w.mode)
+    out = rc.rc_match_blocks(pr["kq"], pr["vq"], qk, qv, pr["kp"], pr["vp"], pk, pv, pr["live"], w.tau, w.mode, workspace=ws)
+    torch.cuda.synchronize()
+    return {k: v.cpu().numpy() for k, v in out.items()}
+
+
+# a small workspace takes 64- and 128-column shares to whole tiles (both modes) and 192 x 320 tiles to 256 x 256; 192 and 64
+# columns that fit either way
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode,L,T,H,P,Q", [(0, 24, 16, 3, 1635, 4), (0, 100, 16, 3, 513, 65), (1, 90, 16, 8, 513, 40), (1, 90, 16, 4, 513, 97),
+                                            (0, 90, 16, 1, 577, 300), (1, 90, 16, 2, 577, 300), (0, 2, 16, 3, 300, 180), (0, 3, 16, 8, 257, 5)])
+def test_search_in_a_small_workspace(oracle, lib, mode, L, T, H, P, Q):
+    print(f"[gpu-case] small workspace mode {mode} L={L} T={T} H={H} P={P} Q={Q}", flush=True)
+    w = synth.scaled(synth.WORKLOADS[2], name="small_ws", L=L, P=P, Q=Q, T=T, H=H, mode=mode, planted_frac=0.3 if P > Q else 0.0,
+                     R=1, E=P + Q, seed=61)
+    pr = synth.make_problem(w, DEV)
+    orc = oracle.match(0, mode, *(synth.bits(pr[n]) for n in ("kq", "vq", "kp", "vp")), pr["live"].cpu().numpy(), w.tau, want_scores=True)
+    floor, full = needed(lib, mode, L, T, H, P, Q), size(lib, mode, L, T, H, P, Q)
+    got = {}
+    for nbytes in {floor, full}:
+        mem, ws = guarded(nbytes)
+        got[nbytes] = search(pr, w, ws)
+        assert (mem[nbytes:] == 0xA5).all(), "written past the workspace"
+        parity.check_match(got[nbytes], orc, w.tau, parity.score_lookup(orc["scores"], got[nbytes]["best_idx"]))
+    if mode == 1:   # scores on a grid, the same on every plan
+        for k in got[full]:
+            assert np.array_equal(got[floor][k], got[full][k]), k
+    with pytest.raises(rc.RcError) as e:
+        search(pr, w, guarded(floor - 1)[1])
+    assert e.value.code == 3
