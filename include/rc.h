@@ -219,7 +219,12 @@ rc_status rc_score_candidates(const rc_kv_desc* qdesc, const rc_kv_desc* pdesc, 
                               float* scores, int32_t* best_idx, float* best_score, int32_t* match_idx,
                               void* hip_stream);
 
-/* Bytes of DEVICE workspace rc_match_blocks_layer_mean needs (0 on bad arguments). */
+/* Bytes of DEVICE workspace with which rc_match_blocks_layer_mean is fastest (0 on bad arguments): the sums of the
+ * tiles (fp32) and 16 bytes per (chunk of at least 32 pool blocks, query block).  It goes up and down with Q and P, up to
+ * 512 MB and more; a call takes less as well, and may be slower then, down to a floor:
+ *   - where rc_match_blocks' floor in RC_SCORE_BLOCK mode is that of whole tiles: 256 KB per tile of 256 x 256 and group
+ *     of layers, at most min(n_layers, ceil(1024 / tiles of a layer)) groups, plus the 16-byte partials;
+ *   - else that floor (256 KB per tile and share). */
 size_t rc_layer_mean_workspace_size(const rc_kv_desc* qdesc, int64_t Q, int64_t P);
 
 /*
@@ -240,7 +245,8 @@ size_t rc_layer_mean_workspace_size(const rc_kv_desc* qdesc, int64_t Q, int64_t 
  *   best_idx        DEVICE int32 [Q]: argmin over live pool blocks, lowest index on exact ties, -1 if none
  *   best_dist       DEVICE float [Q] (+inf if none);  match_idx: best_idx if best_dist <= threshold else -1
  *   second_dist     DEVICE float [Q] or NULL: second-smallest distance, with multiplicity (+inf if fewer than two)
- *   workspace       DEVICE, >= rc_layer_mean_workspace_size() bytes, 16-byte aligned, scratch
+ *   workspace       DEVICE, 16-byte aligned, scratch, rc_layer_mean_workspace_size() bytes or more; less, down to the
+ *                   floor above, is taken and gives a slower plan (distances may then differ in their last bits)
  * fp32 throughout; a radicand that rounding pushes below 0 is clamped to 0.  n_layers must be
  * >= 1 (RC_ERR_INVALID_ARG otherwise); Q == 0 launches nothing; P == 0 writes -1 / +inf.
  */

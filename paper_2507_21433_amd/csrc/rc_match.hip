@@ -1539,6 +1539,28 @@ inline MatchPlan match_plan(int mode, int64_t L, int64_t P, int64_t Q, int T, in
   return p;
 }
 
+// The layer-mean search, in the same way: whole tiles of mean_columns() columns, or shares by the block score's rule.
+inline size_t mean_tiles_bytes(int L, int64_t P, int64_t Q) {
+  const int bq = mean_columns(Q);
+  const int64_t npt = (P + 255) / 256, nqt = (Q + bq - 1) / bq;
+  const int sel_rows = select_rows(P, Q);
+  const int64_t nchunks = (P + sel_rows - 1) / sel_rows;
+  return layer_mean_part_offset(layer_split(L, npt * nqt).groups, npt, nqt, bq) +
+         (size_t)(nchunks > 0 ? nchunks : 1) * (size_t)(Q > 0 ? Q : 1) * sizeof(Part);
+}
+inline size_t mean_plan_bytes(int S, int L, int64_t P, int64_t Q) {
+  return S > 1 ? split_layout(S, L, P, Q).bytes : mean_tiles_bytes(L, P, Q);
+}
+inline size_t mean_floor_bytes(int L, int64_t P, int64_t Q, int T, int H) {
+  const int S = wide_split_count(RC_SCORE_BLOCK, L, P, Q, T, H);
+  return S > 1 ? wide_shares_bytes(S, L, P, Q) : mean_tiles_bytes(L, P, Q);
+}
+// Shares per tile of a call with `avail` bytes, at least mean_floor_bytes(); 1 = whole tiles.
+inline int mean_split_count(int L, int64_t P, int64_t Q, int T, int H, size_t avail) {
+  const int S = split_count(RC_SCORE_BLOCK, L, P, Q, T, H);
+  return mean_plan_bytes(S, L, P, Q) <= avail ? S : wide_split_count(RC_SCORE_BLOCK, L, P, Q, T, H);
+}
+
 template <bool BF16>
 void launch_tiles(int mode, TileShape ts, const MatchParams& mp, unsigned grid, hipStream_t st) {
   auto is = [&](TileShape t) { return ts.bp == t.bp && ts.bq == t.bq; };
@@ -1758,14 +1780,9 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
 extern "C" size_t rc_layer_mean_workspace_size(const rc_kv_desc* qdesc, int64_t Q, int64_t P) {
   using namespace rc;
   if (!qdesc || Q < 0 || P < 0 || qdesc->n_layers <= 0) return 0;
-  const int bq = mean_columns(Q);
-  const int64_t npt = (P + 255) / 256, nqt = (Q + bq - 1) / bq;
-  const int S = split_count(RC_SCORE_BLOCK, qdesc->n_layers, P, Q, qdesc->block_tokens, qdesc->n_kv_heads);
-  if (S > 1) return split_layout(S, qdesc->n_layers, P, Q).bytes;  // few tiles: shares of every tile's reduction
-  const LayerSplit ls = layer_split(qdesc->n_layers, npt * nqt);
-  const int sel_rows = select_rows(P, Q);
-  const int64_t nchunks = (P + sel_rows - 1) / sel_rows;
-  return layer_mean_part_offset(ls.groups, npt, nqt, bq) + (size_t)(nchunks > 0 ? nchunks : 1) * (size_t)(Q > 0 ? Q : 1) * sizeof(Part);
+  const int L = qdesc->n_layers, T = qdesc->block_tokens, H = qdesc->n_kv_heads;
+  const size_t fast = mean_plan_bytes(mean_split_count(L, P, Q, T, H, SIZE_MAX), L, P, Q), floor = mean_floor_bytes(L, P, Q, T, H);
+  return fast > floor ? fast : floor;
 }
 
 extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const rc_kv_desc* pdesc, const void* kq,
@@ -1798,14 +1815,14 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
   const int64_t total = (int64_t)ls.groups * npt * nqt;
   if (Q > 0x7fffffffLL || P > 0x7fffffffLL || total > 0x3fffffffLL || Q > (1LL << 20))
     return fail(RC_ERR_UNSUPPORTED, "rc_match_blocks_layer_mean: problem beyond the grid limits");
-  const size_t need = rc_layer_mean_workspace_size(qdesc, Q, P);
+  const size_t need = mean_floor_bytes(L, P, Q, qdesc->block_tokens, qdesc->n_kv_heads);
   if (!workspace || workspace_bytes < need || !aligned16(workspace))
     return fail(RC_ERR_WORKSPACE, "rc_match_blocks_layer_mean: workspace of %zu bytes needed (16-byte aligned), got %zu",
                 need, workspace_bytes);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   float* dpart = static_cast<float*>(workspace);
   const float scale = 1.0f / ((float)L * 2.0f * (float)qdesc->block_tokens * (float)qdesc->n_kv_heads);
-  const int S = split_count(RC_SCORE_BLOCK, L, P, Q, qdesc->block_tokens, qdesc->n_kv_heads);
+  const int S = mean_split_count(L, P, Q, qdesc->block_tokens, qdesc->n_kv_heads, workspace_bytes);
   if (S > 1) {
     // Few tiles (a call with one or a few layers, a small pool): the launch would leave compute units idle, and
     // giving every workgroup fewer layers does not help below one layer each.  Every tile's reduction is cut into

@@ -71,6 +71,35 @@ def test_one_workspace_for_the_largest_call(lib):
             assert needed(lib, mode, L, T, H, P, Q) <= largest, (mode, L, P, Q)
 
 
+def mean_needed(lib, L, T, H, P, Q):
+    q, p = descs(L, T, H, P, Q)
+    fake = ctypes.c_void_p(0x1000)
+    assert lib.rc_match_blocks_layer_mean(ctypes.byref(q), ctypes.byref(p), fake, fake, Q, fake, fake, fake, fake, P, fake, fake, None,
+                                          0.5, fake, fake, fake, None, None, 0, None) == 3
+    return int(re.search(rb"workspace of (\d+) bytes needed", lib.rc_last_error()).group(1))
+
+
+def mean_size(lib, L, T, H, P, Q):
+    return lib.rc_layer_mean_workspace_size(ctypes.byref(descs(L, T, H, P, Q)[0]), Q, P)
+
+
+# the sums of 256 x 256 tiles (256 KB) of each group of layers, as few groups as make 1024 tiles, and 16-byte partials: a
+# call never needs more, however many shares it is fastest with
+@pytest.mark.parametrize("L,T,H,P,Q", [(43, 16, 10, 704, 27), (64, 16, 8, 1280, 16), (64, 16, 8, 2048, 128), (61, 16, 16, 1100, 8),
+                                       (25, 16, 8, 13134, 3), (13, 16, 8, 11504, 36), (32, 32, 8, 2900, 64), (12, 16, 8, 6144, 169)])
+def test_layer_mean_takes_the_sums_of_whole_tiles(lib, L, T, H, P, Q):
+    tiles = -(-P // 256) * -(-Q // 256)
+    groups = min(L, -(-1024 // tiles))
+    chunks = -(-P // 32)
+    assert mean_needed(lib, L, T, H, P, Q) <= groups * tiles * 262144 + chunks * Q * 16
+    assert mean_needed(lib, L, T, H, P, Q) <= mean_size(lib, L, T, H, P, Q)
+
+
+@pytest.mark.parametrize("L,T,H,P,Q,nbytes", [(1, 16, 8, 459, 8, 33556352), (12, 16, 8, 1537, 169, 177750720)])
+def test_layer_mean_takes_256_column_shares(lib, L, T, H, P, Q, nbytes):
+    assert mean_needed(lib, L, T, H, P, Q) == nbytes <= mean_size(lib, L, T, H, P, Q)
+
+
 # ---- the slower plans give the oracle's results, and no plan writes past its workspace
 
 GUARD = 1 << 20
@@ -112,4 +141,32 @@ def test_search_in_a_small_workspace(oracle, lib, mode, L, T, H, P, Q):
             assert np.array_equal(got[floor][k], got[full][k]), k
     with pytest.raises(rc.RcError) as e:
         search(pr, w, guarded(floor - 1)[1])
+    assert e.value.code == 3
+
+
+# whole tiles of 64 and 128 columns where shares are faster, shares and whole tiles that fit either way
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,T,H,P,Q", [(40, 16, 3, 1900, 9), (50, 16, 4, 1300, 100), (2, 16, 3, 300, 180), (30, 16, 1, 9000, 65)])
+def test_layer_mean_in_a_small_workspace(oracle, lib, L, T, H, P, Q):
+    print(f"[gpu-case] layer mean, small workspace L={L} T={T} H={H} P={P} Q={Q}", flush=True)
+    w = synth.scaled(synth.WORKLOADS[2], name="small_ws_lm", L=L, P=P, Q=Q, T=T, H=H, planted_frac=0.3, R=1, E=P + Q, seed=62)
+    pr = synth.make_problem(w, DEV)
+    live = pr["live"].min(dim=0).values.contiguous()
+    thr = 0.5 * np.sqrt(w.Dh / (T * H))
+    orc = oracle.layer_mean(0, *(synth.bits(pr[n]) for n in ("kq", "vq", "kp", "vp")), live.cpu().numpy(), thr, want_dist=True)
+    norms = [*rc.rc_block_norms(pr["kq"], pr["vq"], 0), *rc.rc_block_norms(pr["kp"], pr["vp"], 0)]
+
+    def call(ws):
+        out = rc.rc_match_blocks_layer_mean(pr["kq"], pr["vq"], *norms[:2], pr["kp"], pr["vp"], *norms[2:], live, thr, workspace=ws)
+        torch.cuda.synchronize()
+        return {k: v.cpu().numpy() for k, v in out.items()}
+
+    floor, full = mean_needed(lib, L, T, H, P, Q), mean_size(lib, L, T, H, P, Q)
+    for nbytes in {floor, full}:
+        mem, ws = guarded(nbytes)
+        got = call(ws)
+        assert (mem[nbytes:] == 0xA5).all(), "written past the workspace"
+        parity.check_layer_mean(got, orc, thr, parity.dist_lookup(orc["dist"], got["best_idx"]), 0.05 * parity.dist_tol(T, H, w.Dh))
+    with pytest.raises(rc.RcError) as e:
+        call(guarded(floor - 1)[1])
     assert e.value.code == 3
