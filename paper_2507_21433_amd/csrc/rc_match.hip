@@ -1496,10 +1496,7 @@ inline SplitLayout split_layout(int S, int64_t L, int64_t P, int64_t Q) {
   r.nqt = (Q + r.bq - 1) / r.bq;
   r.sel_rows = select_rows(P, Q);
   r.nchunks = (P + r.sel_rows - 1) / r.sel_rows;
-  // up to one round of tiles the room for a share is that of a 256-column tile at every width: the workspace of
-  // these shapes has always been that large
-  const size_t room = L * r.npt * r.nqt <= kSplitComputeUnits ? 65536 : 256 * (size_t)r.bq;
-  r.part_offset = (size_t)L * (size_t)S * (size_t)r.npt * (size_t)r.nqt * room * sizeof(float);
+  r.part_offset = (size_t)L * (size_t)S * (size_t)r.npt * (size_t)r.nqt * 256 * (size_t)r.bq * sizeof(float);
   r.bytes = r.part_offset + (size_t)L * (size_t)r.nchunks * (size_t)Q * sizeof(Part);
   return r;
 }

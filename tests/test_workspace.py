@@ -100,6 +100,13 @@ def test_layer_mean_takes_256_column_shares(lib, L, T, H, P, Q, nbytes):
     assert mean_needed(lib, L, T, H, P, Q) == nbytes <= mean_size(lib, L, T, H, P, Q)
 
 
+# at most 2048 shares of at most 256 tiles, and a share is as large as its tile: 64 KB up to 64 queries, 128 KB up to 128
+@pytest.mark.parametrize("mode,L,T,H,P,Q", [(0, 24, 16, 10, 1635, 4), (0, 7, 16, 10, 6272, 1), (1, 46, 16, 8, 915, 1), (0, 45, 16, 8, 700, 65)])
+def test_narrow_shares_take_no_more_than_they_store(lib, mode, L, T, H, P, Q):
+    partials = L * -(-P // 32) * Q * 16
+    assert size(lib, mode, L, T, H, P, Q) <= 2048 * 256 * (64 if Q <= 64 else 128) * 4 + partials
+
+
 # ---- the slower plans give the oracle's results, and no plan writes past its workspace
 
 GUARD = 1 << 20
@@ -170,3 +177,21 @@ def test_layer_mean_in_a_small_workspace(oracle, lib, L, T, H, P, Q):
     with pytest.raises(rc.RcError) as e:
         call(guarded(floor - 1)[1])
     assert e.value.code == 3
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode,L,T,H,P,Q", [(0, 2, 16, 3, 300, 180), (1, 2, 16, 5, 257, 180), (0, 1, 16, 3, 300, 300), (0, 1, 16, 3, 300, 256)])
+def test_shares_stay_within_their_tiles(lib, mode, L, T, H, P, Q):
+    # few tiles: a share is stored as 256 x 192 or 256 floats, behind the shares follow the partials of the pool chunks
+    # (32 rows here), and what a workspace holds beyond is never touched (narrower shares fill theirs: the guards above)
+    print(f"[gpu-case] extent of the shares mode {mode} L={L} T={T} H={H} P={P} Q={Q}", flush=True)
+    w = synth.scaled(synth.WORKLOADS[2], name="extent", L=L, P=P, Q=Q, T=T, H=H, mode=mode, planted_frac=0.0, R=1, E=P + Q, seed=63)
+    pr = synth.make_problem(w, DEV)
+    columns = 192 if Q <= 192 or 256 < Q <= 384 else 256
+    npt, partials = -(-P // 256), L * -(-P // 32) * Q * 16
+    shares, rest = divmod(needed(lib, mode, L, T, H, P, Q) - partials, L * npt * -(-Q // 256) * 262144)
+    assert rest == 0 and shares > 1
+    end = L * npt * -(-Q // columns) * shares * 256 * columns * 4 + partials
+    mem, ws = guarded(size(lib, mode, L, T, H, P, Q))
+    search(pr, w, ws)
+    assert (mem[end:] == 0xA5).all() and not (mem[end - partials:end] == 0xA5).all()
