@@ -376,16 +376,35 @@ inline int cand_layers_per_group(int L, int64_t Q, int64_t C) {
   return (int)((L + groups - 1) / groups);
 }
 
-// Candidates per workgroup of a launch over `lists` lists of C: 4 while a launch of 16 per workgroup has fewer than
-// 512 workgroups and 22 pairs per compute unit, and does not just fill one round of them; beyond, the queries' extra
-// traffic costs more than the parallelism gives.  16 -> 4 per workgroup, us, blocks of 64 KB / 256 KB:
-//   C = 16  120 lists 38 -> 28 / 128 -> 90   180 42 -> 39 / 138 -> 137   250 50 -> 50 / 175 -> 185   320 72 -> 62 / 263 -> 236
-//           400 78 -> 80 / 286 -> 305   500 90 -> 96 / 333 -> 373
-//   C = 22  120 41 -> 36 / 139 -> 126   180 65 -> 53 / 229 -> 196   250 75 -> 67 / 267 -> 251   320 99 -> 98 / 358 -> 359
-inline int cand_per_wg(int64_t lists, int64_t C) {
-  const int64_t wgs = lists * ((C + kCandPerWg - 1) / kCandPerWg);
-  const bool one_round = wgs > 224 && wgs <= 256;
-  return wgs < 512 && lists * C < 22 * 256 && !one_round ? kCandFew : kCandPerWg;
+// Candidates per workgroup of a launch over `lists` lists of C (`lists` x layer groups for the distances): 4 or 16.
+// Four times the workgroups pay while the chip has idle compute units, and cost the query once more per workgroup,
+// most where ceil(C / 4) workgroups are badly filled (C = 5).  The time of both goes in steps, at every 256 workgroups
+// (one per compute unit), so the lines are at multiples of 256 of either count: up to 256 of 4 always; up to 512, where the
+// second round is well filled or a block is small; again where 16 per workgroup are just over 256.  two_trips is false
+// for the kernels that have one trip's loads in flight with 16 candidates (the distances, heads that do not divide 16):
+// four pay longer there.  The lines are drawn through 5800 measured points (C = 1 to 64, 32 to 511 lists, blocks of 4 to
+// 128 KB per tensor): of those that take 4, all but one (7 %) are at most 4 % slower with 4 than with 16.  Some, us, 16 -> 4:
+//   block score, 32 KB   C = 5   120 lists 22 -> 17   400 33 -> 41 (takes 16)   C = 8   64 25 -> 17   288 41 -> 38   400 46 -> 48 (16)
+//                        C = 16  64 37 -> 20   120 39 -> 32   200 46 -> 51 (16)   264 72 -> 63
+//                128 KB  C = 5   120 55 -> 41   160 57 -> 66 (16)   400 100 -> 138 (16)   C = 16  120 115 -> 96   288 252 -> 222
+//   distances,    64 KB  C = 8   200 54 -> 45   C = 12  160 68 -> 51   360 110 -> 111 (16)
+inline int cand_per_wg(int64_t lists, int64_t C, int block_bytes, bool two_trips) {
+  const int64_t n16 = lists * ((C + kCandPerWg - 1) / kCandPerWg), n4 = lists * ((C + kCandFew - 1) / kCandFew);
+  const int kb = block_bytes / 1024;
+  const bool small = kb <= 16;
+  auto few = [&]() {
+    if (n16 >= 512) return false;
+    if (C <= 4) return C < 4 || kb <= 80 || n16 <= 256 || !two_trips;   // the same workgroups, with fewer registers each
+    if (C > 16 && C <= 24) return C <= 23 || n4 <= 1280;                // 16 per workgroup leave a second one almost empty
+    if (kb <= 8) return n16 <= 400;
+    if (n16 > 256) return (C >= 7 || small) && n4 <= (C <= 8 ? 768 : C <= 12 ? 1024 : 1280);
+    if (C > 24) return n4 <= (small || !two_trips ? 768 : 512);
+    if (!two_trips) return kb <= 80 || n4 <= (C == 5 ? 384 : C <= 12 ? 512 : 768);
+    if (small) return C <= 12 || n4 <= 768;
+    if (C <= 8) return n4 <= (kb > 40 ? 256 : C == 5 ? 352 : 448);
+    return n4 <= (kb > 80 && C <= 12 ? 448 : 512);
+  };
+  return few() ? kCandFew : kCandPerWg;
 }
 
 template <bool BF16>
@@ -456,9 +475,9 @@ extern "C" rc_status rc_score_candidates(const rc_kv_desc* qdesc, const rc_kv_de
     cp.C = (int)C;
     cp.block_bytes = qdesc->block_tokens * H * qdesc->head_dim * 2;  // T >= 16, Dh = 128: a multiple of 16 KB / 4
     cp.heads = (mode == RC_SCORE_BLOCK) ? 1 : H;
-    const int per = cand_per_wg((int64_t)L * Q, C);
-    const dim3 grid((unsigned)((C + per - 1) / per), (unsigned)Q, (unsigned)L);
     const bool any_h = mode == RC_SCORE_PER_HEAD_ALL && (16 % H) != 0;  // a thread's chunks wander over the heads
+    const int per = cand_per_wg((int64_t)L * Q, C, cp.block_bytes, !any_h);
+    const dim3 grid((unsigned)((C + per - 1) / per), (unsigned)Q, (unsigned)L);
     if (qdesc->dtype == RC_BF16)
       launch_candidates<true>(any_h, per, grid, cp, st);
     else
@@ -530,7 +549,7 @@ extern "C" rc_status rc_candidate_distances(const rc_kv_desc* qdesc, const rc_kv
     cp.L = L;
     cp.G = G;
     cp.block_bytes = qdesc->block_tokens * qdesc->n_kv_heads * qdesc->head_dim * 2;
-    const int per = cand_per_wg((int64_t)groups * Q, C);
+    const int per = cand_per_wg((int64_t)groups * Q, C, cp.block_bytes, false);
     const dim3 grid((unsigned)((C + per - 1) / per), (unsigned)Q, (unsigned)groups);
     if (per == kCandFew) {
       if (qdesc->dtype == RC_BF16)

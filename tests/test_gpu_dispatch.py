@@ -6,6 +6,7 @@ import torch
 
 from paper_2507_21433_amd import binding as rc
 from paper_2507_21433_amd import synth
+from tests.test_gpu_candidates import compare, compare_distances, gpu_candidates
 from tests.test_gpu_layer_mean import run_case
 from tests.test_gpu_sweep import run_shape
 
@@ -93,3 +94,24 @@ def test_candidates_per_workgroup(oracle, L, Q, C):
     o = oracle.candidate_distances(0, *bits, cand[0], live.cpu().numpy(), 0.5)
     d, fin = g["dist"].cpu().numpy(), np.isfinite(o["dist"])
     assert np.array_equal(np.isfinite(d), fin) and np.allclose(d[fin], o["dist"][fin], rtol=1e-5, atol=0)   # fp32 sums of exact differences
+
+
+# Candidates per workgroup, both sides of the lines of cand_per_wg for blocks of 32, 64 and 128 KB: counts of lists at which
+# workgroups of 4 fill one, one and a half and two rounds of the compute units, and of 16 a round and a little more.
+LINES = [(16, 8, 176, 5), (16, 8, 177, 5), (16, 8, 224, 8), (16, 8, 225, 8), (16, 8, 170, 12), (16, 8, 171, 12), (16, 8, 257, 7), (16, 8, 342, 10),
+         (16, 8, 320, 13), (16, 8, 321, 13), (32, 8, 128, 6), (32, 8, 129, 6), (32, 8, 213, 24), (32, 16, 64, 16), (32, 16, 149, 9), (32, 16, 257, 4)]
+
+
+@pytest.mark.parametrize("T,H,Q,C", LINES)
+def test_candidates_at_the_lines(oracle, T, H, Q, C):
+    w = synth.scaled(synth.WORKLOADS[2], name=f"lines{T}.{H}.{Q}x{C}", L=1, P=60, Q=Q, T=T, H=H, planted_frac=0.0, R=1, E=60 + Q, seed=8300)
+    pr = synth.make_problem(w, "cuda:0")
+    bits = [synth.bits(pr[n]) for n in ("kq", "vq", "kp", "vp")]
+    cand = np.random.RandomState(C).randint(-1, 60, size=(1, Q, C)).astype(np.int32)
+    live = pr["live"].cpu().numpy()
+    for mode in (0, 1):
+        compare(gpu_candidates(synth.scaled(w, mode=mode), pr, cand, pr["live"]), oracle.candidates(0, mode, *bits, cand, live, w.tau), cand, w.tau, tol=2e-5)
+    unit = np.sqrt(w.Dh / (T * H))
+    g = rc.rc_candidate_distances(pr["kq"], pr["vq"], pr["kp"], pr["vp"], pr["live"][0].contiguous(), torch.as_tensor(cand[0], device="cuda:0"), 0.5 * unit)
+    compare_distances({k: v.cpu().numpy() for k, v in g.items()}, oracle.candidate_distances(0, *bits, cand[0], live[0], 0.5 * unit), cand[0],
+                      0.5 * unit, 1e-5 * unit)
