@@ -7,7 +7,9 @@ import torch
 from paper_2507_21433_amd import binding as rc
 from paper_2507_21433_amd import synth
 from tests.test_gpu_candidates import compare, compare_distances, gpu_candidates
-from tests.test_gpu_layer_mean import run_case
+from tests import paths
+from tests.test_gpu_layer_mean import gpu_layer_mean, run_case
+from tests.test_gpu_parity import full_check, run_gpu_match
 from tests.test_gpu_sweep import run_shape
 
 pytestmark = pytest.mark.gpu
@@ -21,7 +23,7 @@ def test_merge_parts(oracle, P, Q):
     run_shape(oracle, dict(L=2, P=P, Q=Q, T=16, H=1, mode=0, dtype="f16", planted_frac=0.3, seed=7100 + P), f"parts{P}x{Q}", P)
 
 
-# Tile width (64 columns up to 64 queries, 128 up to 128, 256 beyond) and shares per tile: per-head mode in whole tiles
+# Tile width (64 columns up to 64 queries, 128 up to 128, 192 or 256 beyond) and shares per tile: per-head mode in whole tiles
 # (256 tiles: one round) and with one share per head, block mode with a share count that is no power of two.
 WIDTHS = [(1, 256, 64, 64, 2), (1, 256, 40, 65, 2), (1, 256, 70, 128, 1), (1, 3, 300, 64, 5), (1, 2, 257, 65, 16),
           (1, 2, 255, 128, 3), (1, 2, 300, 129, 3), (0, 24, 250, 40, 5), (0, 24, 250, 65, 5), (0, 2, 300, 128, 3), (0, 11, 513, 1, 6),
@@ -35,24 +37,31 @@ def test_tile_widths_and_shares(oracle, mode, L, P, Q, H):
 
 
 # Shape of whole tiles beyond 128 queries: 256 x 192, 192 x 320 and 256 x 256 with one and more query tiles, pools that end
-# on and beside an edge of a tile.
-SHAPES = [(0, 260, 8, 129, 1), (0, 260, 193, 192, 1), (0, 260, 257, 193, 1), (0, 260, 192, 257, 1), (0, 260, 193, 320, 1),
-          (0, 260, 31, 321, 1), (0, 260, 40, 640, 1), (0, 260, 5, 641, 1), (1, 260, 193, 160, 1), (1, 130, 191, 300, 2), (1, 260, 40, 384, 1),
-          (1, 260, 20, 640, 1)]
+# on and beside an edge of a tile (256 x 256 with two query tiles in a workspace without room for tiles of 192 rows).
+SHAPES = [(0, 260, 8, 129, 1, (256, 192)), (0, 260, 193, 192, 1, (256, 192)), (0, 260, 257, 193, 1, (192, 320)), (0, 260, 192, 257, 1, (192, 320)),
+          (0, 260, 193, 320, 1, (256, 192)), (0, 260, 31, 321, 1, (256, 192)), (0, 260, 40, 640, 1, (192, 320)), (0, 260, 5, 641, 1, (192, 320)),
+          (1, 260, 193, 160, 1, (256, 192)), (1, 130, 191, 300, 2, (192, 320)), (1, 260, 40, 384, 1, (256, 192)), (1, 260, 20, 640, 1, (192, 320)),
+          (0, 260, 255, 256, 1, (256, 256)), (0, 300, 500, 193, 1, (256, 256)), (1, 260, 129, 250, 1, (256, 256)), (1, 260, 300, 256, 1, (256, 256)),
+          (0, 130, 449, 500, 1, (256, 256)), (0, 260, 193, 385, 1, (256, 256)), (1, 260, 193, 512, 1, (256, 256))]
 
 
-@pytest.mark.parametrize("mode,L,P,Q,H", SHAPES)
-def test_tile_shapes(oracle, mode, L, P, Q, H):
-    run_shape(oracle, dict(L=L, P=P, Q=Q, T=16, H=H, mode=mode, dtype="bf16" if Q % 2 else "f16", planted_frac=0.0 if P < 64 else 0.3,
-                           seed=7500 + P), f"shape{mode}.{L}.{P}x{Q}", P)
+@pytest.mark.parametrize("mode,L,P,Q,H,tile", SHAPES)
+def test_tile_shapes(oracle, mode, L, P, Q, H, tile):
+    w = synth.scaled(synth.WORKLOADS[2], name=f"shape{mode}.{L}.{P}x{Q}", L=L, P=P, Q=Q, T=16, H=H, mode=mode, dtype="bf16" if Q % 2 else "f16",
+                     planted_frac=0.0 if P < 64 else 0.3 * min(1.0, P / Q), R=1, E=P + Q, seed=7500 + P)
+    pr = synth.make_problem(w, "cuda:0")
+    ws = paths.whole_tiles_workspace(w) if tile == (256, 256) and Q > 256 else None
+    paths.assert_tiles(lambda: run_gpu_match(pr, w, pr["live"], workspace=ws), (*tile, mode))
+    full_check(oracle, w, pr, pr["live"], ws)
 
 
-# Layer-mean search at 128 columns (running sums in registers) and at 192 (in memory), layers in groups of 2, 2 and 1: 172
-# pool tiles of 5 layers; and at 192 columns with two query tiles.
-@pytest.mark.parametrize("L,P,Q", [(5, 44000, 65), (5, 44000, 129), (90, 300, 257)])
-def test_layer_mean_widths(oracle, L, P, Q):
+# Layer-mean search at 64 and 128 columns (running sums in registers), 192 and 256 (in memory), layers in groups of 2, 2 and
+# 1 (256 pool tiles of 5 layers) and of 2 with a last one of 1 (two query tiles of 192 columns, 21 pool tiles of 27 layers).
+@pytest.mark.parametrize("L,P,Q,columns", [(5, 65300, 9, 64), (5, 65300, 65, 128), (5, 65300, 129, 192), (5, 65300, 193, 256), (27, 5200, 257, 192)])
+def test_layer_mean_widths(oracle, L, P, Q, columns):
     w = synth.scaled(synth.WORKLOADS[2], name=f"lm{L}.{P}x{Q}", L=L, P=P, Q=Q, T=16, H=1, planted_frac=0.3, R=1, E=P + Q, seed=7700)
-    run_case(oracle, w, 0.5 * np.sqrt(w.Dh / (w.T * w.H)))
+    pr, _, _, _ = run_case(oracle, w, 0.5 * np.sqrt(w.Dh / (w.T * w.H)))
+    paths.assert_tiles(lambda: gpu_layer_mean(pr, None, 0.5), (256, columns, 2))
 
 
 # Shares per pair added by the selection kernels: 8 at a time, then 4, then single ones, K and V layer by layer dealt to four
@@ -83,17 +92,37 @@ def test_candidates_per_workgroup(oracle, L, Q, C):
     bits = [synth.bits(pr[n]) for n in ("kq", "vq", "kp", "vp")]
     cand = np.random.RandomState(C).randint(-1, 90, size=(L, Q, C)).astype(np.int32)
     for mode in (0, 1):
-        norms = [*rc.rc_block_norms(pr["kq"], pr["vq"], mode), *rc.rc_block_norms(pr["kp"], pr["vp"], mode)]
-        g = rc.rc_score_candidates(pr["kq"], pr["vq"], *norms[:2], pr["kp"], pr["vp"], *norms[2:], pr["live"],
-                                   torch.as_tensor(cand, device="cuda:0"), 0.9, mode)
-        o = oracle.candidates(0, mode, *bits, cand, pr["live"].cpu().numpy(), 0.9)
-        s, fin = g["scores"].cpu().numpy(), np.isfinite(o["scores"])
-        assert np.array_equal(np.isfinite(s), fin) and np.abs(s[fin] - o["scores"][fin]).max() <= 2e-5   # as in the sweep
+        g = gpu_candidates(synth.scaled(w, mode=mode), pr, cand, pr["live"])
+        compare(g, oracle.candidates(0, mode, *bits, cand, pr["live"].cpu().numpy(), w.tau), cand, w.tau, tol=2e-5)   # as in the sweep
     live = pr["live"][0].contiguous()
-    g = rc.rc_candidate_distances(pr["kq"], pr["vq"], pr["kp"], pr["vp"], live, torch.as_tensor(cand[0], device="cuda:0"), 0.5)
-    o = oracle.candidate_distances(0, *bits, cand[0], live.cpu().numpy(), 0.5)
-    d, fin = g["dist"].cpu().numpy(), np.isfinite(o["dist"])
-    assert np.array_equal(np.isfinite(d), fin) and np.allclose(d[fin], o["dist"][fin], rtol=1e-5, atol=0)   # fp32 sums of exact differences
+    unit = np.sqrt(w.Dh / (w.T * w.H))
+    thr = float(np.sqrt(2.0)) * unit          # fresh blocks lie on both sides of it
+    g = rc.rc_candidate_distances(pr["kq"], pr["vq"], pr["kp"], pr["vp"], live, torch.as_tensor(cand[0], device="cuda:0"), thr)
+    o = oracle.candidate_distances(0, *bits, cand[0], live.cpu().numpy(), thr)
+    compare_distances({k: v.cpu().numpy() for k, v in g.items()}, o, cand[0], thr, 1e-5 * unit)   # fp32 sums of exact differences
+
+
+# Equal distances go to the lowest pool index, wherever the copies stand in the list: in one lane's trips (64 apart), in
+# different lanes, before and behind lane 63, the higher index first or last.
+@pytest.mark.parametrize("first,second", [(0, 1), (0, 64), (1, 65), (5, 69), (3, 130), (63, 64), (40, 127), (62, 63), (10, 100), (0, 149)])
+def test_tied_candidates_go_to_the_lowest_index(first, second):
+    w = synth.scaled(synth.WORKLOADS[2], name="ties", L=3, P=200, Q=6, T=16, H=3, planted_frac=0.0, R=1, E=206, seed=8200)
+    pr = synth.make_problem(w, "cuda:0")
+    C, copies = 150, (150, 20, 77, 190, 33, 120)
+    cand = np.random.RandomState(first).permutation(np.setdiff1d(np.arange(200), (*copies, 7)))[None, :C].repeat(w.Q, 0).astype(np.int32)
+    for n in ("k", "v"):
+        for p in copies:
+            pr[n + "p"][:, p] = pr[n + "p"][:, 7]
+        pr[n + "q"][:, :] = pr[n + "p"][:, 7:8]      # every copy at distance 0 and score 1
+    for q, (a, b) in enumerate([(150, 20), (20, 150), (190, 77), (77, 190), (120, 33), (33, 120)]):
+        cand[q, first], cand[q, second] = a, b
+    want = np.minimum(cand[:, first], cand[:, second])
+    g = rc.rc_candidate_distances(pr["kq"], pr["vq"], pr["kp"], pr["vp"], None, torch.as_tensor(cand, device="cuda:0"), 0.5)
+    assert np.array_equal(g["best_idx"].cpu().numpy(), want) and np.array_equal(g["match_idx"].cpu().numpy(), want)
+    assert (g["best_dist"] == 0).all()
+    for mode in (0, 1):
+        s = gpu_candidates(synth.scaled(w, mode=mode, tau=0.9), pr, cand[None].repeat(w.L, 0), None)
+        assert np.array_equal(s["best_idx"], want[None].repeat(w.L, 0)) and np.array_equal(s["match_idx"], s["best_idx"])
 
 
 # Candidates per workgroup, both sides of the lines of cand_per_wg for blocks of 32, 64 and 128 KB: counts of lists at which

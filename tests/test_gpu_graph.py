@@ -8,6 +8,7 @@ import torch
 
 from paper_2507_21433_amd import binding as rc
 from paper_2507_21433_amd import synth
+from tests import paths
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -64,16 +65,21 @@ def flat(b, mode):
     return out + ([b["decided"]] if mode == 0 else []) + [b["qk"], b["qv"]]
 
 
-# (the last case has 19 rounds of tiles: the launch whose tile schedule lives in words that a kernel clears first)
+# (the last two cases have 16 rounds of 192 x 320 tiles and, in a workspace without room for a faster shape, 19 rounds of
+# 256 x 256: the launches whose tile schedule lives in words that a kernel clears first)
 @pytest.mark.parametrize("wl,kw", [(1, {}), (2, dict(L=3, P=700, Q=300, R=4, E=260)), (5, dict(L=2, P=300, Q=40, R=1, E=340)),
-                                   (2, dict(L=260, P=513, Q=1300, H=1, R=1, E=1813))])
+                                   (2, dict(L=260, P=513, Q=1300, H=1, R=1, E=1813)), (2, dict(L=260, P=577, Q=1300, H=1, R=1, E=1877, small=True))])
 def test_step_in_a_graph(wl, kw):
+    kw = dict(kw)
+    small = kw.pop("small", False)
     w = synth.scaled(synth.WORKLOADS[wl], name=f"graph_cfg{wl}", **kw)
     say(f"{w.name}: L={w.L} P={w.P} Q={w.Q} mode={w.mode}")
     pr = synth.make_problem(w, DEV)
     pk, pv = rc.rc_block_norms(pr["kp"], pr["vp"], w.mode)
     lv = pr["live"].min(dim=0).values.contiguous()
     eager, graphed = buffers(w, pr), buffers(w, pr)
+    if small:
+        eager["ws_match"], graphed["ws_match"] = paths.whole_tiles_workspace(w), paths.whole_tiles_workspace(w)
     step(w, pr, pk, pv, lv, eager)
     step(w, pr, pk, pv, lv, graphed)          # warm-up on the capture buffers, outside the graph
     torch.cuda.synchronize()

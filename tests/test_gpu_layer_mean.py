@@ -71,9 +71,9 @@ def test_layer_mean_small(oracle, dtype, L, P, Q, T, H):
 
 
 def test_layer_mean_layer_groups(oracle):
-    # enough tiles that a workgroup walks several layers: 5 layers in groups of 2, 2 and 1
-    w = synth.scaled(synth.WORKLOADS[2], name="lm_groups", L=5, P=44000, Q=8, T=16, H=1, planted_frac=0.5, R=1,
-                     E=44008, seed=43)
+    # enough tiles (256 per layer) that a workgroup walks several layers: 5 layers in groups of 2, 2 and 1
+    w = synth.scaled(synth.WORKLOADS[2], name="lm_groups", L=5, P=65300, Q=8, T=16, H=1, planted_frac=0.5, R=1,
+                     E=65308, seed=43)
     say(f"{w.name}: L={w.L} P={w.P} Q={w.Q}")
     thr = 0.5 * np.sqrt(w.Dh / (w.T * w.H))
     pr, gpu, orc, rep = run_case(oracle, w, thr)

@@ -7,7 +7,7 @@ import torch
 
 from paper_2507_21433_amd import binding as rc
 from paper_2507_21433_amd import synth
-from tests import parity
+from tests import parity, paths
 
 pytestmark = pytest.mark.gpu
 
@@ -24,11 +24,11 @@ def dcode(w):
     return 0 if w.dtype == "f16" else 1
 
 
-def run_gpu_match(pr, w, live=None, want_second=True):
+def run_gpu_match(pr, w, live=None, want_second=True, workspace=None):
     qk, qv = rc.rc_block_norms(pr["kq"], pr["vq"], w.mode)
     pk, pv = rc.rc_block_norms(pr["kp"], pr["vp"], w.mode)
     out = rc.rc_match_blocks(pr["kq"], pr["vq"], qk, qv, pr["kp"], pr["vp"], pk, pv, live, w.tau, w.mode,
-                             want_second=want_second)
+                             want_second=want_second, workspace=workspace)
     torch.cuda.synchronize()
     return {k: (v.cpu().numpy() if v is not None else None) for k, v in out.items()}, (qk, qv, pk, pv)
 
@@ -41,9 +41,9 @@ def oracle_match(oracle, pr, w, live, layers=None, queries=None, want_scores=Tru
     return oracle.match(dcode(w), w.mode, *a, lv, w.tau, want_scores=want_scores)
 
 
-def full_check(oracle, w, pr, live_t):
-    gpu, _ = run_gpu_match(pr, w, live_t)
-    orc = oracle_match(oracle, pr, w, live_t)
+def full_check(oracle, w, pr, live_t, workspace=None, orc=None):
+    gpu, _ = run_gpu_match(pr, w, live_t, workspace=workspace)
+    orc = oracle_match(oracle, pr, w, live_t) if orc is None else orc
     rep = parity.check_match(gpu, orc, w.tau, parity.score_lookup(orc["scores"], gpu["best_idx"]))
     say(f"{w.name}: {rep}")
     return gpu, orc, rep
@@ -109,10 +109,10 @@ def test_match_ragged_tiles(oracle, dtype, P, Q):
         assert abs(gpu["best_score"][1, 0] - 1.0) < 1e-5 and abs(gpu["second_score"][1, 0] - 1.0) < 1e-5
 
 
-@pytest.mark.parametrize("L,P,Q", [(48, 513, 257), (80, 700, 64), (70, 513, 128)])
-def test_match_many_layers_whole_tiles(oracle, L, P, Q):
-    # more than 128 tiles: every tile is computed by one workgroup (no split of the reduction), with the
-    # 256-, 64- and 128-column tile; the small cases above all take the split path
+@pytest.mark.parametrize("L,P,Q,tile", [(48, 577, 257, (256, 256, 0)), (80, 700, 64, (256, 64, 0)), (70, 513, 128, (256, 128, 0))])
+def test_match_many_layers_whole_tiles(oracle, L, P, Q, tile):
+    # more than 128 tiles, and a workspace for whole tiles with 256 pool rows only: every tile is computed by one workgroup
+    # (no split of the reduction), with the 256-, 64- and 128-column tile; then the plan of a full workspace
     w = synth.scaled(synth.WORKLOADS[2], name=f"whole_tiles_L{L}_{P}x{Q}", L=L, P=P, Q=Q, planted_frac=0.3, R=1,
                      E=P + Q, seed=13)
     say(w.name)
@@ -124,25 +124,31 @@ def test_match_many_layers_whole_tiles(oracle, L, P, Q):
     pr["vp"][:, P - 2] = pr["vp"][:, 1]
     pr["kq"][:, 0] = pr["kp"][:, 1]
     pr["vq"][:, 0] = pr["vp"][:, 1]
-    gpu, orc, rep = full_check(oracle, w, pr, live)
-    assert (gpu["best_idx"][:, 0] == 1).all() and (gpu["match_idx"][:, 0] == 1).all()
+    small, orc = paths.whole_tiles_workspace(w), None
+    paths.assert_tiles(lambda: run_gpu_match(pr, w, live, workspace=small), tile)
+    for ws in (small, None):
+        gpu, orc, rep = full_check(oracle, w, pr, live, ws, orc)
+        assert (gpu["best_idx"][:, 0] == 1).all() and (gpu["match_idx"][:, 0] == 1).all()
 
 
-@pytest.mark.parametrize("mode,H", [(0, 1), (1, 2)])
-def test_match_many_rounds_tiles_change_hands(oracle, mode, H):
+@pytest.mark.parametrize("mode,H,P", [(0, 1, 513), (1, 2, 513), (0, 1, 577), (1, 2, 577)])
+def test_match_many_rounds_tiles_change_hands(oracle, mode, H, P):
     # 16 rounds of tiles and more: the last tenth of every XCD's list of tiles can be taken over by the workgroups of
     # the XCDs that are through with theirs.  Every tile must still be computed exactly once: the call equals, bit
     # for bit, the same layers scored 20 at a time (two rounds, the fixed schedule), and sampled queries equal the
     # oracle's search.
-    L, P, Q = 260, 513, 1300
+    L, Q = 260, 1300
     w = synth.scaled(synth.WORKLOADS[2 if mode == 0 else 5], name=f"many_rounds_mode{mode}_L{L}_{P}x{Q}", L=L, P=P, Q=Q,
                      T=16, H=H, planted_frac=0.3, R=1, E=P + Q, seed=21)
     say(w.name)
     pr = synth.make_problem(w, DEV)
     live = pr["live"].clone()
     live[:, 9] = 0
-    for rep in range(3):  # who takes which tile differs from run to run
-        whole, _ = run_gpu_match(pr, w, live)
+    plans = {513: [(None, (192, 320, mode))], 577: [(None, (256, 192, mode)), (paths.whole_tiles_workspace(w), (256, 256, mode))]}[P]
+    for ws, tile in plans:
+        paths.assert_tiles(lambda: run_gpu_match(pr, w, live, workspace=ws), tile)
+    for rep in range(4):  # who takes which tile differs from run to run
+        whole, _ = run_gpu_match(pr, w, live, workspace=plans[rep % len(plans)][0])
         for l0 in range(0, L, 20):
             part = {n: pr[n][l0:l0 + 20] for n in ("kq", "vq", "kp", "vp")}
             some, _ = run_gpu_match(part, synth.scaled(w, L=20), live[l0:l0 + 20])
@@ -241,24 +247,33 @@ def test_per_head_mode(oracle, dtype):
     assert (gpu["match_idx"][1][slots] >= 0).all()
 
 
-def test_per_head_many_layers_whole_tiles(oracle):
-    # more than one round of tiles: one workgroup per tile walks all heads and keeps the running minimum in
-    # 16-bit fixed point (the small per-head cases take the one-share-per-head path instead)
-    w = synth.scaled(synth.WORKLOADS[5], name="perhead_whole_tiles", L=90, P=513, Q=40, T=16, R=2, E=300, seed=15)
+@pytest.mark.parametrize("Q,H,tile", [(40, 8, (256, 64, 1)), (97, 4, (256, 128, 1))])
+def test_per_head_many_layers_whole_tiles(oracle, Q, H, tile):
+    # more than one round of tiles, and a workspace for whole tiles only: one workgroup per tile walks all heads and keeps the
+    # running minimum in 16-bit fixed point (with a full workspace these cases take the one-share-per-head path instead)
+    w = synth.scaled(synth.WORKLOADS[5], name=f"perhead_whole_tiles_Q{Q}", L=90, P=513, Q=Q, H=H, T=16, R=1, E=513 + Q, seed=15)
     say(w.name)
     pr = synth.make_problem(w, DEV)
     live = pr["live"].clone()
     live[:, 7] = 0
-    full_check(oracle, w, pr, live)
+    small = paths.whole_tiles_workspace(w)
+    paths.assert_tiles(lambda: run_gpu_match(pr, w, live, workspace=small), tile)
+    full_check(oracle, w, pr, live, small)
 
 
-def test_per_head_scores_do_not_depend_on_the_path():
-    # the same layer scored inside a call of 90 layers (whole tiles, running minimum in 16-bit fixed point) and in a
-    # call of its own (one share per head, minimum taken by the selection kernel): identical bits, identical picks
-    w = synth.scaled(synth.WORKLOADS[5], name="perhead_paths", L=90, P=513, Q=40, T=16, R=2, E=300, seed=16)
+@pytest.mark.parametrize("Q,small,tile,share", [(40, True, (256, 64, 1), (256, 64, 4)), (97, True, (256, 128, 1), (256, 128, 4)),
+                                                (160, False, (256, 192, 1), (256, 192, 4)), (230, False, (256, 256, 1), (256, 256, 4)),
+                                                (300, False, (192, 320, 1), (256, 192, 4)), (300, True, (256, 256, 1), (256, 192, 4))])
+def test_per_head_scores_do_not_depend_on_the_path(Q, small, tile, share):
+    # the same layer scored inside a call of 90 layers (whole tiles of every shape, running minimum in 16-bit fixed point) and
+    # in a call of its own (one share per head, minimum taken by the selection kernel): identical bits, identical picks
+    w = synth.scaled(synth.WORKLOADS[5], name=f"perhead_paths_Q{Q}", L=90, P=577, Q=Q, T=16, R=1, E=577 + Q, seed=16)
     say(w.name)
     pr = synth.make_problem(w, DEV)
-    many, _ = run_gpu_match(pr, w, pr["live"])
+    ws = paths.whole_tiles_workspace(w) if small else None
+    paths.assert_tiles(lambda: run_gpu_match(pr, w, pr["live"], workspace=ws), tile)
+    paths.assert_tiles(lambda: run_gpu_match({n: pr[n][:1] for n in ("kq", "vq", "kp", "vp")}, synth.scaled(w, L=1), pr["live"][:1]), share)
+    many, _ = run_gpu_match(pr, w, pr["live"], workspace=ws)
     for l in (0, 37, 89):
         one = {n: pr[n][l:l + 1] for n in ("kq", "vq", "kp", "vp")}
         alone, _ = run_gpu_match(one, synth.scaled(w, L=1), pr["live"][l:l + 1])

@@ -9,7 +9,7 @@ import torch
 
 from paper_2507_21433_amd import binding as rc
 from paper_2507_21433_amd import synth
-from tests import parity
+from tests import parity, paths
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -34,8 +34,8 @@ def draw(case):
 
 
 def draw_many_layers(case):
-    """More than 256 tiles (one or two small tiles in each of 257-330 layers): the whole-tile paths, which the
-    few-layer shapes above never take."""
+    """More than 256 tiles (one or two small tiles in each of 257-330 layers): the whole-tile paths in a workspace that has room
+    for nothing else, which the few-layer shapes above never take; seven of the ten take shares in a full one."""
     r = np.random.RandomState(3000 + case)
     edges = [1, 2, 31, 33, 64, 65, 127, 129, 255, 257, 300]
     T = int(r.choice([16, 32]))
@@ -79,6 +79,12 @@ def run_shape(oracle, kw, name, case):
     g = {k: v.cpu().numpy() for k, v in m.items()}
     o = oracle.match(d, w.mode, *bits, live.cpu().numpy(), w.tau, want_scores=True)
     rep = parity.check_match(g, o, w.tau, parity.score_lookup(o["scores"], g["best_idx"]))
+    if name.startswith("layers"):
+        whole = rc.rc_match_blocks(pr["kq"], pr["vq"], qk, qv, pr["kp"], pr["vp"], pk, pv, live, w.tau, w.mode,
+                                   workspace=paths.whole_tiles_workspace(w))
+        torch.cuda.synchronize()
+        gw = {k: v.cpu().numpy() for k, v in whole.items()}
+        parity.check_match(gw, o, w.tau, parity.score_lookup(o["scores"], gw["best_idx"]))
     # remap of the GPU's decisions
     r = rc.rc_remap_block_table(pr["tables"], pr["query_ids"], None, m["match_idx"], w.P, w.NB, pr["refcount"])
     torch.cuda.synchronize()

@@ -1,8 +1,5 @@
 """The bytes of workspace a search call insists on.  They do not follow the tile shapes and shares that are fastest: a
 smaller workspace than rc_match_workspace_size() gives a slower plan, down to a floor that is stated in include/rc.h."""
-import ctypes
-import re
-
 import numpy as np
 import pytest
 import torch
@@ -10,6 +7,7 @@ import torch
 from paper_2507_21433_amd import binding as rc
 from paper_2507_21433_amd import synth
 from tests import parity
+from tests.paths import mean_needed, mean_size, needed, size, whole_tiles
 
 DEV = "cuda:0"
 
@@ -21,30 +19,6 @@ def lib():
         from paper_2507_21433_amd import build
         build.build()
     return rc.lib()
-
-
-def descs(L, T, H, P, Q):
-    return [rc.KvDesc(L, T, H, 128, 0, n * T * H * 128) for n in (Q, P)]
-
-
-def needed(lib, mode, L, T, H, P, Q):
-    """What a call without a workspace says it needs (it is refused before anything is launched)."""
-    q, p = descs(L, T, H, P, Q)
-    fake = ctypes.c_void_p(0x1000)
-    assert lib.rc_match_blocks(ctypes.byref(q), ctypes.byref(p), mode, fake, fake, Q, fake, fake, fake, fake, P, fake, fake, None,
-                               0.9, fake, fake, fake, None, None, 0, None) == 3
-    return int(re.search(rb"workspace of (\d+) bytes needed", lib.rc_last_error()).group(1))
-
-
-def size(lib, mode, L, T, H, P, Q):
-    return lib.rc_match_workspace_size(ctypes.byref(descs(L, T, H, P, Q)[0]), mode, Q, P)
-
-
-def whole_tiles(L, P, Q):
-    """16 bytes per (layer, pool tile of 256, query), then the tile schedule: 520 words of 128 bytes, one claim word per
-    tile of the launch (rounded up to rounds of 256) and 512 more."""
-    npt, nqt = -(-P // 256), -(-Q // 256)
-    return L * npt * Q * 16 + 4 * (520 * 32 + -(-L * npt * nqt // 256) * 256 + 512)
 
 
 # more than 256 tiles of 256 x 256, or (block score, at most 128 queries) more than 128: never more than the partials
@@ -69,18 +43,6 @@ def test_one_workspace_for_the_largest_call(lib):
         largest = size(lib, mode, L, T, H, P, 256)
         for Q in (1, 24, 40, 64, 65, 102, 128, 129, 192, 200, 255):
             assert needed(lib, mode, L, T, H, P, Q) <= largest, (mode, L, P, Q)
-
-
-def mean_needed(lib, L, T, H, P, Q):
-    q, p = descs(L, T, H, P, Q)
-    fake = ctypes.c_void_p(0x1000)
-    assert lib.rc_match_blocks_layer_mean(ctypes.byref(q), ctypes.byref(p), fake, fake, Q, fake, fake, fake, fake, P, fake, fake, None,
-                                          0.5, fake, fake, fake, None, None, 0, None) == 3
-    return int(re.search(rb"workspace of (\d+) bytes needed", lib.rc_last_error()).group(1))
-
-
-def mean_size(lib, L, T, H, P, Q):
-    return lib.rc_layer_mean_workspace_size(ctypes.byref(descs(L, T, H, P, Q)[0]), Q, P)
 
 
 # the sums of 256 x 256 tiles (256 KB) of each group of layers, as few groups as make 1024 tiles, and 16-byte partials: a
