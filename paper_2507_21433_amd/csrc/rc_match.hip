@@ -68,7 +68,7 @@ struct MatchParams {
   const float *q_ksq, *q_vsq, *p_ksq, *p_vsq;
   const uint8_t* live;
   Part* part;                          // [L][npt][Q]
-  float* dpart;                        // layer-mean mode: [groups][P][Q] sums of layer distances
+  float* dpart;                        // sums of layer distances, or shares of scores: tiles in register order
   long long q_lstride_b, p_lstride_b;  // bytes between layers
   int L, Q, P;
   int T, H;
@@ -1414,6 +1414,10 @@ inline size_t layer_mean_part_offset(int groups, int64_t npt, int64_t nqt, int b
 // Measured, whole tiles -> shares: per-head, 32 layers x 2531 blocks of 32 tokens, Q = 24 (320 tiles) 2120 -> 1850 us;
 // 256-column shares -> these: one layer of 4096 blocks, Q = 16 (256 shares) 82 -> 53 us, one tile, Q = 32 33 -> 19 us;
 // powers of two only -> any divisor: one layer of 6000 blocks of 10 heads, Q = 40 105 -> 90 us (S = 10).
+// The layer-mean search goes by the block score's estimate; its selection walks all layers in one pass, which that
+// does not count.  Above 256 tiles, whole tiles (a small workspace) -> shares, us: 64 layers of 8 heads, 1100 x 16 931 -> 883,
+// 1280 x 64 1096 -> 1099, 1280 x 128 1243 -> 1267, 1400 x 128 1312 -> 1192; 52 x 1264 x 1, blocks of 128 KB 3545 -> 2735; 25 x
+// 5134 x 1, blocks of 16 KB 746 -> 781 (the worst of 60 shapes).
 // The decision depends on the shape alone (an MI355X has 256 compute units), so that the workspace
 // size does not depend on the device that happens to be current.
 constexpr int kSplitComputeUnits = 256;
