@@ -182,7 +182,7 @@ size_t rc_remap_static_scratch_size(void);
  * RC_REMAP_STATIC_SCRATCH_BYTES (4 MiB) that is part of the library's device code, one copy per
  * GPU, held until the process ends.  The call allocates and frees nothing and does not synchronise.
  * A problem whose rc_remap_workspace_size() exceeds the buffer is refused with RC_ERR_WORKSPACE
- * before anything is launched (the five benchmark workloads need at most 3.3 MB).  Every call on
+ * before anything is launched (the five benchmark workloads need at most 1.25 MB).  Every call on
  * one GPU uses that GPU's buffer: calls on the same GPU must not overlap in time (on different
  * streams, or from different threads), or they race on it.  No part of the buffer has to be
  * cleared between calls: the kernels validate or overwrite everything they read from it.
