@@ -25,15 +25,19 @@ def test_merge_parts(oracle, P, Q):
 
 # Tile width (64 columns up to 64 queries, 128 up to 128, 192 or 256 beyond) and shares per tile: per-head mode in whole tiles
 # (256 tiles: one round) and with one share per head, block mode with a share count that is no power of two.
-WIDTHS = [(1, 256, 64, 64, 2), (1, 256, 40, 65, 2), (1, 256, 70, 128, 1), (1, 3, 300, 64, 5), (1, 2, 257, 65, 16),
-          (1, 2, 255, 128, 3), (1, 2, 300, 129, 3), (0, 24, 250, 40, 5), (0, 24, 250, 65, 5), (0, 2, 300, 128, 3), (0, 11, 513, 1, 6),
-          (0, 2, 300, 192, 3), (0, 2, 300, 257, 3), (1, 2, 257, 384, 3), (1, 2, 40, 385, 5)]
+WIDTHS = [(1, 256, 64, 64, 2, (64, 1)), (1, 256, 40, 65, 2, (128, 1)), (1, 256, 70, 128, 1, (128, 1)), (1, 3, 300, 64, 5, (64, 4)),
+          (1, 2, 257, 65, 16, (128, 4)), (1, 2, 255, 128, 3, (128, 4)), (1, 2, 300, 129, 3, (192, 4)), (0, 24, 250, 40, 5, (64, 3)),
+          (0, 24, 250, 65, 5, (128, 3)), (0, 2, 300, 128, 3, (128, 3)), (0, 11, 513, 1, 6, (64, 3)), (0, 2, 300, 192, 3, (192, 3)),
+          (0, 2, 300, 257, 3, (192, 3)), (1, 2, 257, 384, 3, (192, 4)), (1, 2, 40, 385, 5, (256, 4))]
 
 
-@pytest.mark.parametrize("mode,L,P,Q,H", WIDTHS)
-def test_tile_widths_and_shares(oracle, mode, L, P, Q, H):
+@pytest.mark.parametrize("mode,L,P,Q,H,tile", WIDTHS)
+def test_tile_widths_and_shares(oracle, mode, L, P, Q, H, tile):
     run_shape(oracle, dict(L=L, P=P, Q=Q, T=16, H=H, mode=mode, dtype="bf16" if Q % 2 else "f16", planted_frac=0.3, seed=7300 + P),
               f"width{mode}.{L}.{P}x{Q}", P)
+    w = synth.scaled(synth.WORKLOADS[2], name="width", L=L, P=P, Q=Q, T=16, H=H, mode=mode, planted_frac=0.0, R=1, E=P + Q)
+    pr = synth.make_problem(w, "cuda:0")
+    paths.assert_tiles(lambda: run_gpu_match(pr, w, None), (256, *tile))
 
 
 # Shape of whole tiles beyond 128 queries: 256 x 192, 192 x 320 and 256 x 256 with one and more query tiles, pools that end

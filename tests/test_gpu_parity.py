@@ -165,8 +165,8 @@ def test_match_many_rounds_tiles_change_hands(oracle, mode, H, P):
 
 
 def test_match_split_shapes(oracle):
-    # the split of the reduction at its extremes: one tile over 64 shares (8 steps each), 128 tiles over 2
-    # shares (a whole tensor each), head counts whose step count is not a power of two
+    # the split of the reduction at its extremes: one tile over many shares (at least 8 steps each), 128 tiles over a
+    # few, head counts whose step count is not a power of two
     for (L, P, Q, T, H) in [(1, 200, 30, 16, 8), (32, 1000, 40, 16, 8), (1, 300, 257, 16, 3), (2, 257, 5, 32, 5),
                             (1, 100, 7, 16, 1)]:
         w = synth.scaled(synth.WORKLOADS[2], name=f"split_L{L}_{P}x{Q}_T{T}_H{H}", L=L, P=P, Q=Q, T=T, H=H,
