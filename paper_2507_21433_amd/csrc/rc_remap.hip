@@ -2,7 +2,9 @@
 // (ReasonCache Sec. IV-B: the kept block's reference count goes up, the table entry is
 // rewritten, nothing is copied; a block is freed only at reference count 0).
 //
-// One launch, or two; no atomics anywhere:
+// remap_layer_kernel, one launch: every workgroup of a layer counts the references of the whole table for itself and
+// keeps its share of the layer's reference counts in LDS, so no workgroup needs anything from another one.  It
+// serves what fits (see layer_kernel_fits); the rest goes through
 //   gather  : table_out[e] = target of table_in[e], 16-byte loads and stores when the layout allows,
 //             the next batch of entries in flight while the current one is worked on.  A workgroup
 //             first builds what it needs to decide an entry without touching global memory again:
@@ -21,6 +23,7 @@
 //             references, its target gains them.  Queries that share a target take turns through
 //             a small claim table in LDS, one winner per slot and round.  A launch of its own only
 //             when a layer was gathered by several workgroups.
+// No atomics on global memory anywhere; integer adds only, so the same counts on every run.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -39,12 +42,13 @@ constexpr int kLdsTargets = 4096;                                     // most qu
 constexpr int kFinalThreads = 1024;
 constexpr int kFinalPerThread = kMaxQ / kFinalThreads;
 constexpr int kClaimSlots = 4096;
+constexpr int kLayerCounts = 15872;                                   // reference counts a workgroup of remap_layer_kernel owns, at most
 
 // Workgroups per layer.  One (which then also finalizes its layer) when the layers alone fill the chip or the
 // layer's table is small; otherwise as many as keep the launch at one workgroup per compute unit, of at least
-// a quarter batch each: the second launch that adds their histograms costs less than what a single compute
-// unit takes to stream a large layer (measured at 64 layers of 49 664 entries and 50 176 reference counts:
-// 40 us with one workgroup per layer, 30 with 3, 26 with 4, 33 with 8).
+// a quarter batch each: a single compute unit takes longer to stream a large layer (with a launch that adds the
+// workgroups' histograms, at 64 layers of 49 664 entries and 50 176 reference counts: 40 us with one workgroup per layer,
+// 30 with 3, 26 with 4, 33 with 8).
 inline int64_t chunks_per_layer(int64_t RE, int64_t L) {
   if (L >= 128) return 1;
   int64_t g = 256 / (L > 0 ? L : 1);
@@ -53,6 +57,15 @@ inline int64_t chunks_per_layer(int64_t RE, int64_t L) {
   if (g < 1) g = 1;
   if (g > 65535) g = 65535;
   return g;
+}
+
+// What remap_layer_kernel takes: query slots whose targets and counts fit beside a share of the reference counts in
+// LDS; and, where several workgroups read a layer's table, a table that is short enough to be read by each (at 131 072
+// entries 17 us against 21 with the gather and finalize launches, a lead that shrinks with every entry) and that is not
+// rewritten in place.
+constexpr int64_t kLayerEntries = 131072;
+inline bool layer_kernel_fits(int64_t Q, int64_t RE, int64_t rc_chunk, int64_t per_layer, bool in_place) {
+  return Q <= kLdsTargets && rc_chunk <= kLayerCounts && RE <= (1 << 30) && (per_layer == 1 || (!in_place && RE <= kLayerEntries));
 }
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -409,6 +422,251 @@ __global__ __launch_bounds__(kFinalThreads) void remap_finalize_kernel(
       query_ids, pool_ids, match_idx + l * Q, Q, P, NB, refcount_out + l * NB, freed + l * Q, n_remapped + l, claim, wsum);
 }
 
+struct LayerLds {
+  unsigned short slot[kLdsIds];   // block id - lo -> slot + 1 of the matched query block with that id (0 = none)
+  int target[kLdsTargets];        // target block of a matched slot
+  int hist[kLdsTargets];          // references of the layer to a matched slot
+  int rc[kLayerCounts];           // this workgroup's share of the layer's reference counts
+  int lo[kGatherThreads / 64], hi[kGatherThreads / 64], moved[kGatherThreads / 64];
+};
+static_assert(sizeof(LayerLds) <= 160 * 1024, "fits the LDS of a compute unit");
+
+// The whole remap of a layer by `per_layer` workgroups that do not need each other.  Each reads all of the layer's
+// table and counts the references to the matched query blocks in LDS (integer adds: the same counts in any order),
+// writes its chunk of the table, and owns the reference counts [rlo, rhi) of the layer, which it reads once, edits
+// in LDS and writes once.  What bounds it is a chain of memory round trips, so everything that depends on nothing is
+// asked for before the first wait (ids, decisions, reference counts, four groups of entries), later groups four groups
+// ahead.  A layer's workgroups are dealt to one XCD (consecutive workgroups go round the 8 XCDs), so the repeated
+// reads of the table come from its L2.  Measured against one gather launch and, with several workgroups per layer, a
+// second launch that adds their histograms (us): 1 layer x 288 entries 9.1 -> 6.2, 4 x 8192 12.7 -> 7.2, 64 x 4352
+// 12.4 -> 7.4, 64 x 49 664 entries and 50 176 counts 24.0 -> 15.3, 256 x 15 000 17.8 -> 12.4, 1 x 131 072 20.9 -> 16.9.
+// What is left at 64 x 49 664 is vector work on the 48 entries that every thread looks at (a branch per entry instead of
+// one per four: 16.6; no branch at all: 16.9) and 6 us that a call of one small table takes as well.
+template <bool VEC>
+__global__ __launch_bounds__(kGatherThreads) void remap_layer_kernel(
+    const int32_t* tables_in, int32_t* tables_out, int RE, int chunk, int32_t* slot_of, const int32_t* __restrict__ query_ids,
+    const int32_t* __restrict__ pool_ids, const int32_t* __restrict__ match_idx, int Q, int P, int NB,
+    const int32_t* refcount_in, int32_t* refcount_out, int rc_chunk, int rc_vec, uint8_t* __restrict__ freed,
+    int32_t* __restrict__ n_remapped, int L, int per_layer) {
+  __shared__ LayerLds s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int turn = blockIdx.x >> 3, g = turn % per_layer;
+  const long long l = (long long)(turn / per_layer) * 8 + (blockIdx.x & 7);
+  if (l >= L) return;
+  const int32_t* tin = tables_in + l * RE;
+  int32_t* tout = tables_out + l * RE;
+  const int32_t* m = match_idx + l * Q;
+  const int lo_e = g * chunk, len_e = min(RE - lo_e, chunk);
+  const int rlo = g * rc_chunk, n_counts = min(NB - rlo, rc_chunk);
+
+  // ---- everything that waits for nothing
+  constexpr int kSlots = kLdsTargets / kGatherThreads, kCounts = (kLayerCounts + kGatherThreads * 4 - 1) / (kGatherThreads * 4);
+  constexpr int kGroup = 4 * kGatherThreads, kAhead = 4;  // entries of a group, four per thread; groups in flight
+  int id[kSlots], tgt[kSlots];  // this thread's query slots: block id; decision, then target
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k) {
+    const int q = k * kGatherThreads + tid;
+    id[k] = q < Q ? query_ids[q] : -1;
+    tgt[k] = q < Q ? m[q] : -1;
+  }
+  i32x4 count[kCounts];
+#pragma unroll
+  for (int u = 0; u < kCounts; ++u) {
+    if (rc_vec) {  // four counts of a thread side by side
+      const int i = (u * kGatherThreads + tid) * 4;
+      if (i < n_counts) count[u] = __builtin_nontemporal_load(reinterpret_cast<const i32x4*>(refcount_in + l * NB + rlo + i));
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int i = (u * 4 + c) * kGatherThreads + tid;
+        if (i < n_counts) count[u][c] = refcount_in[l * NB + rlo + i];
+      }
+    }
+  }
+  // entry c of this thread in the group that starts at `base`: four side by side (VEC) or a workgroup apart
+  auto index_of = [&](int base, int c) { return VEC ? base + tid * 4 + c : base + c * kGatherThreads + tid; };
+  auto load_group = [&](int base) {
+    i32x4 v = {-1, -1, -1, -1};
+    if (VEC) {  // RE % 4 == 0: four entries are inside or outside together
+      if (index_of(base, 0) < RE) v = *reinterpret_cast<const i32x4*>(tin + index_of(base, 0));
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (index_of(base, c) < RE) v[c] = tin[index_of(base, c)];
+    }
+    return v;
+  };
+  i32x4 ahead[kAhead];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) ahead[u] = load_group(u * kGroup);
+
+  // ---- the matched query blocks and the range [id_lo, id_hi] of their ids
+  int id_lo = 0x7fffffff, id_hi = -1;
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k) {
+    if (id[k] >= 0 && id[k] < NB && tgt[k] >= 0 && tgt[k] < P) {
+      id_lo = min(id_lo, id[k]);
+      id_hi = max(id_hi, id[k]);
+      if (pool_ids) tgt[k] = pool_ids[tgt[k]];
+    } else {
+      id[k] = -1;
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    id_lo = min(id_lo, __shfl_xor(id_lo, off));
+    id_hi = max(id_hi, __shfl_xor(id_hi, off));
+  }
+  if (lane == 0) {
+    s.lo[wave] = id_lo;
+    s.hi[wave] = id_hi;
+  }
+  lds_barrier();
+#pragma unroll
+  for (int w = 0; w < kGatherThreads / 64; ++w) {
+    id_lo = min(id_lo, s.lo[w]);
+    id_hi = max(id_hi, s.hi[w]);
+  }
+  const unsigned span = id_hi < 0 ? 0u : (unsigned)(id_hi - id_lo) + 1u;  // 0: no matched query block
+  const bool in_lds = span <= kLdsIds;
+  if (in_lds) {
+    unsigned int* z = reinterpret_cast<unsigned int*>(s.slot);
+    for (int i = tid; i < (int)((span + 1) / 2); i += kGatherThreads) z[i] = 0u;
+    lds_barrier();
+  }
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k) {
+    const int q = k * kGatherThreads + tid;
+    if (q < Q) s.hist[q] = 0;
+    if (id[k] >= 0) {
+      if (in_lds)
+        s.slot[id[k] - id_lo] = (unsigned short)(q + 1);  // query ids are distinct: one writer per entry
+      else
+        slot_of[id[k]] = q;  // every workgroup that needs the word writes the same value and reads it back itself
+      s.target[q] = tgt[k];
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kCounts; ++u) {
+    if (rc_vec) {
+      const int i = (u * kGatherThreads + tid) * 4;
+      if (i < n_counts) *reinterpret_cast<i32x4*>(&s.rc[i]) = count[u];
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int i = (u * 4 + c) * kGatherThreads + tid;
+        if (i < n_counts) s.rc[i] = count[u][c];
+      }
+    }
+  }
+  if (in_lds) {
+    lds_barrier();
+  } else {
+    __threadfence_block();
+    __syncthreads();
+  }
+
+  // ---- the table: every entry is counted, those of this workgroup's chunk are written
+  for (int first = 0; first < RE; first += kAhead * kGroup) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int base = first + u * kGroup;
+      i32x4 entry = ahead[u];
+      ahead[u] = load_group(base + kAhead * kGroup);  // entries of none past the end
+      unsigned d[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) d[c] = (unsigned)entry[c] - (unsigned)id_lo;
+      // the table is mostly resident blocks: a wave without a query block among its 256 entries goes on
+      if (d[0] < span || d[1] < span || d[2] < span || d[3] < span) {
+        int slot1[4];
+        if (in_lds) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) slot1[c] = d[c] < span ? (int)s.slot[d[c]] : 0;
+        } else {
+#pragma unroll 1
+          for (int c = 0; c < 4; ++c) {
+            int sl = -1;
+            if (d[c] < span) remap_entry(entry[c], slot_of, query_ids, pool_ids, m, Q, P, NB, sl);
+            slot1[c] = sl + 1;
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (slot1[c] > 0) {
+            atomicAdd(&s.hist[slot1[c] - 1], 1);
+            entry[c] = s.target[slot1[c] - 1];
+          }
+      }
+      if (VEC) {
+        const int e = index_of(base, 0);  // chunks are multiples of four
+        if ((unsigned)(e - lo_e) < (unsigned)len_e) __builtin_nontemporal_store(entry, reinterpret_cast<i32x4*>(tout + e));
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int e = index_of(base, c);
+          if ((unsigned)(e - lo_e) < (unsigned)len_e) tout[e] = entry[c];
+        }
+      }
+    }
+  }
+  lds_barrier();  // the histogram is complete
+
+  // ---- the reference counts
+  int moved = 0;
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k) {
+    const int q = k * kGatherThreads + tid;
+    if (q >= Q) continue;
+    const int c = id[k] >= 0 ? s.hist[q] : 0;
+    const unsigned at = (unsigned)(id[k] - rlo);
+    moved += c;
+    if (id[k] >= 0 && at < (unsigned)n_counts) {  // distinct ids: no other thread touches this count
+      const int left = s.rc[at] - c;
+      s.rc[at] = left;
+      freed[l * Q + q] = left == 0;
+    } else if (id[k] < 0 && g == 0) {
+      freed[l * Q + q] = 0;
+    }
+  }
+  lds_barrier();  // the query blocks have given up theirs before the targets gain them
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k) {
+    const int q = k * kGatherThreads + tid;
+    const unsigned at = (unsigned)(tgt[k] - rlo);
+    if (q < Q && id[k] >= 0 && tgt[k] >= 0 && at < (unsigned)n_counts) {
+      const int c = s.hist[q];
+      if (c > 0) atomicAdd(&s.rc[at], c);
+    }
+  }
+  if (g == 0) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) moved += __shfl_xor(moved, off);
+    if (lane == 0) s.moved[wave] = moved;
+  }
+  lds_barrier();
+#pragma unroll
+  for (int u = 0; u < kCounts; ++u) {
+    if (rc_vec) {
+      const int i = (u * kGatherThreads + tid) * 4;
+      if (i < n_counts)
+        __builtin_nontemporal_store(*reinterpret_cast<const i32x4*>(&s.rc[i]),
+                                    reinterpret_cast<i32x4*>(refcount_out + l * NB + rlo + i));
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int i = (u * 4 + c) * kGatherThreads + tid;
+        if (i < n_counts) refcount_out[l * NB + rlo + i] = s.rc[i];
+      }
+    }
+  }
+  if (g == 0 && tid == 0) {
+    int n = 0;
+#pragma unroll
+    for (int w = 0; w < kGatherThreads / 64; ++w) n += s.moved[w];
+    n_remapped[l] = n;
+  }
+}
+
 }  // namespace
 }  // namespace rc
 
@@ -459,6 +717,19 @@ rc_status remap_run(const char* who, int32_t n_layers, const int32_t* tables_in,
   rc_chunk = (rc_chunk + 3) / 4 * 4;
   const bool vec = RE % 4 == 0 && aligned16(tables_in) && aligned16(tables_out);
   const int rc_vec = NB % 4 == 0 && aligned16(refcount_in) && aligned16(refcount_out);
+
+  if (layer_kernel_fits(Q, RE, rc_chunk, G, tables_in == tables_out)) {
+    const unsigned wgs = (unsigned)((n_layers + 7) / 8 * 8 * G);
+    if (vec)
+      remap_layer_kernel<true><<<wgs, kGatherThreads, 0, st>>>(tables_in, tables_out, (int)RE, (int)chunk, slot_of, query_ids, pool_ids,
+                                                               match_idx, (int)Q, (int)P, (int)NB, refcount_in, refcount_out,
+                                                               (int)rc_chunk, rc_vec, freed, n_remapped, n_layers, (int)G);
+    else
+      remap_layer_kernel<false><<<wgs, kGatherThreads, 0, st>>>(tables_in, tables_out, (int)RE, (int)chunk, slot_of, query_ids, pool_ids,
+                                                                match_idx, (int)Q, (int)P, (int)NB, refcount_in, refcount_out,
+                                                                (int)rc_chunk, rc_vec, freed, n_remapped, n_layers, (int)G);
+    return check_launch("rc_remap_block_table(layers)");
+  }
 
   const dim3 grid((unsigned)G, (unsigned)n_layers);
 #define RC_GATHER(V, F)                                                                                                    \

@@ -1,0 +1,46 @@
+"""Block-table remap where several workgroups read a layer's table, at the edges of what one workgroup holds in LDS."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_21433_amd import binding as rc
+
+pytestmark = pytest.mark.gpu
+
+
+# (layers, entries, blocks, query blocks, pool ids given, id range wider than the LDS table)
+@pytest.mark.parametrize("L,RE,NB,Q,with_pids,wide", [
+    (1, 1, 2, 1, False, False),
+    (3, 4099, 301, 63, True, False),            # no vector access: odd entries, odd counts
+    (2, 16384, 31744, 1024, False, False),      # one batch of entries; two full shares of the counts
+    (2, 16388, 31748, 1025, True, False),       # one group more of each: the counts no longer fit
+    (9, 49664, 50176, 4096, False, False),      # as many query blocks as there are targets in LDS; nine layers on eight XCDs
+    (2, 30000, 33000, 4097, False, False),      # one query block more
+    (1, 131072, 60000, 500, True, True),        # the longest table that every workgroup reads; ids some 59 000 apart
+    (1, 131076, 60000, 500, False, True),
+    (130, 700, 15872, 40, True, False),         # a workgroup per layer, a full share of the counts
+    (130, 701, 15873, 40, False, False),
+])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_remap_layers(oracle, L, RE, NB, Q, with_pids, wide, in_place):
+    rng = np.random.RandomState(L * 1000 + RE % 997 + Q)
+    if with_pids:                                                 # targets anywhere, never a query block
+        ids = rng.permutation(NB).astype(np.int32)
+        qids, pids = ids[:Q], ids[Q:]
+        P = pids.size
+    else:
+        P = 50 if wide else NB - Q
+        qids, pids = np.sort(rng.permutation(np.arange(P, NB, dtype=np.int32))[:Q]), None
+    match = rng.randint(-2, P + 2, (L, Q)).astype(np.int32)
+    match[:, ::7] = match[:, :1]                                  # many query blocks onto one target
+    tables = rng.randint(-1, NB + 1, (L, 1, RE)).astype(np.int32)
+    some = rng.random_sample(tables.shape) < 0.4
+    tables[some] = rng.choice(qids, int(some.sum()))
+    refcount = rng.randint(0, 4, (L, NB)).astype(np.int32)
+    t = lambda a: None if a is None else torch.as_tensor(a, device="cuda:0").contiguous()
+    print(f"remap layers L={L} RE={RE} NB={NB} Q={Q} in_place={in_place}", flush=True)
+    g = rc.rc_remap_block_table(t(tables), t(qids), t(pids), t(match), P, NB, t(refcount), in_place=in_place)
+    torch.cuda.synchronize()
+    o = oracle.remap(tables, qids, pids, match, P, NB, refcount)
+    for k in ("tables", "refcount", "freed", "n_remapped"):
+        np.testing.assert_array_equal(g[k].cpu().numpy(), o[k], err_msg=k)
