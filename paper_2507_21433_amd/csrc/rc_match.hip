@@ -28,9 +28,12 @@
 // them, and the epilogue multiplies by aVq aVp / 2, with a = 1/sqrt(squared norm).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "rc_common.hpp"
+#include "rc_few.hpp"
+#include "rc_select.hpp"
 
 namespace rc {
 namespace {
@@ -88,23 +91,6 @@ struct MatchParams {
   int stagger_wgs;   // workgroups of the first round (one per compute unit) ...
   int stagger_unit;  // ... start (tile % 16) * stagger_unit * 1024 clocks late
 };
-
-__device__ __forceinline__ void top2_push(float v, int i, float& best, int& bidx, float& second) {
-  const bool gt = v > best;
-  second = gt ? best : fmaxf(second, v);
-  bidx = gt ? i : bidx;
-  best = gt ? v : best;
-}
-
-// Merge (b2, i2, s2) into (best, bidx, second): higher score wins, equal scores go to the lower index.
-__device__ __forceinline__ void top2_merge(float& best, int& bidx, float& second, float b2, int i2, float s2) {
-  const bool take = (b2 > best) || (b2 == best && (unsigned)i2 < (unsigned)bidx);
-  const float loser = take ? best : b2;
-  const float wsec = take ? s2 : second;
-  bidx = take ? i2 : bidx;
-  best = take ? b2 : best;
-  second = fmaxf(wsec, loser);
-}
 
 template <bool BF16>
 __device__ __forceinline__ f32x16 mfma(uint4 a, uint4 b, f32x16 c) {
@@ -1642,7 +1628,8 @@ extern "C" size_t rc_match_workspace_size(const rc_kv_desc* qdesc, int32_t mode,
   if (mode != RC_SCORE_BLOCK && mode != RC_SCORE_PER_HEAD_ALL) return 0;
   const int L = qdesc->n_layers, T = qdesc->block_tokens, H = qdesc->n_kv_heads;
   const size_t fast = plan_bytes(match_plan(mode, L, P, Q, T, H, SIZE_MAX), L, P, Q), floor = match_floor_bytes(mode, L, P, Q, T, H);
-  return fast > floor ? fast : floor;
+  const size_t few = mode == RC_SCORE_BLOCK ? few_bytes(few_shares(false, L, P, Q, T, H), L, P, Q) : 0;
+  return std::max({fast, floor, few});
 }
 
 extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* pdesc, int32_t mode, const void* kq,
@@ -1677,6 +1664,12 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
     return fail(RC_ERR_WORKSPACE, "rc_match_blocks: workspace of %zu bytes needed (16-byte aligned), got %zu", need,
                 workspace_bytes);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  if (mode == RC_SCORE_BLOCK)
+    if (const int F = few_shares(false, L, P, Q, qdesc->block_tokens, qdesc->n_kv_heads); F > 0 && few_bytes(F, L, P, Q) <= workspace_bytes) {
+      const FewArgs fa = {qdesc, pdesc, kq, vq, kp, vp, Q, P, q_ksq, q_vsq, p_ksq, p_vsq, pool_live, tau,
+                          best_idx, best_score, match_idx, second_score, workspace, hip_stream};
+      return few_search(fa, F, false, "rc_match_blocks(few queries)");
+    }
   const MatchPlan plan = match_plan(mode, L, P, Q, qdesc->block_tokens, qdesc->n_kv_heads, workspace_bytes);
   const int S = plan.S;
   const TileShape ts = plan.ts;
@@ -1783,7 +1776,7 @@ extern "C" size_t rc_layer_mean_workspace_size(const rc_kv_desc* qdesc, int64_t 
   if (!qdesc || Q < 0 || P < 0 || qdesc->n_layers <= 0) return 0;
   const int L = qdesc->n_layers, T = qdesc->block_tokens, H = qdesc->n_kv_heads;
   const size_t fast = mean_plan_bytes(mean_split_count(L, P, Q, T, H, SIZE_MAX), L, P, Q), floor = mean_floor_bytes(L, P, Q, T, H);
-  return fast > floor ? fast : floor;
+  return std::max({fast, floor, few_bytes(few_shares(true, L, P, Q, T, H), L, P, Q)});
 }
 
 extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const rc_kv_desc* pdesc, const void* kq,
@@ -1823,6 +1816,11 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   float* dpart = static_cast<float*>(workspace);
   const float scale = 1.0f / ((float)L * 2.0f * (float)qdesc->block_tokens * (float)qdesc->n_kv_heads);
+  if (const int F = few_shares(true, L, P, Q, qdesc->block_tokens, qdesc->n_kv_heads); F > 0 && few_bytes(F, L, P, Q) <= workspace_bytes) {
+    const FewArgs fa = {qdesc, pdesc, kq, vq, kp, vp, Q, P, q_ksq, q_vsq, p_ksq, p_vsq, pool_live, threshold,
+                        best_idx, best_dist, match_idx, second_dist, workspace, hip_stream};
+    return few_search(fa, F, true, "rc_match_blocks_layer_mean(few queries)");
+  }
   const int S = mean_split_count(L, P, Q, qdesc->block_tokens, qdesc->n_kv_heads, workspace_bytes);
   if (S > 1) {
     // Few tiles (a call with one or a few layers, a small pool): the launch would leave compute units idle, and
