@@ -102,12 +102,14 @@ def _check(code):
         raise RcError(code, lib().rc_last_error().decode())
 
 
+# What a call spends on marshalling counts where a step's kernels take 20 us: addresses go to ctypes as plain integers, the
+# stream's handle is asked for without a Stream object around it, and a tensor's layout is read from its strides.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dtype_code(t):
@@ -118,13 +120,21 @@ def _dtype_code(t):
     raise TypeError(f"KV dtype {t.dtype} (fp16 or bf16 only)")
 
 
-def kv_desc(t):
-    """Descriptor of a KV tensor shaped [L][n][T][H][Dh] whose inner four dims are contiguous."""
+def _layout(t):
+    """(L, T, H, Dh, dtype code, layer stride) of a KV tensor shaped [L][n][T][H][Dh] whose inner four dims are contiguous."""
     assert t.dim() == 5, "KV tensors are [L][n][T][H][Dh]"
     L, n, T, H, Dh = t.shape
-    assert t[0].is_contiguous(), "blocks of a layer must be contiguous"
-    stride = t.stride(0) if L > 1 else n * T * H * Dh
-    return KvDesc(L, T, H, Dh, _dtype_code(t), stride)
+    s = t.stride()
+    block = T * H * Dh
+    # the plain strides first: a view of layer 0 to ask for is_contiguous() costs more than the rest of this
+    if L == 0 or s[4] != 1 or s[3] != Dh or s[2] != H * Dh or s[1] != block:
+        assert t[0].is_contiguous(), "blocks of a layer must be contiguous"
+    return L, T, H, Dh, _dtype_code(t), s[0] if L > 1 else n * block
+
+
+def kv_desc(t):
+    """Descriptor of a KV tensor shaped [L][n][T][H][Dh] whose inner four dims are contiguous."""
+    return KvDesc(*_layout(t))
 
 
 def _dev(*ts):
@@ -136,7 +146,7 @@ def rc_block_norms(k, v, mode=RC_SCORE_BLOCK, k_sqnorm=None, v_sqnorm=None):
     """Squared norms of every block: returns (k_sqnorm, v_sqnorm), fp32 [L][n] or [L][n][H]."""
     _dev(k, v)
     d = kv_desc(k)
-    assert v.shape == k.shape and v.dtype == k.dtype and kv_desc(v).layer_stride == d.layer_stride
+    assert v.shape == k.shape and v.dtype == k.dtype and _layout(v)[5] == d.layer_stride
     L, n, H = k.shape[0], k.shape[1], k.shape[3]
     shape = (L, n) if mode == RC_SCORE_BLOCK else (L, n, H)
     if k_sqnorm is None:
@@ -158,15 +168,14 @@ def rc_match_blocks(kq, vq, q_ksq, q_vsq, kp, vp, p_ksq, p_vsq, pool_live, tau, 
     """Best live pool block per query.  Returns dict(best_idx, best_score, match_idx, second_score)."""
     _dev(kq, vq, kp, vp, q_ksq, q_vsq, p_ksq, p_vsq, pool_live)
     qd, pd = kv_desc(kq), kv_desc(kp)
-    assert kv_desc(vq).layer_stride == qd.layer_stride and kv_desc(vp).layer_stride == pd.layer_stride
+    assert _layout(vq)[5] == qd.layer_stride and _layout(vp)[5] == pd.layer_stride
     L, Q, P = kq.shape[0], kq.shape[1], kp.shape[1]
     for t in (q_ksq, q_vsq, p_ksq, p_vsq):
         assert t.dtype == torch.float32 and t.is_contiguous()
     if pool_live is not None:
         assert pool_live.dtype == torch.uint8 and pool_live.shape == (L, P) and pool_live.is_contiguous()
-    need = lib().rc_match_workspace_size(ctypes.byref(qd), mode, Q, P)
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=kq.device)
+        workspace = torch.empty(lib().rc_match_workspace_size(ctypes.byref(qd), mode, Q, P), dtype=torch.uint8, device=kq.device)
     if out is None:
         out = dict(best_idx=torch.empty((L, Q), dtype=torch.int32, device=kq.device),
                    best_score=torch.empty((L, Q), dtype=torch.float32, device=kq.device),
@@ -202,9 +211,8 @@ def rc_remap_block_table(tables, query_ids, pool_ids, match_idx, P, NB, refcount
         r_out = refcount if in_place else torch.empty_like(refcount)
         freed = torch.empty((L, Q), dtype=torch.uint8, device=tables.device)
         n_remapped = torch.empty((L,), dtype=torch.int32, device=tables.device)
-    need = lib().rc_remap_workspace_size(L, R, E, Q, NB)
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=tables.device)
+        workspace = torch.empty(lib().rc_remap_workspace_size(L, R, E, Q, NB), dtype=torch.uint8, device=tables.device)
     _check(lib().rc_remap_block_table(L, _ptr(tables), _ptr(t_out), R, E, _ptr(query_ids), _ptr(pool_ids),
                                       _ptr(match_idx), Q, P, NB, _ptr(refcount), _ptr(r_out), _ptr(freed),
                                       _ptr(n_remapped), _ptr(workspace), workspace.numel(), _stream()))
@@ -261,14 +269,14 @@ def rc_match_blocks_layer_mean(kq, vq, q_ksq, q_vsq, kp, vp, p_ksq, p_vsq, pool_
     """Nearest live pool block per query by the layer-mean distance.  Returns dict(best_idx, best_dist, match_idx, second_dist), [Q]."""
     _dev(kq, vq, kp, vp, q_ksq, q_vsq, p_ksq, p_vsq, pool_live)
     qd, pd = kv_desc(kq), kv_desc(kp)
-    assert kv_desc(vq).layer_stride == qd.layer_stride and kv_desc(vp).layer_stride == pd.layer_stride
+    assert _layout(vq)[5] == qd.layer_stride and _layout(vp)[5] == pd.layer_stride
     L, Q, P = kq.shape[0], kq.shape[1], kp.shape[1]
     for t, n in ((q_ksq, Q), (q_vsq, Q), (p_ksq, P), (p_vsq, P)):
         assert t.dtype == torch.float32 and t.is_contiguous() and t.shape == (L, n)
     if pool_live is not None:
         assert pool_live.dtype == torch.uint8 and pool_live.shape == (P,) and pool_live.is_contiguous()
-    need = lib().rc_layer_mean_workspace_size(ctypes.byref(qd), Q, P)
     if workspace is None:
+        need = lib().rc_layer_mean_workspace_size(ctypes.byref(qd), Q, P)
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=kq.device)
     if out is None:
         out = dict(best_idx=torch.empty((Q,), dtype=torch.int32, device=kq.device),
@@ -317,7 +325,7 @@ def rc_pool_admit(kq, vq, q_ksq, q_vsq, kp, vp, p_ksq, p_vsq, pool_live, match_i
     Returns dict(slot_of_query int32 [Q], n_admitted int32 [1])."""
     _dev(kq, vq, kp, vp, q_ksq, q_vsq, p_ksq, p_vsq, pool_live, match_idx)
     qd, pd = kv_desc(kq), kv_desc(kp)
-    assert kv_desc(vq).layer_stride == qd.layer_stride and kv_desc(vp).layer_stride == pd.layer_stride
+    assert _layout(vq)[5] == qd.layer_stride and _layout(vp)[5] == pd.layer_stride
     L, Q, P, H = kq.shape[0], kq.shape[1], kp.shape[1], kq.shape[3]
     qs, ps = ((L, Q), (L, P)) if mode == RC_SCORE_BLOCK else ((L, Q, H), (L, P, H))
     for t, sh in ((q_ksq, qs), (q_vsq, qs), (p_ksq, ps), (p_vsq, ps)):
@@ -340,7 +348,7 @@ def rc_candidate_distances(kq, vq, kp, vp, pool_live, cand, threshold, workspace
     """Layer-mean distance of the listed pairs, cand [Q][C].  Returns dict(dist [Q][C], best_idx, best_dist, match_idx)."""
     _dev(kq, vq, kp, vp, pool_live, cand)
     qd, pd = kv_desc(kq), kv_desc(kp)
-    assert kv_desc(vq).layer_stride == qd.layer_stride and kv_desc(vp).layer_stride == pd.layer_stride
+    assert _layout(vq)[5] == qd.layer_stride and _layout(vp)[5] == pd.layer_stride
     Q, P = kq.shape[1], kp.shape[1]
     assert cand.dtype == torch.int32 and cand.dim() == 2 and cand.shape[0] == Q and cand.is_contiguous()
     C = cand.shape[1]
