@@ -1,8 +1,8 @@
 // rc_score_candidates: Stage 2 restricted to listed candidates (ReasonCache Sec. IV-A: only the
-// blocks of the steps flagged by Stage 1 are compared).  HBM-bound gather: one workgroup per listed
-// pair streams the pool block's K and V tensors (the query block comes from the L2, which the other
-// candidates of the same query keep warm), accumulates the dot products in fp32 and normalises with
-// the cached squared norms.  A second small kernel picks the best candidate of every list.
+// blocks of the steps flagged by Stage 1 are compared).  HBM-bound gather: the pool blocks' K and V
+// tensors are streamed against the query block, the dot products accumulated in fp32 and normalised
+// with the cached squared norms.  A workgroup takes 16 or 4 candidates of a list, or, where lists are
+// many and share blocks, a wave takes a list; a small kernel (or the wave) picks the best candidate.
 #include <hip/hip_runtime.h>
 
 #include "rc_common.hpp"
@@ -314,6 +314,159 @@ __global__ __launch_bounds__(kCandThreads) void candidate_distances_kernel(const
     p.part[((long long)blockIdx.z * p.Q + q) * p.C + c0 + tid] = total;
 }
 
+// ---- many lists: a wave per list
+
+// Up to 2 * SLOTS candidates of one query and a wave for all of them: lanes 0..31 and 32..63 hold the same 512 bytes of
+// the query against two candidates at a time, K first, then V, with no LDS and no barrier.  The waves of a launch start
+// together and advance at the same rate, so the lists of a layer read the same 512-byte window of their blocks at about the
+// same time, and a block that several lists name comes from the L2 (neighbouring lists are dealt to one XCD) or the
+// memory-side cache when the second of them asks for it.  A workgroup per list (above) keeps the lists on a chip apart by up
+// to a whole block each.  A wave is a workgroup of its own, so that few lists spread over all compute units.  What
+// bounds it: the stream of blocks, less what lists share (32 x 4096 x 256 lists of 16, 32-KB tensors: 1219 us = 7.1 TB/s of
+// listed blocks, 1297 in workgroups; 36 x 150 x 65 x 17: 250 -> 84).
+struct WideParams {
+  const char *kq, *vq, *kp, *vp;
+  const float *q_ksq, *q_vsq, *p_ksq, *p_vsq;
+  const uint8_t* live;   // [L][P]; distances: [P]
+  const int32_t* cand;   // [L][Q][C]; distances: [Q][C]
+  float* out;            // scores [L][Q][C]; distances: sums [groups of layers][Q][C]
+  int32_t* best_idx;
+  float* best_score;
+  int32_t* match_idx;
+  long long q_lstride_b, p_lstride_b;
+  int Q, P, C;
+  int L, G;              // distances: layers, layers of a group
+  int per, parts;        // candidates of a wave, waves per list
+  int block_bytes;
+  long long items;       // waves with work
+  long long per_xcd;     // waves of an XCD's run; 0: the lists are dealt out one after the other
+  float tau;
+};
+constexpr int kWindow = 512;   // bytes of a block per step
+
+template <bool BF16, int SLOTS, bool DIST>
+__global__ __launch_bounds__(64, SLOTS == 8 ? 3 : 4) void candidates_wide_kernel(const WideParams p) {
+  const int lane = threadIdx.x, half = lane >> 5;
+  const long long item = p.per_xcd ? (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3) : blockIdx.x;
+  if (item >= p.items) return;
+  const long long list = item / p.parts;  // (layer or group of layers, query)
+  const int c0 = (int)(item % p.parts) * p.per, n = min(p.per, p.C - c0);
+  const long long z = list / p.Q, q = list % p.Q;
+  const long long l0 = DIST ? z * p.G : z;
+  const int nl = DIST ? (int)min((long long)p.G, p.L - l0) : 1;
+  const long long slot0 = list * p.C + c0, cand0 = (DIST ? q : list) * p.C + c0;
+  // lane s + 32 * half keeps candidate 2 * s + half
+  const int mine = 2 * (lane & 31) + half;
+  const bool listed = (lane & 31) < SLOTS && mine < n;
+  const int pidx = listed ? p.cand[cand0 + mine] : -1;
+  const bool valid = pidx >= 0 && pidx < p.P && (!p.live || p.live[(DIST ? 0 : l0 * p.P) + pidx]);
+  constexpr int kNowhere = (int)0x80000000u;  // past the end of the pool's descriptor: reads as zero, no traffic
+  const int moff = valid ? pidx * p.block_bytes : kNowhere;
+  int off[SLOTS];
+#pragma unroll
+  for (int s = 0; s < SLOTS; ++s) off[s] = __shfl(moff, s + 32 * half) + (lane & 31) * 16;
+  const int qoff = (lane & 31) * 16;
+  const int pool_bytes = (int)((long long)p.P * p.block_bytes);  // below 2^31: a condition of this kernel
+  const int steps = p.block_bytes / kWindow;                     // a multiple of 8
+  struct Source {
+    __amdgpu_buffer_rsrc_t q, p;
+  };
+  auto source = [&](int li, bool v) __attribute__((always_inline)) {
+    const long long l = l0 + li;
+    Source r;
+    r.q = __builtin_amdgcn_make_buffer_rsrc((void*)((v ? p.vq : p.kq) + l * p.q_lstride_b + q * p.block_bytes), 0, p.block_bytes, 0x00020000);
+    r.p = __builtin_amdgcn_make_buffer_rsrc((void*)((v ? p.vp : p.kp) + l * p.p_lstride_b), 0, pool_bytes, 0x00020000);
+    return r;
+  };
+  u32x4 x[2][SLOTS], y[2];
+  auto load = [&](int buf, const Source& src, int step) __attribute__((always_inline)) {
+    y[buf] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(src.q, qoff, step * kWindow, 0));
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) x[buf][s] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(src.p, off[s], step * kWindow, 0));
+  };
+  float run[SLOTS];
+  auto add = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) run[s] = DIST ? sqdiff8<BF16>(y[buf], x[buf][s], run[s]) : dot8<BF16>(y[buf], x[buf][s], run[s]);
+  };
+  // the sum over one tensor: lane s + 32 * half gets its candidate's
+  auto walk = [&](const Source& src, const Source& next, bool more) __attribute__((always_inline)) {
+    float d[SLOTS];
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) d[s] = 0.f;
+    // short chains of fp32 adds join the running sums, so that the error stays that of 256 lanes per block: squares, all of one
+    // sign, lose most in long chains (8 steps, blocks of 12 KB: 1.3 times), products of both signs in the running sums (2 steps,
+    // blocks of 64 KB: 1.25 times)
+    constexpr int kFold = DIST ? 2 : 8;  // steps; a block has a multiple of 8
+#pragma unroll 1
+    for (int t0 = 0; t0 < steps; t0 += kFold) {
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s) run[s] = 0.f;
+#pragma unroll 1
+      for (int t = t0; t < t0 + kFold; t += 2) {
+        load(1, src, t + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        add(0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 2 < steps)
+          load(0, src, t + 2);
+        else if (more)
+          load(0, next, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        add(1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int s = 0; s < SLOTS; ++s) d[s] += run[s];
+    }
+    float sum = 0.f;
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+#pragma unroll
+      for (int o = 16; o > 0; o >>= 1) d[s] += __shfl_xor(d[s], o);
+      if ((lane & 31) == s) sum = d[s];
+    }
+    return sum;
+  };
+  float total = 0.f, sk = 0.f, sv = 0.f;
+  load(0, source(0, false), 0);
+  for (int li = 0; li < nl; ++li) {
+    sk = walk(source(li, false), source(li, true), true);
+    sv = walk(source(li, true), source(min(li + 1, nl - 1), false), li + 1 < nl);
+    if (DIST) total += __builtin_amdgcn_sqrtf(sk) + __builtin_amdgcn_sqrtf(sv);
+  }
+  if (DIST) {
+    if (valid) p.out[slot0 + mine] = total;  // the selection kernel derives validity itself
+    return;
+  }
+  float score = -INFINITY;
+  if (valid) {
+    const long long oq = list, op = l0 * p.P + pidx;
+    const float nkq = p.q_ksq[oq], nvq = p.q_vsq[oq], nkp = p.p_ksq[op], nvp = p.p_vsq[op];
+    const float ck = (nkq > 0.f && nkp > 0.f) ? sk * __builtin_amdgcn_rsqf(nkq) * __builtin_amdgcn_rsqf(nkp) : 0.f;
+    const float cv = (nvq > 0.f && nvp > 0.f) ? sv * __builtin_amdgcn_rsqf(nvq) * __builtin_amdgcn_rsqf(nvp) : 0.f;
+    score = 0.5f * (ck + cv);
+  }
+  if (listed) p.out[slot0 + mine] = score;
+  if (p.parts > 1) return;  // the selection kernel picks
+  float best = -INFINITY;
+  int bidx = -1;
+#pragma unroll
+  for (int c = 0; c < 2 * SLOTS; ++c) {  // in list order, as the selection kernel does; an entry that was not scored is -inf
+    const float sc = __shfl(score, (c >> 1) + 32 * (c & 1));
+    const int pi = __shfl(pidx, (c >> 1) + 32 * (c & 1));
+    if (c >= n || sc == -INFINITY) continue;
+    if (sc > best || (sc == best && pi < bidx) || bidx < 0) {
+      best = sc;
+      bidx = pi;
+    }
+  }
+  if (lane != 0) return;
+  p.best_idx[list] = bidx;
+  p.best_score[list] = best;
+  p.match_idx[list] = (bidx >= 0 && best >= p.tau) ? bidx : -1;
+}
+
 // One wave per query, a candidate per lane: layer groups added in order (8 asked for at once), scaled, validity
 // re-derived, nearest candidate.  One thread per query walked all its candidates' groups one load at a time: 96
 // queries x 12 candidates x 24 groups 48 -> 5.6 us.
@@ -407,6 +560,32 @@ inline int cand_per_wg(int64_t lists, int64_t C, int block_bytes, bool two_trips
   return few() ? kCandFew : kCandPerWg;
 }
 
+// Slots (pairs of candidates) of a wave for lists of C: two waves share a list of 17 to 32, and so on.
+struct WideLists {
+  int parts, per, slots;
+};
+inline WideLists wide_lists(int64_t C) {
+  WideLists w;
+  w.parts = (int)((C + kCandPerWg - 1) / kCandPerWg);
+  w.per = (int)((C + w.parts - 1) / w.parts);
+  w.slots = w.per <= 4 ? 2 : w.per <= 8 ? 4 : w.per <= 12 ? 6 : 8;
+  return w;
+}
+// Calls for candidates_wide_kernel: at least half as many pairs as there are pool blocks (per layer, or in all for the
+// distances), so that lists share blocks, or lists of 17 to 24 (33 to 40, ...), of which workgroups of 16 leave half a
+// workgroup idle; and slots enough to keep the chip's memory pipeline full, which a workgroup per list does with fewer.
+// Measured, workgroup per list -> wave per list, us (layers x pool x queries x C):
+//   32 x 4096 x 256 x 16 1304 -> 1209   45 x 533 x 88 x 24 2005 -> 1245   11 x 194 x 66 x 14 102 -> 44   37 x 1823 x 795 x 19 6710 -> 4898
+//   4 x 2343 x 91 x 13 (2912 slots) 118 -> 123   3 x 231 x 60 x 14 (1440) 65 -> 114   13 x 1216 x 29 x 19 (a third of the blocks) 123 -> 95
+//   fewer pairs, full workgroups: 64 x 4096 x 32 x 16 340 -> 366   25 x 2810 x 48 x 9 234 -> 252   48 x 3100 x 96 x 12 (distances) 766 -> 798
+inline bool wide_wins(int64_t lists, int64_t Q, int64_t C, int64_t P, int block_bytes) {
+  if (C < 1 || P < 1 || P > 0x7fffffffLL / block_bytes || lists > (1LL << 28) || C > (1 << 20)) return false;
+  const WideLists w = wide_lists(C);
+  const int64_t slots = lists * w.parts * w.slots;
+  if (lists * w.parts > (1LL << 30)) return false;
+  return (2 * Q * C >= P && slots >= 3000) || (C > 16 && (C - 1) % 16 < 8 && slots >= 4000);
+}
+
 template <bool BF16>
 void launch_candidates(bool any_h, int per, dim3 grid, const CandParams& cp, hipStream_t st) {
   if (per == kCandFew) {
@@ -420,6 +599,31 @@ void launch_candidates(bool any_h, int per, dim3 grid, const CandParams& cp, hip
     else
       candidates_kernel<BF16, false, kCandPerWg><<<grid, kCandThreads, 0, st>>>(cp);
   }
+}
+
+template <bool BF16, bool DIST>
+void launch_wide(const WideParams& wp, hipStream_t st) {
+  const unsigned grid = (unsigned)(wp.per_xcd ? wp.per_xcd * 8 : wp.items);
+  if (wp.per <= 4)
+    candidates_wide_kernel<BF16, 2, DIST><<<grid, 64, 0, st>>>(wp);
+  else if (wp.per <= 8)
+    candidates_wide_kernel<BF16, 4, DIST><<<grid, 64, 0, st>>>(wp);
+  else if (wp.per <= 12)
+    candidates_wide_kernel<BF16, 6, DIST><<<grid, 64, 0, st>>>(wp);
+  else
+    candidates_wide_kernel<BF16, 8, DIST><<<grid, 64, 0, st>>>(wp);
+}
+
+// lists: (layers or groups of layers) x Q.  Neighbouring lists go to one XCD while the lists of a layer are about as many as
+// an XCD works on at once; with more of them its lists would be a small part of the layer's, with few blocks in common, and
+// all XCDs do better on the same part of the layer (4 x 16384 x 1024 x 20: 877 us by XCD, 785 dealt out; 36 x 150 x 65 x 17: 85
+// and 148).
+inline void wide_plan(WideParams& wp, int64_t lists) {
+  const WideLists w = wide_lists(wp.C);
+  wp.parts = w.parts;
+  wp.per = w.per;
+  wp.items = (long long)lists * w.parts;
+  wp.per_xcd = (int64_t)wp.Q * w.parts > 448 ? 0 : (wp.items + 7) / 8;
 }
 
 }  // namespace
@@ -455,7 +659,40 @@ extern "C" rc_status rc_score_candidates(const rc_kv_desc* qdesc, const rc_kv_de
   if (C > 0x7fffffffLL || Q > 65535 || L > 65535 || P > 0x7fffffffLL)
     return fail(RC_ERR_UNSUPPORTED, "rc_score_candidates: C, Q or L beyond the grid limits");
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  if (C > 0) {
+  const int block_bytes = qdesc->block_tokens * H * qdesc->head_dim * 2;
+  if (mode == RC_SCORE_BLOCK && wide_wins((int64_t)L * Q, Q, C, P, block_bytes)) {
+    WideParams wp;
+    wp.kq = static_cast<const char*>(kq);
+    wp.vq = static_cast<const char*>(vq);
+    wp.kp = static_cast<const char*>(kp);
+    wp.vp = static_cast<const char*>(vp);
+    wp.q_ksq = q_ksq;
+    wp.q_vsq = q_vsq;
+    wp.p_ksq = p_ksq;
+    wp.p_vsq = p_vsq;
+    wp.live = pool_live;
+    wp.cand = cand;
+    wp.out = scores;
+    wp.best_idx = best_idx;
+    wp.best_score = best_score;
+    wp.match_idx = match_idx;
+    wp.q_lstride_b = qdesc->layer_stride * 2;
+    wp.p_lstride_b = pdesc->layer_stride * 2;
+    wp.Q = (int)Q;
+    wp.P = (int)P;
+    wp.C = (int)C;
+    wp.L = L;
+    wp.G = 1;
+    wp.block_bytes = block_bytes;
+    wide_plan(wp, (int64_t)L * Q);
+    wp.tau = tau;
+    if (qdesc->dtype == RC_BF16)
+      launch_wide<true, false>(wp, st);
+    else
+      launch_wide<false, false>(wp, st);
+    if (rc_status s = check_launch("rc_score_candidates(lists)")) return s;
+    if (wp.parts == 1) return RC_OK;
+  } else if (C > 0) {
     CandParams cp;
     cp.kq = static_cast<const char*>(kq);
     cp.vq = static_cast<const char*>(vq);
@@ -473,7 +710,7 @@ extern "C" rc_status rc_score_candidates(const rc_kv_desc* qdesc, const rc_kv_de
     cp.Q = (int)Q;
     cp.P = (int)P;
     cp.C = (int)C;
-    cp.block_bytes = qdesc->block_tokens * H * qdesc->head_dim * 2;  // T >= 16, Dh = 128: a multiple of 16 KB / 4
+    cp.block_bytes = block_bytes;  // T >= 16, Dh = 128: a multiple of 16 KB / 4
     cp.heads = (mode == RC_SCORE_BLOCK) ? 1 : H;
     const bool any_h = mode == RC_SCORE_PER_HEAD_ALL && (16 % H) != 0;  // a thread's chunks wander over the heads
     const int per = cand_per_wg((int64_t)L * Q, C, cp.block_bytes, !any_h);
@@ -532,7 +769,31 @@ extern "C" rc_status rc_candidate_distances(const rc_kv_desc* qdesc, const rc_kv
   const int G = cand_layers_per_group(L, Q, C);
   const int groups = (L + G - 1) / G;
   float* part = static_cast<float*>(workspace);
-  if (C > 0 && P > 0) {
+  const int block_bytes = qdesc->block_tokens * qdesc->n_kv_heads * qdesc->head_dim * 2;
+  if (wide_wins((int64_t)groups * Q, Q, C, P, block_bytes)) {
+    WideParams wp = {};
+    wp.kq = static_cast<const char*>(kq);
+    wp.vq = static_cast<const char*>(vq);
+    wp.kp = static_cast<const char*>(kp);
+    wp.vp = static_cast<const char*>(vp);
+    wp.live = pool_live;
+    wp.cand = cand;
+    wp.out = part;
+    wp.q_lstride_b = qdesc->layer_stride * 2;
+    wp.p_lstride_b = pdesc->layer_stride * 2;
+    wp.Q = (int)Q;
+    wp.P = (int)P;
+    wp.C = (int)C;
+    wp.L = L;
+    wp.G = G;
+    wp.block_bytes = block_bytes;
+    wide_plan(wp, (int64_t)groups * Q);
+    if (qdesc->dtype == RC_BF16)
+      launch_wide<true, true>(wp, st);
+    else
+      launch_wide<false, true>(wp, st);
+    if (rc_status s = check_launch("rc_candidate_distances(lists)")) return s;
+  } else if (C > 0 && P > 0) {
     CandDistParams cp;
     cp.kq = static_cast<const char*>(kq);
     cp.vq = static_cast<const char*>(vq);
