@@ -289,7 +289,8 @@ rc_status rc_candidate_distances(const rc_kv_desc* qdesc, const rc_kv_desc* pdes
                                  float* dist, int32_t* best_idx, float* best_dist, int32_t* match_idx,
                                  void* workspace, size_t workspace_bytes, void* hip_stream);
 
-/* Bytes of DEVICE workspace rc_pat_threshold needs (a constant, about 4 KB). */
+/* Bytes of DEVICE workspace with which rc_pat_threshold is fastest (a constant, about 24 KB; a call takes 4112 bytes as
+ * well and is slower then, above 16384 samples). */
 size_t rc_pat_workspace_size(void);
 
 /*
@@ -308,7 +309,7 @@ size_t rc_pat_workspace_size(void);
  *                   passes (p = 0.1 with n_f = 1000 is rank 1; rounded to float it would be rank 2)
  *   threshold       DEVICE float [1], written on the stream (no host synchronisation)
  *   n_finite        DEVICE int64 [1] or NULL: number of samples that took part
- *   workspace       DEVICE, >= rc_pat_workspace_size() bytes, 16-byte aligned, scratch
+ *   workspace       DEVICE, rc_pat_workspace_size() bytes (4112 at least), 16-byte aligned, scratch
  */
 rc_status rc_pat_threshold(const float* samples, int64_t n, double p,
                            float* threshold, int64_t* n_finite,

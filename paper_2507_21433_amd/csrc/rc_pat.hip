@@ -1,10 +1,10 @@
 // rc_pat_threshold, rc_apply_threshold: percentile-based adaptive thresholding (ReasonCache
 // Sec. IV-A, PAT).  The threshold is the nearest-rank p-th percentile of the distances collected
-// during warm-up: an exact order statistic, found by a radix select over the bit patterns (four
-// passes of 8 bits, most significant first).  Each pass histograms one byte of the keys that
-// still match the prefix chosen so far; the next pass derives that prefix again from the
-// histograms (256 bins per pass, every workgroup repeats the short scan), so no pass needs a
-// launch of its own for the scan.  Integer counts only: the result is the same on every run.
+// during warm-up: an exact order statistic, found by a radix select over the bit patterns, most
+// significant bits first (three passes of 11, 11 and 10 bits; four of 8 in a workspace of 4 KB or
+// for few samples).  Each pass histograms the next bits of the keys that still match the prefix
+// chosen so far; the next pass derives that prefix again from the histograms (every workgroup
+// repeats the short scan), so no pass needs a launch of its own for the scan.  Integer counts only: the result is the same on every run.
 #include <hip/hip_runtime.h>
 
 #include "rc_common.hpp"
@@ -107,6 +107,7 @@ __device__ __forceinline__ void count_bin(unsigned int* h, int bin) {
 // Few samples: one workgroup keeps their keys in registers and does all four passes; one launch instead of six
 // (3 to 6 us each).  2000 samples 23 -> 8.5 us, 8000 32 -> 16; at 32 768 one workgroup would take 47 us, the six launches 35.
 constexpr int kPatSmallThreads = 1024, kPatSmallKeys = 16;
+constexpr int kPatFew = 8192;  // where the launches of pat_wide_kernel take less (16 384 samples: 22 us in one workgroup, 17)
 __global__ __launch_bounds__(kPatSmallThreads) void pat_small_kernel(const float* __restrict__ s, int n, double p,
                                                                      float* __restrict__ threshold,
                                                                      long long* __restrict__ n_finite) {
@@ -220,6 +221,129 @@ __global__ __launch_bounds__(kPatThreads) void pat_final_kernel(long long n, dou
   }
 }
 
+// Many samples in three passes of 11, 11 and 10 bits instead of four of 8, the last workgroup to arrive in the third one
+// finishing the job: four launches instead of six, for a larger state.  What bounds it is launches and the chain inside each
+// (state, prefix, samples, counts out), not the samples.  Six launches -> these, us: 30 000 samples 29 -> 17, 1 million 40 -> 27,
+// 4 million 77 -> 38.
+constexpr int kWideThreads = 1024, kWideBins = 2048, kWideUnroll = 4;
+struct PatWideState {
+  unsigned int hist[3][kWideBins];
+  unsigned int nonfinite, arrived;
+  unsigned int pad[2];
+};
+
+__global__ __launch_bounds__(kWideThreads) void pat_wide_clear_kernel(PatWideState* st) {
+  unsigned int* w = reinterpret_cast<unsigned int*>(st);
+  for (int i = threadIdx.x; i < (int)(sizeof(PatWideState) / 4); i += kWideThreads) w[i] = 0u;
+}
+
+// The bin of `hist` that holds rank k, to every thread; k becomes the rank within it.  FRESH: the counts were added by other
+// workgroups of this launch, so the loads go to where their atomic adds went.
+template <bool FRESH>
+__device__ __forceinline__ unsigned int pat_wide_digit(unsigned int* hist, long long& k, unsigned int* s_wave, long long* s_sel) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  unsigned int c[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+    c[b] = FRESH ? __hip_atomic_load(&hist[2 * tid + b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : hist[2 * tid + b];
+  unsigned int incl = c[0] + c[1];
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const unsigned int v = __shfl_up(incl, off);
+    if (lane >= off) incl += v;
+  }
+  if (lane == 63) s_wave[wave] = incl;
+  if (tid == 0) {
+    s_sel[0] = kWideBins - 1;
+    s_sel[1] = 0;
+  }
+  __syncthreads();
+  unsigned int before = incl - c[0] - c[1];
+#pragma unroll
+  for (int w = 0; w < kWideThreads / 64; ++w) before += w < wave ? s_wave[w] : 0u;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    if ((long long)before < k && k <= (long long)before + c[b]) {  // exactly one bin, if k is within the total
+      s_sel[0] = 2 * tid + b;
+      s_sel[1] = before;
+    }
+    before += c[b];
+  }
+  __syncthreads();
+  const unsigned int digit = (unsigned int)s_sel[0];
+  k -= s_sel[1];
+  __syncthreads();  // the two are rewritten by the next call
+  return digit;
+}
+
+template <int PASS>
+__global__ __launch_bounds__(kWideThreads) void pat_wide_kernel(const float* __restrict__ s, long long n, double p, PatWideState* st,
+                                                                float* __restrict__ threshold, long long* __restrict__ n_finite) {
+  constexpr int kShift = PASS == 0 ? 21 : PASS == 1 ? 10 : 0;
+  constexpr unsigned int kBins = PASS == 2 ? 1024u : 2048u;
+  __shared__ unsigned int s_local[kWideBins];
+  __shared__ unsigned int s_wave[kWideThreads / 64], s_bad;
+  __shared__ long long s_sel[2];
+  const int tid = threadIdx.x;
+  const long long stride = (long long)gridDim.x * kWideThreads;
+  // the first samples are on their way while the prefix is worked out
+  float x[kWideUnroll];
+  auto load = [&](long long i0) {
+#pragma unroll
+    for (int u = 0; u < kWideUnroll; ++u) {
+      const long long i = i0 + u * stride;
+      x[u] = i < n ? s[i] : 0.f;
+    }
+  };
+  long long i0 = (long long)blockIdx.x * kWideThreads + tid;
+  load(i0);
+  s_local[tid] = 0u;
+  s_local[tid + kWideThreads] = 0u;
+  if (tid == 0) s_bad = 0u;
+  long long k = 0;
+  unsigned int prefix = 0;
+  bool any = true;
+  if (PASS > 0) {
+    const long long n_f = n - (long long)st->nonfinite;
+    any = n_f > 0;
+    k = any ? pat_rank(p, n_f) : 1;
+    prefix = pat_wide_digit<false>(st->hist[0], k, s_wave, s_sel);
+    if (PASS > 1) prefix = prefix << 11 | pat_wide_digit<false>(st->hist[1], k, s_wave, s_sel);
+  }
+  __syncthreads();
+  unsigned int bad = 0;
+  for (; i0 - tid < n; i0 += kWideUnroll * stride) {  // the same for the whole workgroup
+    unsigned int key[kWideUnroll];
+#pragma unroll
+    for (int u = 0; u < kWideUnroll; ++u) key[u] = key_of(x[u]);
+    const long long here = i0;
+    load(i0 + kWideUnroll * stride);
+#pragma unroll
+    for (int u = 0; u < kWideUnroll; ++u) {
+      if (here + u * stride >= n) break;
+      if (PASS == 0) bad += key[u] == 0xffffffffu;
+      if (PASS == 0 || (key[u] >> (PASS == 1 ? 21 : 10)) == prefix) atomicAdd(&s_local[(key[u] >> kShift) & (kBins - 1u)], 1u);
+    }
+  }
+  if (PASS == 0 && bad) atomicAdd(&s_bad, bad);
+  __syncthreads();
+  for (unsigned int b = tid; b < kBins; b += kWideThreads)
+    if (s_local[b]) __hip_atomic_fetch_add(&st->hist[PASS][b], s_local[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (PASS == 0 && tid == 0 && s_bad) __hip_atomic_fetch_add(&st->nonfinite, s_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (PASS < 2) return;
+  // the last workgroup to arrive has everyone's counts: its own have reached memory before it says so, and so had the others'
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) s_bad = __hip_atomic_fetch_add(&st->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (s_bad != gridDim.x - 1) return;
+  const unsigned int low = pat_wide_digit<true>(st->hist[2], k, s_wave, s_sel);
+  if (tid == 0) {
+    *threshold = any ? value_of(prefix << 10 | low) : -INFINITY;
+    if (n_finite) *n_finite = n - (long long)st->nonfinite;
+  }
+}
+
 __global__ __launch_bounds__(256) void apply_threshold_kernel(const int32_t* __restrict__ best_idx,
                                                               const float* __restrict__ best_dist, long long n,
                                                               const float* __restrict__ threshold,
@@ -234,7 +358,7 @@ __global__ __launch_bounds__(256) void apply_threshold_kernel(const int32_t* __r
 }  // namespace
 }  // namespace rc
 
-extern "C" size_t rc_pat_workspace_size(void) { return sizeof(rc::PatState); }
+extern "C" size_t rc_pat_workspace_size(void) { return sizeof(rc::PatWideState); }
 
 extern "C" rc_status rc_pat_threshold(const float* samples, int64_t n, double p, float* threshold, int64_t* n_finite,
                                       void* workspace, size_t workspace_bytes, void* hip_stream) {
@@ -247,9 +371,22 @@ extern "C" rc_status rc_pat_threshold(const float* samples, int64_t n, double p,
     return fail(RC_ERR_WORKSPACE, "rc_pat_threshold: workspace of %zu bytes needed (16-byte aligned), got %zu",
                 sizeof(PatState), workspace_bytes);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  if (n <= kPatSmallThreads * kPatSmallKeys) {
+  const bool wide = workspace_bytes >= sizeof(PatWideState);
+  if (n <= (wide ? kPatFew : kPatSmallThreads * kPatSmallKeys)) {
     pat_small_kernel<<<1, kPatSmallThreads, 0, st>>>(samples, (int)n, p, threshold, reinterpret_cast<long long*>(n_finite));
     return check_launch("rc_pat_threshold(few samples)");
+  }
+  if (wide) {
+    PatWideState* state = static_cast<PatWideState*>(workspace);
+    pat_wide_clear_kernel<<<1, kWideThreads, 0, st>>>(state);
+    if (rc_status s = check_launch("rc_pat_threshold(clear)")) return s;
+    long long wgs = (n + kWideThreads * kWideUnroll - 1) / (kWideThreads * kWideUnroll);
+    if (wgs > 256) wgs = 256;  // one per compute unit; 512: 3 million samples 42 us, 256: 34
+    long long* nf = reinterpret_cast<long long*>(n_finite);
+    pat_wide_kernel<0><<<(unsigned)wgs, kWideThreads, 0, st>>>(samples, (long long)n, p, state, threshold, nf);
+    pat_wide_kernel<1><<<(unsigned)wgs, kWideThreads, 0, st>>>(samples, (long long)n, p, state, threshold, nf);
+    pat_wide_kernel<2><<<(unsigned)wgs, kWideThreads, 0, st>>>(samples, (long long)n, p, state, threshold, nf);
+    return check_launch("rc_pat_threshold(histograms)");
   }
   PatState* state = static_cast<PatState*>(workspace);
   pat_clear_kernel<<<1, kPatThreads, 0, st>>>(state);
