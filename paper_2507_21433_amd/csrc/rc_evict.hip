@@ -3,8 +3,8 @@
 // block to the free pool only when its reference count has dropped to 0; Sec. IV-A: per-block
 // metadata is kept in LRU order).
 //
-// rc_pool_evict is one workgroup that walks the per-slot metadata (9 bytes per slot; 0.4 MB for
-// the 49 152 slots of the largest benchmark pool) a handful of times: counts, a radix select of
+// rc_pool_evict is one workgroup that goes through the per-slot metadata (9 bytes per slot; 0.4 MB
+// for the 49 152 slots of the largest benchmark pool; up to 16 384 slots in registers) a handful of times: counts, a radix select of
 // the need-th smallest last-use stamp among the unreferenced live slots (four passes of 8 bits
 // over order-preserving keys), then one pass in slot order that lets every candidate below that
 // stamp go and, of those at it, the lowest-numbered ones.  Integer counts only (LDS and global
@@ -147,6 +147,146 @@ __global__ __launch_bounds__(kEvictThreads) void evict_kernel(long long P, uint8
   }
 }
 
+// Pools of up to 16 384 slots: the metadata of a slot is read once, into registers, instead of once per pass (a pass of the
+// kernel above is a chain of two or three memory round trips per 1024 slots).  Thread t holds SLOTS slots t, t + 1024, ...; a
+// slot is dead, kept, or a candidate with its key.  Same victims.  Compiled for 2 slots a thread as well: what a small pool
+// waits for is the kernel's code, read once (at 16 slots 10 us for 500 slots).  us: 500 slots 11 -> 6, 2048 15 -> 7, 5000 25 -> 15,
+// 16 384 58 -> 25.
+constexpr int kEvictSlots = 16;
+template <int SLOTS>
+__global__ __launch_bounds__(kEvictThreads) void evict_small_kernel(int P, uint8_t* __restrict__ live, const int32_t* __restrict__ refcount,
+                                                                    const int32_t* __restrict__ last_used,
+                                                                    const int32_t* __restrict__ match_idx, long long Q, long long extra_wanted,
+                                                                    int32_t* __restrict__ n_free, int32_t* __restrict__ n_evicted) {
+  constexpr int kWaves = kEvictThreads / 64;
+  __shared__ unsigned int s_hist[4][256];
+  __shared__ int s_sum[3][kWaves], s_digit[4], s_before[4];
+  __shared__ int s_at[SLOTS][kWaves], s_at_wave[kWaves / 4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  unsigned int key[SLOTS] = {};
+  unsigned int cand = 0;  // bit i: slot i * 1024 + tid is a candidate
+  int dead = 0, unmatched = 0;
+#pragma unroll
+  for (int i = 0; i < SLOTS; ++i) {
+    const int p = i * kEvictThreads + tid;
+    if (p < P) {
+      const bool alive = live[p] != 0;
+      const int refs = refcount ? refcount[p] : 0;
+      key[i] = stamp_key(last_used[p]);
+      dead += !alive;
+      cand |= (unsigned)(alive && refs == 0) << i;
+    }
+  }
+  for (long long q = tid; q < Q; q += kEvictThreads) unmatched += match_idx[q] < 0;
+  s_hist[wave & 3][(wave >> 2) * 64 + lane] = 0u;
+  int sum[3] = {dead, (int)__popc(cand), unmatched};
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum[j] += __shfl_xor(sum[j], off);
+    if (lane == 0) s_sum[j][wave] = sum[j];
+  }
+  __syncthreads();
+  long long total[3] = {0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) total[j] += s_sum[j][w];
+  long long need = total[2] + extra_wanted - total[0];
+  if (need > total[1]) need = total[1];
+  if (need <= 0) {
+    if (tid == 0) {
+      *n_free = (int32_t)total[0];
+      *n_evicted = 0;
+    }
+    return;
+  }
+  // ---- the need-th smallest stamp among the candidates: radix select, 8 bits per pass
+  unsigned int prefix = 0;
+  int k = (int)need;  // rank still looked for inside the current prefix
+#pragma unroll 1
+  for (int pass = 0; pass < 4; ++pass) {
+    const int shift = 24 - 8 * pass;
+    const unsigned int mask = pass == 0 ? 0u : 0xffffffffu << (32 - 8 * pass);
+#pragma unroll
+    for (int i = 0; i < SLOTS; ++i) {
+      const int bin = (cand >> i & 1) != 0 && (key[i] & mask) == prefix ? (int)(key[i] >> shift & 255u) : -1;
+      // stamps are few and many slots share one: the bin of the wave's first slot goes out as one add
+      const unsigned long long active = __ballot(bin >= 0);
+      if (active != 0) {
+        const int leader = __ffsll((long long)active) - 1;
+        const int theirs = __builtin_amdgcn_readlane(bin, leader);
+        const unsigned long long same = __ballot(bin == theirs);
+        if (lane == leader) atomicAdd(&s_hist[pass][theirs], (unsigned int)__popcll(same));
+        if (bin >= 0 && bin != theirs) atomicAdd(&s_hist[pass][bin], 1u);
+      }
+    }
+    __syncthreads();
+    if (wave == 0) {  // four bins per lane: the bin that holds rank k
+      int c[4], mine = 0;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        c[b] = (int)s_hist[pass][4 * lane + b];
+        mine += c[b];
+      }
+      int incl = mine;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int v = __shfl_up(incl, off);
+        if (lane >= off) incl += v;
+      }
+      int before = incl - mine;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        if (before < k && k <= before + c[b]) {  // exactly one bin of one lane
+          s_digit[pass] = 4 * lane + b;
+          s_before[pass] = before;
+        }
+        before += c[b];
+      }
+    }
+    __syncthreads();
+    prefix |= (unsigned int)s_digit[pass] << shift;
+    k -= s_before[pass];
+  }
+  // prefix = key of the need-th smallest stamp; k = how many of the candidates AT that stamp go: the lowest slots.  Slots of
+  // (i, wave) follow those of (i, wave - 1); the ballots' counts are scanned in that order.
+#pragma unroll
+  for (int i = 0; i < SLOTS; ++i) {
+    const unsigned long long at = __ballot((cand >> i & 1) != 0 && key[i] == prefix);
+    if (lane == 0) s_at[i][wave] = __popcll(at);
+  }
+  __syncthreads();
+  int incl = 0, own = 0;
+  if (tid < SLOTS * kWaves) {  // whole waves at 4 slots and more
+    own = s_at[tid / kWaves][tid % kWaves];
+    incl = own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(incl, off);
+      if (lane >= off) incl += v;
+    }
+    if (lane == 63) s_at_wave[wave] = incl;
+  }
+  __syncthreads();
+  if (tid < SLOTS * kWaves) {
+    for (int w = 0; w < wave; ++w) incl += s_at_wave[w];
+    s_at[tid / kWaves][tid % kWaves] = incl - own;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < SLOTS; ++i) {
+    const bool mine = (cand >> i & 1) != 0, at = mine && key[i] == prefix;
+    const unsigned long long bal = __ballot(at);
+    const int rank = s_at[i][wave] + __popcll(bal & ((1ull << lane) - 1ull));
+    if ((mine && key[i] < prefix) || (at && rank < k)) live[i * kEvictThreads + tid] = 0;
+  }
+  if (tid == 0) {
+    *n_free = (int32_t)(total[0] + need);
+    *n_evicted = (int32_t)need;
+  }
+}
+
 }  // namespace
 }  // namespace rc
 
@@ -185,6 +325,16 @@ extern "C" rc_status rc_pool_evict(int64_t P, uint8_t* pool_live, const int32_t*
   if ((P > 0 && (!pool_live || !last_used)) || (Q > 0 && !match_idx))
     return fail(RC_ERR_INVALID_ARG, "rc_pool_evict: NULL pointer");
   if (P > 0x7fffffffLL || Q > 0x7fffffffLL) return fail(RC_ERR_UNSUPPORTED, "rc_pool_evict: more than 2^31 - 1 slots or queries");
+  if (P <= kEvictThreads * kEvictSlots) {
+    const hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    if (P <= kEvictThreads * 2)
+      evict_small_kernel<2><<<1, kEvictThreads, 0, st>>>((int)P, pool_live, refcount, last_used, match_idx, (long long)Q,
+                                                         (long long)extra_wanted, n_free, n_evicted);
+    else
+      evict_small_kernel<kEvictSlots><<<1, kEvictThreads, 0, st>>>((int)P, pool_live, refcount, last_used, match_idx, (long long)Q,
+                                                                   (long long)extra_wanted, n_free, n_evicted);
+    return check_launch("rc_pool_evict(registers)");
+  }
   evict_kernel<<<1, kEvictThreads, 0, static_cast<hipStream_t>(hip_stream)>>>(
       (long long)P, pool_live, refcount, last_used, match_idx, (long long)Q, (long long)extra_wanted, n_free, n_evicted);
   return check_launch("rc_pool_evict");

@@ -1,8 +1,8 @@
 // rc_pool_admit: streaming pool maintenance (ReasonCache Sec. IV-B: the search runs inside every
 // decoding step, so a new block that found no partner stays resident and is a candidate from the
 // next step on; Sec. IV-A: its squared norms are computed once and kept with the block).
-// Unmatched query blocks, in ascending order, take the lowest free pool slots.  Four launches,
-// no atomics: (1) dead slots per chunk of the pool, (2) one workgroup scans the chunk counts and
+// Unmatched query blocks, in ascending order, take the lowest free pool slots.  Two launches for
+// pools of up to 16 384 slots (a plan by one workgroup, and the copy), else four, no atomics: (1) dead slots per chunk of the pool, (2) one workgroup scans the chunk counts and
 // ranks the unmatched queries, (3) every chunk ranks its dead slots and pairs slot rank r with
 // unmatched query r, (4) one workgroup per (pair, layer) copies the K and V tensors and the norms.
 #include <hip/hip_runtime.h>
@@ -118,6 +118,60 @@ __global__ __launch_bounds__(256) void admit_assign_kernel(uint8_t* __restrict__
   }
 }
 
+// Pools of up to 16 384 slots and steps of up to 4096 queries: the three launches above as one workgroup, the flags of 16
+// consecutive slots per thread in registers, the ranks exchanged through LDS.  Plan and a copy of nothing, us: 64 slots 10 -> 5, 2048 13 -> 6, 16 384 15 -> 6.
+constexpr int kSmallThreads = 1024, kSmallSlots = 16, kSmallQueries = 4096;
+__global__ __launch_bounds__(kSmallThreads) void admit_plan_kernel(uint8_t* __restrict__ live, int P, int live_vec,
+                                                                   const int32_t* __restrict__ match_idx, int Q,
+                                                                   int32_t* __restrict__ slot_of_query, int32_t* __restrict__ n_admitted,
+                                                                   int* __restrict__ pair_q, int* __restrict__ pair_slot) {
+  __shared__ int s_wave[kSmallThreads / 64 + 1];
+  __shared__ int s_slot[kSmallQueries];  // the free slots, in ascending order
+  const int tid = threadIdx.x, base = tid * kSmallSlots;
+  unsigned int dead = 0;  // bit i: slot base + i is free
+  if (live_vec && base + kSmallSlots <= P) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(live + base);
+#pragma unroll
+    for (int i = 0; i < kSmallSlots; ++i) dead |= (unsigned)((v[i >> 2] >> (8 * (i & 3)) & 255u) == 0u) << i;
+  } else {
+#pragma unroll
+    for (int i = 0; i < kSmallSlots; ++i)
+      if (base + i < P) dead |= (unsigned)(live[base + i] == 0) << i;
+  }
+  constexpr int kTurns = kSmallQueries / kSmallThreads;
+  unsigned int without = 0;  // bit k: query k * 1024 + tid found no partner
+#pragma unroll
+  for (int k = 0; k < kTurns; ++k) {
+    const int q = k * kSmallThreads + tid;
+    if (q < Q) without |= (unsigned)(match_idx[q] < 0) << k;
+  }
+  int n_free;
+  int rank = block_exclusive_scan<kSmallThreads>(__popc(dead), s_wave, n_free);
+  for (unsigned int d = dead; d; d &= d - 1) {
+    if (rank < kSmallQueries) s_slot[rank] = base + __ffs(d) - 1;
+    ++rank;
+  }
+  int first = 0;  // rank of the turn's first unmatched query; block_exclusive_scan's barriers publish s_slot
+#pragma unroll
+  for (int k = 0; k < kTurns; ++k) {
+    if (k * kSmallThreads >= Q) break;  // the same for the whole workgroup
+    const int q = k * kSmallThreads + tid;
+    int total;
+    const int r = first + block_exclusive_scan<kSmallThreads>((int)(without >> k & 1), s_wave, total);
+    first += total;
+    if (q >= Q) continue;
+    int slot = -1;
+    if ((without >> k & 1) && r < n_free) {
+      slot = s_slot[r];
+      pair_q[r] = q;
+      pair_slot[r] = slot;
+      live[slot] = 1;
+    }
+    slot_of_query[q] = slot;
+  }
+  if (tid == 0) *n_admitted = min(n_free, first);
+}
+
 struct CopyParams {
   const char *kq, *vq;
   char *kp, *vp;
@@ -215,17 +269,26 @@ extern "C" rc_status rc_pool_admit(const rc_kv_desc* qdesc, const rc_kv_desc* pd
   int* pair_q = reinterpret_cast<int*>(ws + lay.pair_q);
   int* pair_slot = reinterpret_cast<int*>(ws + lay.pair_slot);
   const int nchunks = (int)((P + kChunk - 1) / kChunk);
-  if (nchunks > 0) {
+  const bool small = P <= kSmallThreads * kSmallSlots && Q <= kSmallQueries;
+  if (small) {
+    admit_plan_kernel<<<1, kSmallThreads, 0, st>>>(pool_live, (int)P, aligned16(pool_live), match_idx, (int)Q, slot_of_query, n_admitted,
+                                                   pair_q, pair_slot);
+    if (rc_status s = check_launch("rc_pool_admit(plan)")) return s;
+  } else if (nchunks > 0) {
     admit_count_kernel<<<nchunks, 256, 0, st>>>(pool_live, (int)P, chunk_dead);
     if (rc_status s = check_launch("rc_pool_admit(count)")) return s;
   }
-  admit_scan_kernel<<<1, 1024, 0, st>>>(chunk_dead, nchunks, chunk_off, match_idx, (int)Q, unmatched, slot_of_query,
-                                        n_admitted);
-  if (rc_status s = check_launch("rc_pool_admit(scan)")) return s;
+  if (!small) {
+    admit_scan_kernel<<<1, 1024, 0, st>>>(chunk_dead, nchunks, chunk_off, match_idx, (int)Q, unmatched, slot_of_query,
+                                          n_admitted);
+    if (rc_status s = check_launch("rc_pool_admit(scan)")) return s;
+  }
   if (nchunks > 0 && Q > 0) {
-    admit_assign_kernel<<<nchunks, 256, 0, st>>>(pool_live, (int)P, chunk_off, unmatched, n_admitted, slot_of_query,
-                                                 pair_q, pair_slot);
-    if (rc_status s = check_launch("rc_pool_admit(assign)")) return s;
+    if (!small) {
+      admit_assign_kernel<<<nchunks, 256, 0, st>>>(pool_live, (int)P, chunk_off, unmatched, n_admitted, slot_of_query,
+                                                   pair_q, pair_slot);
+      if (rc_status s = check_launch("rc_pool_admit(assign)")) return s;
+    }
     if (L > 0) {
       CopyParams cp;
       cp.kq = static_cast<const char*>(kq);
