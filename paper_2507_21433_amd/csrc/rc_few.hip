@@ -6,13 +6,11 @@
 #include "rc_common.hpp"
 #include "rc_few.hpp"
 #include "rc_select.hpp"
+#include "rc_tile.hpp"
 
 namespace rc {
 namespace {
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4;
@@ -141,19 +139,160 @@ __global__ __launch_bounds__(64 * kWaves, 2) void few_shares_kernel(const FewPar
   }
 }
 
+// ---- per-head score
+
+// A workgroup scores 64 pool blocks against up to 32 queries on one head: K, rescale, V, one chain of the
+// matrix instructions of the tile kernels in their order, so that a pair reports the same bits here and there.  What a small
+// call waits for is the length of that chain, a step of 64 elements after the other, and the instructions a wave has to issue
+// per step: two waves only load (straight to LDS, eight rows of a 128-byte line at a time, rows XOR-swizzled as in the tile
+// kernels), two only read fragments and multiply (2 x 361 blocks of 8 heads, 3 queries: 22 us, 24 with every wave doing both;
+// 61 x 690 x 2 514 and 536).  Six stages of 12 KB, two workgroups per compute unit: four stages and three 519, seven and one
+// 564.
+constexpr int kHeadThreads = 256, kHeadQueries = 32, kHeadLoaders = 128, kHeadStages = 6;
+struct HeadParams {
+  const char *kq, *vq, *kp, *vp;
+  const float *q_ksq, *q_vsq, *p_ksq, *p_vsq;
+  float* dpart;  // [L][H][Q][npt * 64] scores of a head
+  long long q_lstride_b, p_lstride_b;
+  int Q, P, T, H, npt;
+};
+
+template <bool BF16>
+__global__ __launch_bounds__(kHeadThreads, 1) void head_shares_kernel(const HeadParams p) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
+  constexpr int kRows = kFewRows + kHeadQueries, kStage = kRows * kRowBytes;
+  constexpr int kLoadsA = kFewRows * 8 / kHeadLoaders, kLoadsB = kHeadQueries * 8 / kHeadLoaders, kLoads = kLoadsA + kLoadsB;
+  constexpr int kInFlight = kHeadStages - 1;  // steps
+  static_assert(kLoads * kInFlight <= 63 && kInFlight <= 32, "the counter of outstanding loads has six bits; a tensor has 32 steps at least");
+  __shared__ __attribute__((aligned(1024))) char s_ring[kHeadStages * kStage];
+  const uint32_t ring = lds_offset(s_ring);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int head = blockIdx.x % p.H, pt = blockIdx.x / p.H % p.npt;
+  const long long l = blockIdx.x / p.H / p.npt;
+  const int p0 = pt * kFewRows;
+  const int row_b = p.T * p.H * 256, tok = p.H * 256;
+
+  const int sps = p.T * 2;  // steps of a tensor: two lines per token
+  if (wave >= 2) {
+    // ---- the loading waves.  Rows past the last block fall outside the descriptors and read as zeros.
+    const int lt = tid - kHeadLoaders;
+    const long long poff = l * p.p_lstride_b + (long long)p0 * row_b, qoff = l * p.q_lstride_b;
+    const uint32_t prange = (uint32_t)(min(kFewRows, p.P - p0) * row_b), qrange = (uint32_t)(p.Q * row_b);
+    const uint32_t voff = (uint32_t)(lt >> 3) * (uint32_t)row_b + (uint32_t)(((lt & 7) ^ ((lt >> 3) & 7)) * 16);
+    const uint32_t first_dst = ring + (uint32_t)((wave - 2) * 1024);
+    uint32_t dst = first_dst;
+    auto load = [&](const i32x4& srdA, const i32x4& srdB, int u) __attribute__((always_inline)) {
+      const uint32_t src = (uint32_t)(head * 256 + (u >> 1) * tok + (u & 1) * 128);
+#pragma unroll
+      for (int j = 0; j < kLoadsB; ++j) dma16<false>(srdB, voff, src + (uint32_t)(j * 16 * row_b), dst + (uint32_t)((kLoadsA + j) * kHeadLoaders * 16));
+#pragma unroll
+      for (int j = 0; j < kLoadsA; ++j) dma16<true>(srdA, voff, src + (uint32_t)(j * 16 * row_b), dst + (uint32_t)(j * kHeadLoaders * 16));
+      dst = dst + kStage == first_dst + kHeadStages * kStage ? first_dst : dst + kStage;
+    };
+    // a step's loads go out when every wave has met at the step kInFlight before it: the stage it overwrites has been read
+    auto step = [&](const i32x4& srdA, const i32x4& srdB, int u) __attribute__((always_inline)) {
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kLoads * (kInFlight - 1)) : "memory");
+      load(srdA, srdB, u);
+    };
+    {
+      const i32x4 srdA = make_srd(p.kp + poff, prange), srdB = make_srd(p.kq + qoff, qrange);
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u) load(srdA, srdB, u);
+      for (int u = kInFlight; u < sps; ++u) step(srdA, srdB, u);
+    }
+    {
+      const i32x4 srdA = make_srd(p.vp + poff, prange), srdB = make_srd(p.vq + qoff, qrange);
+      for (int u = 0; u < sps; ++u) step(srdA, srdB, u);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < kInFlight; ++i) __builtin_amdgcn_s_barrier();
+    return;
+  }
+
+  // ---- the multiplying waves, 32 pool blocks each
+  const int col = p0 + wave * 32 + (lane & 31);
+  float rp, fp, rq[16], fq[16];
+  {
+    const long long o = (l * p.P + min(col, p.P - 1)) * p.H + head;
+    norm_factors(p.p_ksq[o], p.p_vsq[o], rp, fp);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int q = min(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), p.Q - 1);
+      const long long oq = (l * p.Q + q) * p.H + head;
+      float av;
+      norm_factors(p.q_ksq[oq], p.q_vsq[oq], rq[r], av);
+      fq[r] = 0.5f * av;
+    }
+  }
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  // fragment reads: row lane % 32 of the queries (rows of the matrix instruction) and of the wave's pool blocks (its columns),
+  // logical chunk 2 * kk + lane / 32
+  uint32_t frag[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk)
+    frag[kk] = (uint32_t)(lane & 31) * kRowBytes + ((((uint32_t)(2 * kk) + (uint32_t)(lane >> 5)) ^ (uint32_t)(lane & 7)) * 16);
+  const char* stage = s_ring;
+  uint4 a[2][4], b[2][4];  // fragments of a step, read while the step before is multiplied
+  auto multiply = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) acc = mfma<BF16>(a[buf][kk], b[buf][kk], acc);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto step = [&](int buf) __attribute__((always_inline)) {
+    // the fragments of the step before are in registers: its stage may be overwritten
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      a[buf][kk] = *reinterpret_cast<const uint4*>(stage + kFewRows * kRowBytes + frag[kk]);
+      b[buf][kk] = *reinterpret_cast<const uint4*>(stage + wave * 32 * kRowBytes + frag[kk]);
+    }
+    stage = stage + kStage == s_ring + kHeadStages * kStage ? s_ring : stage + kStage;
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(buf ^ 1);
+  };
+  auto tensor = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) a[1][kk] = b[1][kk] = make_uint4(0, 0, 0, 0);  // nothing to multiply in the first step
+    for (int u = 0; u < sps; u += 2) {  // an even number
+      step(0);
+      step(1);
+    }
+    multiply(1);
+  };
+  tensor();
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] *= rq[r] * rp;
+  tensor();
+  const int width = p.npt * kFewRows;
+  float* out = p.dpart + (l * p.H + head) * p.Q * (long long)width + col;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int q = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    if (q < p.Q) out[(long long)q * width] = acc[r] * (fq[r] * fp);
+  }
+#endif
+}
+
 constexpr int kSelWaves = 16;
 
 // One workgroup per query (and layer, unless MEAN) adds the shares in a fixed order, forms the cosine or the distance from
 // the cached norms, masks dead blocks and selects; no partial results go through memory.  Bound by round trips: a query's
 // shares of 256 blocks are 64 KB at most.  `pw` waves stand side by side along the pool (256 blocks each), the
 // other factor of the 16 takes turns with the shares (MEAN: with the 2 L distances of a pair, layer by layer, K before V).
-template <bool MEAN>
+// HEADS: the shares are the scores of the S heads, each put on the grid of 1/32767 and the least of them taken, as the
+// selection of the tile kernels' shares does.
+enum class Few { kCosine, kMean, kHeads };
+template <Few MODE>
 __global__ __launch_bounds__(64 * kSelWaves) void few_select_kernel(
     const float* __restrict__ dpart, int S, int L, int Q, int P, int npt, int pw, float scale, const float* __restrict__ q_ksq,
     const float* __restrict__ q_vsq, const float* __restrict__ p_ksq, const float* __restrict__ p_vsq,
     const uint8_t* __restrict__ live, float threshold, int32_t* __restrict__ best_idx, float* __restrict__ best_value,
     int32_t* __restrict__ match_idx, float* __restrict__ second_value) {
-  __shared__ f32x4 s_sum[MEAN ? 1 : 2][kSelWaves][64];
+  constexpr bool MEAN = MODE == Few::kMean, HEADS = MODE == Few::kHeads, TWO = MODE == Few::kCosine;
+  __shared__ f32x4 s_sum[TWO ? 2 : 1][kSelWaves][64];
   __shared__ float s_best[kSelWaves], s_second[kSelWaves];
   __shared__ int s_idx[kSelWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -170,20 +309,32 @@ __global__ __launch_bounds__(64 * kSelWaves) void few_select_kernel(
     const int pp = base + along * 256 + lane * 4;
     f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
     f32x4 nk = {0.f, 0.f, 0.f, 0.f}, nv = {0.f, 0.f, 0.f, 0.f};
+    i32x4 least = {32767, 32767, 32767, 32767};
     unsigned alive = 0;
     if (pp < width) {
       if (turn == 0) {  // what the selection needs is on its way while the shares are added
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int pe = min(pp + e, P - 1);
-          if (!MEAN) {
+          if (TWO) {
             nk[e] = p_ksq[l0 * P + pe];
             nv[e] = p_vsq[l0 * P + pe];
           }
           alive |= (unsigned)(pp + e < P && (!live || live[pe])) << e;
         }
       }
-      if (!MEAN) {
+      if (HEADS) {
+#pragma unroll 4
+        for (int s = turn; s < S; s += turns) {
+          const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src0 + s * share_stride + pp));
+#pragma unroll
+          for (int e = 0; e < 4; e += 2) {
+            const i16x2 g = quantise_pair(v[e], v[e + 1]);
+            least[e] = min(least[e], (int)g[0]);
+            least[e + 1] = min(least[e + 1], (int)g[1]);
+          }
+        }
+      } else if (!MEAN) {
 #pragma unroll 4
         for (int s = turn; s < half; s += turns) {
           sk += __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src0 + s * share_stride + pp));
@@ -208,18 +359,24 @@ __global__ __launch_bounds__(64 * kSelWaves) void few_select_kernel(
       }
     }
     if (turns > 1) {
-      s_sum[0][wave][lane] = sk;
-      if (!MEAN) s_sum[MEAN ? 0 : 1][wave][lane] = sv;
+      s_sum[0][wave][lane] = HEADS ? __builtin_bit_cast(f32x4, least) : sk;
+      if (TWO) s_sum[TWO ? 1 : 0][wave][lane] = sv;
       __syncthreads();
       if (turn == 0)
         for (int t = 1; t < turns; ++t) {
-          sk += s_sum[0][t * pw + along][lane];
-          if (!MEAN) sv += s_sum[MEAN ? 0 : 1][t * pw + along][lane];
+          if (HEADS) {
+            const i32x4 other = __builtin_bit_cast(i32x4, s_sum[0][t * pw + along][lane]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) least[e] = min(least[e], other[e]);
+          } else {
+            sk += s_sum[0][t * pw + along][lane];
+          }
+          if (TWO) sv += s_sum[TWO ? 1 : 0][t * pw + along][lane];
         }
     }
     if (turn == 0 && pp < width) {
       float aq = 0.f, vq = 0.f;
-      if (!MEAN) {
+      if (TWO) {
         const float ksq = q_ksq[l0 * Q + q], vsq = q_vsq[l0 * Q + q];
         aq = ksq > 0.f ? 0.5f * __builtin_amdgcn_rsqf(ksq) : 0.f;  // a zero norm: cosine 0
         vq = vsq > 0.f ? 0.5f * __builtin_amdgcn_rsqf(vsq) : 0.f;
@@ -227,7 +384,9 @@ __global__ __launch_bounds__(64 * kSelWaves) void few_select_kernel(
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         float v;
-        if (MEAN) {
+        if (HEADS) {
+          v = (float)least[e] / 32767.f;
+        } else if (MEAN) {
           v = -(sk[e] * scale);
         } else {
           const float ap = nk[e] > 0.f ? __builtin_amdgcn_rsqf(nk[e]) : 0.f, vp = nv[e] > 0.f ? __builtin_amdgcn_rsqf(nv[e]) : 0.f;
@@ -255,6 +414,13 @@ __global__ __launch_bounds__(64 * kSelWaves) void few_select_kernel(
   best_value[o] = value;
   match_idx[o] = (bidx >= 0 && (MEAN ? value <= threshold : value >= threshold)) ? bidx : -1;
   if (second_value) second_value[o] = MEAN ? -second : second;
+}
+
+// waves of the selection side by side along the pool
+inline int select_waves(int64_t P) {
+  int pw = 1;
+  while (pw < kSelWaves && pw * 256 < P) pw *= 2;
+  return pw;
 }
 
 template <bool BF16, int U>
@@ -331,18 +497,68 @@ rc_status few_search(const FewArgs& a, int S, bool layer_mean, const char* who) 
     if (bf) launch_shares<true, 1>(fp, wgs, st); else launch_shares<false, 1>(fp, wgs, st);
   }
   if (rc_status s = check_launch(who)) return s;
-  int pw = 1;
-  while (pw < kSelWaves && pw * 256 < a.P) pw *= 2;
+  const int pw = select_waves(a.P);
   if (layer_mean) {
     const float scale = 1.0f / ((float)L * 2.0f * (float)T * (float)H);
-    few_select_kernel<true><<<dim3((unsigned)a.Q), 64 * kSelWaves, 0, st>>>(
+    few_select_kernel<Few::kMean><<<dim3((unsigned)a.Q), 64 * kSelWaves, 0, st>>>(
         fp.dpart, S, L, fp.Q, fp.P, fp.npt, pw, scale, a.q_ksq, a.q_vsq, a.p_ksq, a.p_vsq, a.live, a.threshold, a.best_idx,
         a.best_value, a.match_idx, a.second_value);
   } else {
-    few_select_kernel<false><<<dim3((unsigned)a.Q, (unsigned)L), 64 * kSelWaves, 0, st>>>(
+    few_select_kernel<Few::kCosine><<<dim3((unsigned)a.Q, (unsigned)L), 64 * kSelWaves, 0, st>>>(
         fp.dpart, S, L, fp.Q, fp.P, fp.npt, pw, 1.0f, a.q_ksq, a.q_vsq, a.p_ksq, a.p_vsq, a.live, a.threshold, a.best_idx,
         a.best_value, a.match_idx, a.second_value);
   }
+  return check_launch(who);
+}
+
+// Which per-head calls come here.  A share per head and tile of 64 blocks, not of 256, spreads over the chip where the tile
+// kernels' shares do not; more queries are loaded by more workgroups, and a round of the tile kernels that is nearly full
+// leaves nothing to gain.  Measured over 130 shapes (us per call, tile kernels -> these; the scores' bits are the same):
+//   up to 3 queries    2 x 361 blocks x 3 71 -> 22, 47 x 293 x 2 217 -> 149, 62 x 1066 x 2 (5.4 GB) 989 -> 799
+//   up to 8 queries    55 x 258 x 5 (128-KB tensors) 917 -> 606, 4 x 3583 x 7 246 -> 188, 50 x 2269 x 4 (7.4 GB) 1189 -> 1165
+//   up to 16 queries   20 x 260 x 12 244 -> 136, 12 x 1851 x 8 335 -> 289, 15 x 1288 x 9 (2.5 GB) 509 -> 419, 8 x 8093 x 15 (4.2 GB) 630 -> 736
+//   up to 32 queries   1 x 577 x 30 (80 workgroups) 71 -> 26, 14 x 208 x 23 (560) 75 -> 66, 30 x 700 x 30 (2640) 271 -> 286
+//   209 to 256 shares of the tile kernels: 62 x 130 x 4, 4 heads 107 -> 115, 62 x 70 x 16 51 -> 58
+bool few_heads(int64_t L, int64_t P, int64_t Q, int T, int H) {
+  if (L < 1 || L > 65535 || P < 1 || Q < 1 || Q > kHeadQueries) return false;
+  const double mb = (double)L * (double)P * (double)(T * H) * 512e-6;
+  if (mb > 6000.0 || few_bytes(H, L, P, Q) > ((size_t)512 << 20)) return false;
+  const int64_t tile_shares = L * ((P + 255) / 256) * H;
+  if (tile_shares > 208 && tile_shares <= 256) return false;
+  if (Q <= 8) return Q <= 3 || mb <= 3000.0;
+  return Q <= 16 ? mb <= 2500.0 : L * ((P + kFewRows - 1) / kFewRows) * H <= 512;
+}
+
+rc_status few_search_heads(const FewArgs& a, const char* who) {
+  hipStream_t st = static_cast<hipStream_t>(a.hip_stream);
+  const int L = a.qdesc->n_layers;
+  HeadParams hp;
+  hp.kq = static_cast<const char*>(a.kq);
+  hp.vq = static_cast<const char*>(a.vq);
+  hp.kp = static_cast<const char*>(a.kp);
+  hp.vp = static_cast<const char*>(a.vp);
+  hp.q_ksq = a.q_ksq;
+  hp.q_vsq = a.q_vsq;
+  hp.p_ksq = a.p_ksq;
+  hp.p_vsq = a.p_vsq;
+  hp.dpart = static_cast<float*>(a.workspace);
+  hp.q_lstride_b = a.qdesc->layer_stride * 2;
+  hp.p_lstride_b = a.pdesc->layer_stride * 2;
+  hp.Q = (int)a.Q;
+  hp.P = (int)a.P;
+  hp.T = a.qdesc->block_tokens;
+  hp.H = a.qdesc->n_kv_heads;
+  hp.npt = (int)((a.P + kFewRows - 1) / kFewRows);
+  const unsigned wgs = (unsigned)((int64_t)L * hp.npt * hp.H);
+  const bool bf = a.qdesc->dtype == RC_BF16;
+  if (bf)
+    head_shares_kernel<true><<<wgs, kHeadThreads, 0, st>>>(hp);
+  else
+    head_shares_kernel<false><<<wgs, kHeadThreads, 0, st>>>(hp);
+  if (rc_status s = check_launch(who)) return s;
+  few_select_kernel<Few::kHeads><<<dim3((unsigned)a.Q, (unsigned)L), 64 * kSelWaves, 0, st>>>(
+      hp.dpart, hp.H, L, hp.Q, hp.P, hp.npt, select_waves(a.P), 1.0f, nullptr, nullptr, nullptr, nullptr, a.live, a.threshold,
+      a.best_idx, a.best_value, a.match_idx, a.second_value);
   return check_launch(who);
 }
 

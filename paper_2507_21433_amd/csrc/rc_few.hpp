@@ -35,4 +35,8 @@ struct FewArgs {
 // layer_mean: the layer-mean distance and one decision per query, else the cosine per layer
 rc_status few_search(const FewArgs& a, int S, bool layer_mean, const char* who);
 
+// The per-head score (one share per head): whether a call comes here, and the call.
+bool few_heads(int64_t L, int64_t P, int64_t Q, int T, int H);
+rc_status few_search_heads(const FewArgs& a, const char* who);
+
 }  // namespace rc

@@ -18,7 +18,7 @@ DEV = "cuda:0"
 
 
 def takes_few(call):
-    """Whether call() launches few_shares_kernel; None where no kernel trace is to be had.  Three calls in a trace: the
+    """Whether call() launches few_shares_kernel or head_shares_kernel; None where no kernel trace is to be had.  Three calls in a trace: the
     profiler can lose single events."""
     from torch.profiler import ProfilerActivity, profile
     with warnings.catch_warnings():
@@ -28,7 +28,7 @@ def takes_few(call):
                 call()
             torch.cuda.synchronize()
         names = [e.name for e in p.events()]
-    few, tiles = (any(k in n for n in names) for k in ("few_shares_kernel", "rc::match_"))
+    few, tiles = (any(k in n for n in names for k in ks) for ks in (("few_shares_kernel", "head_shares_kernel"), ("rc::match_",)))
     return None if few == tiles else few
 
 
@@ -85,3 +85,37 @@ def test_small_workspaces(oracle, L, P, Q, T, H):
         g, _ = run_gpu_match(pr, w, pr["live"], workspace=mem[:nbytes])
         assert (mem[nbytes:] == 0xA5).all(), "written past the workspace"
         parity.check_match(g, o, w.tau, parity.score_lookup(o["scores"], g["best_idx"]))
+
+
+# per head: one block, ends on and beside a tile of 64 and a wave of 32; 1, 8 / 9, 16 / 17 and 32 queries; one head, odd head counts,
+# 32 tokens; bits as the tile kernels have them, the lowest index on ties
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("L,P,Q,T,H", [(1, 1, 1, 16, 1), (2, 63, 8, 16, 3), (1, 64, 9, 16, 5), (3, 65, 17, 32, 2), (1, 257, 32, 16, 8), (2, 97, 16, 16, 16),
+                                       (5, 300, 5, 32, 10), (1, 4097, 2, 16, 2)])
+def test_few_queries_per_head(oracle, L, P, Q, T, H, dtype):
+    run_shape(oracle, dict(L=L, P=P, Q=Q, T=T, H=H, mode=1, dtype=dtype, planted_frac=0.3 if P > Q else 0.0, seed=9100 + P), f"heads{L}.{P}x{Q}", P)
+    w = synth.scaled(synth.WORKLOADS[5], name="heads", L=L, P=P, Q=Q, T=T, H=H, dtype=dtype, planted_frac=0.3 if P > Q else 0.0, R=1, E=P + Q, seed=9200 + P)
+    pr = synth.make_problem(w, DEV)
+    if P > 70:
+        for n in ("k", "v"):
+            pr[n + "p"][:, 70] = pr[n + "p"][:, 2]
+            pr[n + "q"][:, 0] = pr[n + "p"][:, 2]
+    assert takes_few(lambda: run_gpu_match(pr, w, pr["live"])) in (None, True)
+    g, _ = run_gpu_match(pr, w, pr["live"])
+    mem = torch.full((paths.size(rc.lib(), 1, L, T, H, P, Q) + (1 << 20),), 0xA5, dtype=torch.uint8, device=DEV)
+    again, _ = run_gpu_match(pr, w, pr["live"], workspace=mem[:-(1 << 20)])
+    assert (mem[-(1 << 20):] == 0xA5).all(), "written past the workspace"
+    # the same layers inside a call with more queries than these kernels take: the tile kernels' bits
+    more = dict(pr, **{n: torch.cat([pr[n], pr[n][:, :1].expand(-1, 33, -1, -1, -1)], 1).contiguous() for n in ("kq", "vq")})
+    tiles, _ = run_gpu_match(more, synth.scaled(w, Q=Q + 33), pr["live"])
+    for k in g:
+        assert np.array_equal(g[k], again[k]) and np.array_equal(g[k], tiles[k][:, :Q]), k
+
+
+# 3, 8, 16 and 32 queries; the lines at 6000, 3000 and 2500 MB are too large for a test; 512 workgroups, 208 and 256 shares of the tile kernels
+@pytest.mark.parametrize("L,P,Q,T,H,few", [(8, 200, 32, 16, 16, True), (9, 257, 32, 16, 16, False), (9, 257, 16, 16, 16, True), (2, 100, 33, 16, 4, False),
+                                           (26, 70, 4, 16, 8, True), (27, 70, 4, 16, 8, False), (32, 70, 4, 16, 8, False), (33, 70, 4, 16, 8, True)])
+def test_lines_per_head(L, P, Q, T, H, few):
+    w = synth.scaled(synth.WORKLOADS[5], name="line", L=L, P=P, Q=Q, T=T, H=H, planted_frac=0.3, R=1, E=P + Q, seed=9300)
+    pr = synth.make_problem(w, DEV)
+    assert takes_few(lambda: run_gpu_match(pr, w, None)) in (None, few)
