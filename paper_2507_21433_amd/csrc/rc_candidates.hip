@@ -321,9 +321,11 @@ __global__ __launch_bounds__(kCandThreads) void candidate_distances_kernel(const
 // together and advance at the same rate, so the lists of a layer read the same 512-byte window of their blocks at about the
 // same time, and a block that several lists name comes from the L2 (neighbouring lists are dealt to one XCD) or the
 // memory-side cache when the second of them asks for it.  A workgroup per list (above) keeps the lists on a chip apart by up
-// to a whole block each.  A wave is a workgroup of its own, so that few lists spread over all compute units.  What
-// bounds it: the stream of blocks, less what lists share (32 x 4096 x 256 lists of 16, 32-KB tensors: 1219 us = 7.1 TB/s of
-// listed blocks, 1297 in workgroups; 36 x 150 x 65 x 17: 250 -> 84).
+// to a whole block each.  The waves of a compute unit are served oldest first and drift apart; where there are enough of them
+// eight are a workgroup that meets every two windows, elsewhere a wave is a workgroup of its own, so that few lists spread over
+// all compute units (wide_plan).  What bounds it: the stream of blocks, less what lists share (64 x 4096 x 256 lists of 16,
+// 32-KB tensors: 2120 us = 8.6 TB/s of listed blocks and queries, 7.0 of them from memory; 2431 with waves alone, 2591 in
+// workgroups of a list; 36 x 150 x 65 x 17: 250 -> 84).
 struct WideParams {
   const char *kq, *vq, *kp, *vp;
   const float *q_ksq, *q_vsq, *p_ksq, *p_vsq;
@@ -338,20 +340,25 @@ struct WideParams {
   int L, G;              // distances: layers, layers of a group
   int per, parts;        // candidates of a wave, waves per list
   int block_bytes;
-  long long items;       // waves with work
-  long long per_xcd;     // waves of an XCD's run; 0: the lists are dealt out one after the other
+  int waves;             // of a workgroup, at most kWideWaves
+  long long wgs_z;       // workgroups of a layer, or of a group of layers
+  long long items;       // workgroups
+  long long per_xcd;     // workgroups of an XCD's run; 0: they are dealt out one after the other
   float tau;
 };
 constexpr int kWindow = 512;   // bytes of a block per step
+constexpr int kWideWaves = 8;  // of a workgroup, at most
 
 template <bool BF16, int SLOTS, bool DIST>
-__global__ __launch_bounds__(64, SLOTS == 8 ? 3 : 4) void candidates_wide_kernel(const WideParams p) {
-  const int lane = threadIdx.x, half = lane >> 5;
+__global__ __launch_bounds__(64 * kWideWaves, SLOTS == 8 ? 3 : 4) void candidates_wide_kernel(const WideParams p) {
+  const int lane = threadIdx.x & 63, half = lane >> 5;
   const long long item = p.per_xcd ? (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3) : blockIdx.x;
   if (item >= p.items) return;
-  const long long list = item / p.parts;  // (layer or group of layers, query)
-  const int c0 = (int)(item % p.parts) * p.per, n = min(p.per, p.C - c0);
-  const long long z = list / p.Q, q = list % p.Q;
+  const long long z = item / p.wgs_z;  // layer or group of layers
+  const long long w = item % p.wgs_z * p.waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool idle = w >= (long long)p.Q * p.parts;  // keeps the others company at their barriers
+  const long long q = idle ? 0 : w / p.parts, list = z * p.Q + q;
+  const int c0 = idle ? 0 : (int)(w % p.parts) * p.per, n = idle ? 0 : min(p.per, p.C - c0);
   const long long l0 = DIST ? z * p.G : z;
   const int nl = DIST ? (int)min((long long)p.G, p.L - l0) : 1;
   const long long slot0 = list * p.C + c0, cand0 = (DIST ? q : list) * p.C + c0;
@@ -374,7 +381,7 @@ __global__ __launch_bounds__(64, SLOTS == 8 ? 3 : 4) void candidates_wide_kernel
   auto source = [&](int li, bool v) __attribute__((always_inline)) {
     const long long l = l0 + li;
     Source r;
-    r.q = __builtin_amdgcn_make_buffer_rsrc((void*)((v ? p.vq : p.kq) + l * p.q_lstride_b + q * p.block_bytes), 0, p.block_bytes, 0x00020000);
+    r.q = __builtin_amdgcn_make_buffer_rsrc((void*)((v ? p.vq : p.kq) + l * p.q_lstride_b + q * p.block_bytes), 0, idle ? 0 : p.block_bytes, 0x00020000);
     r.p = __builtin_amdgcn_make_buffer_rsrc((void*)((v ? p.vp : p.kp) + l * p.p_lstride_b), 0, pool_bytes, 0x00020000);
     return r;
   };
@@ -404,6 +411,7 @@ __global__ __launch_bounds__(64, SLOTS == 8 ? 3 : 4) void candidates_wide_kernel
       for (int s = 0; s < SLOTS; ++s) run[s] = 0.f;
 #pragma unroll 1
       for (int t = t0; t < t0 + kFold; t += 2) {
+        __builtin_amdgcn_s_barrier();
         load(1, src, t + 1);
         __builtin_amdgcn_sched_barrier(0);
         add(0);
@@ -435,6 +443,7 @@ __global__ __launch_bounds__(64, SLOTS == 8 ? 3 : 4) void candidates_wide_kernel
     sv = walk(source(li, true), source(min(li + 1, nl - 1), false), li + 1 < nl);
     if (DIST) total += __builtin_amdgcn_sqrtf(sk) + __builtin_amdgcn_sqrtf(sv);
   }
+  if (idle) return;
   if (DIST) {
     if (valid) p.out[slot0 + mine] = total;  // the selection kernel derives validity itself
     return;
@@ -605,25 +614,39 @@ template <bool BF16, bool DIST>
 void launch_wide(const WideParams& wp, hipStream_t st) {
   const unsigned grid = (unsigned)(wp.per_xcd ? wp.per_xcd * 8 : wp.items);
   if (wp.per <= 4)
-    candidates_wide_kernel<BF16, 2, DIST><<<grid, 64, 0, st>>>(wp);
+    candidates_wide_kernel<BF16, 2, DIST><<<grid, 64 * wp.waves, 0, st>>>(wp);
   else if (wp.per <= 8)
-    candidates_wide_kernel<BF16, 4, DIST><<<grid, 64, 0, st>>>(wp);
+    candidates_wide_kernel<BF16, 4, DIST><<<grid, 64 * wp.waves, 0, st>>>(wp);
   else if (wp.per <= 12)
-    candidates_wide_kernel<BF16, 6, DIST><<<grid, 64, 0, st>>>(wp);
+    candidates_wide_kernel<BF16, 6, DIST><<<grid, 64 * wp.waves, 0, st>>>(wp);
   else
-    candidates_wide_kernel<BF16, 8, DIST><<<grid, 64, 0, st>>>(wp);
+    candidates_wide_kernel<BF16, 8, DIST><<<grid, 64 * wp.waves, 0, st>>>(wp);
 }
 
-// lists: (layers or groups of layers) x Q.  Neighbouring lists go to one XCD while the lists of a layer are about as many as
-// an XCD works on at once; with more of them its lists would be a small part of the layer's, with few blocks in common, and
-// all XCDs do better on the same part of the layer (4 x 16384 x 1024 x 20: 877 us by XCD, 785 dealt out; 36 x 150 x 65 x 17: 85
-// and 148).
-inline void wide_plan(WideParams& wp, int64_t lists) {
+// z: layers, or groups of layers; alike: all groups have as many layers.
+// Eight waves to a workgroup, kept together by a barrier per two windows, or one: eight where they fill the rounds of 256
+// workgroups (0.87 of them) and there are 3000 waves; below that compute units idle beside others with a workgroup more.
+// Neighbouring lists go to one XCD while the waves of a layer are about as many as an XCD works on at once, and up to 1700
+// of them (with eight to a workgroup) where a block is listed more than twice in a layer; with fewer blocks in common, all
+// XCDs do better on the same part of the layer.
+// One wave -> eight, us (layers x pool x queries x C): 64 x 4096 x 256 x 16 2431 -> 2120 (17.2 -> 14.7 GB from memory; the
+// blocks and queries once are 11.9)   44 x 257 x 110 x 19, blocks of 128 KB 1106 -> 907   distances 58 x 988 x 125 x 22 2789 -> 2399
+//   rounds filled to 0.78 to 0.85: 48 x 700 x 100 x 16 508 -> 590   64 x 500 x 130 x 6 420 -> 459;  few waves: 33 x 103 x 28 x 21 94 -> 115
+// Dealt out -> by XCD, both of eight: 37 x 788 x 304 x 20 737 -> 590   29 x 1892 x 579 x 23 3040 -> 2621   4 x 1730 x 235 x 23 96 -> 72
+//   17 x 4697 x 226 x 24 (a block listed 1.2 times) 853 -> 864   11 x 6837 x 609 x 17 (1.5) 2171 -> 2354   distances, 2000 waves of a
+//   group, 16 x 2000 x 1000 x 20 2003 -> 2261, groups not alike, 37 x 1985 x 543 x 6 1524 -> 1911
+inline void wide_plan(WideParams& wp, int64_t z, bool alike) {
   const WideLists w = wide_lists(wp.C);
   wp.parts = w.parts;
   wp.per = w.per;
-  wp.items = (long long)lists * w.parts;
-  wp.per_xcd = (int64_t)wp.Q * w.parts > 448 ? 0 : (wp.items + 7) / 8;
+  const int64_t waves = (int64_t)wp.Q * w.parts, wgs = z * ((waves + kWideWaves - 1) / kWideWaves);
+  const int64_t rounds = (wgs + 255) / 256;  // of the 256 compute units of an MI355X
+  const bool shared = waves > 448 && waves <= 1700 && alike && (int64_t)wp.Q * wp.C > 2 * (int64_t)wp.P && z * waves >= 1800;
+  const bool full = z * waves >= 3000 && 100 * z * waves >= 87 * rounds * 256 * kWideWaves;
+  wp.waves = shared || full ? kWideWaves : 1;
+  wp.wgs_z = (waves + wp.waves - 1) / wp.waves;
+  wp.items = z * wp.wgs_z;
+  wp.per_xcd = waves <= 448 || shared ? (wp.items + 7) / 8 : 0;
 }
 
 }  // namespace
@@ -684,7 +707,7 @@ extern "C" rc_status rc_score_candidates(const rc_kv_desc* qdesc, const rc_kv_de
     wp.L = L;
     wp.G = 1;
     wp.block_bytes = block_bytes;
-    wide_plan(wp, (int64_t)L * Q);
+    wide_plan(wp, L, true);
     wp.tau = tau;
     if (qdesc->dtype == RC_BF16)
       launch_wide<true, false>(wp, st);
@@ -787,7 +810,7 @@ extern "C" rc_status rc_candidate_distances(const rc_kv_desc* qdesc, const rc_kv
     wp.L = L;
     wp.G = G;
     wp.block_bytes = block_bytes;
-    wide_plan(wp, (int64_t)groups * Q);
+    wide_plan(wp, groups, L % G == 0);
     if (qdesc->dtype == RC_BF16)
       launch_wide<true, true>(wp, st);
     else

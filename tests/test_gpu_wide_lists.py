@@ -59,3 +59,15 @@ def test_wide_ties_go_to_the_lowest_index():
     assert np.array_equal(s["best_idx"][0], want) and np.array_equal(s["match_idx"][0], want)
     g = rc.rc_candidate_distances(pr["kq"], pr["vq"], pr["kp"], pr["vp"], None, torch.as_tensor(cand, device="cuda:0"), 0.5)
     assert np.array_equal(g["best_idx"].cpu().numpy(), want) and (g["best_dist"] == 0).all()
+
+
+# Eight waves to a workgroup: waves of a layer in whole workgroups and with six idle ones in the last; one layer and two in a
+# group of the distances, a last group of one layer; by XCD and dealt out; 1800 waves and four fewer, 1700 of a layer and 20 more
+EIGHTS = [(16, 64, 256, 16, 1, 3), (30, 64, 250, 16, 1, 4), (11, 50, 680, 16, 1, 3), (4, 40, 449, 16, 2, 5), (4, 40, 450, 16, 2, 5),
+          (2, 60, 850, 16, 1, 17), (2, 60, 860, 16, 1, 17), (8, 700, 500, 16, 1, 2)]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("L,P,Q,T,H,C", EIGHTS)
+def test_wide_lists_in_workgroups(oracle, L, P, Q, T, H, C, dtype):
+    test_wide_lists(oracle, L, P, Q, T, H, C, dtype)
