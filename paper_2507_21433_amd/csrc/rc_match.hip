@@ -1258,27 +1258,35 @@ constexpr TileShape kLowTile = {192, 320};
 //   block     Q = 160 2802 / 2487 / 3427   256 3074 / 4038 / 3903   320 4950 / 4363 / 3987   384 5072 / 4490 / 7117
 //             Q = 512 5475 / 6188 / 7469   640 7470 / 7835 / 7124   960 10230 / 10388 / 10239
 //   per head  Q = 160 3239 / 2647 / 2900   300 5281 / 4007 / 3519   384 4914 / 4098 / 4998   640 7213 / 7005 / 5026
-inline TileShape tile_for(int mode, int64_t L, int64_t P, int64_t Q) {
-  if (Q <= kNarrowTile.bq) return kNarrowTile;
-  if (Q <= kMidTile.bq) return kMidTile;
-  constexpr TileShape shapes[3] = {kBlockTile, kWideTile, kLowTile};
-  constexpr double step_us[2][3][3] = {{{2.0, 1.75, 1.65}, {1.67, 1.42, 1.31}, {1.69, 1.6, 1.57}},
-                                       {{2.0, 2.0, 1.9}, {1.65, 1.5, 1.45}, {2.0, 1.7, 1.65}}};
+constexpr TileShape kShapes[3] = {kBlockTile, kWideTile, kLowTile};
+constexpr double kStepUs[2][3][3] = {{{2.0, 1.75, 1.65}, {1.67, 1.42, 1.31}, {1.69, 1.6, 1.57}},
+                                     {{2.0, 2.0, 1.9}, {1.65, 1.5, 1.45}, {2.0, 1.7, 1.65}}};
+// rounds of one workgroup per compute unit (an MI355X has 256), in full ones
+inline double rounds_of(double wgs) {
+  const double part = wgs / 256.0, full = (double)(int64_t)part;
+  return part > full ? full + 0.55 + 0.45 * (part - full) : full;
+}
+struct TileChoice {
+  TileShape ts;
+  double step_us;  // estimate of the launch, in us per pipeline step of a tile (more than 128 queries)
+};
+inline TileChoice tile_choice(int mode, int64_t L, int64_t P, int64_t Q) {
+  if (Q <= kNarrowTile.bq) return {kNarrowTile, 0.0};
+  if (Q <= kMidTile.bq) return {kMidTile, 0.0};
   int best = 0;
   double best_cost = 0.0;
   for (int i = 0; i < 3; ++i) {
-    const int64_t nqt = (Q + shapes[i].bq - 1) / shapes[i].bq;
-    const double part = (double)(L * ((P + shapes[i].bp - 1) / shapes[i].bp)) * (double)nqt / 256.0;  // an MI355X has 256 compute units
-    double rounds = (double)(int64_t)part;
-    if (part > rounds) rounds += 0.55 + 0.45 * (part - rounds);
-    const double cost = rounds * step_us[mode == RC_SCORE_PER_HEAD_ALL][i][nqt < 3 ? nqt - 1 : 2];
+    const int64_t nqt = (Q + kShapes[i].bq - 1) / kShapes[i].bq;
+    const double tiles = (double)(L * ((P + kShapes[i].bp - 1) / kShapes[i].bp)) * (double)nqt;
+    const double cost = rounds_of(tiles) * kStepUs[mode == RC_SCORE_PER_HEAD_ALL][i][nqt < 3 ? nqt - 1 : 2];
     if (i == 0 || cost < (best == 0 ? 0.96 : 1.0) * best_cost) {
       best = i;
       best_cost = cost;
     }
   }
-  return shapes[best];
+  return {kShapes[best], best_cost};
 }
+inline TileShape tile_for(int mode, int64_t L, int64_t P, int64_t Q) { return tile_choice(mode, L, P, Q).ts; }
 // Columns of a tile whose reduction is shared by several workgroups: 192 where 256 pad badly.  256 -> 192 columns, us per
 // launch: block, 2 layers x 4096, Q = 300 274 -> 231; per head, 3 x 11147, Q = 133 769 -> 707, 42 x 844, Q = 192 430 -> 354,
 // 4 x 4096, Q = 384 579 -> 491.
@@ -1316,7 +1324,7 @@ inline size_t layer_mean_part_offset(int groups, int64_t npt, int64_t nqt, int b
 // constants come from measurements of 1 to 144 tiles of the 256 x 256 shape (within 10 % from 64
 // tiles up; a single layer of 16 tiles takes 116 us against 112 estimated).  A share has at least
 // 8 steps; the shares of all tiles take at most 512 MB; problems of more than one round are left
-// alone.  Block mode only.
+// alone, but for their last layers (tail_layers).  Block mode only.
 // At most 128 queries (64 and 128 columns, bound by the pool stream): a share is cheap to store, so the
 // split also evens out the last round of launches of several rounds.  Estimated in us: a step of a full round
 // takes 1.3 (64 columns) or 1.5 us; a round of which a part r of the compute units has work takes 0.55 + 0.45 r
@@ -1453,6 +1461,47 @@ inline MatchPlan match_plan(int mode, int64_t L, int64_t P, int64_t Q, int T, in
   return p;
 }
 
+// A launch of whole tiles whose last round leaves most compute units idle gives its last layers to a launch of shares, which
+// runs first: the number of layers with the lowest estimate in us, 0 = none.  Whole tiles by tile_choice; shares by rounds of
+// them, with 6 steps to fill the pipeline and store each, 0.06 us for the pass that adds one, 20 us for the four further
+// launches and the drain between.  Used where that is 4 % below whole tiles alone, 2 % per head (there whole tiles take 10 %
+// longer than estimated, shares as long).  96 shapes of 64-KB blocks and larger (smaller ones, whose round is short beside what
+// the launches cost, were not measured), whole tiles -> these, us:
+//   block     40 x 6209 x 300, 10 heads 6288 -> 5961 (2 layers)   3 x 15320 x 412, 16 heads 2865 -> 2448 (1)   14 x 4673 x 382, 10 heads
+//             2431 -> 2091 (1)   45 x 6258 x 187 3919 -> 3714 (5)   8 x 8530 x 139, 4 heads 682 -> 558 (1)   the least: 38 x 2867 x 338,
+//             blocks of 32 tokens 5496 -> 5481 (6, margin of 3 %)   left alone: 7 x 4960 x 883, 16 heads 3630, 3728 with a tail of 1
+//   per head  11 x 6340 x 216, 32 tokens 3692 -> 2400 (1)   39 x 2005 x 195 2028 -> 1528 (7)   5 x 6409 x 415, 10 heads 2040 -> 1596 (1)
+//             left alone: 38 x 2048 x 890, 10 heads 6234, 6431 with a tail of 1
+// Layers are searched in one way each, so identical pool blocks of a layer still see the same instructions.
+inline int tail_layers(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
+  if (Q <= kMidTile.bq || P <= 0 || L < 2 || T * H < 64) return 0;
+  const double steps = 4.0 * T * H;
+  const int64_t tiles = L * ((P + 255) / 256) * ((Q + 255) / 256);
+  if (tiles <= kSplitComputeUnits || tiles >= kDynamicRounds * kSplitComputeUnits) return 0;
+  const int bq = share_columns(Q), shape = bq == kWideTile.bq ? 1 : 0;
+  const int64_t nqt = (Q + bq - 1) / bq, per_layer = (P + 255) / 256 * nqt;
+  const double step_us = kStepUs[mode == RC_SCORE_PER_HEAD_ALL][shape][nqt < 3 ? nqt - 1 : 2];
+  const double margin = mode == RC_SCORE_PER_HEAD_ALL ? 0.98 : 0.96;
+  int best = 0;
+  double best_us = margin * steps * tile_choice(mode, L, P, Q).step_us;
+  for (int n = 1; n < L && n * per_layer <= kSplitComputeUnits; ++n) {
+    const int S = wide_split_count(mode, n, P, Q, T, H);
+    if (S < 2) continue;
+    const double wgs = (double)(n * per_layer * S);
+    const double us = steps * tile_choice(mode, L - n, P, Q).step_us + rounds_of(wgs) * (steps / S + 6.0) * step_us + 0.06 * wgs + 20.0;
+    if (us < best_us) {
+      best = n;
+      best_us = us;
+    }
+  }
+  return best;
+}
+// bytes for both launches, which take the workspace in turn
+inline size_t tail_bytes(int n, int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
+  const MatchPlan head = {1, tile_for(mode, L - n, P, Q)}, tail = {wide_split_count(mode, n, P, Q, T, H), kBlockTile};
+  return std::max(plan_bytes(head, L - n, P, Q), plan_bytes(tail, n, P, Q));
+}
+
 // Shares of a search by the kernels for small problems with few queries, 0 = by tiles.
 inline int few_plan_shares(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
   return mode == RC_SCORE_BLOCK ? few_shares(false, L, P, Q, T, H) : few_heads(L, P, Q, T, H) ? H : 0;
@@ -1560,8 +1609,153 @@ extern "C" size_t rc_match_workspace_size(const rc_kv_desc* qdesc, int32_t mode,
   if (mode != RC_SCORE_BLOCK && mode != RC_SCORE_PER_HEAD_ALL) return 0;
   const int L = qdesc->n_layers, T = qdesc->block_tokens, H = qdesc->n_kv_heads;
   const size_t fast = plan_bytes(match_plan(mode, L, P, Q, T, H, SIZE_MAX), L, P, Q), floor = match_floor_bytes(mode, L, P, Q, T, H);
-  return std::max({fast, floor, few_bytes(few_plan_shares(mode, L, P, Q, T, H), L, P, Q)});
+  const int tail = tail_layers(mode, L, P, Q, T, H);
+  return std::max({fast, floor, few_bytes(few_plan_shares(mode, L, P, Q, T, H), L, P, Q), tail > 0 ? tail_bytes(tail, mode, L, P, Q, T, H) : 0});
 }
+
+namespace rc {
+namespace {
+// What a search in tiles is called with, on all layers or on some of them.
+struct TileSearch {
+  const rc_kv_desc *qdesc, *pdesc;
+  int mode;
+  const char *kq, *vq, *kp, *vp;
+  const float *q_ksq, *q_vsq, *p_ksq, *p_vsq;
+  const uint8_t* live;
+  float tau;
+  int32_t* best_idx;
+  float* best_score;
+  int32_t* match_idx;
+  float* second_score;
+  int64_t L, Q, P;
+  void* workspace;
+  hipStream_t st;
+};
+inline TileSearch some_layers(TileSearch a, int64_t l0, int64_t n) {
+  const int64_t norms = a.mode == RC_SCORE_PER_HEAD_ALL ? a.qdesc->n_kv_heads : 1;
+  a.kq += l0 * a.qdesc->layer_stride * 2;
+  a.vq += l0 * a.qdesc->layer_stride * 2;
+  a.kp += l0 * a.pdesc->layer_stride * 2;
+  a.vp += l0 * a.pdesc->layer_stride * 2;
+  a.q_ksq += l0 * a.Q * norms;
+  a.q_vsq += l0 * a.Q * norms;
+  a.p_ksq += l0 * a.P * norms;
+  a.p_vsq += l0 * a.P * norms;
+  if (a.live) a.live += l0 * a.P;
+  a.best_idx += l0 * a.Q;
+  a.best_score += l0 * a.Q;
+  a.match_idx += l0 * a.Q;
+  if (a.second_score) a.second_score += l0 * a.Q;
+  a.L = n;
+  return a;
+}
+rc_status search_tiles(const TileSearch& a, const MatchPlan& plan) {
+  const int64_t L = a.L, P = a.P, Q = a.Q;
+  const rc_kv_desc *qdesc = a.qdesc, *pdesc = a.pdesc;
+  const int mode = a.mode;
+  void* workspace = a.workspace;
+  hipStream_t st = a.st;
+  const int S = plan.S;
+  const TileShape ts = plan.ts;
+  const int64_t npt = (P + ts.bp - 1) / ts.bp, nqt = (Q + ts.bq - 1) / ts.bq;
+  const int64_t total = (int64_t)L * npt * nqt;
+  const long long LQ = (long long)L * Q;
+
+  if (S > 1) {
+    // few tiles: shares of every tile's reduction, then sum + selection, then the merge over pool chunks
+    const SplitLayout sl = split_layout(S, L, P, Q);
+    MatchParams mp;
+    mp.kq = a.kq;
+    mp.vq = a.vq;
+    mp.kp = a.kp;
+    mp.vp = a.vp;
+    mp.q_ksq = a.q_ksq;
+    mp.q_vsq = a.q_vsq;
+    mp.p_ksq = a.p_ksq;
+    mp.p_vsq = a.p_vsq;
+    mp.live = a.live;
+    mp.part = nullptr;
+    mp.dpart = static_cast<float*>(workspace);
+    mp.q_lstride_b = qdesc->layer_stride * 2;
+    mp.p_lstride_b = pdesc->layer_stride * 2;
+    mp.L = (int)L;
+    mp.Q = (int)Q;
+    mp.P = (int)P;
+    mp.T = qdesc->block_tokens;
+    mp.H = qdesc->n_kv_heads;
+    mp.npt = (int)sl.npt;
+    mp.nqt = (int)sl.nqt;
+    mp.total = (int)(L * sl.npt * sl.nqt * S);
+    mp.chunk = kChunk;
+    mp.raw = 0;
+    mp.G = 1;
+    mp.S = S;
+    mp.stagger_wgs = 0;
+    mp.stagger_unit = 0;
+    mp.vgrid = (int)virtual_grid(mp.total);
+    const unsigned grid = launch_grid((unsigned)mp.vgrid);
+    mp.ctr = nullptr;
+    mp.rounds = 0;
+    mp.steal_min = 0;
+    mp.dyn_from = 0;
+    const bool heads = mode == RC_SCORE_PER_HEAD_ALL;
+    if (qdesc->dtype == RC_BF16)
+      launch_shares<true>(heads, sl.bq, mp, grid, st);
+    else
+      launch_shares<false>(heads, sl.bq, mp, grid, st);
+    if (rc_status s = check_launch("rc_match_blocks(tile shares)")) return s;
+    Part* part = reinterpret_cast<Part*>(static_cast<char*>(workspace) + sl.part_offset);
+    const dim3 sgrid((unsigned)((Q + 63) / 64), (unsigned)sl.nchunks, (unsigned)L);
+    tile_sums_select_kernel<<<sgrid, 64 * kSelRowGroups, 0, st>>>(mp.dpart, S, (int)P, (int)Q, (int)sl.npt, (int)sl.nqt, sl.bq / 64, sl.sel_rows,
+                                                   -1.0f, heads ? 1 : 0, a.live, part);
+    if (rc_status s = check_launch("rc_match_blocks(select)")) return s;
+    return merge_parts<false>(part, sl.nchunks, LQ, (int)Q, a.tau, a.best_idx, a.best_score, a.match_idx, a.second_score, st,
+                              "rc_match_blocks(finalize)");
+  }
+
+  if (P > 0) {
+    MatchParams mp;
+    mp.kq = a.kq;
+    mp.vq = a.vq;
+    mp.kp = a.kp;
+    mp.vp = a.vp;
+    mp.q_ksq = a.q_ksq;
+    mp.q_vsq = a.q_vsq;
+    mp.p_ksq = a.p_ksq;
+    mp.p_vsq = a.p_vsq;
+    mp.live = a.live;
+    mp.part = static_cast<Part*>(workspace);
+    mp.q_lstride_b = qdesc->layer_stride * 2;
+    mp.p_lstride_b = pdesc->layer_stride * 2;
+    mp.L = (int)L;
+    mp.Q = (int)Q;
+    mp.P = (int)P;
+    mp.T = qdesc->block_tokens;
+    mp.H = qdesc->n_kv_heads;
+    mp.npt = (int)npt;
+    mp.nqt = (int)nqt;
+    mp.total = (int)total;
+    mp.chunk = kChunk;
+    mp.raw = 0;
+    mp.dpart = nullptr;
+    mp.G = 1;
+    mp.S = 1;
+    mp.stagger_wgs = compute_units();
+    mp.stagger_unit = kStaggerUnit;
+    mp.vgrid = (int)virtual_grid(total);
+    const unsigned grid = launch_grid((unsigned)mp.vgrid);
+    if (rc_status s = prepare_schedule(mp, grid, static_cast<char*>(workspace) + plan_bytes(plan, L, P, Q) - schedule_bytes(total), st)) return s;
+    if (qdesc->dtype == RC_BF16)
+      launch_tiles<true>(mode, ts, mp, grid, st);
+    else
+      launch_tiles<false>(mode, ts, mp, grid, st);
+    if (rc_status s = check_launch("rc_match_blocks(tiles)")) return s;
+  }
+  return merge_parts<false>(static_cast<const Part*>(workspace), npt, LQ, (int)Q, a.tau, a.best_idx, a.best_score, a.match_idx,
+                            a.second_score, st, "rc_match_blocks(finalize)");
+}
+}  // namespace
+}  // namespace rc
 
 extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* pdesc, int32_t mode, const void* kq,
                                      const void* vq, int64_t Q, const float* q_ksq, const float* q_vsq,
@@ -1601,105 +1795,16 @@ extern "C" rc_status rc_match_blocks(const rc_kv_desc* qdesc, const rc_kv_desc* 
                         best_idx, best_score, match_idx, second_score, workspace, hip_stream};
     return mode == RC_SCORE_BLOCK ? few_search(fa, F, false, "rc_match_blocks(few queries)") : few_search_heads(fa, "rc_match_blocks(few queries)");
   }
-  const MatchPlan plan = match_plan(mode, L, P, Q, qdesc->block_tokens, qdesc->n_kv_heads, workspace_bytes);
-  const int S = plan.S;
-  const TileShape ts = plan.ts;
-  const int64_t npt = (P + ts.bp - 1) / ts.bp, nqt = (Q + ts.bq - 1) / ts.bq;
-  const int64_t total = (int64_t)L * npt * nqt;
-  const long long LQ = (long long)L * Q;
-
-  if (S > 1) {
-    // few tiles: shares of every tile's reduction, then sum + selection, then the merge over pool chunks
-    const SplitLayout sl = split_layout(S, L, P, Q);
-    MatchParams mp;
-    mp.kq = static_cast<const char*>(kq);
-    mp.vq = static_cast<const char*>(vq);
-    mp.kp = static_cast<const char*>(kp);
-    mp.vp = static_cast<const char*>(vp);
-    mp.q_ksq = q_ksq;
-    mp.q_vsq = q_vsq;
-    mp.p_ksq = p_ksq;
-    mp.p_vsq = p_vsq;
-    mp.live = pool_live;
-    mp.part = nullptr;
-    mp.dpart = static_cast<float*>(workspace);
-    mp.q_lstride_b = qdesc->layer_stride * 2;
-    mp.p_lstride_b = pdesc->layer_stride * 2;
-    mp.L = L;
-    mp.Q = (int)Q;
-    mp.P = (int)P;
-    mp.T = qdesc->block_tokens;
-    mp.H = qdesc->n_kv_heads;
-    mp.npt = (int)sl.npt;
-    mp.nqt = (int)sl.nqt;
-    mp.total = (int)(L * sl.npt * sl.nqt * S);
-    mp.chunk = kChunk;
-    mp.raw = 0;
-    mp.G = 1;
-    mp.S = S;
-    mp.stagger_wgs = 0;
-    mp.stagger_unit = 0;
-    mp.vgrid = (int)virtual_grid(mp.total);
-    const unsigned grid = launch_grid((unsigned)mp.vgrid);
-    mp.ctr = nullptr;
-    mp.rounds = 0;
-    mp.steal_min = 0;
-    mp.dyn_from = 0;
-    const bool heads = mode == RC_SCORE_PER_HEAD_ALL;
-    if (qdesc->dtype == RC_BF16)
-      launch_shares<true>(heads, sl.bq, mp, grid, st);
-    else
-      launch_shares<false>(heads, sl.bq, mp, grid, st);
-    if (rc_status s = check_launch("rc_match_blocks(tile shares)")) return s;
-    Part* part = reinterpret_cast<Part*>(static_cast<char*>(workspace) + sl.part_offset);
-    const dim3 sgrid((unsigned)((Q + 63) / 64), (unsigned)sl.nchunks, (unsigned)L);
-    tile_sums_select_kernel<<<sgrid, 64 * kSelRowGroups, 0, st>>>(mp.dpart, S, (int)P, (int)Q, (int)sl.npt, (int)sl.nqt, sl.bq / 64, sl.sel_rows,
-                                                   -1.0f, heads ? 1 : 0, pool_live, part);
-    if (rc_status s = check_launch("rc_match_blocks(select)")) return s;
-    return merge_parts<false>(part, sl.nchunks, LQ, (int)Q, tau, best_idx, best_score, match_idx, second_score, st,
-                              "rc_match_blocks(finalize)");
+  const int T = qdesc->block_tokens, H = qdesc->n_kv_heads;
+  const TileSearch all = {qdesc, pdesc, mode, static_cast<const char*>(kq), static_cast<const char*>(vq), static_cast<const char*>(kp),
+                          static_cast<const char*>(vp), q_ksq, q_vsq, p_ksq, p_vsq, pool_live, tau, best_idx, best_score, match_idx,
+                          second_score, L, Q, P, workspace, st};
+  const int tail = tail_layers(mode, L, P, Q, T, H);
+  if (tail > 0 && tail_bytes(tail, mode, L, P, Q, T, H) <= workspace_bytes) {
+    if (rc_status s = search_tiles(some_layers(all, L - tail, tail), {wide_split_count(mode, tail, P, Q, T, H), kBlockTile})) return s;
+    return search_tiles(some_layers(all, 0, L - tail), {1, tile_for(mode, L - tail, P, Q)});
   }
-
-  if (P > 0) {
-    MatchParams mp;
-    mp.kq = static_cast<const char*>(kq);
-    mp.vq = static_cast<const char*>(vq);
-    mp.kp = static_cast<const char*>(kp);
-    mp.vp = static_cast<const char*>(vp);
-    mp.q_ksq = q_ksq;
-    mp.q_vsq = q_vsq;
-    mp.p_ksq = p_ksq;
-    mp.p_vsq = p_vsq;
-    mp.live = pool_live;
-    mp.part = static_cast<Part*>(workspace);
-    mp.q_lstride_b = qdesc->layer_stride * 2;
-    mp.p_lstride_b = pdesc->layer_stride * 2;
-    mp.L = L;
-    mp.Q = (int)Q;
-    mp.P = (int)P;
-    mp.T = qdesc->block_tokens;
-    mp.H = qdesc->n_kv_heads;
-    mp.npt = (int)npt;
-    mp.nqt = (int)nqt;
-    mp.total = (int)total;
-    mp.chunk = kChunk;
-    mp.raw = 0;
-    mp.dpart = nullptr;
-    mp.G = 1;
-    mp.S = 1;
-    mp.stagger_wgs = compute_units();
-    mp.stagger_unit = kStaggerUnit;
-    mp.vgrid = (int)virtual_grid(total);
-    const unsigned grid = launch_grid((unsigned)mp.vgrid);
-    if (rc_status s = prepare_schedule(mp, grid, static_cast<char*>(workspace) + plan_bytes(plan, L, P, Q) - schedule_bytes(total), st)) return s;
-    if (qdesc->dtype == RC_BF16)
-      launch_tiles<true>(mode, ts, mp, grid, st);
-    else
-      launch_tiles<false>(mode, ts, mp, grid, st);
-    if (rc_status s = check_launch("rc_match_blocks(tiles)")) return s;
-  }
-  return merge_parts<false>(static_cast<const Part*>(workspace), npt, LQ, (int)Q, tau, best_idx, best_score, match_idx,
-                            second_score, st, "rc_match_blocks(finalize)");
+  return search_tiles(all, match_plan(mode, L, P, Q, T, H, workspace_bytes));
 }
 
 extern "C" size_t rc_layer_mean_workspace_size(const rc_kv_desc* qdesc, int64_t Q, int64_t P) {
