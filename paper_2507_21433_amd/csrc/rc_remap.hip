@@ -29,13 +29,11 @@
 #include <mutex>
 
 #include "rc_common.hpp"
+#include "rc_remap_plan.hpp"
 
 namespace rc {
 namespace {
 
-constexpr int kGatherThreads = 1024;
-constexpr int kGatherPerThread = 16;                                  // entries a thread keeps in flight
-constexpr int kGatherBatch = kGatherThreads * kGatherPerThread;       // entries per batch of a workgroup
 constexpr int kMaxQ = 8192;                                           // LDS histogram bins
 constexpr int kLdsIds = 32768;                                        // id range the 16-bit slot table covers
 constexpr int kLdsTargets = 4096;                                     // most query slots with their target in LDS
@@ -43,21 +41,6 @@ constexpr int kFinalThreads = 1024;
 constexpr int kFinalPerThread = kMaxQ / kFinalThreads;
 constexpr int kClaimSlots = 4096;
 constexpr int kLayerCounts = 15872;                                   // reference counts a workgroup of remap_layer_kernel owns, at most
-
-// Workgroups per layer.  One (which then also finalizes its layer) when the layers alone fill the chip or the
-// layer's table is small; otherwise as many as keep the launch at one workgroup per compute unit, of at least
-// a quarter batch each: a single compute unit takes longer to stream a large layer (with a launch that adds the
-// workgroups' histograms, at 64 layers of 49 664 entries and 50 176 reference counts: 40 us with one workgroup per layer,
-// 30 with 3, 26 with 4, 33 with 8).
-inline int64_t chunks_per_layer(int64_t RE, int64_t L) {
-  if (L >= 128) return 1;
-  int64_t g = 256 / (L > 0 ? L : 1);
-  const int64_t most = RE / (kGatherBatch / 4);
-  if (g > most) g = most;
-  if (g < 1) g = 1;
-  if (g > 65535) g = 65535;
-  return g;
-}
 
 // What remap_layer_kernel takes: query slots whose targets and counts fit beside a share of the reference counts in
 // LDS; and, where several workgroups read a layer's table, a table that is short enough to be read by each (at 131 072
@@ -456,8 +439,8 @@ __global__ __launch_bounds__(kGatherThreads) void remap_layer_kernel(
   const int32_t* tin = tables_in + l * RE;
   int32_t* tout = tables_out + l * RE;
   const int32_t* m = match_idx + l * Q;
-  const int lo_e = g * chunk, len_e = min(RE - lo_e, chunk);
-  const int rlo = g * rc_chunk, n_counts = min(NB - rlo, rc_chunk);
+  const int lo_e = g * chunk, len_e = share_items(RE, lo_e, chunk);
+  const int rlo = g * rc_chunk, n_counts = share_items(NB, rlo, rc_chunk);
 
   // ---- everything that waits for nothing
   constexpr int kSlots = kLdsTargets / kGatherThreads, kCounts = (kLayerCounts + kGatherThreads * 4 - 1) / (kGatherThreads * 4);
@@ -711,10 +694,7 @@ rc_status remap_run(const char* who, int32_t n_layers, const int32_t* tables_in,
   int32_t* slot_of = static_cast<int32_t*>(workspace);
   int32_t* partial = slot_of + ((NB + 3) / 4) * 4;
   const int64_t G = chunks_per_layer(RE, n_layers);
-  int64_t chunk = (RE + G - 1) / G;
-  chunk = (chunk + 3) / 4 * 4;
-  int64_t rc_chunk = (NB + G - 1) / G;
-  rc_chunk = (rc_chunk + 3) / 4 * 4;
+  const int64_t chunk = share_length(RE, G), rc_chunk = share_length(NB, G);
   const bool vec = RE % 4 == 0 && aligned16(tables_in) && aligned16(tables_out);
   const int rc_vec = NB % 4 == 0 && aligned16(refcount_in) && aligned16(refcount_out);
 

@@ -44,3 +44,29 @@ def test_remap_layers(oracle, L, RE, NB, Q, with_pids, wide, in_place):
     o = oracle.remap(tables, qids, pids, match, P, NB, refcount)
     for k in ("tables", "refcount", "freed", "n_remapped"):
         np.testing.assert_array_equal(g[k].cpu().numpy(), o[k], err_msg=k)
+
+
+# long tables over few blocks: with the counts dealt out in fours, the last workgroups of a layer own none (the share of one
+# starts exactly at the end: 17 x 4 blocks, 16 workgroups and more); most entries are padding
+@pytest.mark.parametrize("L,RE,NB,Q", [(1, 131072, 3460, 500), (8, 131072, 1025, 200), (1, 100000, 2113, 63), (16, 65536, 897, 100),
+                                       (1, 49152, 433, 16), (64, 49664, 33, 16), (2, 16384, 33, 8), (1, 131072, 68, 30), (1, 131072, 3843, 700)])
+@pytest.mark.parametrize("with_pids", [False, True])
+def test_remap_few_blocks(oracle, L, RE, NB, Q, with_pids):
+    rng = np.random.RandomState(NB + Q)
+    ids = rng.permutation(NB).astype(np.int32)
+    if with_pids:
+        qids, pids, P = ids[:Q], ids[Q:], NB - Q
+    else:
+        qids, pids, P = np.arange(NB - Q, NB, dtype=np.int32), None, NB - Q
+    match = rng.randint(-1, P, (L, Q)).astype(np.int32)
+    tables = np.where(rng.random_sample((L, 1, RE)) < 0.1, rng.randint(0, NB, (L, 1, RE)), -1).astype(np.int32)
+    refcount = np.stack([np.bincount(t[t >= 0], minlength=NB) for t in tables.reshape(L, RE)]).astype(np.int32)
+    refcount += rng.randint(0, 2, refcount.shape).astype(np.int32)        # references left, and gone
+    t = lambda a: None if a is None else torch.as_tensor(a, device="cuda:0").contiguous()
+    print(f"remap few blocks L={L} RE={RE} NB={NB} Q={Q} pids={with_pids}", flush=True)
+    g = rc.rc_remap_block_table(t(tables), t(qids), t(pids), t(match), P, NB, t(refcount))
+    torch.cuda.synchronize()
+    o = oracle.remap(tables, qids, pids, match, P, NB, refcount)
+    assert 0 < o["freed"].sum() < (match >= 0).sum()
+    for k in ("tables", "refcount", "freed", "n_remapped"):
+        np.testing.assert_array_equal(g[k].cpu().numpy(), o[k], err_msg=k)
