@@ -43,12 +43,14 @@ constexpr int kClaimSlots = 4096;
 constexpr int kLayerCounts = 15872;                                   // reference counts a workgroup of remap_layer_kernel owns, at most
 
 // What remap_layer_kernel takes: query slots whose targets and counts fit beside a share of the reference counts in
-// LDS; and, where several workgroups read a layer's table, a table that is short enough to be read by each (at 131 072
-// entries 17 us against 21 with the gather and finalize launches, a lead that shrinks with every entry) and that is not
-// rewritten in place.
-constexpr int64_t kLayerEntries = 131072;
-inline bool layer_kernel_fits(int64_t Q, int64_t RE, int64_t rc_chunk, int64_t per_layer, bool in_place) {
-  return Q <= kLdsTargets && rc_chunk <= kLayerCounts && RE <= (1 << 30) && (per_layer == 1 || (!in_place && RE <= kLayerEntries));
+// LDS; and, where several workgroups read a layer's table, a table that is short enough to be read by each and that is
+// not rewritten in place.  A lead that shrinks with every entry: at 131 072 entries 17 us against 21 with the gather and
+// finalize launches; where there are blocks enough for the query blocks to lie further apart than the 16-bit table reaches,
+// and they do, 20.8 against 19.8 at 98 304 entries with 60 query blocks (24.5 / 27.2 with 500), 25.6 / 21.9 at 131 072.
+constexpr int64_t kLayerEntries = 131072, kLayerEntriesScattered = 98304;
+inline bool layer_kernel_fits(int64_t Q, int64_t RE, int64_t NB, int64_t rc_chunk, int64_t per_layer, bool in_place) {
+  const int64_t most = NB > kLdsIds ? kLayerEntriesScattered : kLayerEntries;
+  return Q <= kLdsTargets && rc_chunk <= kLayerCounts && RE <= (1 << 30) && (per_layer == 1 || (!in_place && RE <= most));
 }
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -405,14 +407,24 @@ __global__ __launch_bounds__(kFinalThreads) void remap_finalize_kernel(
       query_ids, pool_ids, match_idx + l * Q, Q, P, NB, refcount_out + l * NB, freed + l * Q, n_remapped + l, claim, wsum);
 }
 
+constexpr int kHashBits = 14, kHashPlaces = 1 << kHashBits, kHashIdBits = 19;
+constexpr unsigned kHashIdMask = (1u << kHashIdBits) - 1u;
 struct LayerLds {
-  unsigned short slot[kLdsIds];   // block id - lo -> slot + 1 of the matched query block with that id (0 = none)
+  union {
+    unsigned short slot[kLdsIds];    // block id - lo -> slot + 1 of the matched query block with that id (0 = none)
+    unsigned int hash[kHashPlaces];  // ids further apart than that: (slot + 1) << kHashIdBits | id of a matched query block (0 = free)
+  };
   int target[kLdsTargets];        // target block of a matched slot
   int hist[kLdsTargets];          // references of the layer to a matched slot
   int rc[kLayerCounts];           // this workgroup's share of the layer's reference counts
   int lo[kGatherThreads / 64], hi[kGatherThreads / 64], moved[kGatherThreads / 64];
 };
 static_assert(sizeof(LayerLds) <= 160 * 1024, "fits the LDS of a compute unit");
+static_assert(kLdsTargets < kHashPlaces, "a free place ends every search of the hash table");
+static_assert(kLdsTargets < 1 << (32 - kHashIdBits) && kLayerCounts * (kLayerEntries / (kGatherBatch / 4)) <= 1 << kHashIdBits,
+              "slot + 1 and a block id fit in one word: with several workgroups per layer there are as many shares of the counts at most");
+// consecutive ids and ids at a regular distance spread over the table; a 24-bit product runs at four times the rate of a 32-bit one
+__device__ __forceinline__ unsigned hash_place(int id) { return (unsigned)__umul24((unsigned)id, 0x9e3779u) >> (32 - kHashBits); }
 
 // The whole remap of a layer by `per_layer` workgroups that do not need each other.  Each reads all of the layer's
 // table and counts the references to the matched query blocks in LDS (integer adds: the same counts in any order),
@@ -423,11 +435,15 @@ static_assert(sizeof(LayerLds) <= 160 * 1024, "fits the LDS of a compute unit");
 // reads of the table come from its L2.  Measured against one gather launch and, with several workgroups per layer, a
 // second launch that adds their histograms (us): 1 layer x 288 entries 9.1 -> 6.2, 4 x 8192 12.7 -> 7.2, 64 x 4352
 // 12.4 -> 7.4, 64 x 49 664 entries and 50 176 counts 24.0 -> 15.3, 256 x 15 000 17.8 -> 12.4, 1 x 131 072 20.9 -> 16.9.
+// Query blocks whose ids lie further apart than the table of slots reaches are looked up in an open-addressing table in the
+// same LDS.  (Through global memory, entry -> slot -> id -> decision -> target, that is a chain of four round trips for every
+// entry in every workgroup.  Ids all over 50 176 blocks, 1024 query blocks, gather launches / that chain / this table, us:
+// 64 x 49 664 entries 49 / 65 / 21, 8 x 49 152 35 / 49 / 17.)
 // What is left at 64 x 49 664 is vector work on the 48 entries that every thread looks at (a branch per entry instead of
 // one per four: 16.6; no branch at all: 16.9) and 6 us that a call of one small table takes as well.
 template <bool VEC>
 __global__ __launch_bounds__(kGatherThreads) void remap_layer_kernel(
-    const int32_t* tables_in, int32_t* tables_out, int RE, int chunk, int32_t* slot_of, const int32_t* __restrict__ query_ids,
+    const int32_t* tables_in, int32_t* tables_out, int RE, int chunk, const int32_t* __restrict__ query_ids,
     const int32_t* __restrict__ pool_ids, const int32_t* __restrict__ match_idx, int Q, int P, int NB,
     const int32_t* refcount_in, int32_t* refcount_out, int rc_chunk, int rc_vec, uint8_t* __restrict__ freed,
     int32_t* __restrict__ n_remapped, int L, int per_layer) {
@@ -512,20 +528,20 @@ __global__ __launch_bounds__(kGatherThreads) void remap_layer_kernel(
   }
   const unsigned span = id_hi < 0 ? 0u : (unsigned)(id_hi - id_lo) + 1u;  // 0: no matched query block
   const bool in_lds = span <= kLdsIds;
-  if (in_lds) {
-    unsigned int* z = reinterpret_cast<unsigned int*>(s.slot);
-    for (int i = tid; i < (int)((span + 1) / 2); i += kGatherThreads) z[i] = 0u;
-    lds_barrier();
-  }
+  const int words = in_lds ? (int)((span + 1) / 2) : kHashPlaces;
+  for (int i = tid; i < words; i += kGatherThreads) s.hash[i] = 0u;  // of either table
+  lds_barrier();
 #pragma unroll
   for (int k = 0; k < kSlots; ++k) {
     const int q = k * kGatherThreads + tid;
     if (q < Q) s.hist[q] = 0;
     if (id[k] >= 0) {
-      if (in_lds)
+      if (in_lds) {
         s.slot[id[k] - id_lo] = (unsigned short)(q + 1);  // query ids are distinct: one writer per entry
-      else
-        slot_of[id[k]] = q;  // every workgroup that needs the word writes the same value and reads it back itself
+      } else {
+        unsigned at = hash_place(id[k]);
+        while (atomicCAS(&s.hash[at], 0u, (unsigned)(q + 1) << kHashIdBits | (unsigned)id[k]) != 0u) at = (at + 1) & (kHashPlaces - 1);
+      }
       s.target[q] = tgt[k];
     }
   }
@@ -542,12 +558,7 @@ __global__ __launch_bounds__(kGatherThreads) void remap_layer_kernel(
       }
     }
   }
-  if (in_lds) {
-    lds_barrier();
-  } else {
-    __threadfence_block();
-    __syncthreads();
-  }
+  lds_barrier();
 
   // ---- the table: every entry is counted, those of this workgroup's chunk are written
   for (int first = 0; first < RE; first += kAhead * kGroup) {
@@ -566,12 +577,27 @@ __global__ __launch_bounds__(kGatherThreads) void remap_layer_kernel(
 #pragma unroll
           for (int c = 0; c < 4; ++c) slot1[c] = d[c] < span ? (int)s.slot[d[c]] : 0;
         } else {
-#pragma unroll 1
+          unsigned at[4], item[4];
+          bool other[4], more = false;  // the place holds another block
+#pragma unroll
           for (int c = 0; c < 4; ++c) {
-            int sl = -1;
-            if (d[c] < span) remap_entry(entry[c], slot_of, query_ids, pool_ids, m, Q, P, NB, sl);
-            slot1[c] = sl + 1;
+            at[c] = hash_place(entry[c]);
+            item[c] = d[c] < span ? s.hash[at[c]] : 0u;
           }
+#pragma unroll
+          for (int c = 0; c < 4; ++c) more |= other[c] = item[c] != 0u && (int)(item[c] & kHashIdMask) != entry[c];
+          while (more) {
+            more = false;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              at[c] = (at[c] + 1) & (kHashPlaces - 1);
+              if (other[c]) item[c] = s.hash[at[c]];
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) more |= other[c] = item[c] != 0u && (int)(item[c] & kHashIdMask) != entry[c];
+          }
+#pragma unroll
+          for (int c = 0; c < 4; ++c) slot1[c] = (int)(item[c] >> kHashIdBits);
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c)
@@ -698,14 +724,14 @@ rc_status remap_run(const char* who, int32_t n_layers, const int32_t* tables_in,
   const bool vec = RE % 4 == 0 && aligned16(tables_in) && aligned16(tables_out);
   const int rc_vec = NB % 4 == 0 && aligned16(refcount_in) && aligned16(refcount_out);
 
-  if (layer_kernel_fits(Q, RE, rc_chunk, G, tables_in == tables_out)) {
+  if (layer_kernel_fits(Q, RE, NB, rc_chunk, G, tables_in == tables_out)) {
     const unsigned wgs = (unsigned)((n_layers + 7) / 8 * 8 * G);
     if (vec)
-      remap_layer_kernel<true><<<wgs, kGatherThreads, 0, st>>>(tables_in, tables_out, (int)RE, (int)chunk, slot_of, query_ids, pool_ids,
+      remap_layer_kernel<true><<<wgs, kGatherThreads, 0, st>>>(tables_in, tables_out, (int)RE, (int)chunk, query_ids, pool_ids,
                                                                match_idx, (int)Q, (int)P, (int)NB, refcount_in, refcount_out,
                                                                (int)rc_chunk, rc_vec, freed, n_remapped, n_layers, (int)G);
     else
-      remap_layer_kernel<false><<<wgs, kGatherThreads, 0, st>>>(tables_in, tables_out, (int)RE, (int)chunk, slot_of, query_ids, pool_ids,
+      remap_layer_kernel<false><<<wgs, kGatherThreads, 0, st>>>(tables_in, tables_out, (int)RE, (int)chunk, query_ids, pool_ids,
                                                                 match_idx, (int)Q, (int)P, (int)NB, refcount_in, refcount_out,
                                                                 (int)rc_chunk, rc_vec, freed, n_remapped, n_layers, (int)G);
     return check_launch("rc_remap_block_table(layers)");

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
     (2, 16388, 31748, 1025, True, False),       # one group more of each: the counts no longer fit
     (9, 49664, 50176, 4096, False, False),      # as many query blocks as there are targets in LDS; nine layers on eight XCDs
     (2, 30000, 33000, 4097, False, False),      # one query block more
-    (1, 131072, 60000, 500, True, True),        # the longest table that every workgroup reads; ids some 59 000 apart
+    (1, 131072, 60000, 500, True, True),        # ids some 59 000 apart, a table too long for every workgroup to look them up
     (1, 131076, 60000, 500, False, True),
     (130, 700, 15872, 40, True, False),         # a workgroup per layer, a full share of the counts
     (130, 701, 15873, 40, False, False),
@@ -68,5 +68,36 @@ def test_remap_few_blocks(oracle, L, RE, NB, Q, with_pids):
     torch.cuda.synchronize()
     o = oracle.remap(tables, qids, pids, match, P, NB, refcount)
     assert 0 < o["freed"].sum() < (match >= 0).sum()
+    for k in ("tables", "refcount", "freed", "n_remapped"):
+        np.testing.assert_array_equal(g[k].cpu().numpy(), o[k], err_msg=k)
+
+
+# query blocks further apart than the 16-bit table of slots reaches: as many as the hash table takes; odd sizes; ids that all
+# fall on the last places of the hash table, so that searches are long and wrap around
+@pytest.mark.parametrize("L,RE,NB,Q,collide", [(1, 98304, 60000, 4096, False), (1, 98308, 60000, 500, False), (8, 49152, 50176, 1024, False),
+                                               (3, 30001, 45001, 63, False), (64, 12288, 33000, 2, False), (1, 98304, 380000, 4096, True)])
+def test_remap_scattered_ids(oracle, L, RE, NB, Q, collide):
+    rng = np.random.RandomState(NB + Q)
+    ids = np.arange(1, NB - 1, dtype=np.int64)
+    if collide:
+        place = (ids * 0x9E3779 % (1 << 32)) >> (32 - 14)
+        ids = ids[np.argsort(-place, kind="stable")]
+        assert place.max() == 16383 and np.unique((np.sort(-place))[:Q]).size < 200
+    else:
+        ids = rng.permutation(ids)
+    qids, pids = ids[:Q].astype(np.int32), ids[Q:].astype(np.int32)
+    qids[:2] = 0, NB - 1
+    P = pids.size
+    match = rng.randint(-1, P, (L, Q)).astype(np.int32)
+    match[:, :2] = [0, 3]                                         # both ends of the range are matched
+    tables = rng.randint(-1, NB + 1, (L, 1, RE)).astype(np.int32)
+    some = rng.random_sample(tables.shape) < 0.4
+    tables[some] = rng.choice(qids, int(some.sum()))
+    refcount = rng.randint(0, 4, (L, NB)).astype(np.int32)
+    t = lambda a: torch.as_tensor(a, device="cuda:0").contiguous()
+    print(f"remap scattered ids L={L} RE={RE} NB={NB} Q={Q}", flush=True)
+    g = rc.rc_remap_block_table(t(tables), t(qids), t(pids), t(match), P, NB, t(refcount))
+    torch.cuda.synchronize()
+    o = oracle.remap(tables, qids, pids, match, P, NB, refcount)
     for k in ("tables", "refcount", "freed", "n_remapped"):
         np.testing.assert_array_equal(g[k].cpu().numpy(), o[k], err_msg=k)
