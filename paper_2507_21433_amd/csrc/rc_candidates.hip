@@ -5,6 +5,8 @@
 // many and share blocks, a wave takes a list; a small kernel (or the wave) picks the best candidate.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "rc_common.hpp"
 
 namespace rc {
@@ -326,6 +328,13 @@ __global__ __launch_bounds__(kCandThreads) void candidate_distances_kernel(const
 // all compute units (wide_plan).  What bounds it: the stream of blocks, less what lists share (64 x 4096 x 256 lists of 16,
 // 32-KB tensors: 2120 us = 8.6 TB/s of listed blocks and queries, 7.0 of them from memory; 2431 with waves alone, 2591 in
 // workgroups of a list; 36 x 150 x 65 x 17: 250 -> 84).
+// Lists are as long as their fullest one and many are partly or wholly empty.  The valid candidates of a wave move to its first
+// slots; it walks 2 or 4 of the SLOTS where they fit, none where there is none, and a workgroup that is nearly empty throughout
+// keeps no step.  (64 x 4096 x 256 x 16 with a part of the entries empty, workgroup per list -> every slot walked -> this, us:
+// a half 1403 -> 1425 -> 1420, three quarters 836 -> 1188 -> 879, nine tenths 554 -> 1034 -> 472, all 60 -> 889 -> 22;
+// 0 to 16 valid, evenly 1415 -> 1531 -> 1511.  37 x 1823 x 795 x 19, three quarters 2627 -> 2412 -> 1600.  With a slot
+// count for every second number of candidates a group of waves falls out of step where a quarter is empty: 44 x 257 x 110 x 11
+// 565 -> 600, as it is 562.)
 struct WideParams {
   const char *kq, *vq, *kp, *vp;
   const float *q_ksq, *q_vsq, *p_ksq, *p_vsq;
@@ -351,12 +360,13 @@ constexpr int kWideWaves = 8;  // of a workgroup, at most
 
 template <bool BF16, int SLOTS, bool DIST>
 __global__ __launch_bounds__(64 * kWideWaves, SLOTS == 8 ? 3 : 4) void candidates_wide_kernel(const WideParams p) {
+  __shared__ int s_valid[kWideWaves];
   const int lane = threadIdx.x & 63, half = lane >> 5;
   const long long item = p.per_xcd ? (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3) : blockIdx.x;
   if (item >= p.items) return;
   const long long z = item / p.wgs_z;  // layer or group of layers
   const long long w = item % p.wgs_z * p.waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool idle = w >= (long long)p.Q * p.parts;  // keeps the others company at their barriers
+  const bool idle = w >= (long long)p.Q * p.parts;  // a list of none
   const long long q = idle ? 0 : w / p.parts, list = z * p.Q + q;
   const int c0 = idle ? 0 : (int)(w % p.parts) * p.per, n = idle ? 0 : min(p.per, p.C - c0);
   const long long l0 = DIST ? z * p.G : z;
@@ -368,10 +378,14 @@ __global__ __launch_bounds__(64 * kWideWaves, SLOTS == 8 ? 3 : 4) void candidate
   const int pidx = listed ? p.cand[cand0 + mine] : -1;
   const bool valid = pidx >= 0 && pidx < p.P && (!p.live || p.live[(DIST ? 0 : l0 * p.P) + pidx]);
   constexpr int kNowhere = (int)0x80000000u;  // past the end of the pool's descriptor: reads as zero, no traffic
-  const int moff = valid ? pidx * p.block_bytes : kNowhere;
-  int off[SLOTS];
-#pragma unroll
-  for (int s = 0; s < SLOTS; ++s) off[s] = __shfl(moff, s + 32 * half) + (lane & 31) * 16;
+  // the valid candidates move to the front: candidate of rank r to slot r / 2, half r % 2, the others behind them
+  const unsigned long long valids = __ballot(valid);
+  const int n_valid = __popcll(valids);
+  auto seat_of = [&](int at) {
+    const int below = __popcll(valids & ((1ull << at) - 1ull)), rank = valids >> at & 1 ? below : n_valid + at - below;
+    return (rank >> 1) + 32 * (rank & 1);
+  };
+  const int moff = __builtin_amdgcn_ds_permute(seat_of(lane) * 4, valid ? pidx * p.block_bytes : kNowhere);
   const int qoff = (lane & 31) * 16;
   const int pool_bytes = (int)((long long)p.P * p.block_bytes);  // below 2^31: a condition of this kernel
   const int steps = p.block_bytes / kWindow;                     // a multiple of 8
@@ -381,73 +395,105 @@ __global__ __launch_bounds__(64 * kWideWaves, SLOTS == 8 ? 3 : 4) void candidate
   auto source = [&](int li, bool v) __attribute__((always_inline)) {
     const long long l = l0 + li;
     Source r;
-    r.q = __builtin_amdgcn_make_buffer_rsrc((void*)((v ? p.vq : p.kq) + l * p.q_lstride_b + q * p.block_bytes), 0, idle ? 0 : p.block_bytes, 0x00020000);
+    r.q = __builtin_amdgcn_make_buffer_rsrc((void*)((v ? p.vq : p.kq) + l * p.q_lstride_b + q * p.block_bytes), 0, p.block_bytes, 0x00020000);
     r.p = __builtin_amdgcn_make_buffer_rsrc((void*)((v ? p.vp : p.kp) + l * p.p_lstride_b), 0, pool_bytes, 0x00020000);
     return r;
   };
-  u32x4 x[2][SLOTS], y[2];
-  auto load = [&](int buf, const Source& src, int step) __attribute__((always_inline)) {
-    y[buf] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(src.q, qoff, step * kWindow, 0));
+  // the waves of a workgroup meet where one of them at least has more than half of its slots to read
+  bool together = false;
+  if (p.waves > 1) {
+    if (lane == 0) s_valid[threadIdx.x >> 6] = n_valid;
+    __syncthreads();
+    int most = 0;
 #pragma unroll
-    for (int s = 0; s < SLOTS; ++s) x[buf][s] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(src.p, off[s], step * kWindow, 0));
-  };
-  float run[SLOTS];
-  auto add = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int s = 0; s < SLOTS; ++s) run[s] = DIST ? sqdiff8<BF16>(y[buf], x[buf][s], run[s]) : dot8<BF16>(y[buf], x[buf][s], run[s]);
-  };
-  // the sum over one tensor: lane s + 32 * half gets its candidate's
-  auto walk = [&](const Source& src, const Source& next, bool more) __attribute__((always_inline)) {
-    float d[SLOTS];
-#pragma unroll
-    for (int s = 0; s < SLOTS; ++s) d[s] = 0.f;
-    // short chains of fp32 adds join the running sums, so that the error stays that of 256 lanes per block: squares, all of one
-    // sign, lose most in long chains (8 steps, blocks of 12 KB: 1.3 times), products of both signs in the running sums (2 steps,
-    // blocks of 64 KB: 1.25 times)
-    constexpr int kFold = DIST ? 2 : 8;  // steps; a block has a multiple of 8
-#pragma unroll 1
-    for (int t0 = 0; t0 < steps; t0 += kFold) {
-#pragma unroll
-      for (int s = 0; s < SLOTS; ++s) run[s] = 0.f;
-#pragma unroll 1
-      for (int t = t0; t < t0 + kFold; t += 2) {
-        __builtin_amdgcn_s_barrier();
-        load(1, src, t + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        add(0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (t + 2 < steps)
-          load(0, src, t + 2);
-        else if (more)
-          load(0, next, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        add(1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int s = 0; s < SLOTS; ++s) d[s] += run[s];
-    }
-    float sum = 0.f;
-#pragma unroll
-    for (int s = 0; s < SLOTS; ++s) {
-#pragma unroll
-      for (int o = 16; o > 0; o >>= 1) d[s] += __shfl_xor(d[s], o);
-      if ((lane & 31) == s) sum = d[s];
-    }
-    return sum;
-  };
+    for (int i = 0; i < kWideWaves; ++i) most = max(most, s_valid[i]);
+    together = __builtin_amdgcn_readfirstlane(most) > SLOTS;
+  }
   float total = 0.f, sk = 0.f, sv = 0.f;
-  load(0, source(0, false), 0);
-  for (int li = 0; li < nl; ++li) {
-    sk = walk(source(li, false), source(li, true), true);
-    sv = walk(source(li, true), source(min(li + 1, nl - 1), false), li + 1 < nl);
-    if (DIST) total += __builtin_amdgcn_sqrtf(sk) + __builtin_amdgcn_sqrtf(sv);
+  // all layers with the first N slots; the sum of a candidate ends in the lane of its seat
+  auto score_slots = [&](auto n_slots) __attribute__((always_inline)) {
+    constexpr int N = decltype(n_slots)::value;
+    int off[N];
+#pragma unroll
+    for (int s = 0; s < N; ++s) off[s] = __shfl(moff, s + 32 * half) + (lane & 31) * 16;
+    u32x4 x[2][N], y[2];
+    auto load = [&](int buf, const Source& src, int step) __attribute__((always_inline)) {
+      y[buf] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(src.q, qoff, step * kWindow, 0));
+#pragma unroll
+      for (int s = 0; s < N; ++s) x[buf][s] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(src.p, off[s], step * kWindow, 0));
+    };
+    float run[N];
+    auto add = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+      for (int s = 0; s < N; ++s) run[s] = DIST ? sqdiff8<BF16>(y[buf], x[buf][s], run[s]) : dot8<BF16>(y[buf], x[buf][s], run[s]);
+    };
+    auto walk = [&](const Source& src, const Source& next, bool more) __attribute__((always_inline)) {  // one tensor
+      float d[N];
+#pragma unroll
+      for (int s = 0; s < N; ++s) d[s] = 0.f;
+      // short chains of fp32 adds join the running sums, so that the error stays that of 256 lanes per block: squares, all of one
+      // sign, lose most in long chains (8 steps, blocks of 12 KB: 1.3 times), products of both signs in the running sums (2 steps,
+      // blocks of 64 KB: 1.25 times)
+      constexpr int kFold = DIST ? 2 : 8;  // steps; a block has a multiple of 8
+#pragma unroll 1
+      for (int t0 = 0; t0 < steps; t0 += kFold) {
+#pragma unroll
+        for (int s = 0; s < N; ++s) run[s] = 0.f;
+#pragma unroll 1
+        for (int t = t0; t < t0 + kFold; t += 2) {
+          if (together) __builtin_amdgcn_s_barrier();
+          load(1, src, t + 1);
+          __builtin_amdgcn_sched_barrier(0);
+          add(0);
+          __builtin_amdgcn_sched_barrier(0);
+          if (t + 2 < steps)
+            load(0, src, t + 2);
+          else if (more)
+            load(0, next, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          add(1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int s = 0; s < N; ++s) d[s] += run[s];
+      }
+      float sum = 0.f;
+#pragma unroll
+      for (int s = 0; s < N; ++s) {
+#pragma unroll
+        for (int o = 16; o > 0; o >>= 1) d[s] += __shfl_xor(d[s], o);
+        if ((lane & 31) == s) sum = d[s];
+      }
+      return sum;
+    };
+    load(0, source(0, false), 0);
+    for (int li = 0; li < nl; ++li) {
+      sk = walk(source(li, false), source(li, true), true);
+      sv = walk(source(li, true), source(min(li + 1, nl - 1), false), li + 1 < nl);
+      if (DIST) total += __builtin_amdgcn_sqrtf(sk) + __builtin_amdgcn_sqrtf(sv);
+    }
+  };
+  if (n_valid == 0) {
+    if (together)
+      for (int t = 0; t < nl * steps; ++t) __builtin_amdgcn_s_barrier();  // one per two steps of each of the two tensors
+  } else if (SLOTS > 2 && n_valid <= 4) {
+    score_slots(std::integral_constant<int, 2>());
+  } else if (SLOTS == 8 && n_valid <= 8) {
+    score_slots(std::integral_constant<int, 4>());
+  } else {
+    score_slots(std::integral_constant<int, SLOTS>());
   }
   if (idle) return;
+  int lane_again = lane;
+  asm volatile("" : "+v"(lane_again));  // the seat is worked out again: kept, it costs a register that the loops need
+  const int seat = seat_of(lane_again);
   if (DIST) {
+    total = __shfl(total, seat);
     if (valid) p.out[slot0 + mine] = total;  // the selection kernel derives validity itself
     return;
   }
+  sk = __shfl(sk, seat);
+  sv = __shfl(sv, seat);
   float score = -INFINITY;
   if (valid) {
     const long long oq = list, op = l0 * p.P + pidx;

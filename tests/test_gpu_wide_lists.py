@@ -71,3 +71,35 @@ EIGHTS = [(16, 64, 256, 16, 1, 3), (30, 64, 250, 16, 1, 4), (11, 50, 680, 16, 1,
 @pytest.mark.parametrize("L,P,Q,T,H,C", EIGHTS)
 def test_wide_lists_in_workgroups(oracle, L, P, Q, T, H, C, dtype):
     test_wide_lists(oracle, L, P, Q, T, H, C, dtype)
+
+
+# lists that are partly or wholly empty: every number of valid candidates in 2, 4, 6 and 8 slots (a wave walks 2, 4 or all of
+# them), a wave to a workgroup and eight, whole workgroups of empty lists and of nearly empty ones; a pair reports the bits that
+# it has in a full list
+@pytest.mark.parametrize("L,P,Q,T,H,C", [(1, 200, 448, 16, 2, 8), (1, 60, 375, 16, 1, 13), (1, 200, 449, 32, 1, 12), (30, 64, 250, 16, 1, 4),
+                                         (30, 64, 250, 16, 1, 8), (30, 64, 250, 16, 1, 12), (30, 64, 250, 16, 1, 16), (5, 64, 850, 16, 1, 17)])
+def test_wide_lists_partly_filled(oracle, L, P, Q, T, H, C):
+    w = synth.scaled(synth.WORKLOADS[2], name=f"fill{L}.{P}x{Q}x{C}", L=L, P=P, Q=Q, T=T, H=H, planted_frac=0.0, R=1, E=P + Q, seed=8600)
+    print(f"[gpu-case] {w.name} T={T} H={H}", flush=True)
+    pr = synth.make_problem(w, "cuda:0")
+    bits = [synth.bits(pr[n]) for n in ("kq", "vq", "kp", "vp")]
+    rng = np.random.RandomState(C)
+    full = rng.randint(0, P, size=(L, Q, C)).astype(np.int32)
+    n = rng.randint(0, C + 1, size=(L, Q, 1))
+    n[:, 40:80], n[:, 120:200] = 0, rng.randint(0, C // 4 + 1, size=(L, 80, 1))
+    keep = rng.random_sample(full.shape).argsort(-1) < n
+    cand = np.where(keep, full, rng.choice([-1, P], size=full.shape)).astype(np.int32)
+    live = np.ones((L, P), np.uint8)
+    live[:, rng.permutation(P)[:P // 10]] = 0
+    on_gpu = torch.as_tensor(live, device="cuda:0")
+    g, f = gpu_candidates(w, pr, cand, on_gpu), gpu_candidates(w, pr, full, None)
+    compare(g, oracle.candidates(0, 0, *bits, cand, live, w.tau), cand, w.tau, tol=2e-5)   # as in the sweep
+    valid = keep & (np.take_along_axis(live, full.reshape(L, -1), 1).reshape(full.shape) != 0)
+    assert np.array_equal(g["scores"][valid], f["scores"][valid]) and (g["scores"][~valid] == -np.inf).all()
+    unit = np.sqrt(w.Dh / (T * H))
+    thr = float(np.sqrt(2.0)) * unit
+    d = [rc.rc_candidate_distances(pr["kq"], pr["vq"], pr["kp"], pr["vp"], lv, torch.as_tensor(c[0], device="cuda:0"), thr)
+         for c, lv in ((cand, on_gpu[0].contiguous()), (full, None))]
+    g, f = ({k: v.cpu().numpy() for k, v in x.items()} for x in d)
+    compare_distances(g, oracle.candidate_distances(0, *bits, cand[0], live[0], thr), cand[0], thr, 1e-5 * unit)
+    assert np.array_equal(g["dist"][valid[0]], f["dist"][valid[0]]) and (g["dist"][~valid[0]] == np.inf).all()
