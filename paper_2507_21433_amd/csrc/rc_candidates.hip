@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "rc_common.hpp"
+#include "rc_lists_plan.hpp"
 
 namespace rc {
 namespace {
@@ -55,7 +56,7 @@ struct CandParams {
 // hpart[candidate][K or V][head][group]: no two groups share a slot, so plain LDS updates do.
 // Few pairs: kCandFew candidates per workgroup, so that a call of a few queries has workgroups for more of the
 // chip and a thread more of its slices in flight (rule and measurements at cand_per_wg).
-constexpr int kCandPerWg = 16, kCandFew = 4;
+constexpr int kCandFew = 4;
 
 template <bool BF16, bool ANYH, int PER>
 __global__ __launch_bounds__(kCandThreads) void candidates_kernel(const CandParams p) {
@@ -356,7 +357,6 @@ struct WideParams {
   float tau;
 };
 constexpr int kWindow = 512;   // bytes of a block per step
-constexpr int kWideWaves = 8;  // of a workgroup, at most
 
 template <bool BF16, int SLOTS, bool DIST>
 __global__ __launch_bounds__(64 * kWideWaves, SLOTS == 8 ? 3 : 4) void candidates_wide_kernel(const WideParams p) {
@@ -615,32 +615,6 @@ inline int cand_per_wg(int64_t lists, int64_t C, int block_bytes, bool two_trips
   return few() ? kCandFew : kCandPerWg;
 }
 
-// Slots (pairs of candidates) of a wave for lists of C: two waves share a list of 17 to 32, and so on.
-struct WideLists {
-  int parts, per, slots;
-};
-inline WideLists wide_lists(int64_t C) {
-  WideLists w;
-  w.parts = (int)((C + kCandPerWg - 1) / kCandPerWg);
-  w.per = (int)((C + w.parts - 1) / w.parts);
-  w.slots = w.per <= 4 ? 2 : w.per <= 8 ? 4 : w.per <= 12 ? 6 : 8;
-  return w;
-}
-// Calls for candidates_wide_kernel: at least half as many pairs as there are pool blocks (per layer, or in all for the
-// distances), so that lists share blocks, or lists of 17 to 24 (33 to 40, ...), of which workgroups of 16 leave half a
-// workgroup idle; and slots enough to keep the chip's memory pipeline full, which a workgroup per list does with fewer.
-// Measured, workgroup per list -> wave per list, us (layers x pool x queries x C):
-//   32 x 4096 x 256 x 16 1304 -> 1209   45 x 533 x 88 x 24 2005 -> 1245   11 x 194 x 66 x 14 102 -> 44   37 x 1823 x 795 x 19 6710 -> 4898
-//   4 x 2343 x 91 x 13 (2912 slots) 118 -> 123   3 x 231 x 60 x 14 (1440) 65 -> 114   13 x 1216 x 29 x 19 (a third of the blocks) 123 -> 95
-//   fewer pairs, full workgroups: 64 x 4096 x 32 x 16 340 -> 366   25 x 2810 x 48 x 9 234 -> 252   48 x 3100 x 96 x 12 (distances) 766 -> 798
-inline bool wide_wins(int64_t lists, int64_t Q, int64_t C, int64_t P, int block_bytes) {
-  if (C < 1 || P < 1 || P > 0x7fffffffLL / block_bytes || lists > (1LL << 28) || C > (1 << 20)) return false;
-  const WideLists w = wide_lists(C);
-  const int64_t slots = lists * w.parts * w.slots;
-  if (lists * w.parts > (1LL << 30)) return false;
-  return (2 * Q * C >= P && slots >= 3000) || (C > 16 && (C - 1) % 16 < 8 && slots >= 4000);
-}
-
 template <bool BF16>
 void launch_candidates(bool any_h, int per, dim3 grid, const CandParams& cp, hipStream_t st) {
   if (per == kCandFew) {
@@ -656,9 +630,18 @@ void launch_candidates(bool any_h, int per, dim3 grid, const CandParams& cp, hip
   }
 }
 
+inline void set_plan(WideParams& wp, const WidePlan& plan) {
+  wp.parts = plan.lists.parts;
+  wp.per = plan.lists.per;
+  wp.waves = plan.waves;
+  wp.wgs_z = plan.wgs_z;
+  wp.items = plan.items;
+  wp.per_xcd = plan.per_xcd;
+}
+
 template <bool BF16, bool DIST>
 void launch_wide(const WideParams& wp, hipStream_t st) {
-  const unsigned grid = (unsigned)(wp.per_xcd ? wp.per_xcd * 8 : wp.items);
+  const unsigned grid = (unsigned)wide_grid(wp.items, wp.per_xcd);
   if (wp.per <= 4)
     candidates_wide_kernel<BF16, 2, DIST><<<grid, 64 * wp.waves, 0, st>>>(wp);
   else if (wp.per <= 8)
@@ -670,31 +653,6 @@ void launch_wide(const WideParams& wp, hipStream_t st) {
 }
 
 // z: layers, or groups of layers; alike: all groups have as many layers.
-// Eight waves to a workgroup, kept together by a barrier per two windows, or one: eight where they fill the rounds of 256
-// workgroups (0.87 of them) and there are 3000 waves; below that compute units idle beside others with a workgroup more.
-// Neighbouring lists go to one XCD while the waves of a layer are about as many as an XCD works on at once, and up to 1700
-// of them (with eight to a workgroup) where a block is listed more than twice in a layer; with fewer blocks in common, all
-// XCDs do better on the same part of the layer.
-// One wave -> eight, us (layers x pool x queries x C): 64 x 4096 x 256 x 16 2431 -> 2120 (17.2 -> 14.7 GB from memory; the
-// blocks and queries once are 11.9)   44 x 257 x 110 x 19, blocks of 128 KB 1106 -> 907   distances 58 x 988 x 125 x 22 2789 -> 2399
-//   rounds filled to 0.78 to 0.85: 48 x 700 x 100 x 16 508 -> 590   64 x 500 x 130 x 6 420 -> 459;  few waves: 33 x 103 x 28 x 21 94 -> 115
-// Dealt out -> by XCD, both of eight: 37 x 788 x 304 x 20 737 -> 590   29 x 1892 x 579 x 23 3040 -> 2621   4 x 1730 x 235 x 23 96 -> 72
-//   17 x 4697 x 226 x 24 (a block listed 1.2 times) 853 -> 864   11 x 6837 x 609 x 17 (1.5) 2171 -> 2354   distances, 2000 waves of a
-//   group, 16 x 2000 x 1000 x 20 2003 -> 2261, groups not alike, 37 x 1985 x 543 x 6 1524 -> 1911
-inline void wide_plan(WideParams& wp, int64_t z, bool alike) {
-  const WideLists w = wide_lists(wp.C);
-  wp.parts = w.parts;
-  wp.per = w.per;
-  const int64_t waves = (int64_t)wp.Q * w.parts, wgs = z * ((waves + kWideWaves - 1) / kWideWaves);
-  const int64_t rounds = (wgs + 255) / 256;  // of the 256 compute units of an MI355X
-  const bool shared = waves > 448 && waves <= 1700 && alike && (int64_t)wp.Q * wp.C > 2 * (int64_t)wp.P && z * waves >= 1800;
-  const bool full = z * waves >= 3000 && 100 * z * waves >= 87 * rounds * 256 * kWideWaves;
-  wp.waves = shared || full ? kWideWaves : 1;
-  wp.wgs_z = (waves + wp.waves - 1) / wp.waves;
-  wp.items = z * wp.wgs_z;
-  wp.per_xcd = waves <= 448 || shared ? (wp.items + 7) / 8 : 0;
-}
-
 }  // namespace
 }  // namespace rc
 
@@ -753,7 +711,7 @@ extern "C" rc_status rc_score_candidates(const rc_kv_desc* qdesc, const rc_kv_de
     wp.L = L;
     wp.G = 1;
     wp.block_bytes = block_bytes;
-    wide_plan(wp, L, true);
+    set_plan(wp, wide_plan(Q, C, P, L, true));
     wp.tau = tau;
     if (qdesc->dtype == RC_BF16)
       launch_wide<true, false>(wp, st);
@@ -856,7 +814,7 @@ extern "C" rc_status rc_candidate_distances(const rc_kv_desc* qdesc, const rc_kv
     wp.L = L;
     wp.G = G;
     wp.block_bytes = block_bytes;
-    wide_plan(wp, groups, L % G == 0);
+    set_plan(wp, wide_plan(Q, C, P, groups, L % G == 0));
     if (qdesc->dtype == RC_BF16)
       launch_wide<true, true>(wp, st);
     else
