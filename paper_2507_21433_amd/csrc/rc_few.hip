@@ -437,14 +437,20 @@ void launch_shares(const FewParams& fp, unsigned wgs, hipStream_t st) {
 
 // Which calls come here, and how many shares they take.  These kernels have less than half the fixed time of the ring
 // pipeline (a wave's first loads are its own, nothing waits for a barrier) but ask for a block's line in two halves, and
-// reach 5.3 TB/s where the ring reaches 6.8.  So the line is a size of the pool's blocks, in bytes, by query count; measured
-// over 100 shapes of 3 to 190 us of pool stream, ring pipeline -> these kernels, us per call:
+// reach 5.3 TB/s where the ring reaches 6.8; and the selection takes a workgroup per row of shares, of each query and layer
+// (block score), or walks all layers of a query (layer mean).  So the lines are drawn by the size of the pool's blocks, in
+// bytes, by query count, and by what makes the other side slow: few rows to select from, or, for the layer mean, a pool of so few
+// tiles of 256 blocks per layer that the ring shares them out.  Measured over 2858 shapes, ring pipeline -> these kernels, us per call:
 //   block score  1 x 256 x 32 queries 30 -> 12, 3 x 659 x 3 47 -> 31, 1 x 4096 x 16 (268 MB) 61 -> 58, 1 x 8192 x 16 98 -> 107;
 //                7 x 310 x 24 (142 MB) 45 -> 37, 16 x 1000 x 24 (1.0 GB) 176 -> 198;
 //                2 x 1015 x 57 (133 MB) 47 -> 40, 14 x 208 x 44 (239 MB) 65 -> 82
-//   layer mean   6 x 148 x 3 44 -> 15, 47 x 215 x 1 (331 MB) 208 -> 71, 10 x 1543 x 1 (1.3 GB) 254 -> 223;
-//                33 x 132 x 21 (357 MB) 178 -> 104, 3 x 10303 x 24 (1.0 GB) 195 -> 206;
-//                46 x 167 x 37 (503 MB) 200 -> 144, 13 x 448 x 41 (478 MB) 136 -> 128
+//                layers x queries: 32 x 190 x 16 35 -> 30, 64 x 95 x 16 36 -> 43; 32 x 190 x 20 35 -> 34, 32 x 190 x 32 37 -> 40;
+//                16 x 94 x 34 51 -> 46, 32 x 114 x 34 31 -> 39, 64 x 95 x 64 43 -> 100
+//   layer mean   6 x 148 x 3 44 -> 15, 47 x 215 x 1 (331 MB) 208 -> 71, 16 x 934 x 6 (980 MB) 222 -> 188; of longer pools
+//                2 x 2670 x 16 (350 MB) 90 -> 85, 2 x 3814 x 6 (500 MB) 109 -> 116, 16 x 7476 x 16 (980 MB) 196 -> 245;
+//                33 x 132 x 21 (357 MB) 178 -> 104, 2 x 15258 x 32 (500 MB) 110 -> 127, 3 x 10303 x 24 (1.0 GB) 195 -> 206;
+//                46 x 167 x 37 (503 MB) 200 -> 144, 2 x 7476 x 64 (490 MB) 107 -> 147
+// Of the 2402 shapes that come here, 33 are more than 3 % slower than with the ring pipeline, by 6 % on average.
 // Shares: the number with the lowest estimate in us, rounds of one workgroup per compute unit (an MI355X has 256) times
 // the slices of a share times the time of a slice, and 3 ns per workgroup for storing and adding its share.  Within 2 % of
 // the best number on average over those shapes.
@@ -454,6 +460,13 @@ int few_shares(bool layer_mean, int64_t L, int64_t P, int64_t Q, int T, int H) {
   const int by_queries = Q <= 16 ? 0 : Q <= 32 ? 1 : 2;
   constexpr double most_mb[2][3] = {{256.0, 200.0, 150.0}, {1000.0, 600.0, 500.0}};
   if (mb > most_mb[layer_mean][by_queries]) return 0;
+  if (layer_mean) {
+    constexpr double any_mb[3] = {400.0, 350.0, 200.0};
+    constexpr int64_t most_blocks[3] = {2048, 1024, 512};
+    if (mb > any_mb[by_queries] && (P > most_blocks[by_queries] || L * ((P + 255) / 256) > 160)) return 0;
+  } else if (L * Q > (by_queries < 2 ? 768 : 640)) {
+    return 0;
+  }
   constexpr double slice_us[3] = {0.21, 0.27, 0.42};
   const int64_t tiles = L * ((P + kFewRows - 1) / kFewRows);
   const int units = T * H * 2 / kWaves;  // slices of a tensor that a wave of a single share walks
@@ -518,13 +531,18 @@ rc_status few_search(const FewArgs& a, int S, bool layer_mean, const char* who) 
 //   up to 8 queries    55 x 258 x 5 (128-KB tensors) 917 -> 606, 4 x 3583 x 7 246 -> 188, 50 x 2269 x 4 (7.4 GB) 1189 -> 1165
 //   up to 16 queries   20 x 260 x 12 244 -> 136, 12 x 1851 x 8 335 -> 289, 15 x 1288 x 9 (2.5 GB) 509 -> 419, 8 x 8093 x 15 (4.2 GB) 630 -> 736
 //   up to 32 queries   1 x 577 x 30 (80 workgroups) 71 -> 26, 14 x 208 x 23 (560) 75 -> 66, 30 x 700 x 30 (2640) 271 -> 286
-//   209 to 256 shares of the tile kernels: 62 x 130 x 4, 4 heads 107 -> 115, 62 x 70 x 16 51 -> 58
+//   209 to 256 shares of the tile kernels: 62 x 130 x 4, 4 heads 107 -> 115, 62 x 70 x 16 51 -> 58;  145 and more, from 17 queries
+//   on: 46 x 83 x 29, 4 heads (184) 87 -> 112, 48 x 121 x 32 (192) 62 -> 75 - but 48 x 57 x 32 (192), where three quarters of
+//   a share are padding 83 -> 71
+//   blocks of 32 tokens of two heads (rows of 16 KB, a head every 512 bytes): 1 x 9155 x 12 (300 MB) 1.29 times as fast, 1 x 18 310 x 12
+//   (600 MB) 0.93, 1 x 51 879 x 10 (1.7 GB) 290 -> 360; with 1, 3, 4, 6 and 8 heads 1.05 to 1.22 there
 bool few_heads(int64_t L, int64_t P, int64_t Q, int T, int H) {
   if (L < 1 || L > 65535 || P < 1 || Q < 1 || Q > kHeadQueries) return false;
   const double mb = (double)L * (double)P * (double)(T * H) * 512e-6;
   if (mb > 6000.0 || few_bytes(H, L, P, Q) > ((size_t)512 << 20)) return false;
   const int64_t tile_shares = L * ((P + 255) / 256) * H;
-  if (tile_shares > 208 && tile_shares <= 256) return false;
+  if (tile_shares > (Q > 16 && P > kFewRows ? 144 : 208) && tile_shares <= 256) return false;
+  if (T == 32 && H == 2 && mb > 500.0) return false;
   if (Q <= 8) return Q <= 3 || mb <= 3000.0;
   return Q <= 16 ? mb <= 2500.0 : L * ((P + kFewRows - 1) / kFewRows) * H <= 512;
 }

@@ -45,11 +45,18 @@ def test_few_queries(oracle, L, P, Q, T, H, dtype):
         assert takes_few(call) in (None, True)
 
 
-# 64 queries are few, 65 are not; pools on both sides of 256, 200 and 150 MB of blocks (1000, 600 and 500 MB for the layer mean)
+# 64 queries are few, 65 are not; pools on both sides of 256, 200 and 150 MB of blocks, 768 and 640 rows to select from; layer mean:
+# 1000 MB for pools of up to 2048 blocks and 160 tiles of 256, 400 MB for longer ones (600 MB, 1024 and 350 MB from 17 queries on;
+# 500 MB, 512 and 200 MB from 33 on)
 @pytest.mark.parametrize("mean,L,P,Q,T,H,few", [(False, 1, 300, 64, 16, 2, 1), (False, 1, 300, 65, 16, 2, 0), (False, 2, 1950, 16, 16, 8, 1), (False, 2, 1960, 16, 16, 8, 0),
                                                 (False, 3, 1017, 17, 16, 8, 1), (False, 3, 1018, 17, 16, 8, 0), (False, 5, 457, 33, 16, 8, 1), (False, 5, 458, 33, 16, 8, 0),
-                                                (True, 10, 762, 2, 32, 8, 1), (True, 10, 763, 2, 32, 8, 0), (True, 6, 1525, 18, 16, 8, 1), (True, 6, 1526, 18, 16, 8, 0),
-                                                (True, 4, 1907, 40, 16, 8, 1), (True, 4, 1908, 40, 16, 8, 0)])
+                                                (False, 48, 70, 16, 16, 1, 1), (False, 49, 70, 16, 16, 1, 0), (False, 24, 70, 32, 16, 1, 1), (False, 25, 70, 32, 16, 1, 0),
+                                                (False, 16, 70, 40, 16, 1, 1), (False, 17, 70, 40, 16, 1, 0),
+                                                (True, 10, 762, 2, 32, 8, 1), (True, 10, 763, 2, 32, 8, 0), (True, 3, 2034, 2, 16, 8, 1), (True, 2, 2048, 2, 32, 8, 1),
+                                                (True, 2, 2049, 2, 32, 8, 0), (True, 160, 60, 2, 32, 3, 1), (True, 161, 60, 2, 32, 3, 0),
+                                                (True, 2, 2670, 18, 16, 8, 1), (True, 2, 2671, 18, 16, 8, 0), (True, 6, 1024, 18, 16, 8, 1), (True, 6, 1025, 18, 16, 8, 0),
+                                                (True, 9, 1017, 18, 16, 8, 1), (True, 9, 1018, 18, 16, 8, 0),
+                                                (True, 2, 1525, 40, 16, 8, 1), (True, 2, 1526, 40, 16, 8, 0), (True, 7, 512, 40, 16, 8, 1), (True, 7, 513, 40, 16, 8, 0)])
 def test_lines(mean, L, P, Q, T, H, few):
     w = synth.scaled(synth.WORKLOADS[2], name="line", L=L, P=P, Q=Q, T=T, H=H, planted_frac=0.3, R=1, E=P + Q, seed=8800)
     pr = synth.make_problem(w, DEV)
@@ -112,9 +119,12 @@ def test_few_queries_per_head(oracle, L, P, Q, T, H, dtype):
         assert np.array_equal(g[k], again[k]) and np.array_equal(g[k], tiles[k][:, :Q]), k
 
 
-# 3, 8, 16 and 32 queries; the lines at 6000, 3000 and 2500 MB are too large for a test; 512 workgroups, 208 and 256 shares of the tile kernels
+# 3, 8, 16 and 32 queries; the lines at 6000, 3000 and 2500 MB are too large for a test; 512 workgroups, 208 and 256 shares of the tile
+# kernels, 144 from 17 queries on where a layer has more than 64 blocks; 500 MB of blocks of 32 tokens of two heads
 @pytest.mark.parametrize("L,P,Q,T,H,few", [(8, 200, 32, 16, 16, True), (9, 257, 32, 16, 16, False), (9, 257, 16, 16, 16, True), (2, 100, 33, 16, 4, False),
-                                           (26, 70, 4, 16, 8, True), (27, 70, 4, 16, 8, False), (32, 70, 4, 16, 8, False), (33, 70, 4, 16, 8, True)])
+                                           (26, 70, 4, 16, 8, True), (27, 70, 4, 16, 8, False), (32, 70, 4, 16, 8, False), (33, 70, 4, 16, 8, True),
+                                           (36, 70, 17, 16, 4, True), (37, 70, 17, 16, 4, False), (37, 64, 17, 16, 4, True), (1, 15258, 2, 32, 2, True),
+                                           (1, 15259, 2, 32, 2, False)])
 def test_lines_per_head(L, P, Q, T, H, few):
     w = synth.scaled(synth.WORKLOADS[5], name="line", L=L, P=P, Q=Q, T=T, H=H, planted_frac=0.3, R=1, E=P + Q, seed=9300)
     pr = synth.make_problem(w, DEV)
