@@ -29,6 +29,10 @@ def test_percentile_workspaces(oracle, n, nbytes):
         want, n_finite = oracle.pat_threshold(x, p)
         assert g["threshold"].cpu().numpy()[0] == want and int(g["n_finite"][0]) == n_finite
     assert (ws[-256:] == 0xA5).all(), "written past the workspace"
+    x[rng.rand(n) < 0.98] = -np.inf                              # hardly a list had a candidate
+    g = rc.rc_pat_threshold(t(x), 33.3, workspace=ws[:-256])
+    want, n_finite = oracle.pat_threshold(x, 33.3)
+    assert g["threshold"].cpu().numpy()[0] == want and int(g["n_finite"][0]) == n_finite
     g = rc.rc_pat_threshold(t(np.full(n, np.nan, np.float32)), 50.0, workspace=ws[:-256])
     assert g["threshold"].cpu().numpy()[0] == -np.inf and int(g["n_finite"][0]) == 0
 
