@@ -290,7 +290,7 @@ rc_status rc_candidate_distances(const rc_kv_desc* qdesc, const rc_kv_desc* pdes
                                  void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /* Bytes of DEVICE workspace with which rc_pat_threshold is fastest (a constant, about 24 KB; a call takes 4112 bytes as
- * well and is slower then, above 16384 samples). */
+ * well and is slower then, above 11264 samples). */
 size_t rc_pat_workspace_size(void);
 
 /*

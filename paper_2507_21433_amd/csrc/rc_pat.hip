@@ -107,7 +107,7 @@ __device__ __forceinline__ void count_bin(unsigned int* h, int bin) {
 // Few samples: one workgroup keeps their keys in registers and does all four passes; one launch instead of six
 // (3 to 6 us each).  2000 samples 23 -> 8.5 us, 8000 32 -> 16; at 32 768 one workgroup would take 47 us, the six launches 35.
 constexpr int kPatSmallThreads = 1024, kPatSmallKeys = 16;
-constexpr int kPatFew = 8192;  // where the launches of pat_wide_kernel take less (16 384 samples: 22 us in one workgroup, 17)
+constexpr int kPatFew = 11264;  // above, the launches of pat_wide_kernel take less (clustered samples, us, one workgroup and they: 9000 16.8 and 18.8, 11 264 19.1 and 19.1, 16 384 24.4 and 19.5)
 __global__ __launch_bounds__(kPatSmallThreads) void pat_small_kernel(const float* __restrict__ s, int n, double p,
                                                                      float* __restrict__ threshold,
                                                                      long long* __restrict__ n_finite) {

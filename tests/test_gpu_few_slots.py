@@ -15,7 +15,7 @@ def t(a):
 
 # below and above what one workgroup does, one and several samples per thread, one and several trips; both clusters, ties,
 # infinities and NaN; the state of 24 KB and, in 4112 bytes, the one of 4 KB
-@pytest.mark.parametrize("n", [8192, 8193, 16384, 16385, 262145, 1048577])
+@pytest.mark.parametrize("n", [8192, 8193, 11264, 11265, 16384, 16385, 262145, 1048577])
 @pytest.mark.parametrize("nbytes", [4112, None])
 def test_percentile_workspaces(oracle, n, nbytes):
     rng = np.random.RandomState(n % 1000)
