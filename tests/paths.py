@@ -56,16 +56,27 @@ def whole_tiles_workspace(w):
     return torch.empty(n, dtype=torch.uint8, device="cuda:0")
 
 
+def kernel_names(call):
+    """Names of the kernels that call() launches, [] where no kernel trace is to be had.  The profiler can lose events, all of
+    them in a trace of a few microseconds: a trace without any is taken again, of more calls."""
+    from torch.profiler import ProfilerActivity, profile
+    for times in (3, 12, 48):
+        with warnings.catch_warnings():
+            warnings.simplefilter("ignore")
+            with profile(activities=[ProfilerActivity.CUDA]) as p:
+                for _ in range(times):
+                    call()
+                torch.cuda.synchronize()
+        names = [e.name for e in p.events()]
+        if any("rc::" in n for n in names):
+            return names
+    return []
+
+
 def tile_kernels(call):
     """{(pool rows, columns, mode)} of the tile kernels that call() launches; None where no kernel trace is to be had."""
-    from torch.profiler import ProfilerActivity, profile
-    with warnings.catch_warnings():
-        warnings.simplefilter("ignore")
-        with profile(activities=[ProfilerActivity.CUDA]) as p:
-            call()
-            torch.cuda.synchronize()
-        names = [e.name for e in p.events()]
-    if not any("rc::" in n for n in names):
+    names = kernel_names(call)
+    if not names:
         return None
     found = [re.search(r"match_(?:tile|shape)_kernel<\w+, (\d+), (\d+), (\d)", n) for n in names]
     return {tuple(int(x) for x in m.groups()) for m in found if m}

@@ -265,13 +265,14 @@ def test_per_head_many_layers_whole_tiles(oracle, Q, H, tile):
                                                 (160, False, (256, 192, 1), (256, 192, 4)), (230, False, (256, 256, 1), (256, 256, 4)),
                                                 (300, False, (192, 320, 1), (256, 192, 4)), (300, True, (256, 256, 1), (256, 192, 4))])
 def test_per_head_scores_do_not_depend_on_the_path(Q, small, tile, share):
-    # the same layer scored inside a call of 90 layers (whole tiles of every shape, running minimum in 16-bit fixed point) and
-    # in a call of its own (one share per head, minimum taken by the selection kernel): identical bits, identical picks
+    # the same layer scored inside a call of 90 layers (whole tiles of every shape, running minimum in 16-bit fixed point; the last
+    # layers as shares where the workspace has room for them) and in a call of its own (one share per head, minimum taken by the
+    # selection kernel): identical bits, identical picks
     w = synth.scaled(synth.WORKLOADS[5], name=f"perhead_paths_Q{Q}", L=90, P=577, Q=Q, T=16, R=1, E=577 + Q, seed=16)
     say(w.name)
     pr = synth.make_problem(w, DEV)
     ws = paths.whole_tiles_workspace(w) if small else None
-    paths.assert_tiles(lambda: run_gpu_match(pr, w, pr["live"], workspace=ws), tile)
+    paths.assert_tiles(lambda: run_gpu_match(pr, w, pr["live"], workspace=ws), *((tile,) if small else (tile, share)))
     paths.assert_tiles(lambda: run_gpu_match({n: pr[n][:1] for n in ("kq", "vq", "kp", "vp")}, synth.scaled(w, L=1), pr["live"][:1]), share)
     many, _ = run_gpu_match(pr, w, pr["live"], workspace=ws)
     for l in (0, 37, 89):
