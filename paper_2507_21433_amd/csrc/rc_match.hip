@@ -1465,11 +1465,13 @@ inline MatchPlan match_plan(int mode, int64_t L, int64_t P, int64_t Q, int T, in
 // runs first: the number of layers with the lowest estimate in us, 0 = none.  Whole tiles by tile_choice; shares by rounds of
 // them, with 6 steps to fill the pipeline and store each, 0.06 us for the pass that adds one, 20 us for the four further
 // launches and the drain between.  Used where that is 4 % below whole tiles alone, 2 % per head (there whole tiles take 10 %
-// longer than estimated, shares as long).  96 shapes of 64-KB blocks and larger (smaller ones, whose round is short beside what
-// the launches cost, were not measured), whole tiles -> these, us:
+// longer than estimated, shares as long).  For blocks of 32 KB of K and V and larger (smaller ones, whose round is short beside
+// what the launches cost, were not measured).  Of 150 drawn shapes that get a tail the median is 1.11 times as fast and one is more
+// than 0.5 % slower; whole tiles -> these, us:
 //   block     40 x 6209 x 300, 10 heads 6288 -> 5961 (2 layers)   3 x 15320 x 412, 16 heads 2865 -> 2448 (1)   14 x 4673 x 382, 10 heads
-//             2431 -> 2091 (1)   45 x 6258 x 187 3919 -> 3714 (5)   8 x 8530 x 139, 4 heads 682 -> 558 (1)   the least: 38 x 2867 x 338,
-//             blocks of 32 tokens 5496 -> 5481 (6, margin of 3 %)   left alone: 7 x 4960 x 883, 16 heads 3630, 3728 with a tail of 1
+//             2431 -> 2091 (1)   45 x 6258 x 187 3919 -> 3714 (5)   8 x 8530 x 139, 4 heads 682 -> 558 (1)   38 x 2867 x 338,
+//             blocks of 32 tokens 5496 -> 5481 (6)   the least: 9 x 2100 x 982, 10 heads 1559 -> 1580, 3 x 9666 x 592 1160 -> 1176 (in two runs)
+//             left alone: 7 x 4960 x 883, 16 heads 3630, 3728 with a tail of 1
 //   per head  11 x 6340 x 216, 32 tokens 3692 -> 2400 (1)   39 x 2005 x 195 2028 -> 1528 (7)   5 x 6409 x 415, 10 heads 2040 -> 1596 (1)
 //             left alone: 38 x 2048 x 890, 10 heads 6234, 6431 with a tail of 1
 // Layers are searched in one way each, so identical pool blocks of a layer still see the same instructions.

@@ -8,9 +8,9 @@
 ``collect`` runs, once per pass, ``rocprofv3 --pmc <counters of the pass> --kernel-trace --output-format csv
 -d <dir>/pmc_w<N>_<pass> -- python3 bench.py --step-only 1 --workload N --steps 3 --warmup 1`` (one pass per run: the
 profiler does not split a counter list over several runs of the kernels) and keeps, of the CSV files, only the rows of
-this library's kernels and of the device copies.  ``summarise`` turns them into ``profiles/match_tile_kernel_<workload>.md``
-(mean counter values per launch of the tile kernel, the figures derived from them, the commands) and enters the
-workload's HBM traffic into ``profiles/hbm_traffic.json``, which ``bench.py`` reads for ``roofline.traffic``.
+this library's kernels and of the device copies.  ``summarise`` turns them into ``profiles/<kernel>_<workload>.md`` (mean
+counter values per launch of the kernel that multiplies: match_tile_kernel, or few_shares_kernel on a small problem; the
+figures derived from them, the commands) and enters the workload's HBM traffic into ``profiles/hbm_traffic.json``, which ``bench.py`` reads for ``roofline.traffic``.
 
 ``trace`` runs ``rocprofv3 --kernel-trace --stats -- python3 bench.py ...`` on the timed step alone and on the headline
 workload with its side measurements, and writes the per-kernel times of this library's kernels to
@@ -33,7 +33,8 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 KERNEL_SOURCES = ("paper_2507_21433_amd/csrc/rc_match.hip", "paper_2507_21433_amd/csrc/rc_few.hip",
-                  "paper_2507_21433_amd/csrc/rc_tile.hpp", "paper_2507_21433_amd/csrc/rc_common.hpp")
+                  "paper_2507_21433_amd/csrc/rc_tile.hpp", "paper_2507_21433_amd/csrc/rc_select.hpp",
+                  "paper_2507_21433_amd/csrc/rc_common.hpp")
 TILE_KERNELS = ("match_tile_kernel", "match_shape_kernel", "few_shares_kernel", "head_shares_kernel")   # one body, by tile shape; small problems
 COPY_KERNEL = "copyBuffer"
 CAL_BYTES = 1 << 30
@@ -118,6 +119,16 @@ def read_pass(d):
     return vals, durs, bench
 
 
+def tile_kernel_name(d):
+    """The kernel of TILE_KERNELS that a pass saw (all shapes of match_shape_kernel are one body with match_tile_kernel)."""
+    for f in sorted(glob.glob(os.path.join(d, "*", "*_counter_collection.csv")), key=os.path.getmtime, reverse=True):
+        text = open(f).read()
+        found = [t for t in TILE_KERNELS if t in text]
+        if found:
+            return "match_tile_kernel" if found[0] == "match_shape_kernel" else found[0]
+    return TILE_KERNELS[0]
+
+
 def mean(xs):
     xs = list(xs)
     return sum(xs) / len(xs) if xs else float("nan")
@@ -146,8 +157,9 @@ def summarise(args):
         dur_ns[name] = mean(durs["tile"].values())
     launches = len(next(iter(found.values()))[1]["tile"])
     c = {k: mean(v) for k, v in c.items()}
-    lines = [f"# match_tile_kernel on {wname}: hardware counters", ""]
-    lines += ["Mean per launch of `rc::match_tile_kernel` (the kernel inside `rc_match_blocks`) over the "
+    kernel = tile_kernel_name(os.path.join(args.dir, f"pmc_w{wl}_{next(iter(found))}"))
+    lines = [f"# {kernel} on {wname}: hardware counters", ""]
+    lines += [f"Mean per launch of `rc::{kernel}` (the kernel inside `rc_match_blocks` that multiplies) over the "
               f"{launches} launches of one `bench.py --step-only 1` run per pass; one `rocprofv3 --pmc` run per pass, "
               "made with `python3 -m paper_2507_21433_amd.profsum collect` and condensed with its `summarise`.", ""]
     lines += ["Commands (from the repository root, after `cd /tmp && export TMPDIR=/tmp`):", "", "```"]
@@ -230,7 +242,7 @@ def summarise(args):
                      + (f", {traffic['hbm_bytes_per_launch'] / alg_bytes:.2f} x the {alg_bytes / 1e9:.2f} GB of KV that the launch has to read once."
                         if alg_bytes else "."))
     os.makedirs(args.out, exist_ok=True)
-    path = os.path.join(args.out, f"match_tile_kernel_{wname}.md")
+    path = os.path.join(args.out, f"{kernel}_{wname}.md")
     with open(path, "w") as f:
         f.write("\n".join(lines) + "\n")
     print(f"[profsum] wrote {path}")
