@@ -160,7 +160,7 @@ size_t rc_remap_workspace_size(int32_t n_layers, int64_t R, int64_t E, int64_t Q
  *   refcount_in/out DEVICE int32 [L][NB]; refcount_out may be refcount_in
  *   freed           DEVICE uint8 [L][Q];  n_remapped: DEVICE int32 [L]
  *   workspace       DEVICE, >= rc_remap_workspace_size() bytes, 16-byte aligned
- * No atomics are used: the result is the same on every run.  Q is limited to 8192.
+ * No atomics on global memory, integer adds only: the result is the same on every run.  Q is limited to 8192.
  */
 rc_status rc_remap_block_table(int32_t n_layers,
                                const int32_t* tables_in, int32_t* tables_out,
@@ -387,7 +387,8 @@ rc_status rc_refcount_release(const int32_t* ids, int64_t n, int32_t* refcount, 
  *   last_used       DEVICE int32 [P], any monotone stamp (e.g. the step number), see rc_pool_touch
  *   match_idx       DEVICE int32 [Q], the step's decisions
  *   n_free          DEVICE int32 [1]: free slots afterwards;  n_evicted: DEVICE int32 [1]
- * One workgroup walks the metadata (9 bytes per slot) seven times; no workspace.  The same slots on every run.
+ * One workgroup reads the metadata (9 bytes per slot) once for pools of up to 16384 slots and walks it seven times for
+ * larger ones; no workspace.  The same slots on every run.
  */
 rc_status rc_pool_evict(int64_t P, uint8_t* pool_live, const int32_t* refcount, const int32_t* last_used,
                         const int32_t* match_idx, int64_t Q, int64_t extra_wanted,
