@@ -41,16 +41,25 @@ constexpr int kFinalThreads = 1024;
 constexpr int kFinalPerThread = kMaxQ / kFinalThreads;
 constexpr int kClaimSlots = 4096;
 constexpr int kLayerCounts = 15872;                                   // reference counts a workgroup of remap_layer_kernel owns, at most
+constexpr int64_t kLayerEntries = 131072;                             // entries of a table that several of its workgroups read, at most
 
 // What remap_layer_kernel takes: query slots whose targets and counts fit beside a share of the reference counts in
 // LDS; and, where several workgroups read a layer's table, a table that is short enough to be read by each and that is
-// not rewritten in place.  A lead that shrinks with every entry: at 131 072 entries 17 us against 21 with the gather and
-// finalize launches; where there are blocks enough for the query blocks to lie further apart than the 16-bit table reaches,
-// and they do, 20.8 against 19.8 at 98 304 entries with 60 query blocks (24.5 / 27.2 with 500), 25.6 / 21.9 at 131 072.
-constexpr int64_t kLayerEntries = 131072, kLayerEntriesScattered = 98304;
-inline bool layer_kernel_fits(int64_t Q, int64_t RE, int64_t NB, int64_t rc_chunk, int64_t per_layer, bool in_place) {
-  const int64_t most = NB > kLdsIds ? kLayerEntriesScattered : kLayerEntries;
-  return Q <= kLdsTargets && rc_chunk <= kLayerCounts && RE <= (1 << 30) && (per_layer == 1 || (!in_place && RE <= most));
+// not rewritten in place.  Its lead shrinks with every entry, sooner where entries are loaded one by one (`vec` is false: the
+// table's length or address is no multiple of 16 bytes), where there are few query blocks, whose histograms the gather launches
+// add up in no time, and where the query blocks lie further apart than the 16-bit table reaches, which a pool of more
+// than kLdsIds blocks allows.  Gather and finalize launches / this kernel, us, one layer:
+//   16 bytes at a time  500 query blocks  131 072 entries 21.5 / 19.2   far apart 98 304 27.2 / 24.5, 131 072 28.5 / 30.4
+//                       4                 81 920 13.0 / 13.5, 114 688 13.7 / 16.6   16   81 920 13.8 / 13.3, 114 688 14.6 / 15.7
+//   one by one          500               81 920 18.6 / 18.9, 98 304 19.9 / 21.4    64   49 152 14.0 / 13.5, 57 344 14.3 / 15.2
+//                       2                 32 768 12.5 / 11.0, 49 152 12.7 / 13.0, 131 072 14.5 / 24.2
+inline int64_t layer_kernel_entries(int64_t Q, int64_t NB, bool vec) {
+  if (vec) return Q < 32 ? 81920 : NB > kLdsIds ? 98304 : kLayerEntries;
+  return Q < 16 ? 32768 : Q < 256 ? 49152 : 81920;
+}
+inline bool layer_kernel_fits(int64_t Q, int64_t RE, int64_t NB, int64_t rc_chunk, int64_t per_layer, bool in_place, bool vec) {
+  return Q <= kLdsTargets && rc_chunk <= kLayerCounts && RE <= (1 << 30) &&
+         (per_layer == 1 || (!in_place && RE <= layer_kernel_entries(Q, NB, vec)));
 }
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -724,7 +733,7 @@ rc_status remap_run(const char* who, int32_t n_layers, const int32_t* tables_in,
   const bool vec = RE % 4 == 0 && aligned16(tables_in) && aligned16(tables_out);
   const int rc_vec = NB % 4 == 0 && aligned16(refcount_in) && aligned16(refcount_out);
 
-  if (layer_kernel_fits(Q, RE, NB, rc_chunk, G, tables_in == tables_out)) {
+  if (layer_kernel_fits(Q, RE, NB, rc_chunk, G, tables_in == tables_out, vec)) {
     const unsigned wgs = (unsigned)((n_layers + 7) / 8 * 8 * G);
     if (vec)
       remap_layer_kernel<true><<<wgs, kGatherThreads, 0, st>>>(tables_in, tables_out, (int)RE, (int)chunk, query_ids, pool_ids,

@@ -18,6 +18,13 @@ pytestmark = pytest.mark.gpu
     (2, 30000, 33000, 4097, False, False),      # one query block more
     (1, 131072, 60000, 500, True, True),        # ids some 59 000 apart, a table too long for every workgroup to look them up
     (1, 131076, 60000, 500, False, True),
+    (1, 49151, 20000, 20, False, False),        # entries one by one: the longest table that every workgroup reads, and the next
+    (1, 49153, 20000, 20, False, False),
+    (1, 32769, 20000, 15, True, False),         # few query blocks
+    (2, 81919, 20000, 256, True, False),
+    (2, 81921, 20000, 256, True, False),
+    (1, 81920, 20000, 31, False, False),        # few query blocks, 16 bytes at a time
+    (1, 81924, 20000, 31, False, False),
     (130, 700, 15872, 40, True, False),         # a workgroup per layer, a full share of the counts
     (130, 701, 15873, 40, False, False),
 ])
