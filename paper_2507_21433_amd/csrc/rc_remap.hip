@@ -49,10 +49,10 @@ constexpr int64_t kLayerEntries = 131072;                             // entries
 // table's length or address is no multiple of 16 bytes), where there are few query blocks, whose histograms the gather launches
 // add up in no time, and where the query blocks lie further apart than the 16-bit table reaches, which a pool of more
 // than kLdsIds blocks allows.  Gather and finalize launches / this kernel, us, one layer:
-//   16 bytes at a time  500 query blocks  131 072 entries 21.5 / 19.2   far apart 98 304 27.2 / 24.5, 131 072 28.5 / 30.4
-//                       4                 81 920 13.0 / 13.5, 114 688 13.7 / 16.6   16   81 920 13.8 / 13.3, 114 688 14.6 / 15.7
-//   one by one          500               81 920 18.6 / 18.9, 98 304 19.9 / 21.4    64   49 152 14.0 / 13.5, 57 344 14.3 / 15.2
-//                       2                 32 768 12.5 / 11.0, 49 152 12.7 / 13.0, 131 072 14.5 / 24.2
+//   16 bytes at a time  500 query blocks  131 072 entries 21.4 / 19.0   far apart 98 304 27.2 / 24.5, 131 072 28.5 / 30.4
+//                       16                81 920 14.2 / 13.6, 114 688 15.6 / 16.8   4   81 920 13.6 / 13.8, 114 688 14.5 / 17.2
+//   one by one          500               81 920 18.7 / 19.0, 98 304 19.9 / 21.4    64  49 152 14.9 / 13.5, 65 536 16.0 / 16.1
+//                       16                49 152 14.1 / 13.4, 57 344 14.4 / 15.5    2   32 768 12.1 / 10.9, 49 152 12.4 / 13.0, 131 072 14.1 / 23.9
 inline int64_t layer_kernel_entries(int64_t Q, int64_t NB, bool vec) {
   if (vec) return Q < 32 ? 81920 : NB > kLdsIds ? 98304 : kLayerEntries;
   return Q < 16 ? 32768 : Q < 256 ? 49152 : 81920;
