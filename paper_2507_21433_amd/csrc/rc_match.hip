@@ -378,8 +378,22 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
   //    first): the texture unit takes a 1 KB wave load every 16 cycles, and a wave that issues
   //    its loads in one burst sits in that queue instead of feeding the matrix cores.
   // The scheduling barriers pin this order.
-  constexpr int SLOTS = 4 * TP, LPS = (LA + LB + SLOTS - 1) / SLOTS;
-  // One batch = the TP*TQ matrix instructions of a sub-step, row tile by row tile.  Between the
+  // Where the loads of a step stand (a slot is a row of a batch: TQ matrix instructions).  The query slice is waited for at
+  // the end of the step that asks for it, and the first of the workgroups that share it waits for memory, not for the L2: its
+  // last load should go out early.  The pool slice has a step more, and a burst of its loads holds the wave up (a compute
+  // unit has a limited number of lines on their way): they are spread evenly over the rest of the step.  Two query loads to
+  // a slot at 256 columns, all out after a quarter of the step and not after half of it: 64 layers x 4096 x 256, 8 heads 4337
+  // -> 4102 us, 16 heads 5863 -> 5581, per head 32 x 8192 x 512 16 545 -> 15 832, 16 x 8192 x 256 4762 -> 4672; most of that
+  // where a block's tensor is a power of two of bytes (7 and 9 heads: no change), whose slices crowd some channels.  Four
+  // to a slot: 1 to 3 % slower than that.  The cosine mode with several query tiles and the layer-mean mode keep one to a slot:
+  // their slices are asked for by more workgroups, the first of which leads by less, and the bunched loads cost them 0.5 to 1 %.
+  constexpr int SLOTS = 4 * TP;
+  constexpr int BPS = TQ == 5 || (TQ == 4 && MODE != 2 && !SHARED_POOL) ? 2 : 1;  // query loads to a slot
+  constexpr int LBS = LB / BPS;                                                 // slots of the query loads
+  constexpr int PSLOTS = SLOTS - LBS;                                           // the pool loads are spread over the others
+  // One batch = the TP*TQ matrix instructions of a sub-step, row tile by row tile, the columns there and back (what the
+  // clock is under matrix load depends on how many operand registers change from one instruction to the next: a loop
+  // of these instructions alone is 0.6 to 0.8 % faster that way, the launches here 0.1 to 0.4 %).  Between the
   // instructions of row tile i ride the reads of the next sub-step's fragments that belong to it
   // (A fragment i behind the first instruction, B fragment i behind the last) and the row's
   // share of the refill loads (in the middle): LDS reads and loads are spread evenly over the
@@ -388,21 +402,20 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
   // reads per sub-step: 5-7 % on the Q = 1024 workloads, 3-4 % in per-head mode, 1-2 % on cfg2.
   // The scalar bookkeeping of the two feeds (which slice comes next, from which tensor, into which
   // ring stage) and of the read stages rides in those rows too (`slot_work`), a few instructions per
-  // row, in the gap behind the instruction after the load's.  A wave issues one instruction every
+  // row, in the gap behind the instruction after the first load's.  A wave issues one instruction every
   // four cycles and a matrix instruction covers seven more issues; left at the end of the step the
   // bookkeeping sits between the last matrix instruction of one step and the first of the next,
   // some thirty scalar instructions with nothing to hide behind (measured: 200 of the 2400 cycles
-  // of a step).  Slot s is row s % TP of batch s / TP; the query loads are slots 0 .. LB-1, the
-  // pool loads slots LB .. LB+LA-1.  The pool feed moves on just before its loads, the query feed
-  // after its loads (for the next step), then the read stages of the next step.
+  // of a step).  Slot s is row s % TP of batch s / TP.  The pool feed moves on just before its
+  // loads, the query feed after its loads (for the next step), then the read stages of the next step.
   // FAST steps are those whose two feeds stay inside the phase (all but the last two of a phase):
   // the cursor just counts and the tensor does not change; the last two steps take the general code.
   static_assert(TQ <= 2 * TP, "B fragments j and j + TP are read behind row tile j");
-  static_assert(LPS == 1 || (LPS == 2 && LB % 2 == 0 && LA % 2 == 0 && TQ >= 4), "one load per slot, or two with instructions between");
-  static_assert(LB / LPS >= 2 && LB / LPS + 3 < SLOTS, "room for the bookkeeping slots");
+  static_assert(LB % BPS == 0 && (BPS == 1 || TQ >= 4), "one query load per slot, or two with instructions between");
+  static_assert(LA <= PSLOTS, "at most one pool load per slot");
+  static_assert(LBS >= 2 && LBS + 3 < SLOTS, "room for the bookkeeping slots");
   int rdA = 0, rdB = 0;                   // ring stages the current step reads
   const char *sA_next = s_ring, *sB_next = s_ring + SA * A_STAGE;
-  constexpr int LBS = LB / LPS;               // slots of the query loads
   constexpr int W0 = LBS >= 3 ? LBS - 3 : 0;  // first bookkeeping slot
   auto slot_work = [&](auto fast_tag, int slot) __attribute__((always_inline)) {
     constexpr bool FAST = decltype(fast_tag)::value;
@@ -434,23 +447,24 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
   auto batch = [&](auto fast_tag, const uint4 (&af)[TP], const uint4 (&bf)[TQ], int b, const char* sA, const char* sB,
                    int kk, uint4 (&naf)[TP], uint4 (&nbf)[TQ]) __attribute__((always_inline)) {
     const uint32_t c = (((uint32_t)(2 * kk) + (uint32_t)(lane >> 5)) ^ sw) * 16;
-    constexpr int JD = TQ > 1 ? TQ / 2 - 1 : 0;  // the refill load follows this instruction of the row ...
+    constexpr int JD = TQ > 1 ? TQ / 2 - 1 : 0;  // the (first) refill load follows this instruction of the row ...
     constexpr int JW = TQ > 2 ? JD + 1 : JD;     // ... the bookkeeping the next one, where the row has a gap to spare
 #pragma unroll
     for (int i = 0; i < TP; ++i) {
 #pragma unroll
       for (int j = 0; j < TQ; ++j) {
-        acc[i][j] = mfma<BF16>(af[i], bf[j], acc[i][j]);
+        const int jc = (i & 1) ? TQ - 1 - j : j;  // there and back: one operand stays from each instruction to the next
+        acc[i][jc] = mfma<BF16>(af[i], bf[jc], acc[i][jc]);
         if (j == 0) {
           naf[i] = *reinterpret_cast<const uint4*>(sA + fragA + i * 32 * kRowBytes + c);
           __builtin_amdgcn_sched_barrier(0);
         }
-        if (j == JD || (LPS == 2 && j == JD + 2)) {
-          const int n = (b * TP + i) * LPS + (j != JD);
-          if (n < LB)
-            dmaB(n);
-          else if (n < LB + LA)
-            dmaA(n - LB);
+        if (j == JD || (BPS == 2 && j == JD + 2)) {
+          const int slot = b * TP + i, n = slot - LBS;
+          if (slot < LBS)
+            dmaB(slot * BPS + (j != JD));
+          else if (j == JD && (n + 1) * LA / PSLOTS > n * LA / PSLOTS)
+            dmaA(n * LA / PSLOTS);
           __builtin_amdgcn_sched_barrier(0);
         }
         if (j == JW) {
