@@ -231,9 +231,7 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
   // the same moment, step after step.  The workgroups of the first round therefore start spread
   // in time by the position of their pool tile within the XCD's run of tiles (the query tiles of
   // one pool tile stay together: the second one finds the pool slice in the L2 only if it follows
-  // closely); later rounds inherit the spread.  Nothing else changes.  Measured on one box against
-  // an unspread start: 3 % faster with one query tile (Q = 256), 5 % in per-head mode (Q = 512),
-  // within 0.5 % with four query tiles (Q = 1024).
+  // closely); later rounds inherit the spread.  Nothing else changes.  How far, and what it gives: stagger_unit().
   if (round == 0 && (int)blockIdx.x < p.stagger_wgs)
     for (int i = 0; i < (((slot % p.chunk) / p.nqt) & 15) * p.stagger_unit; ++i) __builtin_amdgcn_s_sleep(16);
 
@@ -1244,7 +1242,14 @@ inline rc_status prepare_schedule(MatchParams& mp, unsigned grid, void* schedule
   clear_schedule_kernel<<<(n + 1023) / 1024 < 64 ? (n + 1023) / 1024 : 64, 1024, 0, st>>>(mp.ctr, n);
   return check_launch("rc_match_blocks(tile schedule)");
 }
-constexpr int kStaggerUnit = 6;  // x 1024 clocks per tile index, one to two pipeline steps (flat optimum between 3 and 8)
+// x 1024 clocks per tile index.  One query tile, and per head: two pipeline steps.  Several query tiles share a pool slice,
+// too, and its workgroups should not be far apart: half a step.  Us per launch at 0 / 1 / 2 / 3 / 6:
+//   one query tile       64 x 4096 x 256 4356 / - / 4231 / - / 4171
+//   block score          16 x 8192 x 512 3690 / 3671 / 3670 / 3677 / 3746   32 x 16384 x 1024 25 568 / 25 656 / 25 539 / 25 634 / 25 796
+//                        16 x 8000 x 1000 6787 / 6783 / 6803 / 6826 / 6927   30 x 3000 x 380 2229 / 2228 / 2231 / 2235 / 2266
+//   layer mean           8 x 8192 x 1024 3645 / 3651 / 3656 / 3678 / 3735   16 x 8192 x 512 3932 / 3918 / 3915 / 3904 / 3956
+//   per head             8 x 8192 x 1024, 32 tokens 7594 / 7586 / 7577 / 7565 / 7552   32 x 8192 x 512 15 957 / 16 004 / 15 942 / 15 987 / 15 994
+inline int stagger_unit(bool heads, int64_t nqt) { return nqt > 1 && !heads ? 2 : 6; }
 
 // Tile shape: with many queries a 128x128 accumulator tile per wave (all 256 accumulation registers
 // of a lane) in every mode.  What is carried across phases is kept out of the fp32 register budget: the
@@ -1757,7 +1762,7 @@ rc_status search_tiles(const TileSearch& a, const MatchPlan& plan) {
     mp.G = 1;
     mp.S = 1;
     mp.stagger_wgs = compute_units();
-    mp.stagger_unit = kStaggerUnit;
+    mp.stagger_unit = stagger_unit(mode == RC_SCORE_PER_HEAD_ALL, nqt);
     mp.vgrid = (int)virtual_grid(total);
     const unsigned grid = launch_grid((unsigned)mp.vgrid);
     if (rc_status s = prepare_schedule(mp, grid, static_cast<char*>(workspace) + plan_bytes(plan, L, P, Q) - schedule_bytes(total), st)) return s;
@@ -1958,7 +1963,7 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
     mp.G = ls.G;
     mp.S = 1;
     mp.stagger_wgs = compute_units();
-    mp.stagger_unit = kStaggerUnit;
+    mp.stagger_unit = stagger_unit(false, nqt);
     mp.vgrid = (int)virtual_grid(total);
     const unsigned grid = launch_grid((unsigned)mp.vgrid);
     if (rc_status s = prepare_schedule(mp, grid, nullptr, st)) return s;  // a group of layers per tile: few, long tiles
