@@ -278,10 +278,12 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
   // (MODE 1).  Step u of a phase reads 128 bytes per block at byte offset
   // head*256 + (u/2)*tok + (u%2)*128:  tok = 256 walks the flattened block, tok = H*256 walks
   // one head's [T][Dh] slice.
-  // MODE 3: one phase of (D/kBK)/(S/2) steps of the K tensor (shares 0 .. S/2-1) or of the V tensor
-  // (the others), consecutive slices but for the place where the walk starts.
+  // MODE 3: one phase of the K tensor (shares 0 .. S/2-1) or of the V tensor (the others), an S/2-th of its steps, give or take
+  // one: consecutive slices but for the place where the walk starts.
   // MODE 4: the two phases of head `split`, i.e. phases 2*split and 2*split + 1 of MODE 1.
-  const int sps = (MODE == 3) ? (D / kBK) / (p.S / 2) : !PER_HEAD ? (D / kBK) : (p.T * 2);
+  const int part = (MODE == 3) ? split % (p.S / 2) : 0;
+  const int part_first = (MODE == 3) ? D / kBK * part / (p.S / 2) : 0;
+  const int sps = (MODE == 3) ? D / kBK * (part + 1) / (p.S / 2) - part_first : !PER_HEAD ? (D / kBK) : (p.T * 2);
   const int nphase = (MODE == 3) ? 1 : (MODE == 4) ? 2 * split + 2 : !PER_HEAD ? 2 : 2 * p.H;
   const int ph_first = (MODE == 4) ? 2 * split : 0;
   const int tok = !PER_HEAD ? 256 : p.H * 256;
@@ -290,7 +292,7 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
   // pool blocks keep identical scores).  The shares of a tile are a power of two of KB apart: started together at
   // their first slices, all workgroups ask the same memory channels at the same time.  Measured with one layer of
   // 4096 blocks (16 shares of 4 KB): Q = 16 70 -> 53 us, Q = 100 63-78 -> 63 us; 8192 blocks 92-126 -> 96-111 us.
-  const uint32_t share_beg = (MODE == 3) ? (uint32_t)(split % (p.S / 2) * sps) * 128u : 0u;
+  const uint32_t share_beg = (uint32_t)part_first * 128u;
   const uint32_t share_end = share_beg + (uint32_t)sps * 128u;
   const uint32_t share_rot = (MODE == 3) ? (uint32_t)(split * kShareRotation % sps) * 128u : 0u;
   auto advance = [&](Cursor& c) {
@@ -1419,9 +1421,55 @@ inline int wide_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, in
   }
   return best;
 }
-// 192 and 256 columns cut every query count the 192 are used for into the same number of tiles.
+// The two rules above give a number of shares that divides the work evenly.  Block score and layer mean, up to a round of tiles, take
+// any even number instead (the shares of a tensor are a step longer or shorter) where the estimate below is 7 % less than for theirs:
+// a round of workgroups is filled better, and shares whose first slices are a power of two of KB apart crowd the same memory
+// channels.  What a launch of S shares per tile takes, in us: its rounds (of a last round of which a part r of the compute units has
+// work, idle + (1 - idle) r) times the steps of a share and what it takes to fill its pipeline and store, a time per workgroup for
+// the pass that adds it (the layer mean's reads a share's rows one layer after the other), and the launches behind.  One set of
+// constants per width of the tiles.  Fitted to 473 drawn shapes (1 to 64 layers, 64 to 16 384 blocks, 1 to 1024 queries) of which
+// every number of shares was timed: with this choice a shape takes 1.2 to 1.9 % longer than with its best number, and is 1.03 to 1.08
+// times as fast as with the rules above (a fraction of 0.01 of them, 0.02 at 256 columns, more than 3 % slower).  Us per call:
+//   1 x 3273 x 667 269 -> 175 (6 shares)   6 x 1347 x 456, 16 heads 793 -> 604 (6)   18 x 248 x 54, blocks of 32 tokens, 10 heads 189 -> 146
+//   (14)   9 x 405 x 134, 16 heads 203 -> 140 (14)   1 x 5942 x 139, 32 tokens 245 -> 181 (10)   2 x 9667 x 268, 16 heads 1036 -> 883 (8)
+//   layer mean 4 x 1273 x 261, 32 tokens, 16 heads 722 -> 555 (6)   whole tiles again: 2 x 4737 x 992 664 -> 596, 1 x 12000 x 800 721 -> 618
+struct ShareCost {
+  double step_us, fill_us, idle, wg_us, mean_wg_us, launch_us;
+};
+inline double shares_us(const ShareCost& c, bool mean, int64_t wgs, int64_t steps, int S) {
+  const double part = (double)(wgs % kSplitComputeUnits) / kSplitComputeUnits;
+  const double rounds = (double)(wgs / kSplitComputeUnits) + (part > 0.0 ? c.idle + (1.0 - c.idle) * part : 0.0);
+  return rounds * (2.0 * (double)steps / S * c.step_us + c.fill_us) + (double)wgs * (c.wg_us + (mean ? c.mean_wg_us : 0.0)) + c.launch_us;
+}
+inline int block_split_count(bool mean, int64_t L, int64_t P, int64_t Q, int T, int H) {
+  if (P <= 0 || Q <= 0 || L <= 0) return 1;
+  const bool narrow = Q <= kMidTile.bq;
+  const int even = narrow ? narrow_split_count(RC_SCORE_BLOCK, L, P, Q, T, H) : wide_split_count(RC_SCORE_BLOCK, L, P, Q, T, H);
+  const int bq = share_columns(Q);
+  const int64_t tiles = L * ((P + 255) / 256) * ((Q + bq - 1) / bq), steps = (int64_t)T * H * 128 / kBK;  // of a tensor
+  if (tiles > kSplitComputeUnits) return even;
+  constexpr ShareCost costs[4] = {{1.14, 9.0, 0.54, 0.010, 0.031, 12.0},
+                                  {1.30, 16.0, 0.54, 0.006, 0.036, 12.0},
+                                  {1.45, 22.3, 0.56, 0.009, 0.050, 15.0},
+                                  {1.785, 17.3, 0.45, 0.097, 0.077, 11.0}};
+  const ShareCost& cost = costs[bq / 64 - 1];
+  // whole tiles: by tile_choice, or as one share that is neither added nor another launch; the layer mean takes a fifth longer
+  const double whole = (mean ? 1.2 : 1.0) * (narrow ? shares_us(cost, false, tiles, steps, 1) - cost.launch_us + 6.0
+                                                    : 2.0 * (double)steps * tile_choice(RC_SCORE_BLOCK, L, P, Q).step_us + 8.0);
+  int best = even;
+  double best_us = 0.93 * (even > 1 ? shares_us(cost, mean, tiles * even, steps, even) : whole);
+  for (int half = 1; steps / half >= 8 && tiles * 2 * half <= 2048; ++half) {  // 8 steps of a share, 512 MB for all of them
+    const double us = shares_us(cost, mean, tiles * 2 * half, steps, 2 * half);
+    if (us < best_us) {
+      best = 2 * half;
+      best_us = us;
+    }
+  }
+  return whole < best_us ? 1 : best;
+}
 inline int split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
   if (P <= 0 || Q <= 0 || L <= 0) return 1;
+  if (mode == RC_SCORE_BLOCK) return block_split_count(false, L, P, Q, T, H);
   return Q <= kMidTile.bq ? narrow_split_count(mode, L, P, Q, T, H) : wide_split_count(mode, L, P, Q, T, H);
 }
 
@@ -1546,7 +1594,7 @@ inline size_t mean_floor_bytes(int L, int64_t P, int64_t Q, int T, int H) {
 }
 // Shares per tile of a call with `avail` bytes, at least mean_floor_bytes(); 1 = whole tiles.
 inline int mean_split_count(int L, int64_t P, int64_t Q, int T, int H, size_t avail) {
-  const int S = split_count(RC_SCORE_BLOCK, L, P, Q, T, H);
+  const int S = block_split_count(true, L, P, Q, T, H);
   return mean_plan_bytes(S, L, P, Q) <= avail ? S : wide_split_count(RC_SCORE_BLOCK, L, P, Q, T, H);
 }
 
