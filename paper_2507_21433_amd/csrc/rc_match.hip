@@ -80,6 +80,20 @@ struct MatchParams {
   int stagger_unit;  // ... start (tile % 16) * stagger_unit * 1024 clocks late
 };
 
+// The value that lane N of a lane's 16 holds.
+template <int N>
+__device__ __forceinline__ float row_bcast(float v) {
+  constexpr int kRowNewBcast = 0x150;  // DPP control: lane 0 of the row of 16, and so on
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), kRowNewBcast + N, 0xf, 0xf, true));
+}
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>());
+    static_for<N, I + 1>(f);
+  }
+}
+
 // Position in the reduction: phase ph (tensor = ph & 1, head = ph >> 1), step u of the phase.
 struct Cursor {
   int u, ph;
@@ -554,12 +568,41 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
   // tile i: asked for group by group, every group paid a memory round trip of its own with nothing
   // to do meanwhile (16 per phase end; in per-head mode, with 16 phase ends per tile, a fifth of
   // the launch).
+  // Per head a block's norms lie a head count apart, and loads of one value per row (96 or 128 of a wave per phase end) keep the
+  // texture unit busy for longer than the arithmetic takes.  BY_LANE: a half-wave needs the factors of 16 rows of a row tile; every
+  // lane loads and forms those of one, the row of register lane % 16, and each use reads it from that lane of its own 16
+  // (row_bcast, which costs no instruction of its own).  192 columns: 29 layers x 5983 x 169 2830 -> 2529 us, 40 x 3000 x 190, 10 heads
+  // 2560 -> 2332; 320: 50 x 2158 x 259, 16 heads 5944 -> 5625.  Not at 256 columns, where the steps wait for slices by the time
+  // that the phase ends save (32 x 8192 x 512, 32 tokens 16 195 -> 16 410, 18 x 8262 x 686, 16 heads 15 007 -> 15 671), nor at 64 and
+  // 128, where the pool stream is the limit (+1 %).
+  constexpr bool BY_LANE = MODE == 1 && (BQ == 192 || BQ == 320);
   struct RowScales {
-    f32x4 rp[4], fp[4];
+    f32x4 rp[BY_LANE ? 1 : 4], fp[BY_LANE ? 1 : 4];
   };
   auto row_scales = [&](int i, int head, RowScales& r) {
+    if constexpr (BY_LANE) {
+      const int o = (p0 + row_of(i, (lane >> 2) & 3) + (lane & 3)) * nh * 4;
+      const float ksq = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(nPk, o, head * 4, 0));
+      const float vsq = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(nPv, o, head * 4, 0));
+      float ratio, av;
+      norm_factors(ksq, vsq, ratio, av);
+      r.rp[0][0] = ratio;
+      r.fp[0][0] = av;
+    } else {
 #pragma unroll
-    for (int g = 0; g < 4; ++g) pool_scales(row_of(i, g), head, r.rp[g], r.fp[g]);
+      for (int g = 0; g < 4; ++g) pool_scales(row_of(i, g), head, r.rp[g], r.fp[g]);
+    }
+  };
+  // of register n = 4 * g + e of a row tile
+  auto rp_of = [&](const RowScales& r, auto n) __attribute__((always_inline)) {
+    constexpr int N = decltype(n)::value;
+    if constexpr (BY_LANE) return row_bcast<N>(r.rp[0][0]);
+    else return (float)r.rp[N >> 2][N & 3];
+  };
+  auto fp_of = [&](const RowScales& r, auto n) __attribute__((always_inline)) {
+    constexpr int N = decltype(n)::value;
+    if constexpr (BY_LANE) return row_bcast<N>(r.fp[0][0]);
+    else return (float)r.fp[N >> 2][N & 3];
   };
   // walk the row tiles with the factors of the next one in flight: body(i, factors of row tile i)
   auto for_row_tiles = [&](int head, auto&& body) __attribute__((always_inline)) {
@@ -580,12 +623,11 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
     float rq[TQ], fq[TQ];
     query_scales(head, rq, fq);
     for_row_tiles(head, [&](int i, const RowScales& rs) __attribute__((always_inline)) {
+      static_for<16>([&](auto n) __attribute__((always_inline)) {
+        const float rp = rp_of(rs, n);
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int j = 0; j < TQ; ++j)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[i][j][4 * g + e] *= rq[j] * rs.rp[g][e];
+        for (int j = 0; j < TQ; ++j) acc[i][j][decltype(n)::value] *= rq[j] * rp;
+      });
     });
   };
 
@@ -607,20 +649,20 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
     float rq[TQ], fq[TQ];
     query_scales(head, rq, fq);
     for_row_tiles(head, [&](int i, const RowScales& rs) __attribute__((always_inline)) {
+      static_for<8>([&](auto pair) __attribute__((always_inline)) {
+        constexpr int n = 2 * decltype(pair)::value;
+        const float fp0 = fp_of(rs, std::integral_constant<int, n>()), fp1 = fp_of(rs, std::integral_constant<int, n + 1>());
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int j = 0; j < TQ; ++j)
-#pragma unroll
-          for (int e = 0; e < 4; e += 2) {
-            const float s0 = acc[i][j][4 * g + e] * (fq[j] * rs.fp[g][e]), s1 = acc[i][j][4 * g + e + 1] * (fq[j] * rs.fp[g][e + 1]);
-            // the hardware's conversion to signed normalised 16 bit: clamp to [-1, 1], times 32767, round to nearest
-            const i16x2 nw = quantise_pair(s0, s1);
-            int& slot = smin[SM ? i : 0][SM ? j : 0][2 * g + (e >> 1)];
-            slot = __builtin_bit_cast(int, __builtin_elementwise_min(__builtin_bit_cast(i16x2, slot), nw));
-            acc[i][j][4 * g + e] = 0.f;
-            acc[i][j][4 * g + e + 1] = 0.f;
-          }
+        for (int j = 0; j < TQ; ++j) {
+          const float s0 = acc[i][j][n] * (fq[j] * fp0), s1 = acc[i][j][n + 1] * (fq[j] * fp1);
+          // the hardware's conversion to signed normalised 16 bit: clamp to [-1, 1], times 32767, round to nearest
+          const i16x2 nw = quantise_pair(s0, s1);
+          int& slot = smin[SM ? i : 0][SM ? j : 0][n >> 1];
+          slot = __builtin_bit_cast(int, __builtin_elementwise_min(__builtin_bit_cast(i16x2, slot), nw));
+          acc[i][j][n] = 0.f;
+          acc[i][j][n + 1] = 0.f;
+        }
+      });
     });
   };
 
@@ -863,7 +905,7 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             float sc;
-            if (MODE == 0)
+            if constexpr (MODE == 0)
               sc = acc[i][j][4 * g + e] * (fq[j] * cur.fp[g][e]) + bcur.b[g][e];
             else
               sc = (float)__builtin_bit_cast(i16x2, smin[SM ? i : 0][SM ? j : 0][2 * g + (e >> 1)])[e & 1] / 32767.f + bcur.b[g][e];
