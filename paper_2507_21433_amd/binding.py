@@ -5,6 +5,7 @@ PyTorch supplies device memory and the current stream.  There is no CPU
 fallback: if ``librc.so`` has not been built the first call raises.
 """
 import ctypes
+import functools
 import os
 
 import torch
@@ -108,8 +109,9 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# The device is asked for below torch.cuda's check that CUDA is initialised: the tensors at hand are on it.
 def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dtype_code(t):
@@ -120,11 +122,11 @@ def _dtype_code(t):
     raise TypeError(f"KV dtype {t.dtype} (fp16 or bf16 only)")
 
 
-def _layout(t):
+def _layout(t, shape=None, s=None):
     """(L, T, H, Dh, dtype code, layer stride) of a KV tensor shaped [L][n][T][H][Dh] whose inner four dims are contiguous."""
-    assert t.dim() == 5, "KV tensors are [L][n][T][H][Dh]"
-    L, n, T, H, Dh = t.shape
-    s = t.stride()
+    shape, s = t.shape if shape is None else shape, t.stride() if s is None else s
+    assert len(shape) == 5, "KV tensors are [L][n][T][H][Dh]"
+    L, n, T, H, Dh = shape
     block = T * H * Dh
     # the plain strides first: a view of layer 0 to ask for is_contiguous() costs more than the rest of this
     if L == 0 or s[4] != 1 or s[3] != Dh or s[2] != H * Dh or s[1] != block:
@@ -137,6 +139,21 @@ def kv_desc(t):
     return KvDesc(*_layout(t))
 
 
+# Layouts that calls come with again and again: a descriptor by its values, never changed once made.
+_desc = functools.lru_cache(maxsize=64)(KvDesc)
+
+
+def _kv_pair(k, v, alike=False):
+    """(shape of k, descriptor) of a K and a V tensor with the same layer stride (alike: and shape and type).  A V tensor just like
+    K needs no second look."""
+    shape, strides = k.shape, k.stride()
+    d = _desc(*_layout(k, shape, strides))
+    if v.stride() != strides or v.dtype != k.dtype or v.shape != shape:
+        assert not alike or (v.shape == shape and v.dtype == k.dtype)
+        assert _layout(v)[5] == d.layer_stride
+    return shape, d
+
+
 def _dev(*ts):
     for t in ts:
         assert t is None or t.is_cuda, "device tensors only"
@@ -145,9 +162,7 @@ def _dev(*ts):
 def rc_block_norms(k, v, mode=RC_SCORE_BLOCK, k_sqnorm=None, v_sqnorm=None):
     """Squared norms of every block: returns (k_sqnorm, v_sqnorm), fp32 [L][n] or [L][n][H]."""
     _dev(k, v)
-    d = kv_desc(k)
-    assert v.shape == k.shape and v.dtype == k.dtype and _layout(v)[5] == d.layer_stride
-    L, n, H = k.shape[0], k.shape[1], k.shape[3]
+    (L, n, _, H, _), d = _kv_pair(k, v, alike=True)
     shape = (L, n) if mode == RC_SCORE_BLOCK else (L, n, H)
     if k_sqnorm is None:
         k_sqnorm = torch.empty(shape, dtype=torch.float32, device=k.device)
@@ -167,9 +182,8 @@ def rc_match_blocks(kq, vq, q_ksq, q_vsq, kp, vp, p_ksq, p_vsq, pool_live, tau, 
                     want_second=True, workspace=None, out=None):
     """Best live pool block per query.  Returns dict(best_idx, best_score, match_idx, second_score)."""
     _dev(kq, vq, kp, vp, q_ksq, q_vsq, p_ksq, p_vsq, pool_live)
-    qd, pd = kv_desc(kq), kv_desc(kp)
-    assert _layout(vq)[5] == qd.layer_stride and _layout(vp)[5] == pd.layer_stride
-    L, Q, P = kq.shape[0], kq.shape[1], kp.shape[1]
+    (L, Q, *_), qd = _kv_pair(kq, vq)
+    (_, P, *_), pd = _kv_pair(kp, vp)
     for t in (q_ksq, q_vsq, p_ksq, p_vsq):
         assert t.dtype == torch.float32 and t.is_contiguous()
     if pool_live is not None:
@@ -268,9 +282,8 @@ def rc_match_blocks_layer_mean(kq, vq, q_ksq, q_vsq, kp, vp, p_ksq, p_vsq, pool_
                                workspace=None, out=None):
     """Nearest live pool block per query by the layer-mean distance.  Returns dict(best_idx, best_dist, match_idx, second_dist), [Q]."""
     _dev(kq, vq, kp, vp, q_ksq, q_vsq, p_ksq, p_vsq, pool_live)
-    qd, pd = kv_desc(kq), kv_desc(kp)
-    assert _layout(vq)[5] == qd.layer_stride and _layout(vp)[5] == pd.layer_stride
-    L, Q, P = kq.shape[0], kq.shape[1], kp.shape[1]
+    (L, Q, *_), qd = _kv_pair(kq, vq)
+    (_, P, *_), pd = _kv_pair(kp, vp)
     for t, n in ((q_ksq, Q), (q_vsq, Q), (p_ksq, P), (p_vsq, P)):
         assert t.dtype == torch.float32 and t.is_contiguous() and t.shape == (L, n)
     if pool_live is not None:
@@ -324,9 +337,8 @@ def rc_pool_admit(kq, vq, q_ksq, q_vsq, kp, vp, p_ksq, p_vsq, pool_live, match_i
 
     Returns dict(slot_of_query int32 [Q], n_admitted int32 [1])."""
     _dev(kq, vq, kp, vp, q_ksq, q_vsq, p_ksq, p_vsq, pool_live, match_idx)
-    qd, pd = kv_desc(kq), kv_desc(kp)
-    assert _layout(vq)[5] == qd.layer_stride and _layout(vp)[5] == pd.layer_stride
-    L, Q, P, H = kq.shape[0], kq.shape[1], kp.shape[1], kq.shape[3]
+    (L, Q, _, H, _), qd = _kv_pair(kq, vq)
+    (_, P, *_), pd = _kv_pair(kp, vp)
     qs, ps = ((L, Q), (L, P)) if mode == RC_SCORE_BLOCK else ((L, Q, H), (L, P, H))
     for t, sh in ((q_ksq, qs), (q_vsq, qs), (p_ksq, ps), (p_vsq, ps)):
         assert t.dtype == torch.float32 and t.is_contiguous() and tuple(t.shape) == sh
@@ -347,9 +359,8 @@ def rc_pool_admit(kq, vq, q_ksq, q_vsq, kp, vp, p_ksq, p_vsq, pool_live, match_i
 def rc_candidate_distances(kq, vq, kp, vp, pool_live, cand, threshold, workspace=None, out=None):
     """Layer-mean distance of the listed pairs, cand [Q][C].  Returns dict(dist [Q][C], best_idx, best_dist, match_idx)."""
     _dev(kq, vq, kp, vp, pool_live, cand)
-    qd, pd = kv_desc(kq), kv_desc(kp)
-    assert _layout(vq)[5] == qd.layer_stride and _layout(vp)[5] == pd.layer_stride
-    Q, P = kq.shape[1], kp.shape[1]
+    (_, Q, *_), qd = _kv_pair(kq, vq)
+    (_, P, *_), pd = _kv_pair(kp, vp)
     assert cand.dtype == torch.int32 and cand.dim() == 2 and cand.shape[0] == Q and cand.is_contiguous()
     C = cand.shape[1]
     if pool_live is not None:
