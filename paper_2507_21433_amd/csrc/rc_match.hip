@@ -1483,13 +1483,18 @@ inline double shares_us(const ShareCost& c, bool mean, int64_t wgs, int64_t step
   const double rounds = (double)(wgs / kSplitComputeUnits) + (part > 0.0 ? c.idle + (1.0 - c.idle) * part : 0.0);
   return rounds * (2.0 * (double)steps / S * c.step_us + c.fill_us) + (double)wgs * (c.wg_us + (mean ? c.mean_wg_us : 0.0)) + c.launch_us;
 }
+// The number of the two rules above.  192 and 256 columns cut every query count the 192 are used for into the same number of tiles.
+inline int alike_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
+  if (P <= 0 || Q <= 0 || L <= 0) return 1;
+  return Q <= kMidTile.bq ? narrow_split_count(mode, L, P, Q, T, H) : wide_split_count(mode, L, P, Q, T, H);
+}
 inline int block_split_count(bool mean, int64_t L, int64_t P, int64_t Q, int T, int H) {
   if (P <= 0 || Q <= 0 || L <= 0) return 1;
   const bool narrow = Q <= kMidTile.bq;
-  const int even = narrow ? narrow_split_count(RC_SCORE_BLOCK, L, P, Q, T, H) : wide_split_count(RC_SCORE_BLOCK, L, P, Q, T, H);
+  const int alike = alike_split_count(RC_SCORE_BLOCK, L, P, Q, T, H);
   const int bq = share_columns(Q);
   const int64_t tiles = L * ((P + 255) / 256) * ((Q + bq - 1) / bq), steps = (int64_t)T * H * 128 / kBK;  // of a tensor
-  if (tiles > kSplitComputeUnits) return even;
+  if (tiles > kSplitComputeUnits) return alike;
   constexpr ShareCost costs[4] = {{1.14, 9.0, 0.54, 0.010, 0.031, 12.0},
                                   {1.30, 16.0, 0.54, 0.006, 0.036, 12.0},
                                   {1.45, 22.3, 0.56, 0.009, 0.050, 15.0},
@@ -1498,8 +1503,8 @@ inline int block_split_count(bool mean, int64_t L, int64_t P, int64_t Q, int T, 
   // whole tiles: by tile_choice, or as one share that is neither added nor another launch; the layer mean takes a fifth longer
   const double whole = (mean ? 1.2 : 1.0) * (narrow ? shares_us(cost, false, tiles, steps, 1) - cost.launch_us + 6.0
                                                     : 2.0 * (double)steps * tile_choice(RC_SCORE_BLOCK, L, P, Q).step_us + 8.0);
-  int best = even;
-  double best_us = 0.93 * (even > 1 ? shares_us(cost, mean, tiles * even, steps, even) : whole);
+  int best = alike;
+  double best_us = 0.93 * (alike > 1 ? shares_us(cost, mean, tiles * alike, steps, alike) : whole);
   for (int half = 1; steps / half >= 8 && tiles * 2 * half <= 2048; ++half) {  // 8 steps of a share, 512 MB for all of them
     const double us = shares_us(cost, mean, tiles * 2 * half, steps, 2 * half);
     if (us < best_us) {
@@ -1510,9 +1515,7 @@ inline int block_split_count(bool mean, int64_t L, int64_t P, int64_t Q, int T, 
   return whole < best_us ? 1 : best;
 }
 inline int split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
-  if (P <= 0 || Q <= 0 || L <= 0) return 1;
-  if (mode == RC_SCORE_BLOCK) return block_split_count(false, L, P, Q, T, H);
-  return Q <= kMidTile.bq ? narrow_split_count(mode, L, P, Q, T, H) : wide_split_count(mode, L, P, Q, T, H);
+  return mode == RC_SCORE_BLOCK ? block_split_count(false, L, P, Q, T, H) : alike_split_count(mode, L, P, Q, T, H);
 }
 
 struct SplitLayout {
@@ -1538,7 +1541,8 @@ inline SplitLayout split_layout(int S, int64_t L, int64_t P, int64_t Q) {
 // ---- What a call computes depends on the workspace it is given as well: the plan of the rules above needs from tens of
 // KB (whole tiles) to 512 MB (shares), up and down with Q and P, and an engine that keeps one workspace for all its calls
 // must not be refused for a small step.  So every call takes a workspace of `floor` bytes, the need of the plan with
-// 256-column shares by wide_split_count or else with pool tiles of 256 rows, and uses the faster plan where it fits.
+// 256-column shares by wide_split_count or else with pool tiles of 256 rows, and uses the faster plan where it fits, the plan with
+// shares that are all alike where only that does.
 struct MatchPlan {
   int S;         // shares per tile, 1 = whole tiles of shape ts
   TileShape ts;
@@ -1566,6 +1570,7 @@ inline size_t plan_bytes(const MatchPlan& p, int64_t L, int64_t P, int64_t Q) {
 // The plan of a call with `avail` bytes, at least match_floor_bytes().
 inline MatchPlan match_plan(int mode, int64_t L, int64_t P, int64_t Q, int T, int H, size_t avail) {
   MatchPlan p = {split_count(mode, L, P, Q, T, H), tile_for(mode, L, P, Q)};
+  if (plan_bytes(p, L, P, Q) > avail) p.S = alike_split_count(mode, L, P, Q, T, H);
   if (plan_bytes(p, L, P, Q) > avail) p = {wide_split_count(mode, L, P, Q, T, H), floor_tile(Q)};
   return p;
 }
@@ -1636,8 +1641,9 @@ inline size_t mean_floor_bytes(int L, int64_t P, int64_t Q, int T, int H) {
 }
 // Shares per tile of a call with `avail` bytes, at least mean_floor_bytes(); 1 = whole tiles.
 inline int mean_split_count(int L, int64_t P, int64_t Q, int T, int H, size_t avail) {
-  const int S = block_split_count(true, L, P, Q, T, H);
-  return mean_plan_bytes(S, L, P, Q) <= avail ? S : wide_split_count(RC_SCORE_BLOCK, L, P, Q, T, H);
+  for (const int S : {block_split_count(true, L, P, Q, T, H), alike_split_count(RC_SCORE_BLOCK, L, P, Q, T, H)})
+    if (mean_plan_bytes(S, L, P, Q) <= avail) return S;
+  return wide_split_count(RC_SCORE_BLOCK, L, P, Q, T, H);
 }
 
 template <bool BF16>

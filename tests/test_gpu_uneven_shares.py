@@ -10,6 +10,7 @@ from paper_2507_21433_amd import synth
 from tests import parity, paths
 from tests.test_gpu_layer_mean import gpu_layer_mean, shared_live
 from tests.test_gpu_parity import run_gpu_match
+from tests.test_workspace import guarded, search
 
 pytestmark = pytest.mark.gpu
 
@@ -44,6 +45,21 @@ def test_block_score(oracle, L, T, H, P, Q):
                        pr["live"].cpu().numpy(), w.tau, want_scores=True)
     parity.check_match(g, orc, w.tau, parity.score_lookup(orc["scores"], g["best_idx"]))
     assert (g["best_idx"][:, 0] == 7).all() and np.array_equal(g["best_score"][:, 0], g["second_score"][:, 0])
+
+
+@pytest.mark.parametrize("L,T,H,P,Q", [(3, 16, 5, 1300, 140), (2, 16, 5, 1300, 513), (20, 32, 8, 1226, 13)])
+def test_in_a_workspace_with_no_room_for_them(oracle, L, T, H, P, Q):
+    floor, full = paths.needed(rc.lib(), 0, L, T, H, P, Q), paths.size(rc.lib(), 0, L, T, H, P, Q)
+    print(f"[gpu-case] least workspace L={L} T={T} H={H} P={P} Q={Q}: {floor} of {full}", flush=True)
+    assert floor < full
+    w = synth.scaled(synth.WORKLOADS[2], name="uneven", L=L, P=P, Q=Q, T=T, H=H, planted_frac=0.3, R=1, E=P + Q, seed=9150 + P)
+    pr = synth.make_problem(w, "cuda:0")
+    orc = oracle.match(0, 0, *(synth.bits(pr[k]) for k in ("kq", "vq", "kp", "vp")), pr["live"].cpu().numpy(), w.tau, want_scores=True)
+    for nbytes in (floor, (floor + full) // 32 * 16, full):
+        mem, ws = guarded(nbytes)
+        got = search(pr, w, ws)
+        assert (mem[nbytes:] == 0xA5).all(), "written past the workspace"
+        parity.check_match(got, orc, w.tau, parity.score_lookup(orc["scores"], got["best_idx"]))
 
 
 @pytest.mark.parametrize("L,T,H,P,Q", [(20, 32, 8, 1226, 13), (7, 16, 5, 1300, 140), (7, 16, 5, 520, 300)])
