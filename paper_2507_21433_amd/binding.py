@@ -144,12 +144,14 @@ _desc = functools.lru_cache(maxsize=64)(KvDesc)
 
 
 def _kv_pair(k, v, alike=False):
-    """(shape of k, descriptor) of a K and a V tensor with the same layer stride (alike: and shape and type).  A V tensor just like
-    K needs no second look."""
+    """(shape of k, descriptor) of a K and a V tensor.  The kernels read V by K's descriptor and number of blocks: V has to be of
+    the same type, block shape and layer stride, with K's layers and blocks at least (alike: the same shape).  A V tensor just
+    like K needs no second look."""
     shape, strides = k.shape, k.stride()
     d = _desc(*_layout(k, shape, strides))
     if v.stride() != strides or v.dtype != k.dtype or v.shape != shape:
-        assert not alike or (v.shape == shape and v.dtype == k.dtype)
+        assert v.dtype == k.dtype and v.shape[2:] == shape[2:], "K and V of one type and block shape"
+        assert v.shape == shape if alike else v.shape[0] >= shape[0] and v.shape[1] >= shape[1], "V of K's layers and blocks"
         assert _layout(v)[5] == d.layer_stride
     return shape, d
 
