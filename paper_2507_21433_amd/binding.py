@@ -257,8 +257,8 @@ def rc_remap_block_table_static(tables, query_ids, pool_ids, match_idx, P, NB, r
 def rc_score_candidates(kq, vq, q_ksq, q_vsq, kp, vp, p_ksq, p_vsq, pool_live, cand, tau, mode=RC_SCORE_BLOCK, out=None):
     """Scores of the listed candidates [L][Q][C].  Returns dict(scores, best_idx, best_score, match_idx)."""
     _dev(kq, vq, kp, vp, q_ksq, q_vsq, p_ksq, p_vsq, pool_live, cand)
-    qd, pd = kv_desc(kq), kv_desc(kp)
-    L, Q, P = kq.shape[0], kq.shape[1], kp.shape[1]
+    (L, Q, *_), qd = _kv_pair(kq, vq)
+    (_, P, *_), pd = _kv_pair(kp, vp)
     assert cand.dtype == torch.int32 and cand.dim() == 3 and cand.shape[:2] == (L, Q) and cand.is_contiguous()
     C = cand.shape[2]
     if pool_live is not None:

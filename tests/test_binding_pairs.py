@@ -48,6 +48,7 @@ def calls(kq, vq, kp, vp):
         "rc_match_blocks": lambda: rc.rc_match_blocks(kq, vq, *norm, live, 0.9),
         "rc_match_blocks_layer_mean": lambda: rc.rc_match_blocks_layer_mean(kq, vq, *norm, live[0], 0.9),
         "rc_pool_admit": lambda: rc.rc_pool_admit(kq, vq, *norm, live[0], ids[0, :, 0].contiguous()),
+        "rc_score_candidates": lambda: rc.rc_score_candidates(kq, vq, *norm, live, ids, 0.9),
         "rc_candidate_distances": lambda: rc.rc_candidate_distances(kq, vq, kp, vp, live[0], ids[0], 0.9),
     }
 
@@ -68,6 +69,15 @@ def test_a_value_tensor_that_its_key_tensor_does_not_describe_is_refused(library
     for vq, vp in ((WRONG[what](Q), blocks(P)), (blocks(Q), WRONG[what](P))):
         with pytest.raises(AssertionError):
             calls(kq, vq, kp, vp)[entry]()
+    assert library.calls == []
+
+
+def test_listed_candidates_of_a_value_tensor_with_another_layer_stride_are_refused(library):
+    kq, kp = blocks(Q), blocks(P)
+    for vq, vp in ((blocks(Q, room=9), blocks(P)), (blocks(Q), blocks(P, room=9))):
+        for entry in ("rc_score_candidates", "rc_candidate_distances"):
+            with pytest.raises(AssertionError):
+                calls(kq, vq, kp, vp)[entry]()
     assert library.calls == []
 
 
