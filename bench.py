@@ -28,8 +28,8 @@ PEAK_HBM_GBS = 8000.0
 # The table names the kernel source it was measured on; it is ignored when that source has changed.
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 KERNEL_SOURCES = ("paper_2507_21433_amd/csrc/rc_match.hip", "paper_2507_21433_amd/csrc/rc_few.hip",
-                  "paper_2507_21433_amd/csrc/rc_tile.hpp", "paper_2507_21433_amd/csrc/rc_select.hpp",
-                  "paper_2507_21433_amd/csrc/rc_common.hpp")
+                  "paper_2507_21433_amd/csrc/rc_match_plan.hpp", "paper_2507_21433_amd/csrc/rc_tile.hpp",
+                  "paper_2507_21433_amd/csrc/rc_select.hpp", "paper_2507_21433_amd/csrc/rc_common.hpp")
 
 
 def log(msg):

@@ -33,8 +33,8 @@ import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 KERNEL_SOURCES = ("paper_2507_21433_amd/csrc/rc_match.hip", "paper_2507_21433_amd/csrc/rc_few.hip",
-                  "paper_2507_21433_amd/csrc/rc_tile.hpp", "paper_2507_21433_amd/csrc/rc_select.hpp",
-                  "paper_2507_21433_amd/csrc/rc_common.hpp")
+                  "paper_2507_21433_amd/csrc/rc_match_plan.hpp", "paper_2507_21433_amd/csrc/rc_tile.hpp",
+                  "paper_2507_21433_amd/csrc/rc_select.hpp", "paper_2507_21433_amd/csrc/rc_common.hpp")
 TILE_KERNELS = ("match_tile_kernel", "match_shape_kernel", "few_shares_kernel", "head_shares_kernel")   # one body, by tile shape; small problems
 COPY_KERNEL = "copyBuffer"
 CAL_BYTES = 1 << 30
