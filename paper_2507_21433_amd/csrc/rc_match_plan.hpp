@@ -131,6 +131,19 @@ inline int mean_columns(int64_t Q) {
   const int64_t n256 = (Q + 255) / 256, n192 = (Q + 191) / 192;
   return n192 * step_us[1][n192 < 3 ? n192 - 1 : 2] < 0.96 * n256 * step_us[0][n256 < 3 ? n256 - 1 : 2] ? kWideTile.bq : kBlockTile.bq;
 }
+// What its launch takes in us where every workgroup walks one layer (up to 1024 tiles): rounds, of a last round of which a part r of
+// the compute units has work idle + (1 - idle) r, times the steps of both tensors.  Fitted to 194 timed calls of up to 256 tiles,
+// 0.8 to 1.25 of it each.
+inline double mean_tiles_us(int64_t L, int64_t P, int64_t Q, int64_t steps) {
+  constexpr struct {
+    double step_us, idle;
+  } cost[4] = {{1.24, 0.53}, {1.40, 0.57}, {1.63, 0.55}, {1.70, 0.72}};
+  const int bq = mean_columns(Q);
+  const int64_t tiles = L * ((P + 255) / 256) * ((Q + bq - 1) / bq);
+  const auto& c = cost[bq / 64 - 1];
+  const double part = (double)(tiles % 256) / 256.0;
+  return ((double)(tiles / 256) + (part > 0.0 ? c.idle + (1.0 - c.idle) * part : 0.0)) * 2.0 * (double)steps * c.step_us + 8.0;
+}
 // byte offset of the selection partials inside the layer-mean workspace (after the sums: one
 // tile of 256 x bq floats per (group, pool tile, query tile))
 inline size_t layer_mean_part_offset(int groups, int64_t npt, int64_t nqt, int bq) {
@@ -263,9 +276,9 @@ inline int block_split_count(bool mean, int64_t L, int64_t P, int64_t Q, int T, 
                                   {1.45, 22.3, 0.56, 0.009, 0.050, 15.0},
                                   {1.785, 17.3, 0.45, 0.097, 0.077, 11.0}};
   const ShareCost& cost = costs[bq / 64 - 1];
-  // whole tiles: by tile_choice, or as one share that is neither added nor another launch; the layer mean takes a fifth longer
-  const double whole = (mean ? 1.2 : 1.0) * (narrow ? shares_us(cost, false, tiles, steps, 1) - cost.launch_us + 6.0
-                                                    : 2.0 * (double)steps * tile_choice(RC_SCORE_BLOCK, L, P, Q).step_us + 8.0);
+  const double whole = mean ? mean_tiles_us(L, P, Q, steps)
+                       : narrow ? shares_us(cost, false, tiles, steps, 1) - cost.launch_us + 6.0  // one share, neither added nor another launch
+                                : 2.0 * (double)steps * tile_choice(RC_SCORE_BLOCK, L, P, Q).step_us + 8.0;
   int best = alike;
   double best_us = 0.93 * (alike > 1 ? shares_us(cost, mean, tiles * alike, steps, alike) : whole);
   for (int half = 1; steps / half >= 8 && tiles * 2 * half <= 2048; ++half) {  // 8 steps of a share, 512 MB for all of them
