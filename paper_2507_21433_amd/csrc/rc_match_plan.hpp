@@ -244,7 +244,8 @@ inline int wide_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, in
 // a round of workgroups is filled better, and shares whose first slices are a power of two of KB apart crowd the same memory
 // channels.  What a launch of S shares per tile takes, in us: its rounds (of a last round of which a part r of the compute units has
 // work, idle + (1 - idle) r) times the steps of a share and what it takes to fill its pipeline and store, a time per workgroup for
-// the pass that adds it (the layer mean's reads a share's rows one layer after the other), and the launches behind.  One set of
+// the pass that adds it, one per layer and share for the layer mean's (a thread of it walks the shares of all layers: with a time
+// per workgroup in its place 2 x 5750 x 16 153 -> 182 us, 1 x 11475 x 20 156 -> 170), and the launches behind.  One set of
 // constants per width of the tiles.  Fitted to 473 drawn shapes (1 to 64 layers, 64 to 16 384 blocks, 1 to 1024 queries) of which
 // every number of shares was timed: with this choice a shape takes 1.2 to 1.9 % longer than with its best number, and is 1.03 to 1.08
 // times as fast as with the rules above (a fraction of 0.01 of them, 0.02 at 256 columns, more than 3 % slower).  Us per call:
@@ -252,12 +253,13 @@ inline int wide_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, in
 //   (14)   9 x 405 x 134, 16 heads 203 -> 140 (14)   1 x 5942 x 139, 32 tokens 245 -> 181 (10)   2 x 9667 x 268, 16 heads 1036 -> 883 (8)
 //   layer mean 4 x 1273 x 261, 32 tokens, 16 heads 722 -> 555 (6)   whole tiles again: 2 x 4737 x 992 664 -> 596, 1 x 12000 x 800 721 -> 618
 struct ShareCost {
-  double step_us, fill_us, idle, wg_us, mean_wg_us, launch_us;
+  double step_us, fill_us, idle, wg_us, mean_share_us, launch_us;
 };
-inline double shares_us(const ShareCost& c, bool mean, int64_t wgs, int64_t steps, int S) {
+// `layers`: of a layer mean, 0 for the block score
+inline double shares_us(const ShareCost& c, int64_t layers, int64_t wgs, int64_t steps, int S) {
   const double part = (double)(wgs % kSplitComputeUnits) / kSplitComputeUnits;
   const double rounds = (double)(wgs / kSplitComputeUnits) + (part > 0.0 ? c.idle + (1.0 - c.idle) * part : 0.0);
-  return rounds * (2.0 * (double)steps / S * c.step_us + c.fill_us) + (double)wgs * (c.wg_us + (mean ? c.mean_wg_us : 0.0)) + c.launch_us;
+  return rounds * (2.0 * (double)steps / S * c.step_us + c.fill_us) + (double)wgs * c.wg_us + (double)(layers * S) * c.mean_share_us + c.launch_us;
 }
 // The number of the two rules above.  192 and 256 columns cut every query count the 192 are used for into the same number of tiles.
 inline int alike_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
@@ -271,18 +273,19 @@ inline int block_split_count(bool mean, int64_t L, int64_t P, int64_t Q, int T, 
   const int bq = share_columns(Q);
   const int64_t tiles = L * ((P + 255) / 256) * ((Q + bq - 1) / bq), steps = (int64_t)T * H * 128 / kStepElements;  // of a tensor
   if (tiles > kSplitComputeUnits) return alike;
-  constexpr ShareCost costs[4] = {{1.14, 9.0, 0.54, 0.010, 0.031, 12.0},
-                                  {1.30, 16.0, 0.54, 0.006, 0.036, 12.0},
-                                  {1.45, 22.3, 0.56, 0.009, 0.050, 15.0},
-                                  {1.785, 17.3, 0.45, 0.097, 0.077, 11.0}};
+  constexpr ShareCost costs[4] = {{1.14, 9.0, 0.54, 0.010, 0.064, 12.0},
+                                  {1.30, 16.0, 0.54, 0.006, 0.060, 12.0},
+                                  {1.45, 22.3, 0.56, 0.009, 0.070, 15.0},
+                                  {1.785, 17.3, 0.45, 0.097, 0.100, 11.0}};
   const ShareCost& cost = costs[bq / 64 - 1];
+  const int64_t layers = mean ? L : 0;
   const double whole = mean ? mean_tiles_us(L, P, Q, steps)
-                       : narrow ? shares_us(cost, false, tiles, steps, 1) - cost.launch_us + 6.0  // one share, neither added nor another launch
+                       : narrow ? shares_us(cost, 0, tiles, steps, 1) - cost.launch_us + 6.0  // one share, neither added nor another launch
                                 : 2.0 * (double)steps * tile_choice(RC_SCORE_BLOCK, L, P, Q).step_us + 8.0;
   int best = alike;
-  double best_us = 0.93 * (alike > 1 ? shares_us(cost, mean, tiles * alike, steps, alike) : whole);
+  double best_us = 0.93 * (alike > 1 ? shares_us(cost, layers, tiles * alike, steps, alike) : whole);
   for (int half = 1; steps / half >= 8 && tiles * 2 * half <= 2048; ++half) {  // 8 steps of a share, 512 MB for all of them
-    const double us = shares_us(cost, mean, tiles * 2 * half, steps, 2 * half);
+    const double us = shares_us(cost, layers, tiles * 2 * half, steps, 2 * half);
     if (us < best_us) {
       best = 2 * half;
       best_us = us;

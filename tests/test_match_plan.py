@@ -16,6 +16,14 @@ MEAN_WHOLE = [
     (2, 32, 8, 15486, 458, {1: 1770, 2: 1858, 4: 1902, 6: 2018, 8: 1986}),
     (2, 16, 10, 4751, 905, {1: 984, 2: 952, 4: 828, 6: 820, 8: 833, 10: 963, 12: 1022}),
 ]
+# the layer mean with few layers, whose shares cost less to add than with many
+MEAN_FEW_LAYERS = [
+    (2, 16, 8, 5750, 16, {1: 438, 2: 237, 4: 182, 6: 194, 8: 164, 10: 163, 12: 170, 14: 165, 16: 153, 20: 167}),
+    (6, 16, 8, 1894, 24, {1: 422, 2: 235, 4: 176, 6: 212, 8: 177, 10: 162, 12: 177, 14: 171, 16: 161, 20: 182}),
+    (1, 16, 8, 11475, 20, {1: 447, 2: 236, 4: 170, 6: 212, 8: 181, 10: 158, 12: 174, 14: 167, 16: 156, 20: 177}),
+    (4, 16, 4, 5958, 8, {1: 241, 2: 161, 4: 180, 6: 168, 8: 149, 10: 164, 12: 167, 14: 170, 16: 162}),
+    (1, 16, 8, 899, 67, {1: 392, 16: 57, 20: 53, 24: 50, 32: 49, 36: 49, 48: 47, 64: 47}),
+]
 
 
 def check(mean, L, T, H, P, Q, us):
@@ -25,4 +33,9 @@ def check(mean, L, T, H, P, Q, us):
 
 @pytest.mark.parametrize("L,T,H,P,Q,us", MEAN_WHOLE)
 def test_layer_mean_in_whole_tiles(L, T, H, P, Q, us):
+    check(True, L, T, H, P, Q, us)
+
+
+@pytest.mark.parametrize("L,T,H,P,Q,us", MEAN_FEW_LAYERS)
+def test_layer_mean_of_few_layers(L, T, H, P, Q, us):
     check(True, L, T, H, P, Q, us)
