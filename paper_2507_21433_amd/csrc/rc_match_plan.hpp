@@ -240,20 +240,23 @@ inline int wide_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, in
   return best;
 }
 // The two rules above give a number of shares that divides the work evenly.  Block score and layer mean, up to a round of tiles, take
-// any even number instead (the shares of a tensor are a step longer or shorter) where the estimate below is 7 % less than for theirs:
-// a round of workgroups is filled better, and shares whose first slices are a power of two of KB apart crowd the same memory
-// channels.  What a launch of S shares per tile takes, in us: its rounds (of a last round of which a part r of the compute units has
-// work, idle + (1 - idle) r) times the steps of a share and what it takes to fill its pipeline and store, a time per workgroup for
-// the pass that adds it, one per layer and share for the layer mean's (a thread of it walks the shares of all layers: with a time
-// per workgroup in its place 2 x 5750 x 16 153 -> 182 us, 1 x 11475 x 20 156 -> 170), and the launches behind.  One set of
-// constants per width of the tiles.  Fitted to 473 drawn shapes (1 to 64 layers, 64 to 16 384 blocks, 1 to 1024 queries) of which
-// every number of shares was timed: with this choice a shape takes 1.2 to 1.9 % longer than with its best number, and is 1.03 to 1.08
-// times as fast as with the rules above (a fraction of 0.01 of them, 0.02 at 256 columns, more than 3 % slower).  Us per call:
+// any even number instead (the shares of a tensor are a step longer or shorter) where the estimate below is 4 to 7 % less than for
+// theirs, by the width of the tiles: a round of workgroups is filled better, and shares whose first slices are a power of two of KB
+// apart crowd the same memory channels.  What a launch of S shares per tile takes, in us: its rounds (of a last round of which a part r
+// of the compute units has work, idle + (1 - idle) r) times the steps of a share and what it takes to fill its pipeline and store, a
+// time per workgroup for the pass that adds it, one per layer and share for the layer mean's (a thread of it walks the shares of all
+// layers: with a time per workgroup in its place 2 x 5750 x 16 153 -> 182 us, 1 x 11475 x 20 156 -> 170), and the launches behind.
+// One set of constants per width of the tiles.  Fitted to 749 drawn shapes (1 to 64 layers, 64 to 16 384 blocks, 1 to 1024 queries) of
+// which every number of shares was timed: with this choice a shape takes 0.4 to 1.8 % longer than with its best number, and is 1.02 to
+// 1.09 times as fast as with the rules above; two shapes of 256 columns are more than 3 % slower, 2 x 512 x 209 61 -> 63 us and the layer mean
+// 5 x 3295 x 237 (4 heads) 221 -> 231.  64 columns with a step of 1.14 us and 9 to fill took 2 x 8278 x 42 in 6 shares, 246 us, not
+// the rules' 16, 236, nor 10, 235.  Us per call, the rules above -> this:
 //   1 x 3273 x 667 269 -> 175 (6 shares)   6 x 1347 x 456, 16 heads 793 -> 604 (6)   18 x 248 x 54, blocks of 32 tokens, 10 heads 189 -> 146
 //   (14)   9 x 405 x 134, 16 heads 203 -> 140 (14)   1 x 5942 x 139, 32 tokens 245 -> 181 (10)   2 x 9667 x 268, 16 heads 1036 -> 883 (8)
 //   layer mean 4 x 1273 x 261, 32 tokens, 16 heads 722 -> 555 (6)   whole tiles again: 2 x 4737 x 992 664 -> 596, 1 x 12000 x 800 721 -> 618
 struct ShareCost {
   double step_us, fill_us, idle, wg_us, mean_share_us, launch_us;
+  double margin;  // another number than the rules' is taken where its estimate is below this part of theirs
 };
 // `layers`: of a layer mean, 0 for the block score
 inline double shares_us(const ShareCost& c, int64_t layers, int64_t wgs, int64_t steps, int S) {
@@ -273,17 +276,17 @@ inline int block_split_count(bool mean, int64_t L, int64_t P, int64_t Q, int T, 
   const int bq = share_columns(Q);
   const int64_t tiles = L * ((P + 255) / 256) * ((Q + bq - 1) / bq), steps = (int64_t)T * H * 128 / kStepElements;  // of a tensor
   if (tiles > kSplitComputeUnits) return alike;
-  constexpr ShareCost costs[4] = {{1.14, 9.0, 0.54, 0.010, 0.064, 12.0},
-                                  {1.30, 16.0, 0.54, 0.006, 0.060, 12.0},
-                                  {1.45, 22.3, 0.56, 0.009, 0.070, 15.0},
-                                  {1.785, 17.3, 0.45, 0.097, 0.100, 11.0}};
+  constexpr ShareCost costs[4] = {{1.21, 6.8, 0.58, 0.010, 0.064, 12.0, 0.96},
+                                  {1.30, 16.0, 0.54, 0.006, 0.060, 12.0, 0.95},
+                                  {1.45, 22.3, 0.56, 0.009, 0.070, 15.0, 0.93},
+                                  {1.785, 17.3, 0.45, 0.097, 0.100, 11.0, 0.93}};
   const ShareCost& cost = costs[bq / 64 - 1];
   const int64_t layers = mean ? L : 0;
   const double whole = mean ? mean_tiles_us(L, P, Q, steps)
                        : narrow ? shares_us(cost, 0, tiles, steps, 1) - cost.launch_us + 6.0  // one share, neither added nor another launch
                                 : 2.0 * (double)steps * tile_choice(RC_SCORE_BLOCK, L, P, Q).step_us + 8.0;
   int best = alike;
-  double best_us = 0.93 * (alike > 1 ? shares_us(cost, layers, tiles * alike, steps, alike) : whole);
+  double best_us = cost.margin * (alike > 1 ? shares_us(cost, layers, tiles * alike, steps, alike) : whole);
   for (int half = 1; steps / half >= 8 && tiles * 2 * half <= 2048; ++half) {  // 8 steps of a share, 512 MB for all of them
     const double us = shares_us(cost, layers, tiles * 2 * half, steps, 2 * half);
     if (us < best_us) {

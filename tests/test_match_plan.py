@@ -24,6 +24,14 @@ MEAN_FEW_LAYERS = [
     (4, 16, 4, 5958, 8, {1: 241, 2: 161, 4: 180, 6: 168, 8: 149, 10: 164, 12: 167, 14: 170, 16: 162}),
     (1, 16, 8, 899, 67, {1: 392, 16: 57, 20: 53, 24: 50, 32: 49, 36: 49, 48: 47, 64: 47}),
 ]
+# 64 columns: layer mean or not; the estimate was too low for long shares
+LONG_SHARES = [
+    (False, 2, 16, 8, 8278, 42, {1: 452, 2: 294, 4: 285, 6: 246, 8: 251, 10: 235, 12: 244, 14: 238, 16: 236, 20: 268}),
+    (False, 5, 32, 4, 3305, 16, {1: 453, 2: 295, 4: 276, 6: 237, 8: 234, 10: 228, 12: 229, 14: 221, 16: 230, 20: 238}),
+    (False, 2, 16, 8, 9541, 20, {1: 448, 2: 294, 4: 302, 6: 250, 8: 271, 10: 241, 12: 259, 14: 272, 16: 257, 20: 276}),
+    (True, 2, 16, 8, 8278, 42, {1: 451, 2: 302, 4: 290, 6: 254, 8: 240, 10: 249, 12: 251, 14: 247, 16: 244, 20: 275}),
+    (True, 5, 32, 4, 3187, 39, {1: 458, 2: 298, 4: 241, 6: 250, 8: 234, 10: 231, 12: 241, 14: 237, 16: 242, 20: 263}),
+]
 
 
 def check(mean, L, T, H, P, Q, us):
@@ -39,3 +47,8 @@ def test_layer_mean_in_whole_tiles(L, T, H, P, Q, us):
 @pytest.mark.parametrize("L,T,H,P,Q,us", MEAN_FEW_LAYERS)
 def test_layer_mean_of_few_layers(L, T, H, P, Q, us):
     check(True, L, T, H, P, Q, us)
+
+
+@pytest.mark.parametrize("mean,L,T,H,P,Q,us", LONG_SHARES)
+def test_few_long_shares(mean, L, T, H, P, Q, us):
+    check(mean, L, T, H, P, Q, us)
