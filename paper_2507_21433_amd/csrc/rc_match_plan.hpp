@@ -132,17 +132,15 @@ inline int mean_columns(int64_t Q) {
   return n192 * step_us[1][n192 < 3 ? n192 - 1 : 2] < 0.96 * n256 * step_us[0][n256 < 3 ? n256 - 1 : 2] ? kWideTile.bq : kBlockTile.bq;
 }
 // What its launch takes in us where every workgroup walks one layer (up to 1024 tiles): rounds, of a last round of which a part r of
-// the compute units has work idle + (1 - idle) r, times the steps of both tensors.  Fitted to 194 timed calls of up to 256 tiles,
-// 0.8 to 1.25 of it each.
+// the compute units has work idle + (1 - idle) r, times the steps of both tensors.  More than 128 queries: the steps of the block
+// score's kernels, which are shorter where query tiles share the pool slices; one step for all counts took 7 x 2094 x 534 (16 heads)
+// in 4 shares, 1379 us, not whole, 1184.  Fitted to 230 timed calls of up to 256 tiles, 0.8 to 1.25 of it each.
 inline double mean_tiles_us(int64_t L, int64_t P, int64_t Q, int64_t steps) {
-  constexpr struct {
-    double step_us, idle;
-  } cost[4] = {{1.24, 0.53}, {1.40, 0.57}, {1.63, 0.55}, {1.70, 0.72}};
   const int bq = mean_columns(Q);
-  const int64_t tiles = L * ((P + 255) / 256) * ((Q + bq - 1) / bq);
-  const auto& c = cost[bq / 64 - 1];
-  const double part = (double)(tiles % 256) / 256.0;
-  return ((double)(tiles / 256) + (part > 0.0 ? c.idle + (1.0 - c.idle) * part : 0.0)) * 2.0 * (double)steps * c.step_us + 8.0;
+  const int64_t nqt = (Q + bq - 1) / bq, tiles = L * ((P + 255) / 256) * nqt;
+  const double step_us = bq == kNarrowTile.bq ? 1.24 : bq == kMidTile.bq ? 1.40 : kStepUs[0][bq == kWideTile.bq][nqt < 3 ? nqt - 1 : 2];
+  const double idle = bq <= kMidTile.bq ? 0.55 : 0.62, part = (double)(tiles % 256) / 256.0;
+  return ((double)(tiles / 256) + (part > 0.0 ? idle + (1.0 - idle) * part : 0.0)) * 2.0 * (double)steps * step_us + 8.0;
 }
 // byte offset of the selection partials inside the layer-mean workspace (after the sums: one
 // tile of 256 x bq floats per (group, pool tile, query tile))

@@ -14,6 +14,7 @@ MEAN_WHOLE = [
     (54, 16, 10, 922, 124, {1: 906, 2: 993, 4: 1094, 6: 1122, 8: 1126, 10: 1147}),
     (44, 16, 4, 1243, 111, {1: 373, 2: 454, 4: 484, 6: 495, 8: 497, 10: 579}),
     (2, 32, 8, 15486, 458, {1: 1770, 2: 1858, 4: 1902, 6: 2018, 8: 1986}),
+    (7, 16, 16, 2094, 534, {1: 1184, 4: 1379}),      # three query tiles share the pool slices
     (2, 16, 10, 4751, 905, {1: 984, 2: 952, 4: 828, 6: 820, 8: 833, 10: 963, 12: 1022}),
 ]
 # the layer mean with few layers, whose shares cost less to add than with many
@@ -36,7 +37,7 @@ LONG_SHARES = [
 
 def check(mean, L, T, H, P, Q, us):
     new, old = plans.shares(mean, L, T, H, P, Q), plans.alike(L, T, H, P, Q)
-    assert us[new] <= 1.03 * us[old], f"{new} shares take {us[new]} us, {old} took {us[old]}"
+    assert us[new] <= 1.03 * min(us[old], us[1]), f"{new} shares take {us[new]} us, {old} took {us[old]}"
 
 
 @pytest.mark.parametrize("L,T,H,P,Q,us", MEAN_WHOLE)
