@@ -241,8 +241,9 @@ inline int wide_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, in
 // any even number instead (the shares of a tensor are a step longer or shorter) where the estimate below is 4 to 7 % less than for
 // theirs, by the width of the tiles: a round of workgroups is filled better, and shares whose first slices are a power of two of KB
 // apart crowd the same memory channels.  What a launch of S shares per tile takes, in us: its rounds (of a last round of which a part r
-// of the compute units has work, idle + (1 - idle) r) times the steps of a share and what it takes to fill its pipeline and store, a
-// time per workgroup for the pass that adds it, one per layer and share for the layer mean's (a thread of it walks the shares of all
+// of the compute units has work, idle + (1 - idle) r; 256 columns: 0.75 to 0.8 of a full one from a fifth of the units to two thirds,
+// and without that floor few tiles got too few shares, 2 x 512 x 209 28 of them and not 64, 63 and 61 us, the layer mean 1 x 427 x 208 53
+// and 48) times the steps of a share and what it takes to fill its pipeline and store, a time per workgroup for the pass that adds it, one per layer and share for the layer mean's (a thread of it walks the shares of all
 // layers: with a time per workgroup in its place 2 x 5750 x 16 153 -> 182 us, 1 x 11475 x 20 156 -> 170), and the launches behind.
 // One set of constants per width of the tiles.  Fitted to 749 drawn shapes (1 to 64 layers, 64 to 16 384 blocks, 1 to 1024 queries) of
 // which every number of shares was timed: with this choice a shape takes 0.4 to 1.8 % longer than with its best number, and is 1.02 to
@@ -253,13 +254,14 @@ inline int wide_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, in
 //   (14)   9 x 405 x 134, 16 heads 203 -> 140 (14)   1 x 5942 x 139, 32 tokens 245 -> 181 (10)   2 x 9667 x 268, 16 heads 1036 -> 883 (8)
 //   layer mean 4 x 1273 x 261, 32 tokens, 16 heads 722 -> 555 (6)   whole tiles again: 2 x 4737 x 992 664 -> 596, 1 x 12000 x 800 721 -> 618
 struct ShareCost {
-  double step_us, fill_us, idle, wg_us, mean_share_us, launch_us;
+  double step_us, fill_us, idle, flat, wg_us, mean_share_us, launch_us;
   double margin;  // another number than the rules' is taken where its estimate is below this part of theirs
 };
 // `layers`: of a layer mean, 0 for the block score
 inline double shares_us(const ShareCost& c, int64_t layers, int64_t wgs, int64_t steps, int S) {
   const double part = (double)(wgs % kSplitComputeUnits) / kSplitComputeUnits;
-  const double rounds = (double)(wgs / kSplitComputeUnits) + (part > 0.0 ? c.idle + (1.0 - c.idle) * part : 0.0);
+  const double last = part > 0.0 ? std::max(c.idle + (1.0 - c.idle) * part, c.flat + 0.12 * part) : 0.0;
+  const double rounds = (double)(wgs / kSplitComputeUnits) + last;
   return rounds * (2.0 * (double)steps / S * c.step_us + c.fill_us) + (double)wgs * c.wg_us + (double)(layers * S) * c.mean_share_us + c.launch_us;
 }
 // The number of the two rules above.  192 and 256 columns cut every query count the 192 are used for into the same number of tiles.
@@ -274,10 +276,10 @@ inline int block_split_count(bool mean, int64_t L, int64_t P, int64_t Q, int T, 
   const int bq = share_columns(Q);
   const int64_t tiles = L * ((P + 255) / 256) * ((Q + bq - 1) / bq), steps = (int64_t)T * H * 128 / kStepElements;  // of a tensor
   if (tiles > kSplitComputeUnits) return alike;
-  constexpr ShareCost costs[4] = {{1.21, 6.8, 0.58, 0.010, 0.064, 12.0, 0.96},
-                                  {1.30, 16.0, 0.54, 0.006, 0.060, 12.0, 0.95},
-                                  {1.45, 22.3, 0.56, 0.009, 0.070, 15.0, 0.93},
-                                  {1.785, 17.3, 0.45, 0.097, 0.100, 11.0, 0.93}};
+  constexpr ShareCost costs[4] = {{1.21, 6.8, 0.58, 0.0, 0.010, 0.064, 12.0, 0.96},
+                                  {1.30, 16.0, 0.54, 0.0, 0.006, 0.060, 12.0, 0.95},
+                                  {1.45, 22.3, 0.56, 0.0, 0.009, 0.070, 15.0, 0.93},
+                                  {1.785, 17.3, 0.45, 0.72, 0.097, 0.100, 11.0, 0.93}};
   const ShareCost& cost = costs[bq / 64 - 1];
   const int64_t layers = mean ? L : 0;
   const double whole = mean ? mean_tiles_us(L, P, Q, steps)

@@ -33,6 +33,10 @@ LONG_SHARES = [
     (True, 2, 16, 8, 8278, 42, {1: 451, 2: 302, 4: 290, 6: 254, 8: 240, 10: 249, 12: 251, 14: 247, 16: 244, 20: 275}),
     (True, 5, 32, 4, 3187, 39, {1: 458, 2: 298, 4: 241, 6: 250, 8: 234, 10: 231, 12: 241, 14: 237, 16: 242, 20: 263}),
 ]
+# 256 columns, few tiles: a round that leaves most compute units idle is not that much shorter
+FEW_TILES = [
+    (True, 1, 16, 8, 427, 208, {1: 540, 32: 53, 34: 53, 64: 48}),
+]
 
 
 def check(mean, L, T, H, P, Q, us):
@@ -52,4 +56,9 @@ def test_layer_mean_of_few_layers(L, T, H, P, Q, us):
 
 @pytest.mark.parametrize("mean,L,T,H,P,Q,us", LONG_SHARES)
 def test_few_long_shares(mean, L, T, H, P, Q, us):
+    check(mean, L, T, H, P, Q, us)
+
+
+@pytest.mark.parametrize("mean,L,T,H,P,Q,us", FEW_TILES)
+def test_few_tiles(mean, L, T, H, P, Q, us):
     check(mean, L, T, H, P, Q, us)
