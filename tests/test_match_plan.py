@@ -62,3 +62,22 @@ def test_few_long_shares(mean, L, T, H, P, Q, us):
 @pytest.mark.parametrize("mean,L,T,H,P,Q,us", FEW_TILES)
 def test_few_tiles(mean, L, T, H, P, Q, us):
     check(mean, L, T, H, P, Q, us)
+
+
+# A workspace without room for the chosen number of shares: the older rules' plan where that fits, and only then the least one.
+@pytest.mark.parametrize("mean", [False, True])
+def test_middling_workspace_takes_the_former_number(mean):
+    L, T, H, P, Q = 7, 16, 10, 6134, 13
+    new, old = plans.shares(mean, L, T, H, P, Q), plans.alike(L, T, H, P, Q)
+    full, former = plans.need(mean, new, 64, L, P, Q), plans.need(mean, old, 64, L, P, Q)
+    assert 1 < old < new and plans.least(mean, L, T, H, P, Q) < former < full
+    for avail, want in ((full, new), (full - 16, old), (former, old), (former - 16, 1), (plans.least(mean, L, T, H, P, Q), 1)):
+        assert plans.shares_in(avail, mean, L, T, H, P, Q)[0] == want
+
+
+def test_least_workspace_keeps_the_columns_of_whole_tiles():
+    L, T, H, P, Q = 128, 16, 10, 312, 129
+    assert plans.shares(False, L, T, H, P, Q) > 1 == plans.alike(L, T, H, P, Q)
+    least = plans.least(False, L, T, H, P, Q)
+    assert least == plans.need(False, 1, 256, L, P, Q)
+    assert plans.shares_in(least, False, L, T, H, P, Q) == (1, 192)      # not the 256 that pad 129 queries to twice their work
