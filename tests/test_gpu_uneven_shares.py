@@ -1,13 +1,13 @@
-"""Shares of a tile's reduction that are not alike: a tensor's steps cut into 3 to 9 parts of which some are a step longer, every
-width of the tiles, block score and layer mean, against the CPU oracle; copies of a pool block in other tiles get the same score
-and lose to the lowest index.  Needs a real MI355X."""
+"""Shares of a tile's reduction that are not alike: a tensor's steps cut into 3, 5, 6 or 7 parts of which some are a step longer,
+every width of the tiles, block score and layer mean, against the CPU oracle; copies of a pool block in other tiles get the same
+score and lose to the lowest index.  Needs a real MI355X."""
 import numpy as np
 import pytest
 import torch
 
 from paper_2507_21433_amd import binding as rc
 from paper_2507_21433_amd import synth
-from tests import parity, paths
+from tests import parity, paths, plans
 from tests.test_gpu_layer_mean import gpu_layer_mean, shared_live
 from tests.test_gpu_parity import run_gpu_match
 from tests.test_workspace import guarded, search
@@ -15,22 +15,21 @@ from tests.test_workspace import guarded, search
 pytestmark = pytest.mark.gpu
 
 
-def shares(L, T, H, P, Q, mean):
-    """Shares per tile, from the workspace asked for: a tile of floats for each, then 16 bytes per pool chunk of 32 rows and query."""
+def uneven(mean, L, T, H, P, Q):
+    """(shares per tile by the plan, columns of the tiles): a number that does not divide the steps, with room in the workspace asked for."""
     columns = 64 if Q <= 64 else 128 if Q <= 128 else 192 if Q <= 192 or 256 < Q <= 384 else 256
-    size = paths.mean_size(rc.lib(), L, T, H, P, Q) if mean else paths.size(rc.lib(), 0, L, T, H, P, Q)
-    n, rest = divmod(size - L * -(-P // 32) * Q * 16, L * -(-P // 256) * -(-Q // columns) * 256 * columns * 4)
-    assert rest == 0
-    return n
-
-
-@pytest.mark.parametrize("L,T,H,P,Q", [(20, 32, 8, 1226, 13), (1, 32, 10, 3130, 89), (3, 16, 5, 1300, 140), (7, 16, 5, 520, 192),
-                                       (3, 16, 2, 1300, 300), (2, 16, 5, 1300, 513)])
-def test_block_score(oracle, L, T, H, P, Q):
-    # 128 columns: the 18 narrow shares take less than the least workspace, which is what is asked for
-    n = 18 if 64 < Q <= 128 else shares(L, T, H, P, Q, False)
-    print(f"[gpu-case] uneven shares L={L} T={T} H={H} P={P} Q={Q}: {n}", flush=True)
+    n = plans.shares(mean, L, T, H, P, Q)
     assert T * H * 2 % (n // 2) != 0, "the case is about shares that are not alike"
+    size = paths.mean_size(rc.lib(), L, T, H, P, Q) if mean else paths.size(rc.lib(), 0, L, T, H, P, Q)
+    assert size >= plans.need(mean, n, columns, L, P, Q)
+    return n, columns
+
+
+@pytest.mark.parametrize("L,T,H,P,Q", [(20, 32, 8, 1226, 13), (1, 32, 5, 4179, 70), (3, 16, 5, 1300, 90), (3, 16, 5, 1300, 140),
+                                       (7, 16, 5, 520, 192), (3, 16, 2, 1300, 300), (2, 16, 5, 1300, 513)])
+def test_block_score(oracle, L, T, H, P, Q):
+    n, columns = uneven(False, L, T, H, P, Q)
+    print(f"[gpu-case] uneven shares L={L} T={T} H={H} P={P} Q={Q}: {n}", flush=True)
     w = synth.scaled(synth.WORKLOADS[2], name="uneven", L=L, P=P, Q=Q, T=T, H=H, dtype="bf16" if Q % 2 else "f16", planted_frac=0.3,
                      R=1, E=P + Q, seed=9100 + P)
     pr = synth.make_problem(w, "cuda:0")
@@ -41,6 +40,7 @@ def test_block_score(oracle, L, T, H, P, Q):
         kq[:, 0] = kp[:, 7]
     pr["live"][:, P - 2] = 1
     g, _ = run_gpu_match(pr, w, pr["live"])
+    paths.assert_tiles(lambda: run_gpu_match(pr, w, pr["live"]), (256, columns, 3))
     orc = oracle.match(1 if w.dtype == "bf16" else 0, 0, *(synth.bits(pr[k]) for k in ("kq", "vq", "kp", "vp")),
                        pr["live"].cpu().numpy(), w.tau, want_scores=True)
     parity.check_match(g, orc, w.tau, parity.score_lookup(orc["scores"], g["best_idx"]))
@@ -62,11 +62,11 @@ def test_in_a_workspace_with_no_room_for_them(oracle, L, T, H, P, Q):
         parity.check_match(got, orc, w.tau, parity.score_lookup(orc["scores"], got["best_idx"]))
 
 
-@pytest.mark.parametrize("L,T,H,P,Q", [(20, 32, 8, 1226, 13), (7, 16, 5, 1300, 140), (7, 16, 5, 520, 300)])
+@pytest.mark.parametrize("L,T,H,P,Q", [(20, 32, 8, 1226, 13), (1, 32, 5, 4179, 70), (7, 16, 5, 1300, 140), (7, 16, 5, 520, 300),
+                                       (2, 16, 5, 1300, 513)])
 def test_layer_mean(oracle, L, T, H, P, Q):
-    n = shares(L, T, H, P, Q, True)
+    n, columns = uneven(True, L, T, H, P, Q)
     print(f"[gpu-case] uneven shares, layer mean L={L} T={T} H={H} P={P} Q={Q}: {n}", flush=True)
-    assert T * H * 2 % (n // 2) != 0, "the case is about shares that are not alike"
     w = synth.scaled(synth.WORKLOADS[2], name="uneven", L=L, P=P, Q=Q, T=T, H=H, dtype="bf16" if Q % 2 else "f16", planted_frac=0.3,
                      R=1, E=P + Q, seed=9200 + P)
     pr = synth.make_problem(w, "cuda:0")
@@ -81,6 +81,7 @@ def test_layer_mean(oracle, L, T, H, P, Q):
     live[7] = live[P - 2] = 1
     thr = 0.5 * np.sqrt(128 / (T * H))
     got = gpu_layer_mean(pr, live, thr)
+    paths.assert_tiles(lambda: gpu_layer_mean(pr, live, thr), (256, columns, 3))
     orc = oracle.layer_mean(1 if w.dtype == "bf16" else 0, *(synth.bits(pr[k]) for k in ("kq", "vq", "kp", "vp")), live.cpu().numpy(),
                             thr, want_dist=True)
     parity.check_layer_mean(got, orc, thr, parity.dist_lookup(orc["dist"], got["best_idx"]), 0.05 * parity.dist_tol(T, H, 128))
