@@ -1241,14 +1241,16 @@ inline rc_status prepare_schedule(MatchParams& mp, unsigned grid, void* schedule
   clear_schedule_kernel<<<(n + 1023) / 1024 < 64 ? (n + 1023) / 1024 : 64, 1024, 0, st>>>(mp.ctr, n);
   return check_launch("rc_match_blocks(tile schedule)");
 }
-// x 1024 clocks per tile index.  One query tile, and per head: two pipeline steps.  Several query tiles share a pool slice,
-// too, and its workgroups should not be far apart: half a step.  Us per launch at 0 / 1 / 2 / 3 / 6:
+// x 1024 clocks per tile index (a pipeline step of 256 columns takes about 2400).  One query tile: 6144 clocks, where the pool tiles
+// have only their channels in common.  Several query tiles share a pool slice, too, and its workgroups should not be far apart:
+// 2048, or less, which is the same.  Us per launch at 0 / 1 / 2 / 3 / 6:
 //   one query tile       64 x 4096 x 256 4356 / - / 4231 / - / 4171
 //   block score          16 x 8192 x 512 3690 / 3671 / 3670 / 3677 / 3746   32 x 16384 x 1024 25 568 / 25 656 / 25 539 / 25 634 / 25 796
 //                        16 x 8000 x 1000 6787 / 6783 / 6803 / 6826 / 6927   30 x 3000 x 380 2229 / 2228 / 2231 / 2235 / 2266
 //   layer mean           8 x 8192 x 1024 3645 / 3651 / 3656 / 3678 / 3735   16 x 8192 x 512 3932 / 3918 / 3915 / 3904 / 3956
-//   per head             8 x 8192 x 1024, 32 tokens 7594 / 7586 / 7577 / 7565 / 7552   32 x 8192 x 512 15 957 / 16 004 / 15 942 / 15 987 / 15 994
-inline int stagger_unit(bool heads, int64_t nqt) { return nqt > 1 && !heads ? 2 : 6; }
+// Per head it makes no difference, within 1 %, 6 -> 2: 32 x 8192 x 512, blocks of 32 tokens, 15 483 -> 15 599, 15 723 -> 15 664;
+// 16 x 6000 x 700 4270 -> 4249, 30 x 3000 x 380, 10 heads 2901 -> 2890, 20 x 6000 x 370, 4 heads 1470 -> 1455.
+inline int stagger_unit(int64_t nqt) { return nqt > 1 ? 2 : 6; }
 
 // Shares of a search by the kernels for small problems with few queries, 0 = by tiles.
 inline int few_plan_shares(int mode, int64_t L, int64_t P, int64_t Q, int T, int H) {
@@ -1467,7 +1469,7 @@ rc_status search_tiles(const TileSearch& a, const MatchPlan& plan) {
     mp.G = 1;
     mp.S = 1;
     mp.stagger_wgs = compute_units();
-    mp.stagger_unit = stagger_unit(mode == RC_SCORE_PER_HEAD_ALL, nqt);
+    mp.stagger_unit = stagger_unit(nqt);
     mp.vgrid = (int)virtual_grid(total);
     const unsigned grid = launch_grid((unsigned)mp.vgrid);
     if (rc_status s = prepare_schedule(mp, grid, static_cast<char*>(workspace) + plan_bytes(plan, L, P, Q) - schedule_bytes(total), st)) return s;
@@ -1668,7 +1670,7 @@ extern "C" rc_status rc_match_blocks_layer_mean(const rc_kv_desc* qdesc, const r
     mp.G = ls.G;
     mp.S = 1;
     mp.stagger_wgs = compute_units();
-    mp.stagger_unit = stagger_unit(false, nqt);
+    mp.stagger_unit = stagger_unit(nqt);
     mp.vgrid = (int)virtual_grid(total);
     const unsigned grid = launch_grid((unsigned)mp.vgrid);
     if (rc_status s = prepare_schedule(mp, grid, nullptr, st)) return s;  // a group of layers per tile: few, long tiles
