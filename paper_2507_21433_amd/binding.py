@@ -109,7 +109,7 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-# The device is asked for below torch.cuda's check that CUDA is initialised: the tensors at hand are on it.
+# The device from the call behind torch.cuda.current_device(), which initialises torch.cuda by itself (and refuses a forked child).
 def _stream():
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 

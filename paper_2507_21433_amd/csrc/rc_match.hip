@@ -296,9 +296,10 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
   const int tok = !PER_HEAD ? 256 : p.H * 256;
   const bool split_v = (MODE == 3) && split >= p.S / 2;
   // MODE 3: a share walks its slices from kShareRotation * share in and around, the same for every tile (identical
-  // pool blocks keep identical scores).  The shares of a tile are a power of two of KB apart: started together at
-  // their first slices, all workgroups ask the same memory channels at the same time.  Measured with one layer of
-  // 4096 blocks (16 shares of 4 KB): Q = 16 70 -> 53 us, Q = 100 63-78 -> 63 us; 8192 blocks 92-126 -> 96-111 us.
+  // pool blocks keep identical scores).  Shares that are a power of two of KB apart, started together at their first
+  // slices, all ask the same memory channels at the same time.  Measured with one layer of 4096 blocks (16 shares of
+  // 4 KB): Q = 16 70 -> 53 us, Q = 100 63-78 -> 63 us; 8192 blocks 92-126 -> 96-111 us.  Other numbers of shares lie
+  // elsewhere and are rotated the same way, which was not measured by itself.
   const uint32_t share_beg = (uint32_t)part_first * 128u;
   const uint32_t share_end = share_beg + (uint32_t)sps * 128u;
   const uint32_t share_rot = (MODE == 3) ? (uint32_t)(split * kShareRotation % sps) * 128u : 0u;
@@ -389,11 +390,14 @@ __device__ __forceinline__ void tile_body(const MatchParams& p) {
   // the end of the step that asks for it, and the first of the workgroups that share it waits for memory, not for the L2: its
   // last load should go out early.  The pool slice has a step more, and a burst of its loads holds the wave up (a compute
   // unit has a limited number of lines on their way): they are spread evenly over the rest of the step.  Two query loads to
-  // a slot at 256 columns, all out after a quarter of the step and not after half of it: 64 layers x 4096 x 256, 8 heads 4337
-  // -> 4102 us, 16 heads 5863 -> 5581, per head 32 x 8192 x 512 16 545 -> 15 832, 16 x 8192 x 256 4762 -> 4672; most of that
-  // where a block's tensor is a power of two of bytes (7 and 9 heads: no change), whose slices crowd some channels.  Four
-  // to a slot: 1 to 3 % slower than that.  The cosine mode with several query tiles and the layer-mean mode keep one to a slot:
-  // their slices are asked for by more workgroups, the first of which leads by less, and the bunched loads cost them 0.5 to 1 %.
+  // a slot at 320 columns, which have more loads than slots, and at 256, all out after a quarter of the step and not after half of
+  // it: 64 layers x 4096 x 256, 8 heads 4337 -> 4102 us, 16 heads 5863 -> 5581, per head 32 x 8192 x 512 16 545 -> 15 832, 16 x 8192 x
+  // 256 4762 -> 4672; most of that where a block's tensor is a power of two of bytes (7 and 9 heads: no change), whose slices crowd
+  // some channels.  Four to a slot: 1 to 3 % slower than that.  The cosine mode with several query tiles of 256 columns and the
+  // layer-mean mode keep one to a slot: their slices are asked for by more workgroups, the first of which leads by less, and the
+  // bunched loads cost them 0.5 to 1 %.  64, 128 and 192 columns: one to a slot, and no difference between pool loads spread and in
+  // consecutive slots: 64 x 3877 x 40 2357 and 2359, 64 x 4096 x 128 3159 and 3172, layer mean 64 x 2048 x 128 1600 and 1602, 16
+  // shares of 1 x 4096 x 16 63.7 and 63.7, per head 32 x 2531 x 24, blocks of 32 tokens, 1877 and 1875.
   constexpr int SLOTS = 4 * TP;
   constexpr int BPS = TQ == 5 || (TQ == 4 && MODE != 2 && !SHARED_POOL) ? 2 : 1;  // query loads to a slot
   constexpr int LBS = LB / BPS;                                                 // slots of the query loads

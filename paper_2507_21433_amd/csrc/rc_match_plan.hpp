@@ -245,11 +245,12 @@ inline int wide_split_count(int mode, int64_t L, int64_t P, int64_t Q, int T, in
 // and without that floor few tiles got too few shares, 2 x 512 x 209 28 of them and not 64, 63 and 61 us, the layer mean 1 x 427 x 208 53
 // and 48) times the steps of a share and what it takes to fill its pipeline and store, a time per workgroup for the pass that adds it, one per layer and share for the layer mean's (a thread of it walks the shares of all
 // layers: with a time per workgroup in its place 2 x 5750 x 16 153 -> 182 us, 1 x 11475 x 20 156 -> 170), and the launches behind.
-// One set of constants per width of the tiles.  Fitted to 749 drawn shapes (1 to 64 layers, 64 to 16 384 blocks, 1 to 1024 queries) of
-// which every number of shares was timed: with this choice a shape takes 0.4 to 1.8 % longer than with its best number, and is 1.02 to
-// 1.09 times as fast as with the rules above; two shapes of 256 columns are more than 3 % slower, 2 x 512 x 209 61 -> 63 us and the layer mean
-// 5 x 3295 x 237 (4 heads) 221 -> 231.  64 columns with a step of 1.14 us and 9 to fill took 2 x 8278 x 42 in 6 shares, 246 us, not
-// the rules' 16, 236, nor 10, 235.  Us per call, the rules above -> this:
+// One set of constants per width of the tiles.  Fitted to 819 drawn shapes (1 to 64 layers, 64 to 16 384 blocks, 1 to 1024 queries) of
+// which every number of shares was timed: with this choice a shape takes 0.4 to 2.2 % longer than with its best number, and is 1.02 to
+// 1.08 times as fast as with the rules above.  None of the block score's is more than 3 % slower than by those, three of the layer
+// mean's are: 1 x 699 x 220 52 -> 55 us, 1 x 1013 x 252, 32 tokens 88 -> 92, 5 x 3295 x 237, 4 heads 221 -> 231; of 140 others whose
+// number changed since, the worst are 15 x 3361 x 89, 10 heads 812 -> 865 and 1 x 721 x 212 50 -> 54.  64 columns with a step of 1.14 us and 9 to fill took 2 x 8278 x 42 in 6 shares, 246 us, not the rules' 16, 236, nor 10,
+// 235.  Us per call, the rules above -> this:
 //   1 x 3273 x 667 269 -> 175 (6 shares)   6 x 1347 x 456, 16 heads 793 -> 604 (6)   18 x 248 x 54, blocks of 32 tokens, 10 heads 189 -> 146
 //   (14)   9 x 405 x 134, 16 heads 203 -> 140 (14)   1 x 5942 x 139, 32 tokens 245 -> 181 (10)   2 x 9667 x 268, 16 heads 1036 -> 883 (8)
 //   layer mean 4 x 1273 x 261, 32 tokens, 16 heads 722 -> 555 (6)   whole tiles again: 2 x 4737 x 992 664 -> 596, 1 x 12000 x 800 721 -> 618
