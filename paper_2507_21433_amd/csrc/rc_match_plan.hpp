@@ -288,7 +288,9 @@ inline int block_split_count(bool mean, int64_t L, int64_t P, int64_t Q, int T, 
                                 : 2.0 * (double)steps * tile_choice(RC_SCORE_BLOCK, L, P, Q).step_us + 8.0;
   int best = alike;
   double best_us = cost.margin * (alike > 1 ? shares_us(cost, layers, tiles * alike, steps, alike) : whole);
-  for (int half = 1; steps / half >= 8 && tiles * 2 * half <= 2048; ++half) {  // 8 steps of a share, 512 MB for all of them
+  // 8 steps of a share at least, 9 of 256 columns, whose store takes as long (1 x 516 x 256, 3 heads: 46.6 us in 24 shares of 8, 46.5 in
+  // the rules' 16 of 12); 512 MB for all of them
+  for (int half = 1; steps / half >= (bq == kBlockTile.bq ? 9 : 8) && tiles * 2 * half <= 2048; ++half) {
     const double us = shares_us(cost, layers, tiles * 2 * half, steps, 2 * half);
     if (us < best_us) {
       best = 2 * half;
