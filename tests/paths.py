@@ -83,5 +83,8 @@ def tile_kernels(call):
 
 
 def assert_tiles(call, *want):
-    got = tile_kernels(call)
+    for _ in range(3):      # a trace that has lost some of the wanted kernels is taken again; one that has others is not
+        got = tile_kernels(call)
+        if got is None or not got < set(want):
+            break
     assert got in (None, set(want)), f"tile kernels {sorted(got)}, the test is about {want}"
